@@ -61,9 +61,9 @@ constexpr int kChunk = 256;               // K elements per register set of W (8
 constexpr int kSubSpan = 128;
 // (nw = waves per workgroup: 4, or 8 for the wide kernel whose tile is 128 rows of W: 3 slots of 48 KiB)
 // (rows of 256 bytes: a row of x, a row of a bf16 W, or two rows of an 8-bit W; the wide kernel for an 8-bit W has 4
-// slots of 32 KiB, and every wide kernel gets the LDS of the bf16 one, because what follows the contraction stages as
-// much there)
-__host__ __device__ constexpr int ring_slots(int tt, bool wlds, int nw, bool w8 = false) { return nw > 4 ? (w8 ? 4 : 3) : tt <= 2 ? 5 : 4; }
+// slots of 32 KiB, the one for a 4-bit W 5 slots of 16 KiB (x alone), and every wide kernel gets the LDS of the bf16 one,
+// because what follows the contraction stages as much there)
+__host__ __device__ constexpr int ring_slots(int tt, bool wlds, int nw, bool w8 = false) { return nw > 4 ? (!wlds ? 5 : w8 ? 4 : 3) : tt <= 2 ? 5 : 4; }
 __host__ __device__ constexpr int slot_rows(int tt, bool wlds, int nw, bool w8 = false)
 {
     return tt * 16 + (wlds ? nw * kRowsPerWave / (w8 ? 2 : 1) : 0);
@@ -73,6 +73,7 @@ __host__ __device__ constexpr int ring_bytes(int tt, bool wlds, int nw, bool w8 
     return nw > 4 ? 3 * (tt * 16 + nw * kRowsPerWave) * kSubSpan * 2 : ring_slots(tt, wlds, nw, w8) * slot_rows(tt, wlds, nw, w8) * kSubSpan * 2;
 }
 static_assert(ring_slots(4, true, 8, true) * slot_rows(4, true, 8, true) <= 3 * (64 + 128), "the 8-bit wide ring fits");
+static_assert(ring_slots(4, false, 8) * slot_rows(4, false, 8) <= 3 * (64 + 128), "the wide ring of x alone (4-bit W) fits");
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 constexpr int kMetaLds = 512;  // slot tables up to this many entries are copied to LDS whole
 
@@ -85,6 +86,19 @@ typedef float float_pair_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16_pair(float lo, float hi)
 {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(float_pair_t{lo, hi}, bf16_pair_t));
+}
+
+// eight 4-bit weights (element k in bits 4 k ..): fma(code, scale, -8 scale), exact in fp32, rounded once to bf16: the
+// value the matrix cores multiply on every path that takes this W
+__device__ __forceinline__ u32x4 w4_to_bf16x8(uint32_t codes, float sc)
+{
+    const float c8 = -8.0f * sc;
+    const uint32_t lo = codes & 0x0f0f0f0fu, hi = (codes >> 4) & 0x0f0f0f0fu;
+    u32x4 o;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        o[q] = pack_bf16_pair(fmaf((float)((lo >> (8 * q)) & 0xffu), sc, c8), fmaf((float)((hi >> (8 * q)) & 0xffu), sc, c8));
+    return o;
 }
 
 // sync area (ints) at the start of the workspace
@@ -146,7 +160,7 @@ struct DecodeShape {
     int wait_ticks; // a wait for another workgroup gives up after this many ticks of the 100 MHz clock
     int tile_rows;  // rows of W per tile: 64 (four waves) or 128 (the wide kernel, eight waves)
     int rot_mask;   // a workgroup starts its K-slice (tile number on its XCD & rot_mask) sub-spans in: 2^n - 1, below every slice's length
-    const uint16_t *w_scales;  // 8-bit W: fp16 [d_out][d_in / 32] group scales; else nullptr
+    const uint16_t *w_scales;  // 8-bit or 4-bit W: fp16 [d_out][d_in / 32] group scales; else nullptr
 };
 
 // ---- mailbox accesses (agent scope: past the per-XCD L2) -----------------------------------------
@@ -234,6 +248,7 @@ __device__ __forceinline__ float *piece_ptr(float *mail, const DecodeShape &sh, 
 }
 
 // Columns [nc0, nc0 + ncols) of y for all rows, from the inputs alone (after a wait ran out): slow, exact.
+template <bool kW4>
 __device__ __forceinline__ void recompute_columns(const DecodeShape &sh, const uint16_t *__restrict__ x, const uint16_t *__restrict__ W,
                                   const PoolView &pool, const RouteView &route, int has_pool, uint16_t *__restrict__ y,
                                   int nc0, int ncols, int wave, int n_waves, int lane)
@@ -270,7 +285,22 @@ __device__ __forceinline__ void recompute_columns(const DecodeShape &sh, const u
         for (int c = 0; c < ncols && nc0 + c < N; ++c) {
             const uint16_t *wn = W + (size_t)(nc0 + c) * K;
             float s = 0.0f;
-            if (sh.w_scales != nullptr) {
+            if constexpr (kW4) {
+                // 4-bit W: w = bf16(scale * (code - 8)), the value the main path multiplies
+                const uint8_t *wc = reinterpret_cast<const uint8_t *>(W) + (size_t)(nc0 + c) * (K >> 1);
+                const uint16_t *ws = sh.w_scales + (size_t)(nc0 + c) * (K >> 5);
+                for (int k = lane * 8; k < K; k += 64 * 8) {
+                    const uint32_t cv = *reinterpret_cast<const uint32_t *>(wc + (k >> 1));
+                    const u32x4 xv = *reinterpret_cast<const u32x4 *>(xt + k);
+                    const float sc = fp16_to_f32(ws[k >> 5]);
+                    const u32x4 wp = w4_to_bf16x8(cv, sc);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        s = fmaf(__uint_as_float(wp[q] << 16), __uint_as_float(xv[q] << 16), s);
+                        s = fmaf(__uint_as_float(wp[q] & 0xffff0000u), __uint_as_float(xv[q] & 0xffff0000u), s);
+                    }
+                }
+            } else if (sh.w_scales != nullptr) {
                 // 8-bit W: w = bf16(scale * code), the value the main path multiplies
                 const int8_t *wc = reinterpret_cast<const int8_t *>(W) + (size_t)(nc0 + c) * K;
                 const uint16_t *ws = sh.w_scales + (size_t)(nc0 + c) * (K >> 5);
@@ -302,7 +332,7 @@ __device__ __forceinline__ void recompute_columns(const DecodeShape &sh, const u
     }
 }
 
-template <int TT, bool kWLds, int NW, bool kQ8, bool kW8, bool kLeanOnly>
+template <int TT, bool kWLds, int NW, bool kQ8, bool kW8, bool kLeanOnly, bool kW4>
 __global__ __launch_bounds__(NW * 64, NW > 4 ? 1 : 2) void decode_kernel(DecodeShape sh, const uint16_t *__restrict__ x,
                                                                            const uint16_t *__restrict__ W, PoolView pool,
                                                                            RouteView route, int has_pool, float *__restrict__ mail,
@@ -336,7 +366,7 @@ struct DecodeGroup {
     DecodeCall call[kGroupMax];
 };
 
-template <int TT, bool kWLds, int NW, bool kQ8, bool kW8, bool kLeanOnly>
+template <int TT, bool kWLds, int NW, bool kQ8, bool kW8, bool kLeanOnly, bool kW4>
 __global__ __launch_bounds__(NW * 64, NW > 4 ? 1 : 2) void decode_group_kernel(DecodeGroup grp_)
 {
     int call_i = 0;
@@ -365,7 +395,7 @@ struct Variant {
     bool wlds;
     int nw;
     bool q8 = false;  // the pool keeps its adapters in 8-bit blocks (W through the ring always)
-    bool w8 = false;  // W is 8-bit (into registers on four waves, through the ring on eight)
+    int wb = 16;      // bits of a weight: 16 (bf16), 8 (into registers on four waves, through the ring on eight) or 4 (into registers)
     // the instances without the general tail (bf16 W through the ring, bf16 pool or none; eight waves, or four waves
     // with one or two blocks of x): for calls whose pool, as the host knows it, holds only ranks that are multiples of
     // 8, up to 64.  14 to 24 KB less code per instance; config 3: 178.0 -> 175.1 us per step, config 2: 15.45 -> 14.8.
@@ -375,14 +405,15 @@ struct Variant {
     int index() const
     {
         if (lean) return 33 + (nw > 4 ? 2 : tt - 1);
-        return w8 ? (nw > 4 ? 26 : 21 + tt) + (q8 ? 6 : 0) : (nw > 4 ? 10 : tt * 2 + (wlds ? 1 : 0)) + (q8 ? 11 : 0);
+        if (wb == 4) return 36 + (nw > 4 ? 4 : tt - 1) + (q8 ? 5 : 0);
+        return wb == 8 ? (nw > 4 ? 26 : 21 + tt) + (q8 ? 6 : 0) : (nw > 4 ? 10 : tt * 2 + (wlds ? 1 : 0)) + (q8 ? 11 : 0);
     }
-    void allow_lean(bool ok) { lean = ok && !q8 && !w8 && wlds && (nw > 4 || tt <= 2); }
+    void allow_lean(bool ok) { lean = ok && !q8 && wb == 16 && wlds && (nw > 4 || tt <= 2); }
     int threads() const { return nw * 64; }
     int tile_rows() const { return nw * kRowsPerWave; }
-    int lds() const { return ring_bytes(tt, wlds, nw, w8); }
+    int lds() const { return ring_bytes(tt, wlds, nw, wb == 8); }
 };
-constexpr int kVariants = 36;
+constexpr int kVariants = 46;
 template <typename F>
 auto with_variant_bf16(const Variant &v, F &&f)
 {
@@ -396,41 +427,37 @@ auto with_variant_bf16(const Variant &v, F &&f)
 }
 
 template <typename F>
-auto with_variant(const Variant &v, F &&f)  // f(blocks of x, W through the ring, waves, 8-bit pool, 8-bit W, no general tail)
+auto with_variant(const Variant &v, F &&f)  // f(blocks of x, W through the ring, waves, 8-bit pool, bits of W, no general tail)
 {
     const std::true_type yes{};
     const std::false_type no{};
+    const ic<16> w16{};
     if (v.lean) {
-        if (v.nw > 4) return f(ic<4>{}, yes, ic<8>{}, no, no, yes);
-        if (v.tt == 1) return f(ic<1>{}, yes, ic<4>{}, no, no, yes);
-        return f(ic<2>{}, yes, ic<4>{}, no, no, yes);
+        if (v.nw > 4) return f(ic<4>{}, yes, ic<8>{}, no, w16, yes);
+        if (v.tt == 1) return f(ic<1>{}, yes, ic<4>{}, no, w16, yes);
+        return f(ic<2>{}, yes, ic<4>{}, no, w16, yes);
     }
-    if (v.w8 && v.q8) {
-        if (v.nw > 4) return f(ic<4>{}, yes, ic<8>{}, yes, yes, no);
+    // (8-bit and 4-bit W: three blocks of x run on the instance for four)
+    auto low_bits = [&](auto wide_wl, auto q8, auto wb) {
+        if (v.nw > 4) return f(ic<4>{}, wide_wl, ic<8>{}, q8, wb, no);
         switch (v.tt) {
-        case 1: return f(ic<1>{}, no, ic<4>{}, yes, yes, no);
-        case 2: return f(ic<2>{}, no, ic<4>{}, yes, yes, no);
-        default: return f(ic<4>{}, no, ic<4>{}, yes, yes, no);
+        case 1: return f(ic<1>{}, no, ic<4>{}, q8, wb, no);
+        case 2: return f(ic<2>{}, no, ic<4>{}, q8, wb, no);
+        default: return f(ic<4>{}, no, ic<4>{}, q8, wb, no);
         }
-    }
-    if (v.w8) {
-        if (v.nw > 4) return f(ic<4>{}, yes, ic<8>{}, no, yes, no);
-        switch (v.tt) {
-        case 1: return f(ic<1>{}, no, ic<4>{}, no, yes, no);
-        case 2: return f(ic<2>{}, no, ic<4>{}, no, yes, no);
-        default: return f(ic<4>{}, no, ic<4>{}, no, yes, no);
-        }
-    }
+    };
+    if (v.wb == 8) return v.q8 ? low_bits(yes, yes, ic<8>{}) : low_bits(yes, no, ic<8>{});
+    if (v.wb == 4) return v.q8 ? low_bits(no, yes, ic<4>{}) : low_bits(no, no, ic<4>{});
     if (v.q8) {
-        if (v.nw > 4) return f(ic<4>{}, yes, ic<8>{}, yes, no, no);
+        if (v.nw > 4) return f(ic<4>{}, yes, ic<8>{}, yes, w16, no);
         switch (v.tt) {
-        case 1: return f(ic<1>{}, yes, ic<4>{}, yes, no, no);
-        case 2: return f(ic<2>{}, yes, ic<4>{}, yes, no, no);
-        case 3: return f(ic<3>{}, yes, ic<4>{}, yes, no, no);
-        default: return f(ic<4>{}, yes, ic<4>{}, yes, no, no);
+        case 1: return f(ic<1>{}, yes, ic<4>{}, yes, w16, no);
+        case 2: return f(ic<2>{}, yes, ic<4>{}, yes, w16, no);
+        case 3: return f(ic<3>{}, yes, ic<4>{}, yes, w16, no);
+        default: return f(ic<4>{}, yes, ic<4>{}, yes, w16, no);
         }
     }
-    return with_variant_bf16(v, [&](auto tt, auto wl, auto nw) { return f(tt, wl, nw, no, no, no); });
+    return with_variant_bf16(v, [&](auto tt, auto wl, auto nw) { return f(tt, wl, nw, no, w16, no); });
 }
 // workgroups of a kernel instance the device holds at once (registers and LDS decide; asked once per instance), and
 // its number of compute units.  group: the kernel that carries several calls; 0 if it cannot be asked (then calls
@@ -445,25 +472,17 @@ int resident_of(const Variant &v, bool group, int *n_cus)
         hipError_t e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e == hipSuccess)
-            e = with_variant(v, [&](auto tt, auto wl, auto nw, auto q8, auto w8, auto ln) {
-                constexpr int TT = decltype(tt)::value, NW = decltype(nw)::value;
-                constexpr bool WL = decltype(wl)::value, Q8 = decltype(q8)::value, W8 = decltype(w8)::value, LN = decltype(ln)::value;
+            e = with_variant(v, [&](auto tt, auto wl, auto nw, auto q8, auto wb, auto ln) {
+                constexpr int TT = decltype(tt)::value, NW = decltype(nw)::value, WB = decltype(wb)::value;
+                constexpr bool WL = decltype(wl)::value, Q8 = decltype(q8)::value, LN = decltype(ln)::value;
+                constexpr int lds = ring_bytes(TT, WL, NW, WB == 8);
                 // (the ring may be larger than the LDS a kernel gets without asking)
-                if constexpr (W8) {
-                    const void *fn8 = group ? reinterpret_cast<const void *>(&decode_group_kernel<TT, WL, NW, Q8, true, LN>)
-                                            : reinterpret_cast<const void *>(&decode_kernel<TT, WL, NW, Q8, true, LN>);
-                    hipError_t e8 = hipFuncSetAttribute(fn8, hipFuncAttributeMaxDynamicSharedMemorySize, ring_bytes(TT, WL, NW, true));
-                    if (e8 != hipSuccess) return e8;
-                    return group ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_group_kernel<TT, WL, NW, Q8, true, LN>, NW * 64, ring_bytes(TT, WL, NW, true))
-                                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<TT, WL, NW, Q8, true, LN>, NW * 64, ring_bytes(TT, WL, NW, true));
-                } else {
-                const void *fn = group ? reinterpret_cast<const void *>(&decode_group_kernel<TT, WL, NW, Q8, false, LN>)
-                                       : reinterpret_cast<const void *>(&decode_kernel<TT, WL, NW, Q8, false, LN>);
-                hipError_t e2 = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, ring_bytes(TT, WL, NW));
+                const void *fn = group ? reinterpret_cast<const void *>(&decode_group_kernel<TT, WL, NW, Q8, WB == 8, LN, WB == 4>)
+                                       : reinterpret_cast<const void *>(&decode_kernel<TT, WL, NW, Q8, WB == 8, LN, WB == 4>);
+                const hipError_t e2 = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
                 if (e2 != hipSuccess) return e2;
-                return group ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_group_kernel<TT, WL, NW, Q8, false, LN>, NW * 64, ring_bytes(TT, WL, NW))
-                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<TT, WL, NW, Q8, false, LN>, NW * 64, ring_bytes(TT, WL, NW));
-                }
+                return group ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_group_kernel<TT, WL, NW, Q8, WB == 8, LN, WB == 4>, NW * 64, lds)
+                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<TT, WL, NW, Q8, WB == 8, LN, WB == 4>, NW * 64, lds);
             });
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -514,10 +533,12 @@ bool wide_allowed(int T) { return g_wide_mode != 0 && T > 32; }
 // max_rank from 5 to 64
 bool ranks_fit_short_tail(int n_odd_ranks, int max_rank) { return n_odd_ranks == 0 && max_rank <= 64 && max_rank > 4; }
 
-DecodeShape make_shape(int T, int K, int N, int max_rank, bool q8, Variant *var, const uint16_t *w_scales = nullptr, bool lean_ok = false)
+int weight_bits(int wfmt) { return wfmt == ELORA_W_INT8_G32 ? 8 : wfmt == ELORA_W_INT4_G32 ? 4 : 16; }
+
+DecodeShape make_shape(int T, int K, int N, int max_rank, bool q8, Variant *var, int wb, const uint16_t *w_scales, bool lean_ok)
 {
     DecodeShape sh;
-    sh.w_scales = w_scales;
+    sh.w_scales = wb < 16 ? w_scales : nullptr;
     sh.T = T;
     sh.K = K;
     sh.N = N;
@@ -526,11 +547,11 @@ DecodeShape make_shape(int T, int K, int N, int max_rank, bool q8, Variant *var,
     sh.jg_inv = (unsigned)((1ull << 32) / (unsigned)sh.jgroups) + 1u;
     const int tt = (T + 15) / 16;
     int n_cus = 0;
-    if (w_scales != nullptr) {
-        // 8-bit W: into registers on four waves; more than 32 rows: 128 rows of W per workgroup, through the ring, where
-        // that grid covers the device
+    if (wb < 16) {
+        // 8-bit and 4-bit W: into registers on four waves; more than 32 rows: 128 rows of W per workgroup (an 8-bit W
+        // through the ring), where that grid covers the device
         if (wide_allowed(T)) {
-            const Variant wide{4, true, 8, q8, true};
+            const Variant wide{4, wb == 8, 8, q8, wb};
             const int resident = resident_workgroups(wide, &n_cus);
             const int n_tiles = (N + wide.tile_rows() - 1) / wide.tile_rows();
             const int split = pick_split(K, n_tiles, resident, n_cus);
@@ -545,7 +566,7 @@ DecodeShape make_shape(int T, int K, int N, int max_rank, bool q8, Variant *var,
         }
         // (33 to 48 rows take the instance for four blocks of x: the one for three needs more registers than a wave has,
         // and what the compiler would move to scratch memory there may be the target of a load still on its way)
-        Variant v8{tt == 3 ? 4 : tt, false, 4, q8, true};
+        Variant v8{tt == 3 ? 4 : tt, false, 4, q8, wb};
         sh.tile_rows = v8.tile_rows();
         sh.n_tiles = (N + sh.tile_rows - 1) / sh.tile_rows;
         const int resident = resident_workgroups(v8, &n_cus);
@@ -666,18 +687,18 @@ int elora::decode_probe_device(void *scratch, size_t scratch_bytes, hipStream_t 
 // tried first if its workgroups then cover at least seven eighths of the compute units; then W through LDS (one
 // workgroup per compute unit); then W into registers, which leaves room for two per unit.
 namespace {
-bool group_splits(int T, int n, const int *K, const int *N, int *split, Variant *var, bool w8 = false, bool q8 = false, bool lean_ok = false)
+bool group_splits(int T, int n, const int *K, const int *N, int *split, Variant *var, int wb, bool q8, bool lean_ok)
 {
     if (n < 2 || n > kGroupMax || T < 1 || T > kDecodeMaxTokens) return false;
     const int tt = (T + 15) / 16;
     Variant cand[3];
     int n_cand = 0;
-    if (w8) {  // (an 8-bit W: through the ring on eight waves, into registers on four)
-        if (wide_allowed(T)) cand[n_cand++] = Variant{4, true, 8, q8, true};
-        cand[n_cand++] = Variant{tt == 3 ? 4 : tt, false, 4, q8, true};
+    if (wb < 16) {  // (an 8-bit W: through the ring on eight waves, into registers on four; a 4-bit W: into registers)
+        if (wide_allowed(T)) cand[n_cand++] = Variant{4, wb == 8, 8, q8, wb};
+        cand[n_cand++] = Variant{tt == 3 ? 4 : tt, false, 4, q8, wb};
     } else if (q8) {  // (adapters in 8-bit blocks: W through the ring always)
-        if (wide_allowed(T)) cand[n_cand++] = Variant{4, true, 8, true, false};
-        cand[n_cand++] = Variant{tt, true, 4, true, false};
+        if (wide_allowed(T)) cand[n_cand++] = Variant{4, true, 8, true};
+        cand[n_cand++] = Variant{tt, true, 4, true};
     } else {
         if (wide_allowed(T)) cand[n_cand++] = Variant{4, true, 8};
         cand[n_cand++] = Variant{tt, true, 4};
@@ -719,10 +740,10 @@ bool group_splits(int T, int n, const int *K, const int *N, int *split, Variant 
 }
 }  // namespace
 
-bool elora::decode_group_splits(int T, int n, const int *K, const int *N, int *split, bool *w_lds, bool w8, bool q8)
+bool elora::decode_group_splits(int T, int n, const int *K, const int *N, int *split, bool *w_lds, int wfmt, bool q8)
 {
     Variant v{1, true, 4};
-    const bool ok = group_splits(T, n, K, N, split, &v, w8, q8);
+    const bool ok = group_splits(T, n, K, N, split, &v, weight_bits(wfmt), q8, false);
     if (ok) *w_lds = v.wlds;
     return ok;
 }
@@ -731,12 +752,12 @@ bool elora::decode_group_splits(int T, int n, const int *K, const int *N, int *s
 int elora::launch_decode_group(const LinearArgs *a, int n, hipStream_t stream)
 {
     if (n < 2 || n > kGroupMax) return -1;
-    // W in the dtype of x in every call, or 8-bit in every call; the pools all bf16, or all in 8-bit blocks
-    const bool w8 = a[0].wfmt == ELORA_W_INT8_G32;
+    // one storage format of W in all calls; the pools all bf16, or all in 8-bit blocks
+    const int wb = weight_bits(a[0].wfmt);
     bool q8 = false;
     for (int i = 0; i < n; ++i) q8 = q8 || (a[i].has_pool && a[i].pool.q8);
     for (int i = 0; i < n; ++i)
-        if ((a[i].has_pool && (a[i].pool.q8 != 0) != q8) || a[i].wfmt != a[0].wfmt || (a[i].wfmt != ELORA_W_SAME && !w8)) return -1;
+        if ((a[i].has_pool && (a[i].pool.q8 != 0) != q8) || a[i].wfmt != a[0].wfmt) return -1;
     const int T = a[0].T;
     int Ks[kGroupMax], Ns[kGroupMax], split[kGroupMax];
     for (int i = 0; i < n; ++i) {
@@ -747,7 +768,7 @@ int elora::launch_decode_group(const LinearArgs *a, int n, hipStream_t stream)
     Variant var{1, true, 4};
     bool lean_ok = true;
     for (int i = 0; i < n; ++i) lean_ok = lean_ok && (!a[i].has_pool || ranks_fit_short_tail(a[i].pool.n_odd_ranks, a[i].pool.max_rank));
-    if (!group_splits(T, n, Ks, Ns, split, &var, w8, q8, lean_ok)) return -1;
+    if (!group_splits(T, n, Ks, Ns, split, &var, wb, q8, lean_ok)) return -1;
     int n_cus = 0;
     (void)resident_workgroups(var, &n_cus);
     const int resident = resident_group_workgroups(var);
@@ -757,7 +778,7 @@ int elora::launch_decode_group(const LinearArgs *a, int n, hipStream_t stream)
     for (int i = 0; i < n; ++i) {
         DecodeCall &c = grp.call[i];
         const int max_rank = a[i].has_pool ? a[i].pool.max_rank : 1;
-        c.sh.w_scales = w8 ? static_cast<const uint16_t *>(a[i].w_scales) : nullptr;
+        c.sh.w_scales = wb < 16 ? static_cast<const uint16_t *>(a[i].w_scales) : nullptr;
         c.sh.T = T;
         c.sh.K = a[i].K;
         c.sh.N = a[i].N;
@@ -784,10 +805,10 @@ int elora::launch_decode_group(const LinearArgs *a, int n, hipStream_t stream)
     for (int i = n; i <= kGroupMax; ++i) grp.first[i] = first;
     dim3 grid(first), block(var.threads());
     profile_mark_begin(stream);
-    with_variant(var, [&](auto tt, auto wl, auto nw, auto q8c, auto w8c, auto ln) {
-        constexpr int TT = decltype(tt)::value, NW = decltype(nw)::value;
-        constexpr bool WL = decltype(wl)::value, Q8 = decltype(q8c)::value, W8 = decltype(w8c)::value, LN = decltype(ln)::value;
-        hipLaunchKernelGGL((decode_group_kernel<TT, WL, NW, Q8, W8, LN>), grid, block, ring_bytes(TT, WL, NW, W8), stream, grp);
+    with_variant(var, [&](auto tt, auto wl, auto nw, auto q8c, auto wbc, auto ln) {
+        constexpr int TT = decltype(tt)::value, NW = decltype(nw)::value, WB = decltype(wbc)::value;
+        constexpr bool WL = decltype(wl)::value, Q8 = decltype(q8c)::value, LN = decltype(ln)::value;
+        hipLaunchKernelGGL((decode_group_kernel<TT, WL, NW, Q8, WB == 8, LN, WB == 4>), grid, block, ring_bytes(TT, WL, NW, WB == 8), stream, grp);
         return 0;
     });
     ELORA_HIP_TRY(hipGetLastError());
@@ -822,14 +843,16 @@ extern "C" int elora_trace_clear()
 // 256 rows 88 / 171 / 167 us against 574 / 587 / 868 us.
 int elora::decode_passes(const elora_linear_desc_t &d)
 {
-    const bool w_ok = d.wfmt == ELORA_W_SAME || d.wfmt == ELORA_W_INT8_G32;
-    if (!(d.dtype == ELORA_BF16 && w_ok && d.n_tokens >= 1 && d.d_in % kChunk == 0 && d.d_out % 16 == 0)) return 0;
+    if (!(d.dtype == ELORA_BF16 && d.n_tokens >= 1 && d.d_in % kChunk == 0 && d.d_out % 16 == 0)) return 0;
     const int passes = (d.n_tokens + kDecodeMaxTokens - 1) / kDecodeMaxTokens;
     if (passes == 1) return 1;
     if (passes > kDecodeMaxPasses || g_pass_mode == 0) return 0;
     return passes;
 }
 
+// A 4-bit W takes this path like the others: on the GEMM path a call of few rows is 16 to 112 workgroups that each convert
+// a 256-column slab of W (20 rows: 4096 x 4096 190 us against 16, 4096 x 14336 189 against 27, 14336 x 4096 606 against
+// 32; 200 rows in four launches: 4096 x 4096 221 against 71, 4096 x 14336 221 against 161).
 bool elora::decode_eligible(const elora_linear_desc_t &d, int max_rank)
 {
     (void)max_rank;
@@ -851,7 +874,7 @@ void elora::decode_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
     const int passes = decode_passes(d);
     const int rows = (d.n_tokens + passes - 1) / passes;  // the longest row range
     DecodeShape sh = make_shape(rows, d.d_in, d.d_out, d.pool ? d.pool->max_rank : 1, d.pool && d.pool->q8, &var,
-                                d.wfmt == ELORA_W_INT8_G32 ? static_cast<const uint16_t *>(d.w_scales) : nullptr,
+                                weight_bits(d.wfmt), static_cast<const uint16_t *>(d.w_scales),
                                 !d.pool || ranks_fit_short_tail(d.pool->n_odd_ranks, d.pool->max_rank));
     plan->n_launches = passes;
     plan->split_k = sh.split;
@@ -865,7 +888,7 @@ int elora::launch_decode(const LinearArgs &a, const elora_plan_t &plan, hipStrea
     (void)plan;
     Variant var{1, true, 4};
     DecodeShape sh = make_shape(a.T, a.K, a.N, a.has_pool ? a.pool.max_rank : 1, a.has_pool && a.pool.q8 != 0, &var,
-                                a.wfmt == ELORA_W_INT8_G32 ? static_cast<const uint16_t *>(a.w_scales) : nullptr,
+                                weight_bits(a.wfmt), static_cast<const uint16_t *>(a.w_scales),
                                 !a.has_pool || ranks_fit_short_tail(a.pool.n_odd_ranks, a.pool.max_rank));
     float *mail = reinterpret_cast<float *>(a.ws + a.wsl.mail);
     float *vmail = reinterpret_cast<float *>(a.ws + a.wsl.vmail);
@@ -876,10 +899,10 @@ int elora::launch_decode(const LinearArgs &a, const elora_plan_t &plan, hipStrea
     int has_pool = a.has_pool ? 1 : 0;
     dim3 grid(sh.grid), block(var.threads());
     profile_mark_begin(stream);
-    with_variant(var, [&](auto tt, auto wl, auto nw, auto q8, auto w8, auto ln) {
-        constexpr int TT = decltype(tt)::value, NW = decltype(nw)::value;
-        constexpr bool WL = decltype(wl)::value, Q8 = decltype(q8)::value, W8 = decltype(w8)::value, LN = decltype(ln)::value;
-        hipLaunchKernelGGL((decode_kernel<TT, WL, NW, Q8, W8, LN>), grid, block, ring_bytes(TT, WL, NW, W8), stream, sh, x, W, a.pool, a.route, has_pool,
+    with_variant(var, [&](auto tt, auto wl, auto nw, auto q8, auto wb, auto ln) {
+        constexpr int TT = decltype(tt)::value, NW = decltype(nw)::value, WB = decltype(wb)::value;
+        constexpr bool WL = decltype(wl)::value, Q8 = decltype(q8)::value, LN = decltype(ln)::value;
+        hipLaunchKernelGGL((decode_kernel<TT, WL, NW, Q8, WB == 8, LN, WB == 4>), grid, block, ring_bytes(TT, WL, NW, WB == 8), stream, sh, x, W, a.pool, a.route, has_pool,
                            mail, vmail, sync, y);
         return 0;
     });

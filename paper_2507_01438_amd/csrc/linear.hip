@@ -538,7 +538,7 @@ int elora_linear_group_launches(const elora_linear_desc_t *descs, int n, int *n_
         }
         bool q8 = false;
         for (int i = 0; i < n; ++i) q8 = q8 || (descs[i].pool && descs[i].pool->q8);
-        if (decode_group_splits(descs[0].n_tokens, n, K, N, split, &wlds, descs[0].wfmt == ELORA_W_INT8_G32, q8)) sum = 1;
+        if (decode_group_splits(descs[0].n_tokens, n, K, N, split, &wlds, descs[0].wfmt, q8)) sum = 1;
     } else if (form == kGroupGemmShared) {
         sum -= 2 * (n - 1);  // one route and one shrink launch for all of them
     }
