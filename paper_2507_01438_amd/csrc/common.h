@@ -64,6 +64,8 @@ struct WsLayout {
     size_t v;          // float/bf16 shrink results of the generic and gemm kernels
     size_t wdeq;       // bf16 [d_out][d_in]: a call's dequantised copy of a 4-bit or 8-bit W (gemm_wcopy_bytes(); 0 bytes below
     size_t wdeq_bytes; //   the row count from which converting W once pays)
+    size_t part;       // fp32 sums of K-slices
+    size_t part_bytes; //   room for them (part_want(); less only in the library's own array, with fewer K-slices then)
     size_t total;
 };
 
@@ -71,9 +73,13 @@ constexpr int kDecodeMaxTokens = 64;  // rows the streaming (decode) kernels tak
 constexpr int kDecodeMaxPasses = 4;   // a call with more rows may run as this many launches of that kernel at most
 constexpr int kDecodeMaxSplit = 8;    // K-splits of the base contraction
 constexpr int kMaxRank = 256;
-constexpr int kSyncInts = 1024;       // ints in the workspace's counter area
+constexpr int kSyncInts = 1024;       // ints in the workspace's counter area (the decode kernel's are below 320)
+constexpr int kSyncShortRows = 320;   // GEMM path: how many rows sit in short runs (route counts, gemm clears)
+constexpr int kSyncTiles = 384;       // GEMM path: K-slices of a tile that have posted their sums
+constexpr int kSyncTileCount = kSyncInts - kSyncTiles;
 
 WsLayout ws_layout(int n_tokens, int d_in, int d_out, int max_rank, int wfmt);
+size_t part_want(int d_out);  // bytes the sums of K-slices of a call may take
 
 // ---- host-side pool object --------------------------------------------------
 
@@ -117,8 +123,7 @@ struct LinearArgs {
 int launch_generic(const LinearArgs &a, hipStream_t stream);
 int launch_decode(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream);
 int launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream);
-bool gemm_group_shares_shrink(const LinearArgs *a, int n);  // same x and routing tables, a pool each: one shrink launch serves all
-int launch_gemm_group(const LinearArgs *a, int n, hipStream_t stream);
+int launch_gemm_group(const LinearArgs *a, int n, hipStream_t stream);  // same x and routing tables, a pool each
 int launch_decode_group(const LinearArgs *a, int n, hipStream_t stream);  // -1: the calls do not fit into one launch
 bool decode_group_splits(int T, int n, const int *K, const int *N, int *split, bool *w_lds, int wfmt, bool q8);  // K-slices per call if they fit
 
@@ -240,6 +245,21 @@ __device__ __forceinline__ RowRoute resolve_row(int t, const RouteView &r, const
 
 typedef uint32_t elora_u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 elora_bf16x2 __attribute__((ext_vector_type(2)));
+typedef float elora_f32x2 __attribute__((ext_vector_type(2)));
+
+// eight 4-bit weights (element k in bits 4 k ..): fma(code, scale, -8 scale), exact in fp32, rounded once to bf16: the
+// value the matrix cores multiply on every path that takes this W
+__device__ __forceinline__ elora_u32x4 w4_to_bf16x8(uint32_t codes, float sc)
+{
+    const float c8 = -8.0f * sc;
+    const uint32_t lo = codes & 0x0f0f0f0fu, hi = (codes >> 4) & 0x0f0f0f0fu;
+    elora_u32x4 o;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        o[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(elora_f32x2{fmaf((float)((lo >> (8 * q)) & 0xffu), sc, c8),
+                                                                              fmaf((float)((hi >> (8 * q)) & 0xffu), sc, c8)}, elora_bf16x2));
+    return o;
+}
 
 // Sum over the 64 lanes of a wave, the same value in every lane, with cross-lane operations of the vector ALU only
 // (quad permutes and row mirrors inside rows of 16 lanes, then one lane of each row).  Unlike a shuffle it is no

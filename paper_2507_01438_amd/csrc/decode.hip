@@ -88,19 +88,6 @@ __device__ __forceinline__ uint32_t pack_bf16_pair(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(float_pair_t{lo, hi}, bf16_pair_t));
 }
 
-// eight 4-bit weights (element k in bits 4 k ..): fma(code, scale, -8 scale), exact in fp32, rounded once to bf16: the
-// value the matrix cores multiply on every path that takes this W
-__device__ __forceinline__ u32x4 w4_to_bf16x8(uint32_t codes, float sc)
-{
-    const float c8 = -8.0f * sc;
-    const uint32_t lo = codes & 0x0f0f0f0fu, hi = (codes >> 4) & 0x0f0f0f0fu;
-    u32x4 o;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        o[q] = pack_bf16_pair(fmaf((float)((lo >> (8 * q)) & 0xffu), sc, c8), fmaf((float)((hi >> (8 * q)) & 0xffu), sc, c8));
-    return o;
-}
-
 // sync area (ints) at the start of the workspace
 constexpr int kCntAll = 0;        // XCDs all of whose workgroups have finished
 constexpr int kCntXcd = 32;       // + 32 x (a cache line of its own): workgroups of XCD x that have finished, plus

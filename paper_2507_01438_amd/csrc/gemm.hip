@@ -1,12 +1,8 @@
 // Prefill / mixed path (many rows, MFMA-bound): bf16 activations; bf16, 4-bit or 8-bit base weights.
 //
-// Three launches per call (a 4-bit W with 768 rows or more and an 8-bit W are converted to bf16 once per call, into
-// the workspace, in the shrink's launch, and the bf16 kernel runs on the copy; below that the 4-bit W is converted
-// tile by tile inside the gemm):
-//   route   per row: validated pool slot and scale (Sec. 3.4: each request names its adapter)
-//   shrink  V[t, :] = bf16(s_t * A_i x_t) for every row, with the rows grouped by adapter inside each
-//           32-row tile ("u-batches", Sec. 3.4 / 4.3: rows that share an adapter are computed together):
-//           one masked MFMA pass per run of equal adapters
+// Three launches per call: route and shrink (shrink.hip), then the matrix product.  A 4-bit W with 768 rows or more and an
+// 8-bit W are converted to bf16 once per call, into the workspace, in the route's launch, and the bf16 kernel runs on the
+// copy; below that the 4-bit W is converted tile by tile inside the gemm:
 //   gemm    Y = X W^T (Sec. 3.4: the base product, shared by the whole batch) on 256 x 256 tiles with
 //           LDS-staged 64-wide K blocks and v_mfma_f32_32x32x16_bf16; the expand B_i v_t is appended to
 //           the K loop as extra K blocks: a run of rows that share an adapter takes rank (rounded up to
@@ -16,278 +12,11 @@
 //           instead).  While the next two blocks are base blocks the loop is straight-line code in which the
 //           LDS reads and the direct loads are dealt out by hand over the matrix instructions' slots.  The
 //           epilogue rounds once to bf16 and stores each row at its own position.
-#include <type_traits>
-
-#include "common.h"
+#include "gemm_common.h"
 
 using namespace elora;
 
 namespace {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float float2_t __attribute__((ext_vector_type(2)));
-
-// two floats -> packed bf16 pair, round-to-nearest-even (one v_cvt_pk_bf16_f32 on gfx950)
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
-{
-    bf16x2_t v = __builtin_convertvector(float2_t{lo, hi}, bf16x2_t);
-    return __builtin_bit_cast(uint32_t, v);
-}
-
-// Eight consecutive values of an adapter kept in 8-bit blocks (they lie in one block: ranks and d_in are multiples of
-// 8 there) as matrix-core operands: scale * code, exact in fp32, rounded once to bf16.  (The decode and generic
-// kernels multiply the exact products; here the adapter passes through the matrix cores like every other operand.)
-__device__ __forceinline__ u32x4 q8_to_bf16x8(u32x2 codes, float sc)
-{
-    u32x4 o;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const uint32_t w = codes[b >> 1] >> (16 * (b & 1));
-        o[b] = pack_bf16x2(sc * (float)(int8_t)(w & 0xffu), sc * (float)(int8_t)((w >> 8) & 0xffu));
-    }
-    return o;
-}
-
-// ------------------------------------------------------------------------------------------------
-// route
-// ------------------------------------------------------------------------------------------------
-__global__ void gemm_route_kernel(int T, RouteView route, PoolView pool, int has_pool, int32_t *row_slot,
-                                  float *row_scale)
-{
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
-    RowRoute r{-1, 0, 0.0f};
-    if (has_pool) r = resolve_row(t, route, pool, true);
-    row_slot[t] = r.slot;
-    row_scale[t] = r.scale;
-}
-
-// ------------------------------------------------------------------------------------------------
-// shrink.  Workgroups [0, n_tiles): one 32-row tile each, 4 waves split K, one masked MFMA pass per run
-// of >= kShortRun equal adapters.  Workgroups [n_tiles, n_tiles + T): one row each; a row that sits in a
-// shorter run (a decode row of a mixed batch, or the few rows a run leaves in a neighbouring tile) is
-// computed there with plain FMAs, straight from its own adapter, and all other row workgroups exit at once.
-// Either way V[t, :] = bf16(s_t * A_i x_t), with zeros beyond the rank up to Rpad and in rows without adapter.
-// ------------------------------------------------------------------------------------------------
-constexpr int kShrinkRows = 32;
-constexpr int kShrinkThreads = 256;
-constexpr int kShrinkColsPerPass = 64;  // rank columns per pass (4 MFMA column blocks of 16)
-constexpr int kShortRun = 8;
-constexpr int kShrinkUnroll = 4;        // K steps of 32 whose loads are issued together
-
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
-
-template <bool kQ8>
-__device__ __forceinline__ void shrink_block_t(int block, int T, int K, int n_tiles, const uint16_t *__restrict__ x,
-                                             const PoolView &pool, const int32_t *__restrict__ row_slot,
-                                             const float *__restrict__ row_scale, uint16_t *__restrict__ V, int Rpad,
-                                             int (&s_slot)[kShrinkRows], float (&s_red)[4][kShrinkRows][kShrinkColsPerPass + 1])
-{
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-
-    if (block >= n_tiles) {
-        // ---- one row of a short run ---------------------------------------------------------------
-        // (most rows of a batch of prompts sit in long runs and their workgroups end here: one load of the tile's slots
-        // and a vote, not a walk along the rows with a dependent load per step)
-        const int t = block - n_tiles;
-        const int r0 = t / kShrinkRows * kShrinkRows, r1 = min(r0 + kShrinkRows, T);
-        static_assert(kShrinkRows == 32, "one lane of a half-wave per row of the tile");
-        const int l = lane & 31;
-        const int mine = r0 + l < r1 ? row_slot[r0 + l] : INT32_MIN;
-        const int slot = __builtin_amdgcn_readlane(mine, t - r0);
-        const uint32_t same = (uint32_t)__ballot(mine == slot);       // (both halves of the wave vote alike)
-        const int p = t - r0;
-        const uint32_t below = ~same & ((1u << p) - 1u), above = ~same & ~((2u << p) - 1u);  // (2u << 31 == 0: nothing above)
-        const int lo = below ? 32 - __builtin_clz(below) : 0, hi = above ? __builtin_ctz(above) : 32;  // the run's piece inside this tile
-        if (hi - lo >= kShortRun) return;
-        float *vrow = &s_red[0][0][0];  // Rpad <= 256 floats
-        int rank = 0;
-        if (slot >= 0) {
-            rank = pool.meta[slot].rank;
-            const uint16_t *A = reinterpret_cast<const uint16_t *>(slot_A(pool, slot));
-            for (int j0 = 2 * wave; j0 < rank; j0 += 2 * 4) {
-                const bool two = (j0 + 1) < rank;
-                const int j1 = two ? j0 + 1 : j0;
-                float a0, a1;
-                if constexpr (kQ8) {
-                    const char *Ac = reinterpret_cast<const char *>(A);
-                    const uint16_t *As = slot_A_scales(pool, slot);
-                    shrink_pair_q8(Ac + (size_t)j0 * K, Ac + (size_t)j1 * K, As + (((size_t)j0 * K) >> 5), As + (((size_t)j1 * K) >> 5),
-                                   x + (size_t)t * K, K, lane, a0, a1);
-                } else
-                shrink_pair(A + (size_t)j0 * K, A + (size_t)j1 * K, x + (size_t)t * K, K, lane, a0, a1);
-                if (lane == 0) {
-                    vrow[j0] = a0;
-                    if (two) vrow[j0 + 1] = a1;
-                }
-            }
-        }
-        __syncthreads();
-        const float sc = slot >= 0 ? row_scale[t] : 0.0f;
-        for (int j = tid; j < Rpad; j += kShrinkThreads) V[(size_t)t * Rpad + j] = (j < rank) ? f32_to_bf16(sc * vrow[j]) : (uint16_t)0;
-        return;
-    }
-
-    // ---- 32-row tile ------------------------------------------------------------------------------
-    const int r0 = block * kShrinkRows;
-    if (tid < kShrinkRows) s_slot[tid] = (r0 + tid < T) ? row_slot[r0 + tid] : -1;
-    __syncthreads();
-    // rows of long runs: zero now, the passes below fill in the rank columns (short-run rows belong to
-    // their own workgroups)
-    for (int r = 0; r < kShrinkRows && r0 + r < T;) {
-        int e = r + 1;
-        while (e < kShrinkRows && s_slot[e] == s_slot[r]) ++e;
-        if (e - r >= kShortRun)
-            for (int q = tid; q < (e - r) * Rpad; q += kShrinkThreads) {
-                const int rr = r + q / Rpad;
-                if (r0 + rr < T) V[(size_t)(r0 + rr) * Rpad + q % Rpad] = 0;
-            }
-        r = e;
-    }
-    __syncthreads();
-
-    const int m = lane & 15, g = lane >> 4;
-    const int kq = K / 4;  // K % 64 == 0: each wave's quarter of K is a multiple of 16
-    const int kbeg = wave * kq, kend = kbeg + kq;
-
-    int run_start = 0;
-    while (run_start < kShrinkRows) {
-        const int slot = s_slot[run_start];
-        int run_end = run_start + 1;
-        while (run_end < kShrinkRows && s_slot[run_end] == slot) ++run_end;
-        if (slot >= 0 && run_end - run_start >= kShortRun) {
-            const int rank = pool.meta[slot].rank;
-            const uint16_t *A = reinterpret_cast<const uint16_t *>(slot_A(pool, slot));
-            const char *Ac = reinterpret_cast<const char *>(A);       // (8-bit blocks: codes, and their scales)
-            const uint16_t *As = kQ8 ? slot_A_scales(pool, slot) : nullptr;
-            for (int j0 = 0; j0 < rank; j0 += kShrinkColsPerPass) {
-                floatx4 acc[2][4];
-#pragma unroll
-                for (int a = 0; a < 2; ++a)
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-                const int ncb = min(4, (rank - j0 + 15) / 16);  // 16-column blocks in this pass
-                for (int k = kbeg; k < kend; k += 32 * kShrinkUnroll) {
-                    bf16x8 xa[kShrinkUnroll][2], ab[kShrinkUnroll][4];
-#pragma unroll
-                    for (int u = 0; u < kShrinkUnroll; ++u) {
-                        const int kk = k + u * 32 + g * 8;
-                        const bool kin = kk < kend;  // the tail of a quarter may be partly empty
-#pragma unroll
-                        for (int a = 0; a < 2; ++a) {
-                            const int row = min(r0 + a * 16 + m, T - 1);
-                            u32x4 v = *reinterpret_cast<const u32x4 *>(x + (size_t)row * K + (kin ? kk : kbeg));
-                            if (!kin) v = u32x4{0, 0, 0, 0};
-                            xa[u][a] = __builtin_bit_cast(bf16x8, v);
-                        }
-#pragma unroll
-                        for (int b = 0; b < 4; ++b) {
-                            const int j = j0 + b * 16 + m;
-                            u32x4 v{0, 0, 0, 0};
-                            if constexpr (kQ8) {
-                                if (b < ncb) {
-                                    const size_t e = (size_t)min(j, rank - 1) * K + (kin ? kk : kbeg);
-                                    v = q8_to_bf16x8(*reinterpret_cast<const u32x2 *>(Ac + e), fp16_to_f32(As[e >> 5]));
-                                }
-                            } else {
-                                if (b < ncb) v = *reinterpret_cast<const u32x4 *>(A + (size_t)min(j, rank - 1) * K + (kin ? kk : kbeg));
-                            }
-                            if (j >= rank) v = u32x4{0, 0, 0, 0};
-                            ab[u][b] = __builtin_bit_cast(bf16x8, v);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < kShrinkUnroll; ++u)
-#pragma unroll
-                        for (int a = 0; a < 2; ++a)
-#pragma unroll
-                            for (int b = 0; b < 4; ++b)
-                                if (b < ncb) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab[u][b], xa[u][a], acc[a][b], 0, 0, 0);
-                }
-                // MFMA rows = rank rows j (A-operand), columns = batch rows (B-operand):
-                // lane holds batch row (lane % 16), rank rows (lane / 16) * 4 + 0..3
-#pragma unroll
-                for (int a = 0; a < 2; ++a)
-#pragma unroll
-                    for (int b = 0; b < 4; ++b)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) s_red[wave][a * 16 + m][b * 16 + g * 4 + i] = acc[a][b][i];
-                __syncthreads();
-                for (int e = tid; e < kShrinkRows * kShrinkColsPerPass; e += kShrinkThreads) {
-                    const int r = e / kShrinkColsPerPass, c = e - r * kShrinkColsPerPass;
-                    const int j = j0 + c;
-                    if (r >= run_start && r < run_end && j < rank && r0 + r < T) {
-                        float s = s_red[0][r][c] + s_red[1][r][c] + s_red[2][r][c] + s_red[3][r][c];
-                        V[(size_t)(r0 + r) * Rpad + j] = f32_to_bf16(row_scale[r0 + r] * s);
-                    }
-                }
-                __syncthreads();
-            }
-        }
-        run_start = run_end;
-    }
-}
-
-// (the pool's storage format is a property of the launch: decided at run time inside the kernel, the bf16 shrink of two
-// projections in one launch took 114 instead of 83 us)
-template <bool kQ8>
-__device__ __forceinline__ void shrink_block(int block, int T, int K, int n_tiles, const uint16_t *__restrict__ x,
-                                             const PoolView &pool, const int32_t *__restrict__ row_slot,
-                                             const float *__restrict__ row_scale, uint16_t *__restrict__ V, int Rpad)
-{
-    __shared__ int s_slot[kShrinkRows];
-    __shared__ float s_red[4][kShrinkRows][kShrinkColsPerPass + 1];
-    shrink_block_t<kQ8>(block, T, K, n_tiles, x, pool, row_slot, row_scale, V, Rpad, s_slot, s_red);
-}
-
-template <bool kQ8>
-__global__ __launch_bounds__(kShrinkThreads) void sgmv_shrink_kernel(int T, int K, int n_tiles,
-                                                                     const uint16_t *__restrict__ x, PoolView pool,
-                                                                     const int32_t *__restrict__ row_slot,
-                                                                     const float *__restrict__ row_scale,
-                                                                     uint16_t *__restrict__ V, int Rpad)
-{
-    shrink_block<kQ8>((int)blockIdx.x, T, K, n_tiles, x, pool, row_slot, row_scale, V, Rpad);
-}
-
-// The shrink of several projections that read the same x (q / k / v, gate / up: Sec. 4.3 builds base model and adapters
-// of a batch into one graph; Sec. 5.3: the adapters target Q, K, V, Up, Down) in one launch: block `blk` of projection p
-// is workgroup ((blk / 8) * n + p) * 8 + blk % 8, so the workgroups that read the same rows of x run next to each other
-// on one XCD (workgroup b runs on XCD b % 8) and all but the first find those rows in its L2.
-constexpr int kShrinkMulti = 3;
-struct ShrinkMulti {
-    int n;
-    PoolView pool[kShrinkMulti];
-    int32_t *row_slot[kShrinkMulti];
-    float *row_scale[kShrinkMulti];
-    uint16_t *V[kShrinkMulti];
-    int Rpad[kShrinkMulti];
-};
-// route of several projections with the same routing tables (each against its own pool) in one launch
-__global__ void gemm_route_multi_kernel(int T, RouteView route, ShrinkMulti sm)
-{
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
-    for (int p = 0; p < sm.n; ++p) {
-        const RowRoute r = resolve_row(t, route, sm.pool[p], true);
-        sm.row_slot[p][t] = r.slot;
-        sm.row_scale[p][t] = r.scale;
-    }
-}
-template <bool kQ8>
-__global__ __launch_bounds__(kShrinkThreads) void sgmv_shrink_multi_kernel(int T, int K, int n_tiles, const uint16_t *__restrict__ x,
-                                                                           ShrinkMulti sm)
-{
-    const int xcd = blockIdx.x % 8, j = blockIdx.x / 8;
-    const int p = j % sm.n, blk = (j / sm.n) * 8 + xcd;
-    if (blk >= n_tiles + T) return;
-    shrink_block<kQ8>(blk, T, K, n_tiles, x, sm.pool[p], sm.row_slot[p], sm.row_scale[p], sm.V[p], sm.Rpad[p]);
-}
 
 // ------------------------------------------------------------------------------------------------
 // gemm
@@ -302,7 +31,7 @@ constexpr int kPieces = BM * (BK / 8) / kGemmThreads;  // 16-byte pieces per ope
 // (the direct global->LDS loads can only fill LDS contiguously, 1 KiB per wave and instruction).
 __device__ __forceinline__ int lds_pos(int r, int c) { return r * BK + ((c ^ ((r >> 1) & 7)) << 3); }
 constexpr int kMaxRuns = BM;
-constexpr int kXcds = 8, kSuperM = 4, kSuperN = 8;  // tile block per XCD (32 compute units each)
+constexpr int kSuperM = 4, kSuperN = 8;  // tile block per XCD (32 compute units each)
 
 int gemm_grid(int tiles_m, int tiles_n) { return (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds; }
 
@@ -316,6 +45,7 @@ struct GemmArgs {
     int Rpad;
     uint16_t *y;
     int tiles_m, tiles_n;
+    int *sync;  // the workspace's counters (the count of rows in short runs goes back to zero here)
 };
 
 struct Run {
@@ -330,8 +60,6 @@ struct Item {
     uint16_t pad;
 };
 constexpr int kMaxItems = kMaxRuns * (kMaxRank / BK);
-
-template <int V> using ic = std::integral_constant<int, V>;
 
 // Short runs (decode rows of a mixed batch, short prompts).  As columns of an expand block a run costs its rank's
 // share of a whole 256 x 256 x 64 block whatever its length; a run of at most 32 rows is instead added after the K
@@ -382,6 +110,7 @@ __global__ __launch_bounds__(kGemmThreads) void lora_gemm_kernel(GemmArgs ga, Po
     const int n_valid = ga.tiles_m * ga.tiles_n, per_xcd = (n_valid + kXcds - 1) / kXcds;
     const int xcd = blockIdx.x % kXcds, seq = blockIdx.x / kXcds;
     int pos = xcd * per_xcd + seq;
+    if (blockIdx.x == 0 && tid == 0) ga.sync[kSyncShortRows] = 0;  // (what read it, the shrink, is over)
     if (seq >= per_xcd || pos >= n_valid) return;
     const int sc = pos / (ga.tiles_m * kSuperN);            // only the last column of blocks can be narrower than 8
     const int sw = min(kSuperN, ga.tiles_n - sc * kSuperN);
@@ -924,90 +653,7 @@ __global__ __launch_bounds__(kGemmThreads) void lora_gemm_kernel(GemmArgs ga, Po
     else store_tile(std::true_type{});
 }
 
-int round_up(int v, int m) { return (v + m - 1) / m * m; }
-
-// ------------------------------------------------------------------------------------------------
-// 4-bit W, many rows: W is converted to bf16 once per call, into the workspace, and the bf16 kernel runs on the copy.
-// Converted tile by tile inside the GEMM (WFMT = ELORA_W_INT4_G32 above) every row tile of the batch repeats the
-// conversion of the W tiles it meets, on the same vector units that feed the matrix cores, and the kernel runs at half
-// the bf16 rate; the copy costs one pass over W at memory speed (d_out x d_in x 2.6 bytes), which that saving repays
-// from a few hundred rows on.  Same arithmetic as park_codes: w = fma(code, scale, -8 scale) in fp32, rounded once.
-// One thread per 8 weights (4 bytes of codes in, 16 bytes out; four threads share a group's fp16 scale): a wave
-// reads 256 and writes 1024 consecutive bytes.
-// ------------------------------------------------------------------------------------------------
 int g_dequant_first_rows = 768;  // (elora_debug_w4_copy_rows)
-
-// 8-bit W (groups of 32 along d_in, w = scale * code: exact in fp32, rounded once to bf16): the same copy, one thread
-// per 8 weights (8 bytes of codes in, 16 bytes out).
-__device__ __forceinline__ void w8_dequant_piece(size_t i, size_t n_pieces, const uint32_t *__restrict__ codes,
-                                                 const uint16_t *__restrict__ scales, u32x4 *__restrict__ out)
-{
-    if (i >= n_pieces) return;
-    const u32x2 q = reinterpret_cast<const u32x2 *>(codes)[i];
-    const float sc = fp16_to_f32(scales[i >> 2]);
-    u32x4 o;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const uint32_t w = q[b >> 1] >> (16 * (b & 1));
-        o[b] = pack_bf16x2(sc * (float)(int8_t)(w & 0xffu), sc * (float)(int8_t)((w >> 8) & 0xffu));
-    }
-    out[i] = o;
-}
-
-__device__ __forceinline__ void w4_dequant_piece(size_t i, size_t n_pieces, const uint32_t *__restrict__ codes,
-                                                 const uint16_t *__restrict__ scales, u32x4 *__restrict__ out)
-{
-    if (i >= n_pieces) return;
-    const uint32_t q = codes[i];
-    const float sc = fp16_to_f32(scales[i >> 2]), c8 = -8.0f * sc;
-    const uint32_t lo = q & 0x0f0f0f0fu, hi = (q >> 4) & 0x0f0f0f0fu;
-    u32x4 o;
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-        o[b] = pack_bf16x2(fmaf((float)((lo >> (8 * b)) & 0xffu), sc, c8), fmaf((float)((hi >> (8 * b)) & 0xffu), sc, c8));
-    out[i] = o;
-}
-
-template <int WFMT>
-__device__ __forceinline__ void w_dequant_piece(size_t i, size_t n_pieces, const uint32_t *__restrict__ codes,
-                                                const uint16_t *__restrict__ scales, u32x4 *__restrict__ out)
-{
-    if (WFMT == ELORA_W_INT8_G32) w8_dequant_piece(i, n_pieces, codes, scales, out);
-    else w4_dequant_piece(i, n_pieces, codes, scales, out);
-}
-
-template <int WFMT>
-__global__ __launch_bounds__(256) void w_dequant_kernel(size_t n_pieces, const uint32_t *__restrict__ codes,
-                                                        const uint16_t *__restrict__ scales, u32x4 *__restrict__ out)
-{
-    w_dequant_piece<WFMT>((size_t)blockIdx.x * 256 + threadIdx.x, n_pieces, codes, scales, out);
-}
-
-// The shrink and the copy of W do not depend on each other, and the shrink of a few hundred rows is a few dozen
-// workgroups that wait for memory most of the time: in one launch (the shrink's workgroups first, so that they start
-// at once) the copy fills the rest of the device meanwhile and the call is one launch and one kernel's time shorter.
-static_assert(kShrinkThreads == 256, "one block shape for both halves");
-constexpr int kCopyPerThread = 8;
-template <int WFMT, bool kQ8>
-__global__ __launch_bounds__(kShrinkThreads) void sgmv_shrink_w_dequant_kernel(int n_shrink, int T, int K, int n_tiles,
-                                                                                const uint16_t *__restrict__ x, PoolView pool,
-                                                                                const int32_t *__restrict__ row_slot,
-                                                                                const float *__restrict__ row_scale,
-                                                                                uint16_t *__restrict__ V, int Rpad, size_t n_pieces,
-                                                                                const uint32_t *__restrict__ codes,
-                                                                                const uint16_t *__restrict__ scales,
-                                                                                u32x4 *__restrict__ out)
-{
-    if ((int)blockIdx.x < n_shrink) {
-        shrink_block<kQ8>((int)blockIdx.x, T, K, n_tiles, x, pool, row_slot, row_scale, V, Rpad);
-        return;
-    }
-    // (the shrink's LDS counts for these workgroups too and halves how many of them a compute unit holds: each takes
-    // kCopyPerThread pieces per thread, their loads under way together)
-    const size_t base = (size_t)(blockIdx.x - n_shrink) * (256 * kCopyPerThread) + threadIdx.x;
-#pragma unroll
-    for (int u = 0; u < kCopyPerThread; ++u) w_dequant_piece<WFMT>(base + (size_t)u * 256, n_pieces, codes, scales, out);
-}
 
 }  // namespace
 
@@ -1024,7 +670,7 @@ bool elora::gemm_eligible(const elora_linear_desc_t &d, int max_rank)
 void elora::gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
 {
     const bool copy_first = gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0;
-    plan->n_launches = (d.pool ? 3 : 2) + (copy_first && !d.pool ? 1 : 0);  // (with a pool the copy shares the shrink's launch)
+    plan->n_launches = (d.pool ? 3 : 1) + (copy_first && !d.pool ? 1 : 0);  // (with a pool the copy shares the route's launch)
     plan->tile_rows = BM;
     plan->tile_cols = BN;
     plan->grid = gemm_grid((d.n_tokens + BM - 1) / BM, (d.d_out + BN - 1) / BN);
@@ -1049,44 +695,30 @@ size_t elora::gemm_wcopy_bytes(int wfmt, int n_tokens, int d_in, int d_out)
 size_t elora::gemm_v_bytes(int n_tokens, int max_rank) { return (size_t)n_tokens * round_up(max_rank, BK) * sizeof(uint16_t); }
 
 namespace {
-// what follows route and shrink: (the copy of a 4-bit W and) the GEMM with the expand in its K loop
-int launch_gemm_back(const LinearArgs &a, hipStream_t stream, bool copy_done = false)
+int enqueue_gemm(const LinearArgs &a, hipStream_t stream)
 {
-    int32_t *row_slot = reinterpret_cast<int32_t *>(a.ws + a.wsl.row_slot);
-    uint16_t *V = reinterpret_cast<uint16_t *>(a.ws + a.wsl.v);
-    const int Rpad = round_up(a.pool.max_rank, BK);
-    const int has_pool = a.has_pool ? 1 : 0;
-    // 4-bit W and enough rows: the bf16 kernel on a copy made now
-    const bool copy_first = a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
-    if (copy_first && !copy_done) {
-        const size_t n_pieces = (size_t)a.N * (size_t)(a.K / 8);
-        const dim3 cgrid((unsigned)((n_pieces + 255) / 256));
-        if (a.wfmt == ELORA_W_INT8_G32)
-            hipLaunchKernelGGL(w_dequant_kernel<ELORA_W_INT8_G32>, cgrid, dim3(256), 0, stream, n_pieces, static_cast<const uint32_t *>(a.W),
-                               static_cast<const uint16_t *>(a.w_scales), reinterpret_cast<u32x4 *>(a.ws + a.wsl.wdeq));
-        else
-            hipLaunchKernelGGL(w_dequant_kernel<ELORA_W_INT4_G32>, cgrid, dim3(256), 0, stream, n_pieces, static_cast<const uint32_t *>(a.W),
-                               static_cast<const uint16_t *>(a.w_scales), reinterpret_cast<u32x4 *>(a.ws + a.wsl.wdeq));
-        ELORA_HIP_TRY(hipGetLastError());
-    }
-    if (a.wfmt == ELORA_W_INT8_G32 && !copy_first) return ELORA_E_DTYPE;  // (no tile-by-tile conversion for 8-bit W)
+    // 4-bit or 8-bit W and enough rows: the bf16 kernel on the call's copy
+    const bool copied = a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
+    if (a.wfmt == ELORA_W_INT8_G32 && !copied) return ELORA_E_DTYPE;  // (no tile-by-tile conversion for 8-bit W)
     GemmArgs ga;
     ga.T = a.T;
     ga.K = a.K;
     ga.N = a.N;
     ga.x = static_cast<const uint16_t *>(a.x);
-    ga.W = copy_first ? static_cast<const void *>(a.ws + a.wsl.wdeq) : a.W;
+    ga.W = copied ? static_cast<const void *>(a.ws + a.wsl.wdeq) : a.W;
     ga.w_scales = static_cast<const uint16_t *>(a.w_scales);
-    ga.row_slot = row_slot;
-    ga.V = V;
-    ga.Rpad = Rpad;
+    ga.row_slot = reinterpret_cast<int32_t *>(a.ws + a.wsl.row_slot);
+    ga.V = reinterpret_cast<uint16_t *>(a.ws + a.wsl.v);
+    ga.Rpad = round_up(a.pool.max_rank, kRankPad);
     ga.y = static_cast<uint16_t *>(a.y);
     ga.tiles_m = (a.T + BM - 1) / BM;
     ga.tiles_n = (a.N + BN - 1) / BN;
+    ga.sync = reinterpret_cast<int *>(a.ws + a.wsl.sync);
+    const int has_pool = a.has_pool ? 1 : 0;
     const size_t lds = (size_t)2 * kStageElems * sizeof(uint16_t);
     dim3 grid(gemm_grid(ga.tiles_m, ga.tiles_n)), block(kGemmThreads);
     profile_mark_begin(stream);
-    if (a.wfmt == ELORA_W_SAME || copy_first) {
+    if (a.wfmt == ELORA_W_SAME || copied) {
         static bool attr_done = false;
         if (!attr_done) {
             ELORA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&lora_gemm_kernel<ELORA_W_SAME>),
@@ -1112,88 +744,29 @@ int launch_gemm_back(const LinearArgs &a, hipStream_t stream, bool copy_done = f
 int elora::launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream)
 {
     (void)plan;
-    int32_t *row_slot = reinterpret_cast<int32_t *>(a.ws + a.wsl.row_slot);
-    float *row_scale = reinterpret_cast<float *>(a.ws + a.wsl.row_scale);
-    uint16_t *V = reinterpret_cast<uint16_t *>(a.ws + a.wsl.v);
-    const int Rpad = round_up(a.pool.max_rank, BK);
-    const int has_pool = a.has_pool ? 1 : 0;
-    hipLaunchKernelGGL(gemm_route_kernel, dim3((a.T + 255) / 256), dim3(256), 0, stream, a.T, a.route, a.pool, has_pool,
-                       row_slot, row_scale);
-    ELORA_HIP_TRY(hipGetLastError());
-    bool copy_done = false;
-    if (a.has_pool) {
-        const int n_tiles = (a.T + kShrinkRows - 1) / kShrinkRows;
-        const size_t n_pieces = (size_t)a.N * (size_t)(a.K / 8), n_copy = (n_pieces + 256 * kCopyPerThread - 1) / (256 * kCopyPerThread);
-        if (a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0 && n_copy + (size_t)(n_tiles + a.T) < (size_t)1 << 31) {
-            const dim3 mgrid((unsigned)(n_tiles + a.T + n_copy));
-            auto go = [&](auto kern) {
-                hipLaunchKernelGGL(kern, mgrid, dim3(kShrinkThreads), 0, stream, n_tiles + a.T, a.T, a.K, n_tiles,
-                                   static_cast<const uint16_t *>(a.x), a.pool, row_slot, row_scale, V, Rpad, n_pieces,
-                                   static_cast<const uint32_t *>(a.W), static_cast<const uint16_t *>(a.w_scales),
-                                   reinterpret_cast<u32x4 *>(a.ws + a.wsl.wdeq));
-            };
-            if (a.wfmt == ELORA_W_INT8_G32) {
-                if (a.pool.q8) go(sgmv_shrink_w_dequant_kernel<ELORA_W_INT8_G32, true>);
-                else go(sgmv_shrink_w_dequant_kernel<ELORA_W_INT8_G32, false>);
-            } else {
-                if (a.pool.q8) go(sgmv_shrink_w_dequant_kernel<ELORA_W_INT4_G32, true>);
-                else go(sgmv_shrink_w_dequant_kernel<ELORA_W_INT4_G32, false>);
-            }
-            copy_done = true;
-        } else if (a.pool.q8) {
-            hipLaunchKernelGGL(sgmv_shrink_kernel<true>, dim3(n_tiles + a.T), dim3(kShrinkThreads), 0, stream, a.T, a.K, n_tiles,
-                               static_cast<const uint16_t *>(a.x), a.pool, row_slot, row_scale, V, Rpad);
-        } else {
-            hipLaunchKernelGGL(sgmv_shrink_kernel<false>, dim3(n_tiles + a.T), dim3(kShrinkThreads), 0, stream, a.T, a.K, n_tiles,
-                               static_cast<const uint16_t *>(a.x), a.pool, row_slot, row_scale, V, Rpad);
-        }
-        ELORA_HIP_TRY(hipGetLastError());
-    }
-    return launch_gemm_back(a, stream, copy_done);
+    ShrinkArgs s;
+    shrink_args(s, &a, 1);
+    const bool copy = a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
+    int rc = launch_route(s, &a, copy, stream);
+    if (rc == ELORA_OK && a.has_pool) rc = launch_shrink(s, stream);
+    if (rc != ELORA_OK) return rc;
+    return enqueue_gemm(a, stream);
 }
 
 // Two or three calls of this path that read the same x with the same routing tables (each with a pool of its own):
 // one route launch, ONE shrink launch over the adapters of all of them, then each call's GEMM.
-bool elora::gemm_group_shares_shrink(const LinearArgs *a, int n)
-{
-    if (n < 2 || n > kShrinkMulti) return false;
-    for (int i = 0; i < n; ++i) {
-        if (!a[i].has_pool || a[i].x != a[0].x || a[i].T != a[0].T || a[i].K != a[0].K) return false;
-        if ((a[i].pool.q8 != 0) != (a[0].pool.q8 != 0)) return false;  // (one storage format of the pools per shrink launch)
-        const RouteView &r = a[i].route, &r0 = a[0].route;
-        if (r.adapter_idx != r0.adapter_idx || r.seg_offsets != r0.seg_offsets || r.seg_adapter != r0.seg_adapter ||
-            r.n_segments != r0.n_segments || r.scales != r0.scales)
-            return false;
-    }
-    return true;
-}
-
 int elora::launch_gemm_group(const LinearArgs *a, int n, hipStream_t stream)
 {
-    ShrinkMulti sm;
-    sm.n = n;
-    for (int i = 0; i < n; ++i) {
-        sm.pool[i] = a[i].pool;
-        sm.row_slot[i] = reinterpret_cast<int32_t *>(a[i].ws + a[i].wsl.row_slot);
-        sm.row_scale[i] = reinterpret_cast<float *>(a[i].ws + a[i].wsl.row_scale);
-        sm.V[i] = reinterpret_cast<uint16_t *>(a[i].ws + a[i].wsl.v);
-        sm.Rpad[i] = round_up(a[i].pool.max_rank, BK);
+    ShrinkArgs s;
+    shrink_args(s, a, n);
+    auto copied = [&](int i) { return a[i].wfmt != ELORA_W_SAME && a[i].wsl.wdeq_bytes != 0; };
+    int rc = launch_route(s, a, copied(0), stream);
+    if (rc == ELORA_OK) rc = launch_shrink(s, stream);
+    for (int i = 0; i < n && rc == ELORA_OK; ++i) {
+        LinearArgs base = a[i];
+        base.has_pool = false;  // (the copy alone)
+        if (i > 0 && copied(i)) rc = launch_route(s, &base, true, stream);
+        if (rc == ELORA_OK) rc = enqueue_gemm(a[i], stream);
     }
-    const int T = a[0].T, K = a[0].K;
-    hipLaunchKernelGGL(gemm_route_multi_kernel, dim3((T + 255) / 256), dim3(256), 0, stream, T, a[0].route, sm);
-    ELORA_HIP_TRY(hipGetLastError());
-    const int n_tiles = (T + kShrinkRows - 1) / kShrinkRows;
-    const int per = (n_tiles + T + 7) / 8 * 8;
-    if (a[0].pool.q8)
-        hipLaunchKernelGGL(sgmv_shrink_multi_kernel<true>, dim3(per * n), dim3(kShrinkThreads), 0, stream, T, K, n_tiles,
-                           static_cast<const uint16_t *>(a[0].x), sm);
-    else
-        hipLaunchKernelGGL(sgmv_shrink_multi_kernel<false>, dim3(per * n), dim3(kShrinkThreads), 0, stream, T, K, n_tiles,
-                           static_cast<const uint16_t *>(a[0].x), sm);
-    ELORA_HIP_TRY(hipGetLastError());
-    for (int i = 0; i < n; ++i) {
-        const int rc = launch_gemm_back(a[i], stream);
-        if (rc != ELORA_OK) return rc;
-    }
-    return ELORA_OK;
+    return rc;
 }

@@ -1,0 +1,73 @@
+// What the kernels of the GEMM path (route, shrink, matrix products) share.
+#pragma once
+
+#include <type_traits>
+
+#include "common.h"
+
+namespace elora {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+
+template <int V> using ic = std::integral_constant<int, V>;
+
+constexpr int kXcds = 8;     // workgroup b runs on XCD b % 8
+constexpr int kRankPad = 64; // rows of V (the shrink results) are padded to this many rank entries, with zeros
+
+inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
+
+// two floats -> packed bf16 pair, round-to-nearest-even (one v_cvt_pk_bf16_f32 on gfx950)
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
+{
+    bf16x2_t v = __builtin_convertvector(float2_t{lo, hi}, bf16x2_t);
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+// Eight consecutive values of an adapter kept in 8-bit blocks (they lie in one block: ranks and d_in are multiples of
+// 8 there) as matrix-core operands: scale * code, exact in fp32, rounded once to bf16.  (The decode and generic
+// kernels multiply the exact products; here the adapter passes through the matrix cores like every other operand.)
+__device__ __forceinline__ u32x4 q8_to_bf16x8(u32x2 codes, float sc)
+{
+    u32x4 o;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const uint32_t w = codes[b >> 1] >> (16 * (b & 1));
+        o[b] = pack_bf16x2(sc * (float)(int8_t)(w & 0xffu), sc * (float)(int8_t)((w >> 8) & 0xffu));
+    }
+    return o;
+}
+
+// The projections a shrink launch serves: one, or two or three that read the same x (q / k / v, gate / up), each with
+// a pool and a workspace of its own.
+constexpr int kShrinkMulti = 3;
+struct ShrinkProj {
+    PoolView pool;
+    int32_t *row_slot;   // [T] from the route kernel
+    float *row_scale;    // [T]
+    int32_t *short_rows; // [T]: the rows that sit in runs shorter than kShortRun, in any order
+    uint16_t *V;         // [T][Rpad] bf16(s * A_i x_t), zeros beyond the rank and in rows without adapter
+    float *part;         // fp32 sums of the K-slices: [tile][slice][kShrinkRows][Rpad]
+    int *sync;           // the workspace's counters
+    int Rpad;
+};
+struct ShrinkArgs {
+    int n;               // projections
+    int T, K;
+    int n_tiles;         // kShrinkRows-row tiles
+    int ks;              // K-slices per tile
+    int wgs_per_xcd;     // workgroups per projection and XCD
+    const uint16_t *x;
+    ShrinkProj proj[kShrinkMulti];
+};
+
+void shrink_args(ShrinkArgs &s, const LinearArgs *a, int n);      // everything the three launches below need
+int launch_route(const ShrinkArgs &s, const LinearArgs *a, bool copy, hipStream_t stream);  // copy: and the bf16 copy of a[0]'s 4-bit or 8-bit W into a[0].wsl.wdeq
+int launch_shrink(const ShrinkArgs &s, hipStream_t stream);
+
+}  // namespace elora

@@ -74,11 +74,23 @@ WsLayout elora::ws_layout(int T, int K, int N, int R, int wfmt)
     l.wdeq = off;
     l.wdeq_bytes = gemm_wcopy_bytes(wfmt, T, K, N);
     off += align_up(l.wdeq_bytes);
-    l.total = off;
+    l.part = off;
+    l.part_bytes = part_want(N);
+    l.total = off + align_up(l.part_bytes);
     return l;
 }
 
-static int validate(const elora_linear_desc_t *d, WsLayout *wsl_out)
+// Sums of K-slices (fp32): the matrix products of a few hundred rows cut K so that 256 tiles of up to 224 x 128 sums are
+// under way (fewer where d_out is small), the shrink at most 1024 tiles of 32 rows x 64 entries.
+size_t elora::part_want(int d_out)
+{
+    const size_t by_columns = ((size_t)d_out + 127) / 128 * 128 * 8192, most = (size_t)256 * 224 * 128 * sizeof(float);
+    const size_t shrink = (size_t)1024 * 32 * 64 * sizeof(float);
+    return by_columns > most ? most : by_columns > shrink ? by_columns : shrink;
+}
+
+// part_optional: a workspace that ends before or inside the room for the sums of K-slices will do (fewer slices then)
+static int validate(const elora_linear_desc_t *d, WsLayout *wsl_out, bool part_optional = false)
 {
     if (d == nullptr) return ELORA_E_NULL;
     if (d->dtype != ELORA_F32 && d->dtype != ELORA_BF16) return ELORA_E_DTYPE;
@@ -105,6 +117,11 @@ static int validate(const elora_linear_desc_t *d, WsLayout *wsl_out)
     if (d->w_scales != nullptr && !aligned16(d->w_scales)) return ELORA_E_ALIGN;
     if (reinterpret_cast<uintptr_t>(d->workspace) % kAlign) return ELORA_E_ALIGN;
     WsLayout wsl = ws_layout(d->n_tokens, d->d_in, d->d_out, max_rank, d->wfmt);
+    if (part_optional && d->workspace_bytes < wsl.total) {
+        if (d->workspace_bytes < wsl.part) return ELORA_E_STORAGE;
+        wsl.part_bytes = d->workspace_bytes - wsl.part;
+        wsl.total = d->workspace_bytes;
+    }
     if (d->workspace_bytes < wsl.total) return ELORA_E_STORAGE;
     const auto bound = g_ws_d_out.find(d->workspace);
     if (bound != g_ws_d_out.end() && bound->second != d->d_out) return ELORA_E_STORAGE;
@@ -417,15 +434,16 @@ int elora_batched_lora_linear_noalloc(const elora_linear_desc_t *desc, elora_str
     d.workspace = st.ptr;
     d.workspace_bytes = kScratchBytes;
     WsLayout wsl;
-    const int rc = validate(&d, &wsl);  // E_STORAGE: the call needs more than the array holds
+    const int rc = validate(&d, &wsl, true);  // E_STORAGE: the call needs more than the array holds
     if (rc != ELORA_OK) return rc;
     if (d.n_tokens == 0) return ELORA_OK;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     // The idle state (counters zero, everything else all-ones) is written by a fill kernel on the call's stream: over
     // what this call's layout covers before the first call, and again, over everything calls have written so far, when
-    // d_out changes (what a call with another d_out wrote may lie where this one's mailboxes are).
-    if (st.idle < wsl.total || st.d_out != d.d_out) {
-        const size_t bytes = st.used > wsl.total ? st.used : wsl.total;
+    // d_out changes (what a call with another d_out wrote may lie where this one's mailboxes are).  (The sums of K-slices,
+    // the last part of the layout, need no idle state of their own.)
+    if (st.idle < wsl.part || st.d_out != d.d_out) {
+        const size_t bytes = st.used > wsl.part ? st.used : wsl.part;
         const size_t n_words = bytes / sizeof(uint32_t), blocks = (n_words + 255) / 256;
         hipLaunchKernelGGL(ws_init_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, stream,
                            reinterpret_cast<uint32_t *>(st.ptr), n_words, (size_t)kSyncInts);
@@ -433,7 +451,10 @@ int elora_batched_lora_linear_noalloc(const elora_linear_desc_t *desc, elora_str
         st.idle = bytes;
         st.d_out = d.d_out;
     }
-    if (wsl.total > st.used) st.used = wsl.total;
+    elora_plan_t plan;
+    make_plan(&d, &plan);
+    const size_t writes = plan.path == ELORA_PATH_GEMM ? wsl.total : wsl.part;
+    if (writes > st.used) st.used = writes;
     return enqueue_linear(&d, wsl, stream);
 }
 

@@ -1,0 +1,37 @@
+"""The GEMM path's shrink at the sizes where it can go wrong: tiles where two or more runs meet, K-slices whose sums meet in
+memory, ranks around its passes of 16, 32 and 64 columns, rows without adapter, runs around the length of 8 below which
+rows are computed one by one; bf16 pools and pools of 8-bit blocks, against the oracle.  (The shrink results are rounded to
+bf16 like every matrix-core operand: 2^-9 of the adapter term, far inside the layer's 1e-2.)"""
+import numpy as np
+import pytest
+
+from gpu_harness import DeviceCase, assert_close
+from paper_2507_01438_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+GEMM = 2
+
+SHAPES = [
+    # (K, pool, ranks, segment lengths, adapter-less segments)
+    (64, 3, (8, 16), [32, 33, 7, 8, 20], ()),                       # one span of K: three of the four waves have none
+    (576, 5, (8, 16, 24), [9, 7, 8, 8, 40, 3, 25], (2,)),           # runs of 7, 8 and 9; three runs in one tile
+    (2048, 4, (32, 24), [300], ()),                                 # K-slices
+    (4096, 4, (32, 8), [50, 14, 100, 1, 1, 1, 60], (5,)),           # K-slices, tiles with two runs, single rows
+    (4160, 3, (64, 40), [70, 90, 129], ()),                         # 65 spans on four slices; ranks up to 64
+    (2048, 3, (136, 72, 8), [40, 260], ()),                         # ranks above one pass
+    (14336, 3, (16,), [45, 230], (0,)),
+]
+
+
+@pytest.mark.parametrize("q8", [False, True])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_shrink_shapes(shape, q8):
+    K, pool, ranks, lengths, none = shape
+    w = I.small_workload(1700 + K, I.BF16, K, 96, sum(lengths), pool, ranks, segments=lengths, no_adapter_rows=none)
+    case = DeviceCase(w, w.projections[0], q8=q8)
+    y = case.run(force_path=GEMM)
+    assert case.last_plan.path == GEMM
+    assert_close(y, case.reference(), case.base_reference(), f"{shape}")
+    assert np.array_equal(y, case.run(force_path=GEMM))     # fixed summation order, counters back at zero
+    assert case.pool.poll_error() == (0, -1)
+    case.close()
