@@ -443,6 +443,12 @@ int elora_debug_decode_passes(int mode);
 int elora_debug_decode_wide(int mode);
 
 /*
+ * Testing hook: the kernel of the GEMM path for a few hundred rows.  mode -1: where it is the faster one (default), 0:
+ * never, 1: for every call of that path; tiles_m, slices: row tiles and K-slices (up to 8) to use, 0: as chosen.
+ */
+int elora_debug_band(int mode, int tiles_m, int slices);
+
+/*
  * Test hook: 0 makes every workgroup of the decode kernel walk its K-slice from the start; 1 (default) starts
  * the workgroups of an XCD at different places of their slices, so that they do not ask the same memory channels
  * for the same rows of x at the same moment.  Results differ only in the order of fp32 additions.  Errors: E_SHAPE.

@@ -37,7 +37,7 @@ EXPORTED = [
     "elora_pool_destroy", "elora_pool_storage_bytes_q8", "elora_pool_create_q8", "elora_pool_load_adapter", "elora_pool_load_adapters", "elora_pool_load_adapters_q8", "elora_pool_evict", "elora_pool_slot_info",
     "elora_pool_poll_error", "elora_workspace_bytes", "elora_workspace_bytes_w", "elora_linear_plan", "elora_batched_lora_linear",
     "elora_batched_lora_linear_group", "elora_linear_group_launches", "elora_batched_lora_linear_noalloc", "elora_force_path", "elora_profile_arm", "elora_profile_read", "elora_workspace_init",
-    "elora_debug_spin_limit", "elora_debug_xcd_local", "elora_debug_k_rotate", "elora_debug_decode_wide", "elora_debug_decode_passes", "elora_debug_wait_limit_us", "elora_debug_w4_copy_rows",
+    "elora_debug_spin_limit", "elora_debug_xcd_local", "elora_debug_k_rotate", "elora_debug_band", "elora_debug_decode_wide", "elora_debug_decode_passes", "elora_debug_wait_limit_us", "elora_debug_w4_copy_rows",
     "elora_cache_create", "elora_cache_destroy", "elora_cache_acquire", "elora_cache_release", "elora_cache_lookup",
     "elora_cache_acquire_batch", "elora_cache_release_batch", "elora_cache_select",
     "elora_cache_drop", "elora_cache_stats", "elora_cache_reset_stats", "elora_cache_load_begin",
@@ -123,6 +123,8 @@ lib.elora_debug_decode_passes.restype = ctypes.c_int
 lib.elora_debug_decode_passes.argtypes = [ctypes.c_int]
 lib.elora_debug_decode_wide.restype = ctypes.c_int
 lib.elora_debug_decode_wide.argtypes = [ctypes.c_int]
+lib.elora_debug_band.restype = ctypes.c_int
+lib.elora_debug_band.argtypes = [ctypes.c_int] * 3
 lib.elora_debug_k_rotate.restype = ctypes.c_int
 lib.elora_debug_k_rotate.argtypes = [ctypes.c_int]
 lib.elora_profile_arm.restype = ctypes.c_int
@@ -354,6 +356,10 @@ def elora_debug_decode_passes(mode: int) -> None:
 
 def elora_debug_decode_wide(mode: int) -> None:
     _check(lib.elora_debug_decode_wide(int(mode)), "elora_debug_decode_wide")
+
+
+def elora_debug_band(mode: int, tiles_m: int = 0, slices: int = 0) -> None:
+    _check(lib.elora_debug_band(int(mode), int(tiles_m), int(slices)), "elora_debug_band")
 
 
 def elora_debug_k_rotate(on: int) -> None:

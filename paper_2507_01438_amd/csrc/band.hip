@@ -1,0 +1,541 @@
+// The matrix product of the GEMM path for a few hundred rows: y = x W^T + s B_i (A_i x) on tiles of 32 MA x 128 outputs, cut
+// into K-slices until the launch fills the chip.
+//
+// The 256 x 256 tiles of gemm.hip leave most compute units idle here (one prompt of 389 rows x 4096 columns is 32 tiles)
+// and multiply padding (389 rows -> 512).  So the height of a tile follows the batch, in steps of 32 rows up to 224; a
+// tile is 128 columns wide; and K is cut into slices whose fp32 sums the last workgroup of a tile adds in slice order.
+//   - x and W travel global -> LDS in whole cache lines through a ring of as many 64-wide K blocks as LDS holds (3 for
+//     224 rows, up to 8): what bounds a launch of few rows is how many bytes of W are under way.
+//   - 4 waves, 2 along the rows x 2 along the columns, 16 MA rows x 64 columns each with 16x16x32 matrix instructions
+//     (the 32x32 form would need tiles in steps of 64 rows).  W is the first operand, so a lane holds four neighbouring
+//     outputs of one row.
+//   - a 4-bit or 8-bit W stays as it is in LDS; a fragment is converted on its way to the matrix cores.
+//   - the expand B_i v_t comes after the K loop: every wave walks the runs of equal adapters in its own rows, 16 rows and
+//     32 rank entries at a time, through a ring of its own (no barriers), and a row only takes what its own adapter gives.
+// A call with one adapter of rank 32 (route, shrink and product), on the 256 x 256 tiles / here: 389 rows 4096 x 4096 116 /
+// 42 us, 4096 x 14336 121 / 73, 14336 x 4096 348 / 86; 1000 rows 4096 x 4096 121 / 58.  A K block of 224 x 128 takes 1300
+// cycles (matrix instructions 900, LDS 1060), a tile's beginning and end 20000, most of it code that is fetched once.
+#include "gemm_common.h"
+
+#include <algorithm>
+#include <cmath>
+
+using namespace elora;
+
+namespace {
+
+constexpr int BN = 128, BK = 64;
+constexpr int kThreads = 256, kWaveCols = 64;
+constexpr int kMaxMA = 7;
+constexpr int kMaxSlices = 8;
+constexpr int kLdsBytes = 160 * 1024 - 512;  // (the rest: what the kernel declares by itself)
+
+typedef __attribute__((address_space(3))) void *lptr_t;
+
+// one direct load of the wave: 16 (4) bytes per lane from base + off to lds + 16 (4) * lane.  M0 holds the LDS address and
+// needs a cycle to settle; nothing else of this kernel keeps a value in M0 across statements.
+__device__ __forceinline__ void dma16(uint32_t lds, const void *base, uint32_t off)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
+}
+__device__ __forceinline__ void dma4(uint32_t lds, const void *base, uint32_t off)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
+}
+template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// everybody's loads up to N younger ones have landed, and everybody's LDS reads are over
+template <int N> __device__ __forceinline__ void wait_and_meet() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory"); }
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(ic<I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+// LDS of a workgroup: `kDepth` stages of a K block each; after the K loop the same bytes are four rings, one per wave, of
+// `kSteps` expand steps each.
+template <int WFMT, int MA>
+struct Band {
+    static constexpr int kRows = MA * 32, kWaveRows = MA * 16;
+    static constexpr int kXBytes = kRows * BK * 2;
+    static constexpr int kWBytes = BN * BK * (WFMT == ELORA_W_SAME ? 4 : WFMT == ELORA_W_INT8_G32 ? 2 : 1) / 2;
+    static constexpr int kScaleBytes = WFMT == ELORA_W_SAME ? 0 : BN * 4;  // a row's two fp16 scales
+    static constexpr int kStage = kXBytes + kWBytes + kScaleBytes;
+    static constexpr int kDepth = kLdsBytes / kStage < 8 ? kLdsBytes / kStage : 8;
+    static constexpr int kWLoads = kWBytes / 4096;                         // per wave
+    static constexpr int kLoads = MA + kWLoads + (kScaleBytes ? 1 : 0);    // per wave and K block
+    static constexpr int kBytes = kDepth * kStage;
+    static constexpr int kStepBytes = 5 * 1024;                            // 16 rows of V and 64 columns of B_i, 32 rank entries
+    static constexpr int kWaveBytes = kBytes / 4 / 1024 * 1024;
+    static constexpr int kTableBytes = kWaveRows * (kMaxRank / 32) * 8;    // the wave's expand steps at most
+    static constexpr int kStepRoom = (kWaveBytes - kTableBytes) / kStepBytes;
+    static constexpr int kSteps = kStepRoom < 8 ? kStepRoom : 8;
+    static_assert(kDepth >= 3 && kSteps >= 2 && kDepth * kLoads < 64 && kSteps * 5 < 64, "the load counter has six bits");
+};
+
+struct BandArgs {
+    int T, K, N;
+    int tiles_m, tiles_n, ks;
+    const uint16_t *x;
+    const void *W;
+    const uint16_t *w_scales;
+    const int32_t *row_slot;
+    const uint16_t *V;
+    int Rpad;
+    uint16_t *y;
+    float *part;   // sums of K-slices: [tile][slice][wave][fragment][lane] x 4
+    int *sync;
+};
+
+template <int WFMT, int MA>
+__global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolView pool, int has_pool)
+{
+    typedef Band<WFMT, MA> G;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    __shared__ int s_last;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1, m = lane & 15, g = lane >> 4;
+    const int T = ba.T, K = ba.K, N = ba.N;
+    if (blockIdx.x == 0 && tid == 0) ba.sync[kSyncShortRows] = 0;  // (what read it, the shrink, is over)
+    // Workgroup b runs on XCD b % 8; an XCD takes a contiguous eighth of the list of (column tile, K-slice, row tile), so that
+    // the row tiles that read the same piece of W run side by side and share it in the XCD's L2.
+    const int units = ba.tiles_m * ba.tiles_n * ba.ks, per_xcd = (units + kXcds - 1) / kXcds;
+    const int seq = (int)blockIdx.x / kXcds;
+    int u = (int)blockIdx.x % kXcds * per_xcd + seq;
+    if (seq >= per_xcd || u >= units) return;
+    const int tm = u % ba.tiles_m;
+    u /= ba.tiles_m;
+    const int slice = u % ba.ks, tn = u / ba.ks, tile = tn * ba.tiles_m + tm;
+    const int m0 = tm * G::kRows, n0 = tn * BN;
+    const int r0 = m0 + wm * G::kWaveRows, c0 = n0 + wn * kWaveCols;  // the wave's corner of y
+
+    // ---- K loop ------------------------------------------------------------------------------------------------------
+    const unsigned blocks = (unsigned)K / BK;
+    const int kb = (int)(blocks * (unsigned)slice / (unsigned)ba.ks);
+    const int n_blk = (int)(blocks * (unsigned)(slice + 1) / (unsigned)ba.ks) - kb;
+    // A direct load moves whole rows of a block: 8 rows of 128 bytes (x, bf16 W), 16 of 64 (8-bit W) or 32 of 32 (4-bit W).
+    // A row's 16-byte chunks are permuted (chunk ^ row / 2, row / 4, row / 8) so that the fragment reads hit all banks.
+    // Rows past the end of x and W repeat the last one; what they give is never stored.
+    uint32_t xoff[MA], woff[G::kWLoads], soff = 0;
+#pragma unroll
+    for (int i = 0; i < MA; ++i) {
+        const int row = 8 * (wave * MA + i) + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
+        xoff[i] = (uint32_t)(((size_t)(min(m0 + row, T - 1) - m0) * K + chunk * 8) * 2);
+    }
+#pragma unroll
+    for (int i = 0; i < G::kWLoads; ++i) {
+        const int q = wave * G::kWLoads + i;
+        if constexpr (WFMT == ELORA_W_SAME) {
+            const int row = 8 * q + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
+            woff[i] = (uint32_t)(((size_t)(min(n0 + row, N - 1) - n0) * K + chunk * 8) * 2);
+        } else if constexpr (WFMT == ELORA_W_INT8_G32) {
+            const int row = 16 * q + (lane >> 2), chunk = (lane & 3) ^ ((row >> 2) & 3);
+            woff[i] = (uint32_t)((size_t)(min(n0 + row, N - 1) - n0) * K + chunk * 16);
+        } else {
+            const int row = 32 * q + (lane >> 1), chunk = (lane & 1) ^ ((row >> 3) & 1);
+            woff[i] = (uint32_t)((size_t)(min(n0 + row, N - 1) - n0) * (K >> 1) + chunk * 16);
+        }
+    }
+    if constexpr (WFMT != ELORA_W_SAME) soff = (uint32_t)((size_t)(min(n0 + (wave & 1) * 64 + lane, N - 1) - n0) * (K >> 5) * 2);
+    const char *const xbase = reinterpret_cast<const char *>(ba.x + (size_t)m0 * K + (size_t)kb * BK);
+    constexpr int kWRowBits = WFMT == ELORA_W_SAME ? 16 : WFMT == ELORA_W_INT8_G32 ? 8 : 4;
+    const char *const wbase = static_cast<const char *>(ba.W) + ((size_t)n0 * K + (size_t)kb * BK) * kWRowBits / 8;
+    const char *const sbase = reinterpret_cast<const char *>(ba.w_scales) + (((size_t)n0 * K + (size_t)kb * BK) >> 5) * 2;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
+    // Column tiles and slices begin at different blocks: rows lie a multiple of the memory channels' pitch apart, and
+    // workgroups that walk side by side would all ask the same channels (80 rows x 14336: 49.5 -> 45.7 us).
+    const int turn = (int)((unsigned)(tn * ba.ks + slice) % (unsigned)n_blk);
+    // load i of a block's kLoads
+    auto issue_one = [&](int blk, int stage, auto ic_) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic_)::value;
+        const uint32_t at = lds0 + (uint32_t)stage * G::kStage;
+        blk += turn;
+        if (blk >= n_blk) blk -= n_blk;
+        if constexpr (i < MA) {
+            dma16(at + (wave * MA + i) * 1024, xbase + (size_t)blk * (BK * 2), xoff[i]);
+        } else if constexpr (i < MA + G::kWLoads) {
+            dma16(at + G::kXBytes + (wave * G::kWLoads + i - MA) * 1024, wbase + (size_t)blk * (BK * kWRowBits / 8), woff[i - MA]);
+        } else {
+            // (waves 2 and 3 fetch the same scales once more: every wave has the same number of loads to count)
+            dma4(at + G::kXBytes + G::kWBytes + (wave & 1) * 256, sbase + (size_t)blk * (BK / 32 * 2), soff);
+        }
+    };
+    auto issue_block = [&](int blk, int stage) __attribute__((always_inline)) {
+        static_for<0, G::kLoads>([&](auto i) __attribute__((always_inline)) { issue_one(blk, stage, i); });
+    };
+
+    floatx4 acc[MA][4];
+#pragma unroll
+    for (int a = 0; a < MA; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+            // (as values of their own: as copies of one zero the compiler finds no place for them in the loop, and moves every
+            // sum between registers once per block: 389 rows x 4096 x 14336 112 us, without 87)
+            asm volatile("" : "+a"(acc[a][b]));
+        }
+
+    // fragments of a 32-wide K step: rows of x, rows of W as they are stored; double-buffered
+    typedef typename std::conditional<WFMT == ELORA_W_SAME, bf16x8, typename std::conditional<WFMT == ELORA_W_INT8_G32, u32x2, uint32_t>::type>::type wraw_t;
+    bf16x8 xf[2][MA];
+    wraw_t wf[2][4];
+    uint16_t wsc[2][4];
+    // fragment f of K step s of the block in `stage`: 0 .. 3 rows of W, 4 .. rows of x
+    auto read_frag = [&](int to, int stage, int s, auto fc) __attribute__((always_inline)) {
+        constexpr int f = decltype(fc)::value;
+        const unsigned char *st = smem + stage * G::kStage;
+        if constexpr (f >= 4) {
+            xf[to][f - 4] = *reinterpret_cast<const bf16x8 *>(st + (wm * G::kWaveRows + (f - 4) * 16 + m) * 128 + (((s * 4 + g) ^ ((m >> 1) & 7)) * 16));
+        } else {
+            const int row = wn * kWaveCols + f * 16 + m;
+            const unsigned char *w = st + G::kXBytes;
+            if constexpr (WFMT == ELORA_W_SAME) {
+                wf[to][f] = *reinterpret_cast<const wraw_t *>(w + row * 128 + (((s * 4 + g) ^ ((m >> 1) & 7)) * 16));
+            } else {
+                if constexpr (WFMT == ELORA_W_INT8_G32) wf[to][f] = *reinterpret_cast<const wraw_t *>(w + row * 64 + (((s * 2 + (g >> 1)) ^ ((m >> 2) & 3)) * 16) + (g & 1) * 8);
+                else wf[to][f] = *reinterpret_cast<const wraw_t *>(w + row * 32 + ((s ^ ((m >> 3) & 1)) * 16) + g * 4);
+                wsc[to][f] = *reinterpret_cast<const uint16_t *>(w + G::kWBytes + row * 4 + s * 2);
+            }
+        }
+    };
+    auto w_operand = [&](int from, int b) __attribute__((always_inline)) {
+        if constexpr (WFMT == ELORA_W_SAME) return wf[from][b];
+        else if constexpr (WFMT == ELORA_W_INT8_G32) return __builtin_bit_cast(bf16x8, q8_to_bf16x8(wf[from][b], fp16_to_f32(wsc[from][b])));
+        else return __builtin_bit_cast(bf16x8, w4_to_bf16x8(wf[from][b], fp16_to_f32(wsc[from][b])));
+    };
+    // One K step: 4 MA matrix instructions on the fragments `from`.  Behind those of the first half the fragments of the
+    // next step are read, behind those of the second half the next block's direct loads are issued, a few per slot: a
+    // matrix instruction keeps its pipe busy for 16 cycles, during which the wave issues what else it has to.
+    constexpr int kFirstLoads = (G::kLoads + 1) / 2;
+    auto k_step = [&](auto from_c, int rstage, int rs, int lblk, int lstage) __attribute__((always_inline)) {
+        constexpr int from = decltype(from_c)::value;
+        constexpr int kSlots = 4 * MA, kHalf = kSlots / 2, kReads = MA + 4;
+        // (the first half of a block's loads in step 1, the second half in step 0 of the next block)
+        constexpr int kFirst = from == 1 ? 0 : kFirstLoads, kLoads = from == 1 ? kFirstLoads : G::kLoads - kFirstLoads;
+        bf16x8 w = w_operand(from, 0);
+        static_for<0, kSlots>([&](auto ec) __attribute__((always_inline)) {
+            constexpr int e = decltype(ec)::value, b = e / MA, a = e % MA;
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, xf[from][a], acc[a][b], 0, 0, 0);
+            if constexpr (a == MA - 1 && b < 3) w = w_operand(from, b + 1);
+            if constexpr (e < kHalf) static_for<e * kReads / kHalf, (e + 1) * kReads / kHalf>([&](auto f) __attribute__((always_inline)) { read_frag(from ^ 1, rstage, rs, f); });
+            else static_for<(e - kHalf) * kLoads / kHalf, (e + 1 - kHalf) * kLoads / kHalf>([&](auto i) __attribute__((always_inline)) { issue_one(lblk, lstage, ic<kFirst + decltype(i)::value>{}); });
+            if constexpr (WFMT == ELORA_W_SAME) __builtin_amdgcn_sched_barrier(0);
+        });
+        // (a W that is converted on the way: a few vector instructions behind every matrix instruction, not all in a row)
+        if constexpr (WFMT != ELORA_W_SAME)
+            static_for<0, kSlots>([&](auto) __attribute__((always_inline)) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // the slots and ranks of the wave's rows (the ranks are on their way during the K loop)
+    int slot_v[2] = {INT32_MIN, INT32_MIN}, rank_v[2] = {0, 0};
+    if (has_pool) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (h * 64 + lane < G::kWaveRows && r0 + h * 64 + lane < T) slot_v[h] = ba.row_slot[r0 + h * 64 + lane];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (slot_v[h] >= 0) rank_v[h] = pool.meta[slot_v[h]].rank;
+    }
+#pragma unroll 1
+    for (int i = 0; i < G::kDepth - 1; ++i) issue_block(min(i, n_blk - 1), i);
+    // (the loop's first turn asks for the second half of block kDepth - 1)
+    static_for<0, kFirstLoads>([&](auto i) __attribute__((always_inline)) { issue_one(min(G::kDepth - 1, n_blk - 1), G::kDepth - 1, i); });
+    wait_and_meet<(G::kDepth - 2) * G::kLoads + kFirstLoads>();
+    static_for<0, MA + 4>([&](auto f) __attribute__((always_inline)) { read_frag(0, 0, 0, f); });
+    // One loop, in which nothing depends on how much is left: the last blocks ask for the last block once more, into stages
+    // that nobody reads again.
+    int stage = 0, before = G::kDepth - 1;  // (the stage of the block before, which block blk + kDepth - 1 goes into)
+    for (int blk = 0; blk < n_blk; ++blk) {
+        const int next = stage + 1 == G::kDepth ? 0 : stage + 1;
+        k_step(ic<0>{}, stage, 1, min(blk + G::kDepth - 1, n_blk - 1), before);
+        wait_and_meet<(G::kDepth - 2) * G::kLoads>();  // block blk + 1 has landed, and the stage of block blk has been read
+        k_step(ic<1>{}, next, 0, min(blk + G::kDepth, n_blk - 1), stage);
+        before = stage;
+        stage = next;
+    }
+    wait_loads<0>();
+
+    // ---- expand, and what the wave has of y, 16 rows at a time -----------------------------------------------------------
+    // A step is (16-row block, run of equal adapters in it, 32 rank entries): 1 KiB of V and 4 KiB of B_i for four matrix
+    // instructions; a tile's K-slices take turns at the runs.  The wave first writes its steps out as a table, a lane per row;
+    // the loads of kSteps - 1 steps are under way while one is multiplied.  Ranks that are no multiples of 8, and adapters in
+    // 8-bit blocks, have rows of B_i that a 16-byte load cannot take: their fragments are gathered when the step is due.
+    // What bounds this part is instructions (fetched once, a cache line of code takes 250 cycles): so the blocks go through
+    // one loop, always as acc[0], and the others move up behind each.  (A switch over the blocks made the compiler copy all
+    // sums at every step: 2050 cycles a step; unrolled, 389 rows of one adapter took 3000.)
+    int n_steps = 0, first[2] = {0, 0};  // (first: steps before the lane's row)
+    unsigned char *const own = smem + wave * G::kWaveBytes;
+    uint64_t *const table = reinterpret_cast<uint64_t *>(own + G::kSteps * G::kStepBytes);
+    struct Step {
+        int row, end, j0, rank, slot;
+    };
+    auto step_at = [&](int i) __attribute__((always_inline)) {
+        const u32x2 r = *reinterpret_cast<const u32x2 *>(table + min(i, n_steps - 1));
+        const int a = __builtin_amdgcn_readfirstlane(r[0]), slot = __builtin_amdgcn_readfirstlane(r[1]);
+        return Step{a & 255, (a >> 8) & 255, ((a >> 16) & 15) * 32, a >> 20, slot};
+    };
+    const bool q8 = pool.q8 != 0;
+    const uint32_t ring0 = lds0 + (uint32_t)(wave * G::kWaveBytes);
+    const char *const vbase = reinterpret_cast<const char *>(ba.V + (size_t)r0 * ba.Rpad);
+    const int line = lane >> 2, chunk = (lane & 3) ^ ((line >> 2) & 3);
+    uint32_t col[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) col[i] = (uint32_t)min(c0 + i * 16 + line, N - 1);
+    auto issue = [&](const Step &st, int at) __attribute__((always_inline)) {
+        const uint32_t lds = ring0 + (uint32_t)at * G::kStepBytes;
+        const int row = min((st.row & ~15) + line, T - 1 - r0);
+        const uint32_t voff = (uint32_t)((row * ba.Rpad + st.j0 + chunk * 8) * 2);
+        dma16(lds, vbase, voff);
+        // (a gathered step loads its row of V again, so that all steps have the same number of loads)
+        const bool gather = q8 || (st.rank & 7) != 0;
+        const char *const Bm = gather ? vbase : slot_B(pool, st.slot);
+        const uint32_t j = gather ? voff : 2u * (uint32_t)(st.j0 + chunk * 8 < st.rank ? st.j0 + chunk * 8 : st.j0);
+        const uint32_t stride = gather ? 0u : 2u * (uint32_t)st.rank;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dma16(lds + 1024 + i * 1024, Bm, col[i] * stride + j);
+    };
+    if (has_pool) {
+        const int before0 = __shfl_up(slot_v[0], 1), before1 = __shfl_up(slot_v[1], 1), last0 = __builtin_amdgcn_readlane(slot_v[0], 63);
+        const bool cut = (lane & 15) == 0;
+        const uint64_t starts[2] = {__ballot(cut || slot_v[0] != before0), __ballot(cut || slot_v[1] != (lane == 0 ? last0 : before1))};
+        const uint64_t run[2] = {starts[0] & __ballot(rank_v[0] > 0), starts[1] & __ballot(rank_v[1] > 0)};  // first rows of runs with an adapter
+        __syncthreads();  // every wave is done with the stages
+#pragma unroll
+        for (int h = 0; h < (G::kWaveRows + 63) / 64; ++h) {
+            const uint64_t below = (1ull << lane) - 1;
+            const int number = (int)__popcll(run[h] & below) + (h ? (int)__popcll(run[0]) : 0);
+            const int n = ((run[h] >> lane) & 1) && number % ba.ks == slice ? (rank_v[h] + 31) >> 5 : 0;
+            int upto = n;  // steps of the rows up to this one
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int v = __shfl_up(upto, d);
+                if (lane >= d) upto += v;
+            }
+            first[h] = n_steps + upto - n;
+            const uint64_t after = lane == 63 ? 0 : starts[h] & (~0ull << (lane + 1));
+            const int row = h * 64 + lane, end = h * 64 + (after ? (int)__builtin_ctzll(after) : 64);
+            // step record: first row | end row << 8 | 32 entries number << 16 | rank << 20, slot
+            for (int i = 0; i < n; ++i)
+                table[first[h] + i] = (uint64_t)(uint32_t)(row | (end << 8) | (i << 16) | (rank_v[h] << 20)) | ((uint64_t)(uint32_t)slot_v[h] << 32);
+            n_steps += __builtin_amdgcn_readlane(upto, 63);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (a wave reads what its own lanes wrote)
+        if (n_steps > 0) {
+#pragma unroll 1
+            for (int i = 0; i < G::kSteps - 1; ++i) issue(step_at(i), i);
+        }
+    }
+    // sums of K-slices, written through to memory and read past the first-level cache (nothing depends on where a tile's
+    // workgroups run)
+    constexpr int kFrags = MA * 4, kCoherent = 16;  // sc1
+    auto rsrc = __builtin_amdgcn_make_buffer_rsrc(ba.part + (size_t)tile * ba.ks * (4 * kFrags * 256), 0, ba.ks * (4 * kFrags * 1024), 0x00020000);
+    const int part_at = wave * kFrags * 1024 + lane * 16, slice_bytes = 4 * kFrags * 1024;
+    auto move_up = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a + 1 < MA; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[a][b] = acc[a + 1][b];
+    };
+    // block a of y, from acc[0]: a lane has four neighbouring outputs of row m
+    auto store_y = [&](int a) __attribute__((always_inline)) {
+        const int row = r0 + a * 16 + m;
+        uint16_t *const yrow = ba.y + (size_t)row * N;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int c = c0 + b * 16 + g * 4;
+            if (row < T && c < N) *reinterpret_cast<u32x2 *>(yrow + c) = u32x2{pack_bf16x2(acc[0][b][0], acc[0][b][1]), pack_bf16x2(acc[0][b][2], acc[0][b][3])};
+        }
+    };
+    int step = 0, at = 0;
+#pragma unroll 1
+    for (int a = 0; a < MA; ++a) {
+        const int stop = a + 1 == MA ? n_steps : __builtin_amdgcn_readlane(a + 1 < 4 ? first[0] : first[1], ((a + 1) & 3) * 16);
+#pragma unroll 1
+        for (; step < stop; ++step) {
+            const Step cur = step_at(step);
+            // (the place read a step ago; behind the last step its loads are asked for again, so that the count stays)
+            issue(step_at(step + G::kSteps - 1), at == 0 ? G::kSteps - 1 : at - 1);
+            wait_loads<5 * (G::kSteps - 1)>();
+            const unsigned char *const st = own + at * G::kStepBytes;
+            const int place = (g ^ ((m >> 2) & 3)) * 16, j = cur.j0 + g * 8;
+            bf16x8 v = *reinterpret_cast<const bf16x8 *>(st + m * 64 + place), bm[4];
+            const u32x4 zero{0, 0, 0, 0};
+#pragma unroll
+            for (int b = 0; b < 4; ++b) bm[b] = *reinterpret_cast<const bf16x8 *>(st + 1024 + (b * 16 + m) * 64 + place);
+            if (q8 || (cur.rank & 7) != 0) {
+                const char *const Bm = slot_B(pool, cur.slot);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const size_t e = (size_t)min(c0 + b * 16 + m, N - 1) * cur.rank + j;
+                    u32x4 o = zero;
+                    if (q8) {
+                        if (j < cur.rank) o = q8_to_bf16x8(*reinterpret_cast<const u32x2 *>(Bm + e), fp16_to_f32(slot_B_scales(pool, cur.slot)[e >> 5]));
+                    } else {
+                        const uint16_t *const src = reinterpret_cast<const uint16_t *>(Bm) + e;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const uint32_t lo = j + 2 * q < cur.rank ? src[2 * q] : 0u, hi = j + 2 * q + 1 < cur.rank ? src[2 * q + 1] : 0u;
+                            o[q] = lo | (hi << 16);
+                        }
+                    }
+                    // (waited for here: behind the branch, the wait would be one of every step, and for all loads under way)
+                    asm volatile("" : "+v"(o));
+                    bm[b] = __builtin_bit_cast(bf16x8, o);
+                }
+            }
+            if (j >= cur.rank) {  // (entries past the rank: zero in V; zero here too, whatever the adapter holds)
+                v = __builtin_bit_cast(bf16x8, zero);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) bm[b] = __builtin_bit_cast(bf16x8, zero);
+            }
+            const int row = a * 16 + m;
+            const bool in = row >= cur.row && row < cur.end;  // (a row of another run takes nothing, not even zero times this adapter)
+            floatx4 d[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) d[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[0][b][q] += in ? d[b][q] : 0.0f;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (this step's place has been read)
+            at = at + 1 == G::kSteps ? 0 : at + 1;
+        }
+        if (ba.ks == 1) {
+            store_y(a);
+        } else {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[0][b]), rsrc, part_at + a * 4096 + b * 1024, slice * slice_bytes, kCoherent);
+        }
+        move_up();
+    }
+    wait_loads<0>();
+    if (ba.ks == 1) return;
+
+    // ---- sums of the K-slices: the last workgroup of the tile to come adds them, in slice order -----------------------------
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's sums have reached memory
+    __syncthreads();
+    if (tid == 0) {
+        const int before_me = __hip_atomic_fetch_add(&ba.sync[kSyncTiles + tile], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = before_me == ba.ks - 1;
+        if (s_last) __hip_atomic_store(&ba.sync[kSyncTiles + tile], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!s_last) return;
+    // (its own sums as well: the order of the additions does not depend on who comes last)
+#pragma unroll
+    for (int f = 0; f < kFrags; ++f) acc[f >> 2][f & 3] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int k = 0; k < ba.ks; ++k) {
+        u32x4 w[kFrags];
+#pragma unroll
+        for (int f = 0; f < kFrags; ++f) w[f] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, part_at + f * 1024, k * slice_bytes, kCoherent);
+#pragma unroll
+        for (int f = 0; f < kFrags; ++f) acc[f >> 2][f & 3] += __builtin_bit_cast(floatx4, w[f]);
+    }
+#pragma unroll 1
+    for (int a = 0; a < MA; ++a) {
+        store_y(a);
+        move_up();
+    }
+}
+
+int g_mode = -1, g_mode_tiles = 0, g_mode_slices = 0;  // (elora_debug_band)
+
+}  // namespace
+
+void elora::band_set(int mode, int tiles_m, int slices)
+{
+    g_mode = mode;
+    g_mode_tiles = tiles_m;
+    g_mode_slices = slices;
+}
+
+// Which tiles, and whether this kernel or the 256 x 256 tiles: the launch's time in cycles, from what a K block, a tile's
+// beginning and end and the sums of slices were measured to take, times the rounds of 256 workgroups (one per compute unit).
+//   here: a K block 270 + 160 ma (a W that is converted on the way 1550 + 105 ma), a tile 6000 + 2300 ma, its slices'
+//   sums 2000 + 450 ma each; there: a K block 3400 (from the bf16 copy of W 2600, converted on the way 5700), a tile 6000,
+//   the copy 1.04e-3 per weight.
+// (1500 rows x 4096 x 14336: 227 us here, 216 there; 600 rows 109 and 119; 1000 rows x 4096 columns 58 and 121.)
+bool elora::band_shape(int T, int K, int N, int wfmt, size_t part_bytes, bool copied, BandShape *s)
+{
+    if (g_mode == 0 || K % BK != 0 || N % 8 != 0) return false;
+    const int tiles_n = (N + BN - 1) / BN, blocks = K / BK;
+    const int least = (T + 32 * kMaxMA - 1) / (32 * kMaxMA);
+    auto rounds = [](double workgroups) { return std::ceil(workgroups / 256); };
+    double best = -1.0;
+    for (int tiles_m = g_mode_tiles > least ? g_mode_tiles : least; tiles_m <= (g_mode_tiles ? g_mode_tiles : least + 2); ++tiles_m) {
+        const int ma = ((T + tiles_m - 1) / tiles_m + 31) / 32, tm = (T + 32 * ma - 1) / (32 * ma);
+        const double block = wfmt == ELORA_W_SAME ? 270 + 160 * ma : 1550 + 105 * ma;
+        for (int ks = g_mode_slices ? g_mode_slices : 1; ks <= (g_mode_slices ? g_mode_slices : kMaxSlices); ++ks) {
+            if (ks > blocks || (ks > 1 && ((long long)tm * tiles_n > kSyncTileCount || (size_t)tm * tiles_n * ks * (ma * 32 * BN * 4) > part_bytes))) continue;
+            const double cycles = rounds((double)tm * tiles_n * ks) * ((blocks + ks - 1) / ks * block + 6000 + 2300 * ma) + (ks > 1 ? 2000 + 450.0 * ks * ma : 0);
+            if (best < 0 || cycles < best) {
+                best = cycles;
+                *s = BandShape{ma, tm, ks};
+            }
+        }
+    }
+    if (best < 0 || g_mode == 1) return best >= 0;
+    const double there = rounds((double)((T + 255) / 256) * ((N + 255) / 256)) * (blocks * (wfmt == ELORA_W_SAME ? 3400.0 : copied ? 2600.0 : 5700.0) + 6000) +
+                         (copied ? 1.04e-3 * K * N : 0);
+    return best < there;
+}
+
+int elora::enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t stream)
+{
+    BandArgs b;
+    b.T = a.T;
+    b.K = a.K;
+    b.N = a.N;
+    b.tiles_m = s.tiles_m;
+    b.tiles_n = (a.N + BN - 1) / BN;
+    b.ks = s.ks;
+    b.x = static_cast<const uint16_t *>(a.x);
+    b.W = a.W;
+    b.w_scales = static_cast<const uint16_t *>(a.w_scales);
+    b.row_slot = reinterpret_cast<const int32_t *>(a.ws + a.wsl.row_slot);
+    b.V = reinterpret_cast<const uint16_t *>(a.ws + a.wsl.v);
+    b.Rpad = round_up(a.pool.max_rank, kRankPad);
+    b.y = static_cast<uint16_t *>(a.y);
+    b.part = reinterpret_cast<float *>(a.ws + a.wsl.part);
+    b.sync = reinterpret_cast<int *>(a.ws + a.wsl.sync);
+    const dim3 grid(round_up(b.tiles_m * b.tiles_n * b.ks, kXcds));
+    auto launch = [&](auto wfmt, auto ma) -> int {
+        constexpr int WFMT = decltype(wfmt)::value, MA = decltype(ma)::value, lds = Band<WFMT, MA>::kBytes;
+        static bool attr_done = false;
+        if (!attr_done) {
+            ELORA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&lora_band_kernel<WFMT, MA>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+            attr_done = true;
+        }
+        hipLaunchKernelGGL((lora_band_kernel<WFMT, MA>), grid, dim3(kThreads), lds, stream, b, a.pool, a.has_pool ? 1 : 0);
+        ELORA_HIP_TRY(hipGetLastError());
+        return ELORA_OK;
+    };
+    auto with_rows = [&](auto wfmt) -> int {
+        switch (s.ma) {
+        case 1: return launch(wfmt, ic<1>{});
+        case 2: return launch(wfmt, ic<2>{});
+        case 3: return launch(wfmt, ic<3>{});
+        case 4: return launch(wfmt, ic<4>{});
+        case 5: return launch(wfmt, ic<5>{});
+        case 6: return launch(wfmt, ic<6>{});
+        default: return launch(wfmt, ic<7>{});
+        }
+    };
+    profile_mark_begin(stream);
+    int rc;
+    if (a.wfmt == ELORA_W_SAME) rc = with_rows(ic<ELORA_W_SAME>{});
+    else if (a.wfmt == ELORA_W_INT8_G32) rc = with_rows(ic<ELORA_W_INT8_G32>{});
+    else rc = with_rows(ic<ELORA_W_INT4_G32>{});
+    if (rc == ELORA_OK) profile_mark_end(stream);
+    return rc;
+}

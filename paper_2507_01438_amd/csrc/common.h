@@ -139,6 +139,13 @@ bool decode_eligible(const elora_linear_desc_t &d, int max_rank);
 int decode_passes(const elora_linear_desc_t &d);  // launches of the decode kernel this call is cut into (1 up to 64 rows), 0: not that path
 void decode_plan(const elora_linear_desc_t &d, elora_plan_t *plan);
 size_t decode_mail_bytes(int d_out);  // mailboxes of the decode kernel for d_out output columns
+// The product of a few hundred rows: tiles of 32 ma x 128 outputs, tiles_m of them along the rows, ks K-slices
+struct BandShape {
+    int ma, tiles_m, ks;
+};
+bool band_shape(int T, int K, int N, int wfmt, size_t part_bytes, bool copied, BandShape *s);  // copied: they would run on a bf16 copy of W; false: the 256 x 256 tiles are the better choice
+int enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t stream);
+void band_set(int mode, int tiles_m, int slices);  // -1: where it pays, 0: never, 1: wherever the shape allows; 0: as chosen
 bool gemm_eligible(const elora_linear_desc_t &d, int max_rank);
 void gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan);
 size_t gemm_wcopy_bytes(int wfmt, int n_tokens, int d_in, int d_out);  // (see below)

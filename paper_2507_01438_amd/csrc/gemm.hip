@@ -1,6 +1,7 @@
 // Prefill / mixed path (many rows, MFMA-bound): bf16 activations; bf16, 4-bit or 8-bit base weights.
 //
-// Three launches per call: route and shrink (shrink.hip), then the matrix product.  A 4-bit W with 768 rows or more and an
+// Three launches per call: route and shrink (shrink.hip), then the matrix product, here or, where its tiles are the better
+// choice (a few hundred rows), in band.hip.  A 4-bit W with 768 rows or more and an
 // 8-bit W are converted to bf16 once per call, into the workspace, in the route's launch, and the bf16 kernel runs on the
 // copy; below that the 4-bit W is converted tile by tile inside the gemm:
 //   gemm    Y = X W^T (Sec. 3.4: the base product, shared by the whole batch) on 256 x 256 tiles with
@@ -670,7 +671,16 @@ bool elora::gemm_eligible(const elora_linear_desc_t &d, int max_rank)
 void elora::gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
 {
     const bool copy_first = gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0;
-    plan->n_launches = (d.pool ? 3 : 1) + (copy_first && !d.pool ? 1 : 0);  // (with a pool the copy shares the route's launch)
+    BandShape s;
+    const bool band = band_shape(d.n_tokens, d.d_in, d.d_out, d.wfmt, part_want(d.d_out), copy_first, &s);
+    plan->n_launches = (d.pool ? 3 : 1) + (copy_first && !band && !d.pool ? 1 : 0);  // (with a pool the copy shares the route's launch)
+    if (band) {
+        plan->split_k = s.ks;
+        plan->tile_rows = 32 * s.ma;
+        plan->tile_cols = 128;
+        plan->grid = round_up(s.tiles_m * ((d.d_out + 127) / 128) * s.ks, kXcds);
+        return;
+    }
     plan->tile_rows = BM;
     plan->tile_cols = BN;
     plan->grid = gemm_grid((d.n_tokens + BM - 1) / BM, (d.d_out + BN - 1) / BN);
@@ -741,16 +751,23 @@ int enqueue_gemm(const LinearArgs &a, hipStream_t stream)
 }
 }  // namespace
 
+static bool band_for(const LinearArgs &a, BandShape *s)
+{
+    return band_shape(a.T, a.K, a.N, a.wfmt, a.wsl.part_bytes, a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0, s);
+}
+
 int elora::launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream)
 {
     (void)plan;
     ShrinkArgs s;
     shrink_args(s, &a, 1);
-    const bool copy = a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
+    BandShape band;
+    const bool in_band = band_for(a, &band);
+    const bool copy = !in_band && a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
     int rc = launch_route(s, &a, copy, stream);
     if (rc == ELORA_OK && a.has_pool) rc = launch_shrink(s, stream);
     if (rc != ELORA_OK) return rc;
-    return enqueue_gemm(a, stream);
+    return in_band ? enqueue_band(a, band, stream) : enqueue_gemm(a, stream);
 }
 
 // Two or three calls of this path that read the same x with the same routing tables (each with a pool of its own):
@@ -759,14 +776,17 @@ int elora::launch_gemm_group(const LinearArgs *a, int n, hipStream_t stream)
 {
     ShrinkArgs s;
     shrink_args(s, a, n);
-    auto copied = [&](int i) { return a[i].wfmt != ELORA_W_SAME && a[i].wsl.wdeq_bytes != 0; };
+    BandShape band[kShrinkMulti];
+    bool in_band[kShrinkMulti];
+    for (int i = 0; i < n; ++i) in_band[i] = band_for(a[i], &band[i]);
+    auto copied = [&](int i) { return !in_band[i] && a[i].wfmt != ELORA_W_SAME && a[i].wsl.wdeq_bytes != 0; };
     int rc = launch_route(s, a, copied(0), stream);
     if (rc == ELORA_OK) rc = launch_shrink(s, stream);
     for (int i = 0; i < n && rc == ELORA_OK; ++i) {
         LinearArgs base = a[i];
         base.has_pool = false;  // (the copy alone)
         if (i > 0 && copied(i)) rc = launch_route(s, &base, true, stream);
-        if (rc == ELORA_OK) rc = enqueue_gemm(a[i], stream);
+        if (rc == ELORA_OK) rc = in_band[i] ? enqueue_band(a[i], band[i], stream) : enqueue_gemm(a[i], stream);
     }
     return rc;
 }

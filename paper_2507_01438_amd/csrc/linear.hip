@@ -266,6 +266,13 @@ int elora_debug_decode_wide(int mode)
     return ELORA_OK;
 }
 
+int elora_debug_band(int mode, int tiles_m, int slices)
+{
+    if (mode < -1 || mode > 1 || tiles_m < 0 || slices < 0 || slices > 8) return ELORA_E_SHAPE;
+    band_set(mode, tiles_m, slices);
+    return ELORA_OK;
+}
+
 int elora_debug_k_rotate(int on)
 {
     if (on != 0 && on != 1) return ELORA_E_SHAPE;

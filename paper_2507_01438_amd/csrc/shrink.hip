@@ -55,20 +55,24 @@ __device__ __forceinline__ void route_rows(const RouteView &route, const ShrinkA
 
 __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteView route, ShrinkArgs s) { route_rows(route, s, (int)blockIdx.x); }
 
-// ---- one row of a short run (any rank): a wave takes two rank rows at a time --------------------------------------------
+// ---- rows of short runs (any rank), one by one: 16 rank entries of a row per call, a wave takes two at a time --------------
+// Bound by latency: a pass over two rows of A_i is one trip to memory.  (150 rows of ranks 8 to 64, K = 4096: a whole row
+// per workgroup on half as many workgroups as rows 35 us, pieces of 16 entries on one workgroup per row 24.)
+constexpr int kRowPiece = 16;
 template <bool kQ8>
-__device__ __forceinline__ void shrink_row(const ShrinkArgs &s, const ShrinkProj &pr, int t, float *vrow)
+__device__ __forceinline__ void shrink_row_piece(const ShrinkArgs &s, const ShrinkProj &pr, int t, int first)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), K = s.K;
     const int slot = pr.row_slot[t];
-    int rank = 0;
-    if (slot >= 0) {
-        rank = pr.pool.meta[slot].rank;
-        const uint16_t *A = reinterpret_cast<const uint16_t *>(slot_A(pr.pool, slot));
-        for (int j0 = 2 * wave; j0 < rank; j0 += 2 * kWaves) {
-            const bool two = (j0 + 1) < rank;
+    const int rank = slot >= 0 ? pr.pool.meta[slot].rank : 0;
+    const float sc = slot >= 0 ? pr.row_scale[t] : 0.0f;
+    uint16_t *const vrow = pr.V + (size_t)t * pr.Rpad;
+    for (int j0 = first + 2 * wave; j0 < first + kRowPiece; j0 += 2 * kWaves) {
+        const bool two = j0 + 1 < rank;
+        float a0 = 0.0f, a1 = 0.0f;
+        if (j0 < rank) {
             const int j1 = two ? j0 + 1 : j0;
-            float a0, a1;
+            const uint16_t *A = reinterpret_cast<const uint16_t *>(slot_A(pr.pool, slot));
             if constexpr (kQ8) {
                 const char *Ac = reinterpret_cast<const char *>(A);
                 const uint16_t *As = slot_A_scales(pr.pool, slot);
@@ -77,16 +81,12 @@ __device__ __forceinline__ void shrink_row(const ShrinkArgs &s, const ShrinkProj
             } else {
                 shrink_pair(A + (size_t)j0 * K, A + (size_t)j1 * K, s.x + (size_t)t * K, K, lane, a0, a1);
             }
-            if (lane == 0) {
-                vrow[j0] = a0;
-                if (two) vrow[j0 + 1] = a1;
-            }
+        }
+        if (lane == 0) {
+            vrow[j0] = j0 < rank ? f32_to_bf16(sc * a0) : (uint16_t)0;
+            vrow[j0 + 1] = two ? f32_to_bf16(sc * a1) : (uint16_t)0;
         }
     }
-    __syncthreads();
-    const float sc = slot >= 0 ? pr.row_scale[t] : 0.0f;
-    for (int j = tid; j < pr.Rpad; j += kThreads) pr.V[(size_t)t * pr.Rpad + j] = (j < rank) ? f32_to_bf16(sc * vrow[j]) : (uint16_t)0;
-    __syncthreads();
 }
 
 // ---- a 32-row tile and one K-slice of it ---------------------------------------------------------------------------------
@@ -357,11 +357,8 @@ __device__ __forceinline__ void shrink_workgroup(const ShrinkArgs &s, int wg)
     const int n_short = pr.sync[kSyncShortRows];
     if (u < units && tile < s.n_tiles) shrink_tile<kQ8, NCB>(s, pr, tile, u % s.ks, part_q, s_last, ring);
     // the rows of short runs are shared by all workgroups (workgroups of their own would each wait for a ring's worth of LDS)
-    const int wgs = s.wgs_per_xcd * kXcds;
-    for (int i = seq * kXcds + xcd; i < n_short; i += wgs) {
-        __syncthreads();
-        shrink_row<kQ8>(s, pr, pr.short_rows[i], reinterpret_cast<float *>(ring));
-    }
+    const int wgs = s.wgs_per_xcd * kXcds, pieces = pr.Rpad / kRowPiece;
+    for (int i = seq * kXcds + xcd; i < n_short * pieces; i += wgs) shrink_row_piece<kQ8>(s, pr, pr.short_rows[i / pieces], i % pieces * kRowPiece);
 }
 int shrink_grid(const ShrinkArgs &s) { return s.wgs_per_xcd * kXcds * s.n; }
 
@@ -438,8 +435,8 @@ void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n)
     while (s.ks < kMaxSlices && s.n_tiles * (s.ks + 1) <= (s.K / (s.ks + 1) >= 4096 ? 512 : 256) && s.n_tiles <= kSyncTileCount &&
            s.K / kSpan >= (s.ks + 1) * 2 * kWaves && per_slice * (s.ks + 1) <= room)
         ++s.ks;
-    // (at least one workgroup per two rows, up to one per compute unit: the rows of short runs are shared by all of them)
-    s.wgs_per_xcd = std::max((s.n_tiles + kXcds - 1) / kXcds * s.ks * 2, std::min((s.T + 15) / 16, 32));
+    // (at least four workgroups per row, up to two per compute unit: the rows of short runs are shared by all of them)
+    s.wgs_per_xcd = std::max((s.n_tiles + kXcds - 1) / kXcds * s.ks * 2, std::min((s.T + 1) / 2, 64));
     for (int p = 0; p < n; ++p) {
         ShrinkProj &q = s.proj[p];
         q.pool = a[p].pool;
