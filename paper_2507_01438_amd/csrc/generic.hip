@@ -1,5 +1,5 @@
-// Plain-ALU kernels for any dtype and shape: the fp32 parity configuration, odd shapes, and the
-// fallback for everything the MFMA paths do not take.  Three launches:
+// Plain-ALU kernels for any bf16 shape and weight format: the fallback for everything the MFMA paths do not take (fp32
+// has kernels of its own in fp32.hip).  Three launches:
 //   route   per row: which pool slot, which scale (Sec. 3.4: each request names its adapter)
 //   shrink  v_t = A_i x_t                          (Sec. 2.1 shapes: A [r, d_in])
 //   base    y_t = W x_t + s * B_i v_t, written at row t (Sec. 3.4 closing equation)
@@ -157,7 +157,7 @@ int launch_typed(const LinearArgs &a, hipStream_t stream)
 
 int elora::launch_generic(const LinearArgs &a, hipStream_t stream)
 {
-    if (a.dtype == ELORA_F32) return launch_typed<ELORA_W_SAME, float>(a, stream);
+    if (a.dtype == ELORA_F32) return launch_fp32(a, stream);
     if (a.wfmt == ELORA_W_SAME) return launch_typed<ELORA_W_SAME, uint16_t>(a, stream);
     if (a.wfmt == ELORA_W_INT8_G32) return launch_typed<ELORA_W_INT8_G32, uint16_t>(a, stream);
     return launch_typed<ELORA_W_INT4_G32, uint16_t>(a, stream);

@@ -1,0 +1,41 @@
+"""The fp32 kernels at the sizes where they can go wrong: fewer rows than a tile, one more than a tile, K below and around a
+turn of 16 and a round of 8 waves, rows whose length is no multiple of anything, odd ranks and ranks above one piece of 16,
+rows without adapter, every tile form.  Against the fp64 oracle; sums of at most K products in fp32 differ from it by at
+most (K + rank) * 2^-24 of the sum of the products' magnitudes, in practice by the square root of the count: 1e-5 of the
+largest output is 20 times what the largest K here gives."""
+import numpy as np
+import pytest
+
+from gpu_harness import DeviceCase, rel_err
+from paper_2507_01438_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # (K, N, T, pool, ranks)
+    (1, 1, 1, 1, (1,)),
+    (3, 5, 2, 2, (1, 3)),
+    (15, 17, 16, 3, (4, 7)),
+    (16, 16, 17, 3, (8,)),
+    (127, 31, 33, 4, (5, 16, 1)),
+    (129, 33, 16, 4, (17, 33)),
+    (512, 512, 8, 4, (8,)),
+    (1000, 1430, 155, 8, (3, 5, 8, 16)),
+    (1030, 2050, 140, 5, (40, 9)),       # 32 x 32 tiles, the last ones of 2 columns and 12 rows
+    (2049, 700, 65, 4, (128, 3)),
+    (4097, 48, 3, 2, (256,)),
+]
+
+
+@pytest.mark.parametrize("segments", [False, True])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_fp32_shapes(shape, segments):
+    K, N, T, pool, ranks = shape
+    lengths = [T - T // 2, 0, T // 2] if segments else None
+    w = I.small_workload(4100 + K, I.F32, K, N, T, pool, ranks, segments=lengths, no_adapter_rows=(1,) if T > 1 else ())
+    case = DeviceCase(w, w.projections[0])
+    y = case.run()
+    assert rel_err(y, case.reference()) <= 1e-5
+    assert np.array_equal(y, case.run())       # fixed summation order
+    assert case.pool.poll_error() == (0, -1)
+    case.close()
