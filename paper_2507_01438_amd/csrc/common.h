@@ -66,11 +66,14 @@ struct WsLayout {
     size_t wdeq_bytes; //   the row count from which converting W once pays)
     size_t part;       // fp32 sums of K-slices
     size_t part_bytes; //   room for them (part_want(); less only in the library's own array, with fewer K-slices then)
+    size_t v_lo;       // GEMM path, up to kSplitRows rows: bf16 of what bf16 leaves of the shrink results
+    size_t v_lo_bytes; //   (0 where the library's own array ends before)
     size_t total;
 };
 
 constexpr int kDecodeMaxTokens = 64;  // rows the streaming (decode) kernels take per launch
 constexpr int kDecodeMaxPasses = 4;   // a call with more rows may run as this many launches of that kernel at most
+constexpr int kSplitRows = kDecodeMaxTokens * kDecodeMaxPasses;  // see WsLayout::v_lo
 constexpr int kDecodeMaxSplit = 8;    // K-splits of the base contraction
 constexpr int kMaxRank = 256;
 constexpr int kSyncInts = 1024;       // ints in the workspace's counter area (the decode kernel's are below 320)
@@ -137,6 +140,7 @@ void decode_set_k_rotate(int on);  // 0: every workgroup walks its K-slice from 
 void decode_set_local_override(int mode);  // 0: never assume XCD-local hand-overs, -1: as probed
 int decode_probe_device(void *scratch, size_t scratch_bytes, hipStream_t stream);  // finds out, once per device, how workgroups are placed on the XCDs
 bool decode_eligible(const elora_linear_desc_t &d, int max_rank);
+bool decode_passes_forced();  // (elora_debug_decode_passes)
 int decode_passes(const elora_linear_desc_t &d);  // launches of the decode kernel this call is cut into (1 up to 64 rows), 0: not that path
 void decode_plan(const elora_linear_desc_t &d, elora_plan_t *plan);
 size_t decode_mail_bytes(int d_out);  // mailboxes of the decode kernel for d_out output columns
@@ -144,9 +148,10 @@ size_t decode_mail_bytes(int d_out);  // mailboxes of the decode kernel for d_ou
 struct BandShape {
     int ma, tiles_m, ks;
 };
-bool band_shape(int T, int K, int N, int wfmt, size_t part_bytes, bool copied, BandShape *s);  // copied: they would run on a bf16 copy of W; false: the 256 x 256 tiles are the better choice
+bool band_shape(int T, int K, int N, int wfmt, size_t part_bytes, bool copied, bool only, BandShape *s);  // copied: they would run on a bf16 copy of W; only: they cannot take this call; false: the 256 x 256 tiles are the better choice
 int enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t stream);
 void band_set(int mode, int tiles_m, int slices);  // -1: where it pays, 0: never, 1: wherever the shape allows; 0: as chosen
+bool band_instead_of_passes(const elora_linear_desc_t &d);  // a call of 65 to 256 rows: better as one product than as launches of the decode kernel
 bool gemm_eligible(const elora_linear_desc_t &d, int max_rank);
 void gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan);
 size_t gemm_wcopy_bytes(int wfmt, int n_tokens, int d_in, int d_out);  // (see below)

@@ -668,11 +668,28 @@ bool elora::gemm_eligible(const elora_linear_desc_t &d, int max_rank)
     return d.wfmt != ELORA_W_INT8_G32 || gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0;
 }
 
+// A call of 65 to 256 rows on a W of 4 million weights or more (smaller ones were not measured).  The decode kernel reads W
+// once per 64 rows; here it is read once, and the call's fixed part (route, shrink, a tile's beginning and end) is about 30 us.
+// Decode launches / here, a row per adapter of ranks 8 to 64, 4096 x 4096, 4096 x 14336, 14336 x 4096: 65 rows 41 / 47, 88 /
+// 69, 75 / 70 us; 129 rows 66 / 53, 128 / 92, 113 / 95; 256 rows 99 / 71, 184 / 125, 170 / 134.  One adapter: 65 rows of an
+// 8-bit W 38 / 35, 75 / 54, 72 / 60; 128 rows of bf16 4096 x 14336 78 / 50.  16 adapters of 8 rows: 128 rows 40 / 40, of an
+// 8-bit W 41 / 48.  A 4-bit or 8-bit W, a row per adapter of rank 16: 130 rows 4096 x 4096 57 / 59, 4096 x 14336 122 / 104.
+// Adapters that the expand has to gather (8-bit blocks, ranks that are no multiples of 8) stay with the decode kernel.
+bool elora::band_instead_of_passes(const elora_linear_desc_t &d)
+{
+    if (decode_passes_forced() || d.d_in % BK != 0 || d.d_out % 8 != 0 || d.d_in > (1 << 22) || d.d_out > (1 << 22)) return false;
+    if ((long long)d.d_in * d.d_out < (1 << 22)) return false;
+    if (d.pool != nullptr && (d.pool->q8 || d.pool->n_odd_ranks != 0)) return false;
+    const bool many_runs = d.pool != nullptr && (d.adapter_idx != nullptr || (long long)d.n_segments * 32 > d.n_tokens);
+    if (!many_runs) return true;
+    return d.n_tokens > (d.wfmt == ELORA_W_SAME || d.d_out >= 8192 ? 128 : 192);
+}
+
 void elora::gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
 {
     const bool copy_first = gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0;
     BandShape s;
-    const bool band = band_shape(d.n_tokens, d.d_in, d.d_out, d.wfmt, part_want(d.d_out), copy_first, &s);
+    const bool band = band_shape(d.n_tokens, d.d_in, d.d_out, d.wfmt, part_want(d.d_out), copy_first, d.wfmt == ELORA_W_INT8_G32 && !copy_first, &s);
     plan->n_launches = (d.pool ? 3 : 1) + (copy_first && !band && !d.pool ? 1 : 0);  // (with a pool the copy shares the route's launch)
     if (band) {
         plan->split_k = s.ks;
@@ -753,7 +770,8 @@ int enqueue_gemm(const LinearArgs &a, hipStream_t stream)
 
 static bool band_for(const LinearArgs &a, BandShape *s)
 {
-    return band_shape(a.T, a.K, a.N, a.wfmt, a.wsl.part_bytes, a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0, s);
+    const bool copied = a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
+    return band_shape(a.T, a.K, a.N, a.wfmt, a.wsl.part_bytes, copied, a.wfmt == ELORA_W_INT8_G32 && !copied, s);
 }
 
 int elora::launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream)

@@ -29,6 +29,20 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
     return __builtin_bit_cast(uint32_t, v);
 }
 
+// A float as the sum of two bf16 (to 2^-17 of it).  hi stays finite where v is, and where it is not, lo is zero.
+__device__ __forceinline__ void split_bf16(float v, uint16_t &hi, uint16_t &lo)
+{
+    hi = f32_to_bf16(v);
+    if ((hi & 0x7f80u) == 0x7f80u) {
+        if ((__float_as_uint(v) & 0x7f800000u) != 0x7f800000u) hi = (uint16_t)(__float_as_uint(v) >> 16);
+        else {
+            lo = 0;
+            return;
+        }
+    }
+    lo = f32_to_bf16(v - bf16_to_f32(hi));
+}
+
 // Eight consecutive values of an adapter kept in 8-bit blocks (they lie in one block: ranks and d_in are multiples of
 // 8 there) as matrix-core operands: scale * code, exact in fp32, rounded once to bf16.  (The decode and generic
 // kernels multiply the exact products; here the adapter passes through the matrix cores like every other operand.)
@@ -52,6 +66,7 @@ struct ShrinkProj {
     float *row_scale;    // [T]
     int32_t *short_rows; // [T]: the rows that sit in runs shorter than kShortRun, in any order
     uint16_t *V;         // [T][Rpad] bf16(s * A_i x_t), zeros beyond the rank and in rows without adapter
+    uint16_t *V_lo;      // [T][Rpad] bf16 of what V leaves of s * A_i x_t, or nullptr
     float *part;         // fp32 sums of the K-slices: [tile][slice][kShrinkRows][Rpad]
     int *sync;           // the workspace's counters
     int Rpad;

@@ -1,4 +1,5 @@
 // Host side of elora_batched_lora_linear: validation, workspace layout, kernel-family selection.
+#include <algorithm>
 #include <unordered_map>
 
 #include "common.h"
@@ -76,7 +77,10 @@ WsLayout elora::ws_layout(int T, int K, int N, int R, int wfmt)
     off += align_up(l.wdeq_bytes);
     l.part = off;
     l.part_bytes = part_want(N);
-    l.total = off + align_up(l.part_bytes);
+    off += align_up(l.part_bytes);
+    l.v_lo = off;
+    l.v_lo_bytes = (t < (size_t)kSplitRows ? t : (size_t)kSplitRows) * (size_t)((R + 63) / 64 * 64) * sizeof(uint16_t);
+    l.total = off + align_up(l.v_lo_bytes);
     return l;
 }
 
@@ -119,7 +123,8 @@ static int validate(const elora_linear_desc_t *d, WsLayout *wsl_out, bool part_o
     WsLayout wsl = ws_layout(d->n_tokens, d->d_in, d->d_out, max_rank, d->wfmt);
     if (part_optional && d->workspace_bytes < wsl.total) {
         if (d->workspace_bytes < wsl.part) return ELORA_E_STORAGE;
-        wsl.part_bytes = d->workspace_bytes - wsl.part;
+        wsl.part_bytes = std::min(wsl.part_bytes, d->workspace_bytes - wsl.part);
+        wsl.v_lo_bytes = 0;
         wsl.total = d->workspace_bytes;
     }
     if (d->workspace_bytes < wsl.total) return ELORA_E_STORAGE;
@@ -144,7 +149,8 @@ static void make_plan(const elora_linear_desc_t *d, elora_plan_t *plan)
         if (g_forced_path == ELORA_PATH_DECODE && dec) path = ELORA_PATH_DECODE;
         if (g_forced_path == ELORA_PATH_GEMM && gem) path = ELORA_PATH_GEMM;
     } else if (dec) {
-        path = ELORA_PATH_DECODE;
+        const bool room = d->workspace_bytes >= ws_layout(d->n_tokens, d->d_in, d->d_out, max_rank, d->wfmt).total;
+        path = d->n_tokens > kDecodeMaxTokens && room && band_instead_of_passes(*d) ? ELORA_PATH_GEMM : ELORA_PATH_DECODE;
     } else if (gem) {
         path = ELORA_PATH_GEMM;
     }

@@ -83,8 +83,11 @@ __device__ __forceinline__ void shrink_row_piece(const ShrinkArgs &s, const Shri
             }
         }
         if (lane == 0) {
-            vrow[j0] = j0 < rank ? f32_to_bf16(sc * a0) : (uint16_t)0;
-            vrow[j0 + 1] = two ? f32_to_bf16(sc * a1) : (uint16_t)0;
+            uint16_t hi[2], lo[2];
+            split_bf16(j0 < rank ? sc * a0 : 0.0f, hi[0], lo[0]);
+            split_bf16(two ? sc * a1 : 0.0f, hi[1], lo[1]);
+            *reinterpret_cast<uint32_t *>(vrow + j0) = hi[0] | ((uint32_t)hi[1] << 16);
+            if (pr.V_lo) *reinterpret_cast<uint32_t *>(pr.V_lo + (size_t)t * pr.Rpad + j0) = lo[0] | ((uint32_t)lo[1] << 16);
         }
     }
 }
@@ -184,9 +187,12 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
     const int swz = (m >> 1) & 7;  // (rows 16 b + m: the same for every block b)
 
     auto put = [&](int r, int c, floatx4 v, float scale) {  // four rank entries of a row, final
-        const uint64_t packed = (uint64_t)f32_to_bf16(scale * v[0]) | ((uint64_t)f32_to_bf16(scale * v[1]) << 16) |
-                                ((uint64_t)f32_to_bf16(scale * v[2]) << 32) | ((uint64_t)f32_to_bf16(scale * v[3]) << 48);
-        *reinterpret_cast<uint64_t *>(pr.V + (size_t)(r0 + r) * Rpad + c) = packed;
+        uint16_t hi[4], lo[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) split_bf16(scale * v[i], hi[i], lo[i]);
+        auto packed = [](const uint16_t *h) { return (uint64_t)h[0] | ((uint64_t)h[1] << 16) | ((uint64_t)h[2] << 32) | ((uint64_t)h[3] << 48); };
+        *reinterpret_cast<uint64_t *>(pr.V + (size_t)(r0 + r) * Rpad + c) = packed(hi);
+        if (pr.V_lo) *reinterpret_cast<uint64_t *>(pr.V_lo + (size_t)(r0 + r) * Rpad + c) = packed(lo);
     };
     // sums of slice k: [row][entry], written through to memory and read past the caches' first level (the workgroups of a
     // tile run on one XCD as a rule, but nothing depends on it)
@@ -444,6 +450,7 @@ void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n)
         q.row_scale = reinterpret_cast<float *>(a[p].ws + a[p].wsl.row_scale);
         q.short_rows = reinterpret_cast<int32_t *>(a[p].ws + a[p].wsl.row_rank);
         q.V = reinterpret_cast<uint16_t *>(a[p].ws + a[p].wsl.v);
+        q.V_lo = s.T <= kSplitRows && a[p].wsl.v_lo_bytes != 0 ? reinterpret_cast<uint16_t *>(a[p].ws + a[p].wsl.v_lo) : nullptr;
         q.part = reinterpret_cast<float *>(a[p].ws + a[p].wsl.part);
         q.sync = reinterpret_cast<int *>(a[p].ws + a[p].wsl.sync);
         q.Rpad = round_up(a[p].pool.max_rank, kRankPad);

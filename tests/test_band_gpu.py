@@ -6,7 +6,7 @@ the layer (matrix-core operands rounded to bf16, sums in fp32, one rounding of y
 import numpy as np
 import pytest
 
-from gpu_harness import DeviceCase, assert_close
+from gpu_harness import DeviceCase, assert_close, rel_err
 from paper_2507_01438_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
@@ -52,4 +52,57 @@ def test_band_shapes(shape, wfmt, q8):
         assert case.last_plan.path == GEMM
         assert_close(y, ref, base, f"{shape} {t} {s}")
         assert np.array_equal(y, again)  # fixed summation order, counters back at zero
+    case.close()
+
+
+@pytest.mark.parametrize("wfmt", [I.W_SAME, I.W_INT8_G32, I.W_INT4_G32])
+@pytest.mark.parametrize("T, segments", [(129, False), (193, False), (256, True), (100, True)])
+def test_65_to_256_rows_on_a_large_w_run_as_one_product(T, segments, wfmt):
+    """They have fp32 shrink results as sums of two bf16: no further from the oracle than the decode kernel, whose shrink
+    results are fp32 (y is rounded to bf16 in both, which is nearly all of either's error)."""
+    import torch
+
+    from paper_2507_01438_amd import binding as B
+    lengths = ([T - 21, 0, 21] if T <= 128 else [T - 40, 0, 17, 1, 1, 21]) if segments else None
+    w = I.small_workload(5100 + T, I.BF16, 2048, 2056 if wfmt == I.W_SAME else 2064, T, 9, (8, 16, 32, 64, 24), segments=lengths, wfmt=wfmt,
+                         no_adapter_rows=(1,) if segments else (0, 64, T - 1))
+    case = DeviceCase(w, w.projections[0])
+    y = case.run()
+    decode = T == 129 and wfmt != I.W_SAME     # (a row per adapter on a converted W: from 193 rows)
+    assert case.last_plan.path == (1 if decode else GEMM) and case.last_plan.n_launches == 3
+    ref = case.reference()
+    assert_close(y, ref, case.base_reference(), f"{T} rows")
+    assert np.array_equal(y, case.run())
+    if w.projections[0].N % 16 == 0:
+        d = case.run(force_path=1)
+        assert case.last_plan.path == 1
+        assert np.linalg.norm(y - ref) <= 1.005 * np.linalg.norm(d - ref)
+    n = len(lengths) if segments else T
+    over = np.linspace(0.25, 3.0, n).astype(np.float32)
+    y = case.run(scales=torch.from_numpy(over).to("cuda:0"))
+    rows = np.repeat(over, lengths) if segments else over
+    assert_close(y, case.reference(row_scale=rows), case.base_reference(), f"{T} rows, scales given")
+    assert case.pool.poll_error() == (0, -1)
+    case.close()
+
+
+def test_an_infinite_adapter_stays_in_its_own_rows():
+    """A row takes nothing from another row's adapter, not even zero times its entries."""
+    import torch
+
+    from paper_2507_01438_amd import binding as B
+    w = I.small_workload(5400, I.BF16, 512, 256, 40, 3, (16,), segments=[5, 3, 20, 12])
+    w.seg_adapter = np.array([0, 1, 2, 0], dtype=np.int32)
+    case = DeviceCase(w, w.projections[0])
+    A, Bm, s = case.adapters[1]
+    case.pool.load(1, torch.from_numpy(A.view(np.int16)), torch.from_numpy(np.full_like(Bm, 0x7F80).view(np.int16)), s)
+    torch.cuda.synchronize()
+    B.elora_debug_band(1)
+    try:
+        y = case.run(force_path=GEMM)
+    finally:
+        B.elora_debug_band(-1)
+    rest = np.r_[0:5, 8:40]
+    assert not np.isfinite(y[5:8]).any() and np.isfinite(y[rest]).all()
+    assert rel_err(y[rest], case.reference(rows=rest)) <= 1e-2
     case.close()
