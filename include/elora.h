@@ -430,8 +430,8 @@ int elora_debug_xcd_local(int mode);
 
 /*
  * Test hook: calls of 65 to 256 rows (bf16, d_in a multiple of 256, d_out of 16) may run as 2 to 4 launches of the
- * decode kernel over balanced row ranges instead of on the MFMA GEMM path.  -1 (default) and 1: they do; 0: they
- * take the GEMM path.  Errors: E_SHAPE.
+ * decode kernel over balanced row ranges instead of on the MFMA GEMM path.  -1 (default): they do, unless one matrix
+ * product is the faster form (a large W); 1: they do; 0: they take the GEMM path.  Errors: E_SHAPE.
  */
 int elora_debug_decode_passes(int mode);
 

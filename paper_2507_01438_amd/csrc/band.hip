@@ -467,34 +467,45 @@ void elora::band_set(int mode, int tiles_m, int slices)
 }
 
 // Which tiles, and whether this kernel or the 256 x 256 tiles: the launch's time in cycles, from what a K block, a tile's
-// beginning and end and the sums of slices were measured to take, times the rounds of 256 workgroups (one per compute unit).
-//   here: a K block 270 + 160 ma (a W that is converted on the way 1550 + 105 ma), a tile 6000 + 2300 ma, its slices'
-//   sums 2000 + 450 ma each; there: a K block 3400 (from the bf16 copy of W 2600, converted on the way 5700), a tile 6000,
-//   the copy 1.04e-3 per weight.
-// (1500 rows x 4096 x 14336: 227 us here, 216 there; 600 rows 109 and 119; 1000 rows x 4096 columns 58 and 121.)
-bool elora::band_shape(int T, int K, int N, int wfmt, size_t part_bytes, bool copied, bool only, BandShape *s)
+// beginning and end, a step of the expand and the sums of slices were measured to take, times the rounds of 256 workgroups
+// (one per compute unit).
+//   here: a K block 270 + 160 ma (a W that is converted on the way 1550 + 105 ma), a tile 6000 + 2300 ma, an expand step
+//   1100 (adapters in 8-bit blocks 6500; ranks above 32 are taken to be mixed with smaller ones), the slices' sums 2000 + 450
+//   ma each; 20 % more than that where there is more than one round;
+//   there: a K block 3300, in further rounds 2900 (from the bf16 copy of W 2600, converted on the way 5700), a tile 6000, 16
+//   rank entries of a short run 850 (adapters in 8-bit blocks 4000), the copy 1.04e-3 per weight.
+// (4096 x 14336, here / there: 600 rows of one adapter 109 / 119 us, 800 of two 124 / 119, 1800 235 / 208, 600 of an adapter
+// each 217 / 188; 4096 x 4096: 600 of an adapter each 103 / 185, 1000 of one 58 / 121; 2560 x 7680, 3000 rows: 171 / 140.)
+bool elora::band_shape(const BandCall &c, size_t part_bytes, BandShape *s)
 {
-    if ((g_mode == 0 && !only) || K % BK != 0 || N % 8 != 0) return false;
+    const int T = c.T, K = c.K, N = c.N;
+    if ((g_mode == 0 && !c.only) || K % BK != 0 || N % 8 != 0) return false;
     const int tiles_n = (N + BN - 1) / BN, blocks = K / BK;
     const int least = (T + 32 * kMaxMA - 1) / (32 * kMaxMA);
     auto rounds = [](double workgroups) { return std::ceil(workgroups / 256); };
     double best = -1.0;
     for (int tiles_m = g_mode_tiles > least ? g_mode_tiles : least; tiles_m <= (g_mode_tiles ? g_mode_tiles : least + 2); ++tiles_m) {
         const int ma = ((T + tiles_m - 1) / tiles_m + 31) / 32, tm = (T + 32 * ma - 1) / (32 * ma);
-        const double block = wfmt == ELORA_W_SAME ? 270 + 160 * ma : 1550 + 105 * ma;
+        const double block = c.wfmt == ELORA_W_SAME ? 270 + 160 * ma : 1550 + 105 * ma;
+        // a wave's steps: where the runs are spread over the batch, and what the tile with most of them has above that
+        const double row = (c.q8 ? 6500.0 : 1100.0) * (1 + 0.5 * ((c.max_rank - 1) / 32));
+        const double spread = row * 16 * ma * c.runs / T, above = std::max(0.0, row * std::min(16 * ma, c.runs) - spread);
         for (int ks = g_mode_slices ? g_mode_slices : 1; ks <= (g_mode_slices ? g_mode_slices : kMaxSlices); ++ks) {
             if (ks > blocks || (ks > 1 && ((long long)tm * tiles_n > kSyncTileCount || (size_t)tm * tiles_n * ks * (ma * 32 * BN * 4) > part_bytes))) continue;
-            const double cycles = rounds((double)tm * tiles_n * ks) * ((blocks + ks - 1) / ks * block + 6000 + 2300 * ma) + (ks > 1 ? 2000 + 450.0 * ks * ma : 0);
+            const double n = rounds((double)tm * tiles_n * ks);
+            const double tile = (blocks + ks - 1) / ks * block + 6000 + 2300 * ma + spread / ks;
+            const double cycles = (n * tile + above / ks) * (n > 1 ? 1.2 : 1.0) + (ks > 1 ? 2000 + 450.0 * ks * ma : 0);
             if (best < 0 || cycles < best) {
                 best = cycles;
                 *s = BandShape{ma, tm, ks};
             }
         }
     }
-    if (best < 0 || g_mode == 1 || only) return best >= 0;
-    const double there = rounds((double)((T + 255) / 256) * ((N + 255) / 256)) * (blocks * (wfmt == ELORA_W_SAME ? 3400.0 : copied ? 2600.0 : 5700.0) + 6000) +
-                         (copied ? 1.04e-3 * K * N : 0);
-    return best < there;
+    if (best < 0 || g_mode == 1 || c.only) return best >= 0;
+    const double n = rounds((double)((T + 255) / 256) * ((N + 255) / 256));
+    const double block = c.copied ? 2600 : c.wfmt != ELORA_W_SAME ? 5700 : n > 1 ? 2900 : 3300;
+    const double steps = (c.q8 ? 4000.0 : 850.0) * std::min(128, c.runs) * ((c.max_rank + 15) / 16);
+    return best < n * (blocks * block + 6000) + steps + (c.copied ? 1.04e-3 * K * N : 0);
 }
 
 int elora::enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t stream)

@@ -148,7 +148,13 @@ size_t decode_mail_bytes(int d_out);  // mailboxes of the decode kernel for d_ou
 struct BandShape {
     int ma, tiles_m, ks;
 };
-bool band_shape(int T, int K, int N, int wfmt, size_t part_bytes, bool copied, bool only, BandShape *s);  // copied: they would run on a bf16 copy of W; only: they cannot take this call; false: the 256 x 256 tiles are the better choice
+// runs: of equal adapters, at most; q8: pool of 8-bit blocks; copied: the 256 x 256 tiles would run on a bf16 copy of W; only:
+// they cannot take this call
+struct BandCall {
+    int T, K, N, wfmt, runs, max_rank;
+    bool q8, copied, only;
+};
+bool band_shape(const BandCall &c, size_t part_bytes, BandShape *s);  // false: the 256 x 256 tiles are the better choice
 int enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t stream);
 void band_set(int mode, int tiles_m, int slices);  // -1: where it pays, 0: never, 1: wherever the shape allows; 0: as chosen
 bool band_instead_of_passes(const elora_linear_desc_t &d);  // a call of 65 to 256 rows: better as one product than as launches of the decode kernel

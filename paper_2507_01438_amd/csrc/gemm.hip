@@ -689,7 +689,9 @@ void elora::gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
 {
     const bool copy_first = gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0;
     BandShape s;
-    const bool band = band_shape(d.n_tokens, d.d_in, d.d_out, d.wfmt, part_want(d.d_out), copy_first, d.wfmt == ELORA_W_INT8_G32 && !copy_first, &s);
+    const int runs = !d.pool ? 0 : d.adapter_idx ? d.n_tokens : d.n_segments;
+    const bool band = band_shape(BandCall{d.n_tokens, d.d_in, d.d_out, d.wfmt, runs, d.pool ? d.pool->max_rank : 1, d.pool && d.pool->q8, copy_first,
+                                          d.wfmt == ELORA_W_INT8_G32 && !copy_first}, part_want(d.d_out), &s);
     plan->n_launches = (d.pool ? 3 : 1) + (copy_first && !band && !d.pool ? 1 : 0);  // (with a pool the copy shares the route's launch)
     if (band) {
         plan->split_k = s.ks;
@@ -771,7 +773,8 @@ int enqueue_gemm(const LinearArgs &a, hipStream_t stream)
 static bool band_for(const LinearArgs &a, BandShape *s)
 {
     const bool copied = a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
-    return band_shape(a.T, a.K, a.N, a.wfmt, a.wsl.part_bytes, copied, a.wfmt == ELORA_W_INT8_G32 && !copied, s);
+    const int runs = !a.has_pool ? 0 : a.route.adapter_idx ? a.T : a.route.n_segments;
+    return band_shape(BandCall{a.T, a.K, a.N, a.wfmt, runs, a.pool.max_rank, a.has_pool && a.pool.q8, copied, a.wfmt == ELORA_W_INT8_G32 && !copied}, a.wsl.part_bytes, s);
 }
 
 int elora::launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream)

@@ -149,8 +149,10 @@ static void make_plan(const elora_linear_desc_t *d, elora_plan_t *plan)
         if (g_forced_path == ELORA_PATH_DECODE && dec) path = ELORA_PATH_DECODE;
         if (g_forced_path == ELORA_PATH_GEMM && gem) path = ELORA_PATH_GEMM;
     } else if (dec) {
-        const bool room = d->workspace_bytes >= ws_layout(d->n_tokens, d->d_in, d->d_out, max_rank, d->wfmt).total;
-        path = d->n_tokens > kDecodeMaxTokens && room && band_instead_of_passes(*d) ? ELORA_PATH_GEMM : ELORA_PATH_DECODE;
+        // (the library's own array may end before the room for the second half of the shrink results)
+        const bool one_product = d->n_tokens > kDecodeMaxTokens && band_instead_of_passes(*d) &&
+                                 d->workspace_bytes >= ws_layout(d->n_tokens, d->d_in, d->d_out, max_rank, d->wfmt).total;
+        path = one_product ? ELORA_PATH_GEMM : ELORA_PATH_DECODE;
     } else if (gem) {
         path = ELORA_PATH_GEMM;
     }
