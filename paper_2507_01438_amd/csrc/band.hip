@@ -479,7 +479,7 @@ void elora::band_set(int mode, int tiles_m, int slices)
 bool elora::band_shape(const BandCall &c, size_t part_bytes, BandShape *s)
 {
     const int T = c.T, K = c.K, N = c.N;
-    if ((g_mode == 0 && !c.only) || K % BK != 0 || N % 8 != 0) return false;
+    if (g_mode == 0 || K % BK != 0 || N % 8 != 0) return false;
     const int tiles_n = (N + BN - 1) / BN, blocks = K / BK;
     const int least = (T + 32 * kMaxMA - 1) / (32 * kMaxMA);
     auto rounds = [](double workgroups) { return std::ceil(workgroups / 256); };

@@ -140,6 +140,7 @@ void decode_set_k_rotate(int on);  // 0: every workgroup walks its K-slice from 
 void decode_set_local_override(int mode);  // 0: never assume XCD-local hand-overs, -1: as probed
 int decode_probe_device(void *scratch, size_t scratch_bytes, hipStream_t stream);  // finds out, once per device, how workgroups are placed on the XCDs
 bool decode_eligible(const elora_linear_desc_t &d, int max_rank);
+bool decode_shape(int K, int N);  // a W that the decode kernel takes
 bool decode_passes_forced();  // (elora_debug_decode_passes)
 int decode_passes(const elora_linear_desc_t &d);  // launches of the decode kernel this call is cut into (1 up to 64 rows), 0: not that path
 void decode_plan(const elora_linear_desc_t &d, elora_plan_t *plan);
@@ -149,12 +150,16 @@ struct BandShape {
     int ma, tiles_m, ks;
 };
 // runs: of equal adapters, at most; q8: pool of 8-bit blocks; copied: the 256 x 256 tiles would run on a bf16 copy of W; only:
-// they cannot take this call
+// they are no alternative to this call (band_only)
 struct BandCall {
     int T, K, N, wfmt, runs, max_rank;
     bool q8, copied, only;
 };
-bool band_shape(const BandCall &c, size_t part_bytes, BandShape *s);  // false: the 256 x 256 tiles are the better choice
+// Calls of 65 to 256 rows that the decode kernel takes as well, with shrink results in fp32: on this path they run as the
+// product of band.hip alone, which keeps these whole; the 256 x 256 tiles multiply them rounded to bf16 (and an 8-bit W from
+// a copy that these calls have no room for).
+inline bool band_only(int T, int K, int N) { return T > kDecodeMaxTokens && T <= kSplitRows && decode_shape(K, N); }
+bool band_shape(const BandCall &c, size_t part_bytes, BandShape *s);  // false: not here (the 256 x 256 tiles; where only: nowhere on this path)
 int enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t stream);
 void band_set(int mode, int tiles_m, int slices);  // -1: where it pays, 0: never, 1: wherever the shape allows; 0: as chosen
 bool band_instead_of_passes(const elora_linear_desc_t &d);  // a call of 65 to 256 rows: better as one product than as launches of the decode kernel

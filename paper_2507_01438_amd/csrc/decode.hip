@@ -829,11 +829,13 @@ extern "C" int elora_trace_clear()
 // 4096 x 4096 / 4096 x 14336 / 14336 x 4096: 128 rows 47 / 91 / 90 us against 384 / 388 / 657 us on the GEMM path,
 // 256 rows 88 / 171 / 167 us against 574 / 587 / 868 us.  (Where W is large the product of band.hip is the better choice
 // for many of these calls: band_instead_of_passes.)
+bool elora::decode_shape(int K, int N) { return K % kChunk == 0 && N % 16 == 0; }
+
 bool elora::decode_passes_forced() { return g_pass_mode >= 0; }
 
 int elora::decode_passes(const elora_linear_desc_t &d)
 {
-    if (!(d.dtype == ELORA_BF16 && d.n_tokens >= 1 && d.d_in % kChunk == 0 && d.d_out % 16 == 0)) return 0;
+    if (!(d.dtype == ELORA_BF16 && d.n_tokens >= 1 && decode_shape(d.d_in, d.d_out))) return 0;
     const int passes = (d.n_tokens + kDecodeMaxTokens - 1) / kDecodeMaxTokens;
     if (passes == 1) return 1;
     if (passes > kDecodeMaxPasses || g_pass_mode == 0) return 0;

@@ -668,6 +668,12 @@ bool elora::gemm_eligible(const elora_linear_desc_t &d, int max_rank)
     return d.wfmt != ELORA_W_INT8_G32 || gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0;
 }
 
+static BandCall band_call(const elora_linear_desc_t &d)
+{
+    return BandCall{d.n_tokens, d.d_in, d.d_out, d.wfmt, !d.pool ? 0 : d.adapter_idx ? d.n_tokens : d.n_segments, d.pool ? d.pool->max_rank : 1, d.pool && d.pool->q8,
+                    gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0, band_only(d.n_tokens, d.d_in, d.d_out)};
+}
+
 // A call of 65 to 256 rows on a W of 4 million weights or more (smaller ones were not measured).  The decode kernel reads W
 // once per 64 rows; here it is read once, and the call's fixed part (route, shrink, a tile's beginning and end) is about 30 us.
 // Decode launches / here, a row per adapter of ranks 8 to 64, 4096 x 4096, 4096 x 14336, 14336 x 4096: 65 rows 41 / 47, 88 /
@@ -681,17 +687,17 @@ bool elora::band_instead_of_passes(const elora_linear_desc_t &d)
     if ((long long)d.d_in * d.d_out < (1 << 22)) return false;
     if (d.pool != nullptr && (d.pool->q8 || d.pool->n_odd_ranks != 0)) return false;
     const bool many_runs = d.pool != nullptr && (d.adapter_idx != nullptr || (long long)d.n_segments * 32 > d.n_tokens);
-    if (!many_runs) return true;
-    return d.n_tokens > (d.wfmt == ELORA_W_SAME || d.d_out >= 8192 ? 128 : 192);
+    if (many_runs && d.n_tokens <= (d.wfmt == ELORA_W_SAME || d.d_out >= 8192 ? 128 : 192)) return false;
+    BandShape s;
+    return band_shape(band_call(d), part_want(d.d_out), &s);
 }
 
 void elora::gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
 {
-    const bool copy_first = gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0;
+    const BandCall c = band_call(d);
+    const bool copy_first = c.copied;
     BandShape s;
-    const int runs = !d.pool ? 0 : d.adapter_idx ? d.n_tokens : d.n_segments;
-    const bool band = band_shape(BandCall{d.n_tokens, d.d_in, d.d_out, d.wfmt, runs, d.pool ? d.pool->max_rank : 1, d.pool && d.pool->q8, copy_first,
-                                          d.wfmt == ELORA_W_INT8_G32 && !copy_first}, part_want(d.d_out), &s);
+    const bool band = band_shape(c, part_want(d.d_out), &s);
     plan->n_launches = (d.pool ? 3 : 1) + (copy_first && !band && !d.pool ? 1 : 0);  // (with a pool the copy shares the route's launch)
     if (band) {
         plan->split_k = s.ks;
@@ -774,7 +780,7 @@ static bool band_for(const LinearArgs &a, BandShape *s)
 {
     const bool copied = a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
     const int runs = !a.has_pool ? 0 : a.route.adapter_idx ? a.T : a.route.n_segments;
-    return band_shape(BandCall{a.T, a.K, a.N, a.wfmt, runs, a.pool.max_rank, a.has_pool && a.pool.q8, copied, a.wfmt == ELORA_W_INT8_G32 && !copied}, a.wsl.part_bytes, s);
+    return band_shape(BandCall{a.T, a.K, a.N, a.wfmt, runs, a.pool.max_rank, a.has_pool && a.pool.q8, copied, band_only(a.T, a.K, a.N)}, a.wsl.part_bytes, s);
 }
 
 int elora::launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream)
