@@ -11,8 +11,9 @@
 //     outputs of one row.
 //   - a 4-bit or 8-bit W stays as it is in LDS; a fragment is converted on its way to the matrix cores.
 //   - the expand B_i v_t comes after the K loop: every wave walks the runs of equal adapters in its own rows, 16 rows and
-//     32 rank entries at a time, through a ring of its own (no barriers), and a row only takes what its own adapter gives.  Calls of up to 256 rows, which
-//     the decode kernel took before with fp32 shrink results, have these as sums of two bf16.
+//     32 rank entries at a time, through a ring of its own (no barriers), and a row only takes what its own adapter gives.
+//     Calls of up to 256 rows, which the decode kernel takes too, with fp32 shrink results, have these whole here as well:
+//     three bf16 each (24 bits), three matrix instructions in the place of one, and the scale applied to what they give.
 // A call with one adapter of rank 32 (route, shrink and product), on the 256 x 256 tiles / here: 389 rows 4096 x 4096 116 /
 // 42 us, 4096 x 14336 121 / 73, 14336 x 4096 348 / 86; 1000 rows 4096 x 4096 121 / 58.  A K block of 224 x 128 takes 1300
 // cycles (matrix instructions 900, LDS 1060), a tile's beginning and end 20000, most of it code that is fetched once.
@@ -68,13 +69,15 @@ struct Band {
     static constexpr int kDepth = kLdsBytes / kStage < 8 ? kLdsBytes / kStage : 8;
     static constexpr int kWLoads = kWBytes / 4096;                         // per wave
     static constexpr int kLoads = MA + kWLoads + (kScaleBytes ? 1 : 0);    // per wave and K block
-    static constexpr int kBytes = kDepth * kStage;
-    static constexpr int kStepLoads = 6, kStepBytes = kStepLoads * 1024;    // 16 rows of V and of V_lo, 64 columns of B_i, 32 rank entries
+    // 16 rows of V, of its second and of its third parts, 64 columns of B_i, 32 rank entries
+    static constexpr int kWholeLoads = 7, kRoundedLoads = 5, kStepBytes = kWholeLoads * 1024;
+    // (all of LDS, unless the K loop leaves room for a second workgroup)
+    static constexpr int kBytes = kDepth * kStage * 2 > kLdsBytes ? kLdsBytes / 4096 * 4096 : kDepth * kStage;
     static constexpr int kWaveBytes = kBytes / 4 / 1024 * 1024;
     static constexpr int kTableBytes = kWaveRows * (kMaxRank / 32) * 8;    // the wave's expand steps at most
     static constexpr int kStepRoom = (kWaveBytes - kTableBytes) / kStepBytes;
     static constexpr int kSteps = kStepRoom < 8 ? kStepRoom : 8;
-    static_assert(kDepth >= 3 && kSteps >= 2 && kDepth * kLoads < 64 && kSteps * kStepLoads < 64, "the load counter has six bits");
+    static_assert(kDepth >= 3 && kSteps >= 2 && kDepth * kLoads < 64 && kSteps * kWholeLoads < 64, "the load counter has six bits");
 };
 
 struct BandArgs {
@@ -84,7 +87,8 @@ struct BandArgs {
     const void *W;
     const uint16_t *w_scales;
     const int32_t *row_slot;
-    const uint16_t *V, *V_lo;  // V_lo: what bf16 leaves of the shrink results, or V again
+    const float *row_scale;
+    const uint16_t *V, *V_rest;  // V_rest: [2][T][Rpad] the second and third parts of the shrink results, or nullptr
     int Rpad;
     uint16_t *y;
     float *part;   // sums of K-slices: [tile][slice][wave][fragment][lane] x 4
@@ -235,12 +239,17 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // the slots and ranks of the wave's rows (the ranks are on their way during the K loop)
+    // the slots, scales and ranks of the wave's rows (the ranks are on their way during the K loop)
+    const bool whole = ba.V_rest != nullptr;
     int slot_v[2] = {INT32_MIN, INT32_MIN}, rank_v[2] = {0, 0};
+    float scale_v[2] = {1.0f, 1.0f};  // (V that is rounded has the scale in it)
     if (has_pool) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            if (h * 64 + lane < G::kWaveRows && r0 + h * 64 + lane < T) slot_v[h] = ba.row_slot[r0 + h * 64 + lane];
+            if (h * 64 + lane < G::kWaveRows && r0 + h * 64 + lane < T) {
+                slot_v[h] = ba.row_slot[r0 + h * 64 + lane];
+                if (whole) scale_v[h] = ba.row_scale[r0 + h * 64 + lane];
+            }
 #pragma unroll
         for (int h = 0; h < 2; ++h)
             if (slot_v[h] >= 0) rank_v[h] = pool.meta[slot_v[h]].rank;
@@ -265,8 +274,8 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
     wait_loads<0>();
 
     // ---- expand, and what the wave has of y, 16 rows at a time -----------------------------------------------------------
-    // A step is (16-row block, run of equal adapters in it, 32 rank entries): 1 KiB of V, 1 of V_lo and 4 of B_i for four or
-    // eight matrix instructions; a tile's K-slices take turns at the runs.  The wave first writes its steps out as a table, a lane per row;
+    // A step is (16-row block, run of equal adapters in it, 32 rank entries): 1 or 3 KiB of V and 4 of B_i for four or twelve
+    // matrix instructions; a tile's K-slices take turns at the runs.  The wave first writes its steps out as a table, a lane per row;
     // the loads of kSteps - 1 steps are under way while one is multiplied.  Ranks that are no multiples of 8, and adapters in
     // 8-bit blocks, have rows of B_i that a 16-byte load cannot take: their fragments are gathered when the step is due.
     // What bounds this part is instructions (fetched once, a cache line of code takes 250 cycles): so the blocks go through
@@ -285,8 +294,8 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
     };
     const bool q8 = pool.q8 != 0;
     const uint32_t ring0 = lds0 + (uint32_t)(wave * G::kWaveBytes);
-    const char *const vbase = reinterpret_cast<const char *>(ba.V + (size_t)r0 * ba.Rpad), *const vlo = reinterpret_cast<const char *>(ba.V_lo + (size_t)r0 * ba.Rpad);
-    const bool split = ba.V_lo != ba.V;
+    const char *const vbase = reinterpret_cast<const char *>(ba.V + (size_t)r0 * ba.Rpad), *const vmid = reinterpret_cast<const char *>(ba.V_rest + (size_t)r0 * ba.Rpad),
+               *const vlast = vmid + (size_t)T * ba.Rpad * 2;
     const int line = lane >> 2, chunk = (lane & 3) ^ ((line >> 2) & 3);
     uint32_t col[4];
 #pragma unroll
@@ -296,14 +305,17 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
         const int row = min((st.row & ~15) + line, T - 1 - r0);
         const uint32_t voff = (uint32_t)((row * ba.Rpad + st.j0 + chunk * 8) * 2);
         dma16(lds, vbase, voff);
-        dma16(lds + 1024, vlo, voff);
+        if (whole) {
+            dma16(lds + 1024, vmid, voff);
+            dma16(lds + 2048, vlast, voff);
+        }
         // (a gathered step loads its row of V again, so that all steps have the same number of loads)
         const bool gather = q8 || (st.rank & 7) != 0;
         const char *const Bm = gather ? vbase : slot_B(pool, st.slot);
         const uint32_t j = gather ? voff : 2u * (uint32_t)(st.j0 + chunk * 8 < st.rank ? st.j0 + chunk * 8 : st.j0);
         const uint32_t stride = gather ? 0u : 2u * (uint32_t)st.rank;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) dma16(lds + 2048 + i * 1024, Bm, col[i] * stride + j);
+        for (int i = 0; i < 4; ++i) dma16(lds + 3072 + i * 1024, Bm, col[i] * stride + j);
     };
     if (has_pool) {
         const int before0 = __shfl_up(slot_v[0], 1), before1 = __shfl_up(slot_v[1], 1), last0 = __builtin_amdgcn_readlane(slot_v[0], 63);
@@ -360,19 +372,22 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
     int step = 0, at = 0;
 #pragma unroll 1
     for (int a = 0; a < MA; ++a) {
+        float row_scale = 1.0f;
+        if (whole) row_scale = __shfl(a < 4 ? scale_v[0] : scale_v[1], (a & 3) * 16 + m);
         const int stop = a + 1 == MA ? n_steps : __builtin_amdgcn_readlane(a + 1 < 4 ? first[0] : first[1], ((a + 1) & 3) * 16);
 #pragma unroll 1
         for (; step < stop; ++step) {
             const Step cur = step_at(step);
             // (the place read a step ago; behind the last step its loads are asked for again, so that the count stays)
             issue(step_at(step + G::kSteps - 1), at == 0 ? G::kSteps - 1 : at - 1);
-            wait_loads<G::kStepLoads * (G::kSteps - 1)>();
+            if (whole) wait_loads<G::kWholeLoads *(G::kSteps - 1)>();
+            else wait_loads<G::kRoundedLoads *(G::kSteps - 1)>();
             const unsigned char *const st = own + at * G::kStepBytes;
             const int place = (g ^ ((m >> 2) & 3)) * 16, j = cur.j0 + g * 8;
-            bf16x8 v = *reinterpret_cast<const bf16x8 *>(st + m * 64 + place), lo = *reinterpret_cast<const bf16x8 *>(st + 1024 + m * 64 + place), bm[4];
+            bf16x8 v = *reinterpret_cast<const bf16x8 *>(st + m * 64 + place), bm[4];
             const u32x4 zero{0, 0, 0, 0};
 #pragma unroll
-            for (int b = 0; b < 4; ++b) bm[b] = *reinterpret_cast<const bf16x8 *>(st + 2048 + (b * 16 + m) * 64 + place);
+            for (int b = 0; b < 4; ++b) bm[b] = *reinterpret_cast<const bf16x8 *>(st + 3072 + (b * 16 + m) * 64 + place);
             if (q8 || (cur.rank & 7) != 0) {
                 const char *const Bm = slot_B(pool, cur.slot);
 #pragma unroll
@@ -395,7 +410,7 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
                 }
             }
             if (j >= cur.rank) {  // (entries past the rank: zero in V; zero here too, whatever the adapter holds)
-                v = lo = __builtin_bit_cast(bf16x8, zero);
+                v = __builtin_bit_cast(bf16x8, zero);
 #pragma unroll
                 for (int b = 0; b < 4; ++b) bm[b] = __builtin_bit_cast(bf16x8, zero);
             }
@@ -404,14 +419,18 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
             floatx4 d[4];
 #pragma unroll
             for (int b = 0; b < 4; ++b) d[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-            if (split) {
+            if (whole) {
+                const bf16x8 mid = *reinterpret_cast<const bf16x8 *>(st + 1024 + m * 64 + place), last = *reinterpret_cast<const bf16x8 *>(st + 2048 + m * 64 + place);
 #pragma unroll
-                for (int b = 0; b < 4; ++b) d[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], lo, d[b], 0, 0, 0);
+                for (int b = 0; b < 4; ++b) d[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], mid, d[b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) d[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], last, d[b], 0, 0, 0);
             }
+            const float scale = in ? row_scale : 0.0f;
 #pragma unroll
             for (int b = 0; b < 4; ++b)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) acc[0][b][q] += in ? d[b][q] : 0.0f;
+                for (int q = 0; q < 4; ++q) acc[0][b][q] = fmaf(in ? d[b][q] : 0.0f, scale, acc[0][b][q]);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (this step's place has been read)
             at = at + 1 == G::kSteps ? 0 : at + 1;
         }
@@ -508,6 +527,8 @@ bool elora::band_shape(const BandCall &c, size_t part_bytes, BandShape *s)
     return best < n * (blocks * block + 6000) + steps + (c.copied ? 1.04e-3 * K * N : 0);
 }
 
+bool elora::band_whole(const LinearArgs &a) { return a.has_pool && a.T <= kWholeRows && a.wsl.v_rest_bytes != 0; }
+
 int elora::enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t stream)
 {
     BandArgs b;
@@ -522,7 +543,8 @@ int elora::enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t str
     b.w_scales = static_cast<const uint16_t *>(a.w_scales);
     b.row_slot = reinterpret_cast<const int32_t *>(a.ws + a.wsl.row_slot);
     b.V = reinterpret_cast<const uint16_t *>(a.ws + a.wsl.v);
-    b.V_lo = a.T <= kSplitRows && a.wsl.v_lo_bytes != 0 ? reinterpret_cast<const uint16_t *>(a.ws + a.wsl.v_lo) : b.V;
+    b.V_rest = band_whole(a) ? reinterpret_cast<const uint16_t *>(a.ws + a.wsl.v_rest) : nullptr;
+    b.row_scale = reinterpret_cast<const float *>(a.ws + a.wsl.row_scale);
     b.Rpad = round_up(a.pool.max_rank, kRankPad);
     b.y = static_cast<uint16_t *>(a.y);
     b.part = reinterpret_cast<float *>(a.ws + a.wsl.part);

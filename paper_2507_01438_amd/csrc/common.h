@@ -66,14 +66,14 @@ struct WsLayout {
     size_t wdeq_bytes; //   the row count from which converting W once pays)
     size_t part;       // fp32 sums of K-slices
     size_t part_bytes; //   room for them (part_want(); less only in the library's own array, with fewer K-slices then)
-    size_t v_lo;       // GEMM path, up to kSplitRows rows: bf16 of what bf16 leaves of the shrink results
-    size_t v_lo_bytes; //   (0 where the library's own array ends before)
+    size_t v_rest;       // GEMM path, up to kWholeRows rows: the second and third bf16 of the shrink results
+    size_t v_rest_bytes; //   (0 where the library's own array ends before)
     size_t total;
 };
 
 constexpr int kDecodeMaxTokens = 64;  // rows the streaming (decode) kernels take per launch
 constexpr int kDecodeMaxPasses = 4;   // a call with more rows may run as this many launches of that kernel at most
-constexpr int kSplitRows = kDecodeMaxTokens * kDecodeMaxPasses;  // see WsLayout::v_lo
+constexpr int kWholeRows = kDecodeMaxTokens * kDecodeMaxPasses;  // see WsLayout::v_rest
 constexpr int kDecodeMaxSplit = 8;    // K-splits of the base contraction
 constexpr int kMaxRank = 256;
 constexpr int kSyncInts = 1024;       // ints in the workspace's counter area (the decode kernel's are below 320)
@@ -158,8 +158,9 @@ struct BandCall {
 // Calls of 65 to 256 rows that the decode kernel takes as well, with shrink results in fp32: on this path they run as the
 // product of band.hip alone, which keeps these whole; the 256 x 256 tiles multiply them rounded to bf16 (and an 8-bit W from
 // a copy that these calls have no room for).
-inline bool band_only(int T, int K, int N) { return T > kDecodeMaxTokens && T <= kSplitRows && decode_shape(K, N); }
+inline bool band_only(int T, int K, int N) { return T > kDecodeMaxTokens && T <= kWholeRows && decode_shape(K, N); }
 bool band_shape(const BandCall &c, size_t part_bytes, BandShape *s);  // false: not here (the 256 x 256 tiles; where only: nowhere on this path)
+bool band_whole(const LinearArgs &a);  // band.hip takes this call's shrink results whole, as sums of three bf16
 int enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t stream);
 void band_set(int mode, int tiles_m, int slices);  // -1: where it pays, 0: never, 1: wherever the shape allows; 0: as chosen
 bool band_instead_of_passes(const elora_linear_desc_t &d);  // a call of 65 to 256 rows: better as one product than as launches of the decode kernel

@@ -786,10 +786,10 @@ static bool band_for(const LinearArgs &a, BandShape *s)
 int elora::launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream)
 {
     (void)plan;
-    ShrinkArgs s;
-    shrink_args(s, &a, 1);
     BandShape band;
-    const bool in_band = band_for(a, &band);
+    const bool in_band = band_for(a, &band), whole = in_band && band_whole(a);
+    ShrinkArgs s;
+    shrink_args(s, &a, 1, &whole);
     const bool copy = !in_band && a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
     int rc = launch_route(s, &a, copy, stream);
     if (rc == ELORA_OK && a.has_pool) rc = launch_shrink(s, stream);
@@ -801,11 +801,14 @@ int elora::launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_
 // one route launch, ONE shrink launch over the adapters of all of them, then each call's GEMM.
 int elora::launch_gemm_group(const LinearArgs *a, int n, hipStream_t stream)
 {
-    ShrinkArgs s;
-    shrink_args(s, a, n);
     BandShape band[kShrinkMulti];
-    bool in_band[kShrinkMulti];
-    for (int i = 0; i < n; ++i) in_band[i] = band_for(a[i], &band[i]);
+    bool in_band[kShrinkMulti], whole[kShrinkMulti];
+    for (int i = 0; i < n; ++i) {
+        in_band[i] = band_for(a[i], &band[i]);
+        whole[i] = in_band[i] && band_whole(a[i]);
+    }
+    ShrinkArgs s;
+    shrink_args(s, a, n, whole);
     auto copied = [&](int i) { return !in_band[i] && a[i].wfmt != ELORA_W_SAME && a[i].wsl.wdeq_bytes != 0; };
     int rc = launch_route(s, a, copied(0), stream);
     if (rc == ELORA_OK) rc = launch_shrink(s, stream);

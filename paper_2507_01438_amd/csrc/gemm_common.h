@@ -29,18 +29,18 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
     return __builtin_bit_cast(uint32_t, v);
 }
 
-// A float as the sum of two bf16 (to 2^-17 of it).  hi stays finite where v is, and where it is not, lo is zero.
-__device__ __forceinline__ void split_bf16(float v, uint16_t &hi, uint16_t &lo)
+// A float as the sum of three bf16, exactly (down to 2^-133): the eight leading bits of its 24, the next eight and the last
+// eight, cut off and not rounded, so that the first is finite where the float is.  An infinity or a NaN is the first part
+// alone.
+__device__ __forceinline__ void split_bf16(float v, uint16_t part[3])
 {
-    hi = f32_to_bf16(v);
-    if ((hi & 0x7f80u) == 0x7f80u) {
-        if ((__float_as_uint(v) & 0x7f800000u) != 0x7f800000u) hi = (uint16_t)(__float_as_uint(v) >> 16);
-        else {
-            lo = 0;
-            return;
-        }
-    }
-    lo = f32_to_bf16(v - bf16_to_f32(hi));
+    const uint32_t u = __float_as_uint(v);
+    const bool finite = (u & 0x7f800000u) != 0x7f800000u;
+    const float rest = finite ? v - __uint_as_float(u & 0xffff0000u) : 0.0f;
+    const uint32_t ur = __float_as_uint(rest);
+    part[0] = (uint16_t)((u >> 16) | ((u & 0x7fffffffu) > 0x7f800000u ? 0x40u : 0u));  // (a NaN stays one)
+    part[1] = (uint16_t)(ur >> 16);
+    part[2] = (uint16_t)(__float_as_uint(rest - __uint_as_float(ur & 0xffff0000u)) >> 16);
 }
 
 // Eight consecutive values of an adapter kept in 8-bit blocks (they lie in one block: ranks and d_in are multiples of
@@ -66,7 +66,9 @@ struct ShrinkProj {
     float *row_scale;    // [T]
     int32_t *short_rows; // [T]: the rows that sit in runs shorter than kShortRun, in any order
     uint16_t *V;         // [T][Rpad] bf16(s * A_i x_t), zeros beyond the rank and in rows without adapter
-    uint16_t *V_lo;      // [T][Rpad] bf16 of what V leaves of s * A_i x_t, or nullptr
+    // Where the product takes the shrink results whole (band_whole): [2][T][Rpad] the second and third bf16 of A_i x_t, of
+    // which V then holds the first (see split_bf16; the scale comes after the expand, as in the decode kernel).  Else nullptr.
+    uint16_t *V_rest;
     float *part;         // fp32 sums of the K-slices: [tile][slice][kShrinkRows][Rpad]
     int *sync;           // the workspace's counters
     int Rpad;
@@ -81,7 +83,8 @@ struct ShrinkArgs {
     ShrinkProj proj[kShrinkMulti];
 };
 
-void shrink_args(ShrinkArgs &s, const LinearArgs *a, int n);      // everything the three launches below need
+// everything the launches below need; whole[i]: projection i's product takes the shrink results whole
+void shrink_args(ShrinkArgs &s, const LinearArgs *a, int n, const bool *whole);
 int launch_route(const ShrinkArgs &s, const LinearArgs *a, bool copy, hipStream_t stream);  // copy: and the bf16 copy of a[0]'s 4-bit or 8-bit W into a[0].wsl.wdeq
 int launch_shrink(const ShrinkArgs &s, hipStream_t stream);
 

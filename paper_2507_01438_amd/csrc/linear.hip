@@ -78,9 +78,9 @@ WsLayout elora::ws_layout(int T, int K, int N, int R, int wfmt)
     l.part = off;
     l.part_bytes = part_want(N);
     off += align_up(l.part_bytes);
-    l.v_lo = off;
-    l.v_lo_bytes = (t < (size_t)kSplitRows ? t : (size_t)kSplitRows) * (size_t)((R + 63) / 64 * 64) * sizeof(uint16_t);
-    l.total = off + align_up(l.v_lo_bytes);
+    l.v_rest = off;
+    l.v_rest_bytes = 2 * (t < (size_t)kWholeRows ? t : (size_t)kWholeRows) * (size_t)((R + 63) / 64 * 64) * sizeof(uint16_t);
+    l.total = off + align_up(l.v_rest_bytes);
     return l;
 }
 
@@ -124,7 +124,7 @@ static int validate(const elora_linear_desc_t *d, WsLayout *wsl_out, bool part_o
     if (part_optional && d->workspace_bytes < wsl.total) {
         if (d->workspace_bytes < wsl.part) return ELORA_E_STORAGE;
         wsl.part_bytes = std::min(wsl.part_bytes, d->workspace_bytes - wsl.part);
-        wsl.v_lo_bytes = 0;
+        wsl.v_rest_bytes = 0;
         wsl.total = d->workspace_bytes;
     }
     if (d->workspace_bytes < wsl.total) return ELORA_E_STORAGE;
@@ -149,7 +149,7 @@ static void make_plan(const elora_linear_desc_t *d, elora_plan_t *plan)
         if (g_forced_path == ELORA_PATH_DECODE && dec) path = ELORA_PATH_DECODE;
         if (g_forced_path == ELORA_PATH_GEMM && gem) path = ELORA_PATH_GEMM;
     } else if (dec) {
-        // (the library's own array may end before the room for the second half of the shrink results)
+        // (the library's own array may end before the room for the other parts of the shrink results)
         const bool one_product = d->n_tokens > kDecodeMaxTokens && band_instead_of_passes(*d) &&
                                  d->workspace_bytes >= ws_layout(d->n_tokens, d->d_in, d->d_out, max_rank, d->wfmt).total;
         path = one_product ? ELORA_PATH_GEMM : ELORA_PATH_DECODE;

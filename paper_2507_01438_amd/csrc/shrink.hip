@@ -1,7 +1,7 @@
 // Route and shrink of the GEMM path.
 //   route   per row: validated pool slot and scale (Sec. 3.4: each request names its adapter), and the list of the rows
 //           that sit in short runs of equal adapters
-//   shrink  V[t, :] = bf16(s_t * A_i x_t) for every row, with the rows grouped by adapter inside each 32-row tile
+//   shrink  V[t, :] = bf16(s_t * A_i x_t) for every row (or A_i x_t whole, as the sum of three bf16), with the rows grouped by adapter inside each 32-row tile
 //           ("u-batches", Sec. 3.4 / 4.3: rows that share an adapter are computed together): one masked MFMA pass per
 //           run of equal adapters; the rows of runs shorter than 8 are computed one by one with plain FMAs
 #include "gemm_common.h"
@@ -65,8 +65,8 @@ __device__ __forceinline__ void shrink_row_piece(const ShrinkArgs &s, const Shri
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), K = s.K;
     const int slot = pr.row_slot[t];
     const int rank = slot >= 0 ? pr.pool.meta[slot].rank : 0;
-    const float sc = slot >= 0 ? pr.row_scale[t] : 0.0f;
-    uint16_t *const vrow = pr.V + (size_t)t * pr.Rpad;
+    const float sc = slot >= 0 && !pr.V_rest ? pr.row_scale[t] : 1.0f;
+    const size_t at = (size_t)t * pr.Rpad;
     for (int j0 = first + 2 * wave; j0 < first + kRowPiece; j0 += 2 * kWaves) {
         const bool two = j0 + 1 < rank;
         float a0 = 0.0f, a1 = 0.0f;
@@ -83,11 +83,18 @@ __device__ __forceinline__ void shrink_row_piece(const ShrinkArgs &s, const Shri
             }
         }
         if (lane == 0) {
-            uint16_t hi[2], lo[2];
-            split_bf16(j0 < rank ? sc * a0 : 0.0f, hi[0], lo[0]);
-            split_bf16(two ? sc * a1 : 0.0f, hi[1], lo[1]);
-            *reinterpret_cast<uint32_t *>(vrow + j0) = hi[0] | ((uint32_t)hi[1] << 16);
-            if (pr.V_lo) *reinterpret_cast<uint32_t *>(pr.V_lo + (size_t)t * pr.Rpad + j0) = lo[0] | ((uint32_t)lo[1] << 16);
+            const float v0 = j0 < rank ? sc * a0 : 0.0f, v1 = two ? sc * a1 : 0.0f;
+            auto store = [&](uint16_t *to, uint16_t lo, uint16_t hi) { *reinterpret_cast<uint32_t *>(to + at + j0) = lo | ((uint32_t)hi << 16); };
+            if (pr.V_rest) {
+                uint16_t p0[3], p1[3];
+                split_bf16(v0, p0);
+                split_bf16(v1, p1);
+                store(pr.V, p0[0], p1[0]);
+                store(pr.V_rest, p0[1], p1[1]);
+                store(pr.V_rest + (size_t)s.T * pr.Rpad, p0[2], p1[2]);
+            } else {
+                store(pr.V, f32_to_bf16(v0), f32_to_bf16(v1));
+            }
         }
     }
 }
@@ -181,18 +188,26 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
     if (n_mine > 0) issue_x(0);
     const int my_row = r0 + (lane & 31);
     const int slot_v = my_row < T ? pr.row_slot[my_row] : INT32_MIN;
-    const float scale_v = my_row < T ? pr.row_scale[my_row] : 0.0f;
+    const float scale_v = my_row < T && !pr.V_rest ? pr.row_scale[my_row] : 1.0f;
     const int rank_v = slot_v >= 0 ? pr.pool.meta[slot_v].rank : 0;
     const uint32_t starts = run_starts(slot_v, lane);
     const int swz = (m >> 1) & 7;  // (rows 16 b + m: the same for every block b)
 
     auto put = [&](int r, int c, floatx4 v, float scale) {  // four rank entries of a row, final
-        uint16_t hi[4], lo[4];
+        const size_t at = (size_t)(r0 + r) * Rpad + c;
+        auto store = [&](uint16_t *to, uint16_t h0, uint16_t h1, uint16_t h2, uint16_t h3) {
+            *reinterpret_cast<uint64_t *>(to + at) = (uint64_t)h0 | ((uint64_t)h1 << 16) | ((uint64_t)h2 << 32) | ((uint64_t)h3 << 48);
+        };
+        if (pr.V_rest) {
+            uint16_t p[4][3];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) split_bf16(scale * v[i], hi[i], lo[i]);
-        auto packed = [](const uint16_t *h) { return (uint64_t)h[0] | ((uint64_t)h[1] << 16) | ((uint64_t)h[2] << 32) | ((uint64_t)h[3] << 48); };
-        *reinterpret_cast<uint64_t *>(pr.V + (size_t)(r0 + r) * Rpad + c) = packed(hi);
-        if (pr.V_lo) *reinterpret_cast<uint64_t *>(pr.V_lo + (size_t)(r0 + r) * Rpad + c) = packed(lo);
+            for (int i = 0; i < 4; ++i) split_bf16(v[i], p[i]);
+            store(pr.V, p[0][0], p[1][0], p[2][0], p[3][0]);
+            store(pr.V_rest, p[0][1], p[1][1], p[2][1], p[3][1]);
+            store(pr.V_rest + (size_t)T * Rpad, p[0][2], p[1][2], p[2][2], p[3][2]);
+        } else {
+            store(pr.V, f32_to_bf16(scale * v[0]), f32_to_bf16(scale * v[1]), f32_to_bf16(scale * v[2]), f32_to_bf16(scale * v[3]));
+        }
     };
     // sums of slice k: [row][entry], written through to memory and read past the caches' first level (the workgroups of a
     // tile run on one XCD as a rule, but nothing depends on it)
@@ -419,7 +434,7 @@ auto with_cols(const ShrinkArgs &s, F &&f)  // f(8-bit blocks, MFMA column block
 
 }  // namespace
 
-void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n)
+void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n, const bool *whole)
 {
     s.n = n;
     s.T = a[0].T;
@@ -450,7 +465,7 @@ void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n)
         q.row_scale = reinterpret_cast<float *>(a[p].ws + a[p].wsl.row_scale);
         q.short_rows = reinterpret_cast<int32_t *>(a[p].ws + a[p].wsl.row_rank);
         q.V = reinterpret_cast<uint16_t *>(a[p].ws + a[p].wsl.v);
-        q.V_lo = s.T <= kSplitRows && a[p].wsl.v_lo_bytes != 0 ? reinterpret_cast<uint16_t *>(a[p].ws + a[p].wsl.v_lo) : nullptr;
+        q.V_rest = whole[p] ? reinterpret_cast<uint16_t *>(a[p].ws + a[p].wsl.v_rest) : nullptr;
         q.part = reinterpret_cast<float *>(a[p].ws + a[p].wsl.part);
         q.sync = reinterpret_cast<int *>(a[p].ws + a[p].wsl.sync);
         q.Rpad = round_up(a[p].pool.max_rank, kRankPad);

@@ -58,8 +58,8 @@ def test_band_shapes(shape, wfmt, q8):
 @pytest.mark.parametrize("wfmt", [I.W_SAME, I.W_INT8_G32, I.W_INT4_G32])
 @pytest.mark.parametrize("T, segments", [(129, False), (193, False), (256, True), (100, True)])
 def test_65_to_256_rows_on_a_large_w_run_as_one_product(T, segments, wfmt):
-    """They have fp32 shrink results as sums of two bf16: no further from the oracle than the decode kernel, whose shrink
-    results are fp32 (y is rounded to bf16 in both, which is nearly all of either's error)."""
+    """No further from the oracle than the decode kernel, whose shrink results are fp32 (y is rounded to bf16 in both, which
+    is nearly all of either's error; test_one_product_gpu.py has a comparison that shows every bit of them)."""
     import torch
 
     from paper_2507_01438_amd import binding as B
