@@ -30,17 +30,23 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 }
 
 // A float as the sum of three bf16, exactly (down to 2^-133): the eight leading bits of its 24, the next eight and the last
-// eight, cut off and not rounded, so that the first is finite where the float is.  An infinity or a NaN is the first part
-// alone.
+// eight, cut off and not rounded, so that a part is finite where the float is.  Times an infinity the parts have to add up
+// to what the float gives: all three have its sign, and none is zero unless the float is (a part that would be leaves the
+// last unit of the one before it to it); of an infinity or a NaN every part is one.
 __device__ __forceinline__ void split_bf16(float v, uint16_t part[3])
 {
     const uint32_t u = __float_as_uint(v);
-    const bool finite = (u & 0x7f800000u) != 0x7f800000u;
-    const float rest = finite ? v - __uint_as_float(u & 0xffff0000u) : 0.0f;
-    const uint32_t ur = __float_as_uint(rest);
-    part[0] = (uint16_t)((u >> 16) | ((u & 0x7fffffffu) > 0x7f800000u ? 0x40u : 0u));  // (a NaN stays one)
-    part[1] = (uint16_t)(ur >> 16);
-    part[2] = (uint16_t)(__float_as_uint(rest - __uint_as_float(ur & 0xffff0000u)) >> 16);
+    if ((u & 0x7f800000u) == 0x7f800000u) {
+        part[0] = part[1] = part[2] = (uint16_t)((u >> 16) | ((u & 0x007fffffu) != 0 ? 0x40u : 0u));
+        return;
+    }
+    auto cut = [](uint32_t bits) { return (bits & 0xffffu) != 0 || bits << 1 == 0 ? bits >> 16 : (bits >> 16) - 1; };
+    const uint32_t p0 = cut(u);
+    const float r1 = v - __uint_as_float(p0 << 16);
+    const uint32_t p1 = cut(__float_as_uint(r1));
+    part[0] = (uint16_t)p0;
+    part[1] = (uint16_t)p1;
+    part[2] = (uint16_t)(__float_as_uint(r1 - __uint_as_float(p1 << 16)) >> 16);
 }
 
 // Eight consecutive values of an adapter kept in 8-bit blocks (they lie in one block: ranks and d_in are multiples of

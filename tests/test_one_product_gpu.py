@@ -77,3 +77,52 @@ def test_shrink_results_reach_the_expand_whole(K, N, T, lengths, wfmt):
         got = I.bf16_bits_to_f32(y.cpu().numpy().view(np.uint16)).astype(np.float64)
         np.testing.assert_array_equal(got, want)
     pool.close()
+
+
+@pytest.mark.parametrize("scale", [1.5, np.inf])
+@pytest.mark.parametrize("lengths", [None, [70, 1, 2, 100, 27]])
+def test_an_infinite_entry_of_an_adapter_gives_an_infinity_of_its_sign(lengths, scale):
+    """As a sum of fp32 products gives it: one infinite entry in a row of B_i makes that output infinite with the sign of the
+    entry's shrink result; the other outputs, and the rows of other adapters, are as they were.  An infinite scale makes
+    every output of its row infinite."""
+    K = N = 2048
+    T, P = 200, 4
+    rng = np.random.default_rng(77)
+    pool = B.AdapterPool(K, N, 32, P, B.ELORA_BF16)
+    x = I.bf16_bits_to_f32(I.f32_to_bf16_bits(rng.standard_normal((T, K)).astype(np.float32))).astype(np.float64)
+    keep = []
+    for i, r in enumerate((8, 32, 24, 16)):
+        A, Bm = [I.bf16_bits_to_f32(I.f32_to_bf16_bits(0.05 * rng.standard_normal(s).astype(np.float32))).astype(np.float64) for s in ((r, K), (N, r))]
+        if i == 1:
+            Bm[5, 9], Bm[700, 31], Bm[N - 1, 0] = np.inf, -np.inf, np.inf
+        keep.append((A, Bm))
+        pool.load(i, _bf16(A), _bf16(Bm), 1.0)
+    torch.cuda.synchronize()
+    n_req = T if lengths is None else len(lengths)
+    who = (np.arange(n_req) % P).astype(np.int32)
+    rows = who if lengths is None else np.repeat(who, lengths)
+    route = dict(adapter_idx=torch.from_numpy(who).to(DEV)) if lengths is None else dict(
+        seg_offsets=torch.tensor([0] + np.cumsum(lengths).tolist(), dtype=torch.int32, device=DEV), seg_adapter=torch.from_numpy(who).to(DEV))
+    over = np.full(n_req, 1.5, dtype=np.float32)
+    over[2] = scale
+    row_scale = (over if lengths is None else np.repeat(over, lengths)).astype(np.float64)
+    W, _ = _zero_w(K, N, I.W_SAME)
+    lin = B.LoraLinear(K, N, B.ELORA_BF16, pool, T, DEV)
+    xd, y = _bf16(x).to(DEV), torch.full((T, N), 7, dtype=torch.int16, device=DEV)
+    d = lin.desc(xd, W, y, scales=torch.from_numpy(over).to(DEV), **route)
+    assert B.elora_linear_plan(d).tile_cols == 128
+    B.elora_batched_lora_linear(d)
+    torch.cuda.synchronize()
+    got = I.bf16_bits_to_f32(y.cpu().numpy().view(np.uint16)).astype(np.float64)
+    want = np.zeros((T, N))
+    for i, (A, Bm) in enumerate(keep):
+        at = np.flatnonzero(rows == i)
+        want[at] = row_scale[at, None] * ((x[at] @ A.T) @ Bm.T)
+    assert not np.isnan(want).any() and (np.isinf(want).sum(axis=1)[rows == 1] >= 3).all()
+    np.testing.assert_array_equal(np.isinf(got), np.isinf(want))
+    inf = np.isinf(want)
+    np.testing.assert_array_equal(got[inf], want[inf])
+    got, want = got[~inf], want[~inf]
+    # (one rounding of y, 2^-9; fp32 sums of cancelling products: 2^-20 of the largest)
+    assert (np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + 2.0 ** -18 * np.abs(want).max()).all()
+    pool.close()
