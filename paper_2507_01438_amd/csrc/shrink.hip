@@ -211,7 +211,9 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
     };
     // sums of slice k: [row][entry], written through to memory and read past the caches' first level (the workgroups of a
     // tile run on one XCD as a rule, but nothing depends on it)
-    auto part_at = [&](int k, int r, int c) { return pr.part + (((size_t)tile * s.ks + k) * kShrinkRows + r) * Rpad + c; };
+    constexpr int kCoherent = 16;  // sc1
+    auto rsrc = __builtin_amdgcn_make_buffer_rsrc(pr.part + (size_t)tile * s.ks * kShrinkRows * Rpad, 0, s.ks * kShrinkRows * Rpad * 4, 0x00020000);
+    auto part_at = [&](int k, int r, int c) { return ((k * kShrinkRows + r) * Rpad + c) * 4; };
 
     bool x_under_way = true;
     int n_long = 0;  // long runs with an adapter met so far
@@ -256,7 +258,6 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
                 for (int n = 0; n < n_mine; ++n) {
                     // (the reads of the stage that the next loads go to, one turn ago, are over)
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    const int later = n_mine - 1 - n;
                     if (n + 1 < n_mine) {
                         issue_x(n + 1);
                         issue_a(n + 1);
@@ -308,7 +309,7 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
                     for (int i = 0; i < 4; ++i)
                         if (j0 + c4 + i >= rank) v[i] = 0.0f;
                     if (s.ks == 1) put(r, j0 + c4, v, scale);
-                    else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 2" ::"v"(part_at(slice, r, j0 + c4)), "v"(v) : "memory");
+                    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, part_at(slice, r, j0 + c4), 0, kCoherent);
                 }
                 __syncthreads();
             }
@@ -344,15 +345,13 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
             for (int e0 = 0; e0 < (end - start) * cols; e0 += kThreads) {
                 const int e = e0 + tid, r = min(start + e / cols, end - 1), c = (e % cols) * 4;
                 const float scale = __shfl(scale_v, r);
-                floatx4 w[kMaxSlices];
+                u32x4 w[kMaxSlices];
 #pragma unroll
-                for (int k = 0; k < kMaxSlices; ++k)
-                    if (k < s.ks) asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=&v"(w[k]) : "v"(part_at(k, r, c)) : "memory");
-                asm volatile("s_waitcnt vmcnt(0)" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]) : : "memory");
-                floatx4 v = w[0];
+                for (int k = 0; k < kMaxSlices; ++k) w[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, part_at(min(k, s.ks - 1), r, c), 0, kCoherent);
+                floatx4 v = __builtin_bit_cast(floatx4, w[0]);
 #pragma unroll
                 for (int k = 1; k < kMaxSlices; ++k)
-                    if (k < s.ks) v += w[k];
+                    if (k < s.ks) v += __builtin_bit_cast(floatx4, w[k]);
                 if (e < (end - start) * cols) put(r, c, v, scale);
             }
         }
