@@ -193,7 +193,11 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
     const uint32_t starts = run_starts(slot_v, lane);
     const int swz = (m >> 1) & 7;  // (rows 16 b + m: the same for every block b)
 
-    auto put = [&](int r, int c, floatx4 v, float scale) {  // four rank entries of a row, final
+    // four rank entries of a row, final; those past the rank are zero whatever the sums and the scale are (an infinite scale
+    // times zero would be NaN)
+    auto put = [&](int r, int c, floatx4 v, int rank, float scale) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = c + i < rank ? v[i] * scale : 0.0f;
         const size_t at = (size_t)(r0 + r) * Rpad + c;
         auto store = [&](uint16_t *to, uint16_t h0, uint16_t h1, uint16_t h2, uint16_t h3) {
             *reinterpret_cast<uint64_t *>(to + at) = (uint64_t)h0 | ((uint64_t)h1 << 16) | ((uint64_t)h2 << 32) | ((uint64_t)h3 << 48);
@@ -206,7 +210,7 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
             store(pr.V_rest, p[0][1], p[1][1], p[2][1], p[3][1]);
             store(pr.V_rest + (size_t)T * Rpad, p[0][2], p[1][2], p[2][2], p[3][2]);
         } else {
-            store(pr.V, f32_to_bf16(scale * v[0]), f32_to_bf16(scale * v[1]), f32_to_bf16(scale * v[2]), f32_to_bf16(scale * v[3]));
+            store(pr.V, f32_to_bf16(v[0]), f32_to_bf16(v[1]), f32_to_bf16(v[2]), f32_to_bf16(v[3]));
         }
     };
     // sums of slice k: [row][entry], written through to memory and read past the caches' first level (the workgroups of a
@@ -305,10 +309,7 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
                     floatx4 v = *reinterpret_cast<const floatx4 *>(&s_red[0][r][c4]);
 #pragma unroll
                     for (int w = 1; w < kWaves; ++w) v += *reinterpret_cast<const floatx4 *>(&s_red[w][r][c4]);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (j0 + c4 + i >= rank) v[i] = 0.0f;
-                    if (s.ks == 1) put(r, j0 + c4, v, scale);
+                    if (s.ks == 1) put(r, j0 + c4, v, rank, scale);
                     else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, part_at(slice, r, j0 + c4), 0, kCoherent);
                 }
                 __syncthreads();
@@ -318,11 +319,11 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
                 const int done = (rank + kCols - 1) / kCols * kCols, left = (Rpad - done) / 4;
                 if (left > 0)
                     for (int e = tid; e < (end - start) * left; e += kThreads)
-                        put(start + e / left, done + (e % left) * 4, floatx4{0.f, 0.f, 0.f, 0.f}, 0.0f);
+                        put(start + e / left, done + (e % left) * 4, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 1.0f);
             }
         } else if (slot == -1 && end - start >= kShortRun && slice == 0 && part_q == 0) {
             for (int e = tid; e < (end - start) * (Rpad / 4); e += kThreads)
-                put(start + e / (Rpad / 4), (e % (Rpad / 4)) * 4, floatx4{0.f, 0.f, 0.f, 0.f}, 0.0f);
+                put(start + e / (Rpad / 4), (e % (Rpad / 4)) * 4, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 1.0f);
         }
         start = end;
     }
@@ -341,7 +342,7 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
     for (int start = 0; start < kShrinkRows;) {
         const int slot = __builtin_amdgcn_readlane(slot_v, start), end = run_end(starts, start);
         if (slot >= 0 && end - start >= kShortRun) {
-            const int cols = (__builtin_amdgcn_readlane(rank_v, start) + kCols - 1) / kCols * (kCols / 4);
+            const int rank = __builtin_amdgcn_readlane(rank_v, start), cols = (rank + kCols - 1) / kCols * (kCols / 4);
             for (int e0 = 0; e0 < (end - start) * cols; e0 += kThreads) {
                 const int e = e0 + tid, r = min(start + e / cols, end - 1), c = (e % cols) * 4;
                 const float scale = __shfl(scale_v, r);
@@ -352,7 +353,7 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
 #pragma unroll
                 for (int k = 1; k < kMaxSlices; ++k)
                     if (k < s.ks) v += __builtin_bit_cast(floatx4, w[k]);
-                if (e < (end - start) * cols) put(r, c, v, scale);
+                if (e < (end - start) * cols) put(r, c, v, rank, scale);
             }
         }
         start = end;

@@ -35,3 +35,41 @@ def test_shrink_shapes(shape, q8):
     assert np.array_equal(y, case.run(force_path=GEMM))     # fixed summation order, counters back at zero
     assert case.pool.poll_error() == (0, -1)
     case.close()
+
+
+@pytest.mark.parametrize("band", [0, 1])
+@pytest.mark.parametrize("K", [256, 4096])
+def test_an_infinite_scale_makes_its_rows_infinite(K, band):
+    """Everything is positive, so an infinite scale gives plus infinity in every output of its rows: entries past the rank are
+    zero whatever the scale (rank 3 in steps of 8 and 64, rank 8 in a step of 16), in long and short runs, with K-slices
+    and without."""
+    import torch
+
+    from gpu_harness import to_dev
+    from paper_2507_01438_amd import binding as B
+    N, lengths, ranks = 264, [150, 5, 90, 20, 60], (3, 8, 16, 24)
+    w = I.small_workload(1790 + K, I.BF16, K, N, sum(lengths), 4, ranks, segments=lengths)
+    w.seg_adapter = np.array([0, 1, 2, 3, 1], dtype=np.int32)
+    case = DeviceCase(w, w.projections[0])
+    case.x_h &= 0x7FFF
+    case.W_h &= 0x7FFF
+    case.x.copy_(to_dev(case.x_h))
+    case.W.copy_(to_dev(case.W_h))
+    for i, (A, Bm, s) in list(case.adapters.items()):
+        A, Bm = A & 0x7FFF, Bm & 0x7FFF
+        case.adapters[i] = (A, Bm, s)
+        case.pool.load(i, torch.from_numpy(A.view(np.int16)), torch.from_numpy(Bm.view(np.int16)), s)
+    torch.cuda.synchronize()
+    scales = np.array([np.inf, np.inf, 2.0, 0.5, np.inf], dtype=np.float32)
+    B.elora_debug_band(band)
+    try:
+        y = case.run(scales=torch.from_numpy(scales).to("cuda:0"), force_path=GEMM)
+    finally:
+        B.elora_debug_band(-1)
+    assert case.last_plan.tile_cols == (128 if band else 256)
+    rows = np.repeat(scales, lengths)
+    assert (y[np.isinf(rows)] == np.inf).all()
+    rest = np.flatnonzero(np.isfinite(rows))
+    ref = case.reference(row_scale=np.where(np.isfinite(rows), rows, 1.0).astype(np.float32))[rest]
+    assert np.abs(y[rest] - ref).max() <= 1e-2 * np.abs(ref).max()
+    case.close()
