@@ -301,7 +301,9 @@ typedef struct {
 } elora_linear_desc_t;
 
 /* Device scratch one call may use, for up to n_tokens_max rows, with W in the dtype of x (ELORA_W_SAME).
- * 0 if an argument is invalid. */
+ * 0 if an argument is invalid.  About 2 KiB per output column (mailboxes of the decode kernel) and some bytes per row; calls
+ * that may run as a matrix product (more than 64 rows, or a d_in, d_out or max_rank that the decode kernel leaves to it) have
+ * up to 28 MiB more for the sums of K-slices, as far as their rows and columns can fill them. */
 size_t elora_workspace_bytes(int n_tokens_max, int d_in, int d_out, int max_rank);
 /* The same for a given weight format (elora_wfmt_t): with a 4-bit W and 768 rows or more, or an 8-bit W and more than
  * 256 rows, the workspace also holds the call's bf16 copy of W (d_out x d_in x 2 bytes). */

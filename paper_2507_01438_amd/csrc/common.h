@@ -64,10 +64,10 @@ struct WsLayout {
     size_t v;          // float/bf16 shrink results of the generic and gemm kernels
     size_t wdeq;       // bf16 [d_out][d_in]: a call's dequantised copy of a 4-bit or 8-bit W (gemm_wcopy_bytes(); 0 bytes below
     size_t wdeq_bytes; //   the row count from which converting W once pays)
-    size_t part;       // fp32 sums of K-slices
-    size_t part_bytes; //   room for them (part_want(); less only in the library's own array, with fewer K-slices then)
     size_t v_rest;       // GEMM path, up to kWholeRows rows: the second and third bf16 of the shrink results
-    size_t v_rest_bytes; //   (0 where the library's own array ends before)
+    size_t v_rest_bytes; //   (0 where no call needs them, or the library's own array ends before)
+    size_t part;         // fp32 sums of K-slices
+    size_t part_bytes;   //   room for them (part_want(); less only in the library's own array, with fewer K-slices then)
     size_t total;
 };
 
@@ -81,8 +81,8 @@ constexpr int kSyncShortRows = 320;   // GEMM path: how many rows sit in short r
 constexpr int kSyncTiles = 384;       // GEMM path: K-slices of a tile that have posted their sums
 constexpr int kSyncTileCount = kSyncInts - kSyncTiles;
 
-WsLayout ws_layout(int n_tokens, int d_in, int d_out, int max_rank, int wfmt);
-size_t part_want(int d_out);  // bytes the sums of K-slices of a call may take
+WsLayout ws_layout(int n_tokens, int d_in, int d_out, int max_rank, int wfmt, int dtype);
+size_t part_want(int n_tokens, int d_in, int d_out, int max_rank);  // bytes the sums of K-slices of a call may take
 
 // ---- host-side pool object --------------------------------------------------
 

@@ -689,7 +689,7 @@ bool elora::band_instead_of_passes(const elora_linear_desc_t &d)
     const bool many_runs = d.pool != nullptr && (d.adapter_idx != nullptr || (long long)d.n_segments * 32 > d.n_tokens);
     if (many_runs && d.n_tokens <= (d.wfmt == ELORA_W_SAME || d.d_out >= 8192 ? 128 : 192)) return false;
     BandShape s;
-    return band_shape(band_call(d), part_want(d.d_out), &s);
+    return band_shape(band_call(d), part_want(d.n_tokens, d.d_in, d.d_out, d.pool ? d.pool->max_rank : 1), &s);
 }
 
 void elora::gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
@@ -697,7 +697,7 @@ void elora::gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
     const BandCall c = band_call(d);
     const bool copy_first = c.copied;
     BandShape s;
-    const bool band = band_shape(c, part_want(d.d_out), &s);
+    const bool band = band_shape(c, part_want(d.n_tokens, d.d_in, d.d_out, c.max_rank), &s);
     plan->n_launches = (d.pool ? 3 : 1) + (copy_first && !band && !d.pool ? 1 : 0);  // (with a pool the copy shares the route's launch)
     if (band) {
         plan->split_k = s.ks;

@@ -50,7 +50,11 @@ void elora::profile_mark_end(hipStream_t stream)
         if (hipEventRecord(g_prof_events[2 * g_prof_ended + 1], stream) == hipSuccess) ++g_prof_ended;
 }
 
-WsLayout elora::ws_layout(int T, int K, int N, int R, int wfmt)
+// Rows that the decode kernel takes in one launch, of a W that it takes, and ranks that it takes in any storage: these calls
+// run on that kernel alone.
+static bool decode_alone(int T, int K, int N, int R) { return T <= kDecodeMaxTokens && decode_shape(K, N) && R <= 64; }
+
+WsLayout elora::ws_layout(int T, int K, int N, int R, int wfmt, int dtype)
 {
     WsLayout l;
     size_t t = (size_t)(T > 0 ? T : 1);
@@ -75,25 +79,34 @@ WsLayout elora::ws_layout(int T, int K, int N, int R, int wfmt)
     l.wdeq = off;
     l.wdeq_bytes = gemm_wcopy_bytes(wfmt, T, K, N);
     off += align_up(l.wdeq_bytes);
-    l.part = off;
-    l.part_bytes = part_want(N);
-    off += align_up(l.part_bytes);
     l.v_rest = off;
-    l.v_rest_bytes = 2 * (t < (size_t)kWholeRows ? t : (size_t)kWholeRows) * (size_t)((R + 63) / 64 * 64) * sizeof(uint16_t);
-    l.total = off + align_up(l.v_rest_bytes);
+    l.part_bytes = dtype == ELORA_F32 ? 0 : part_want((int)t, K, N, R);
+    l.v_rest_bytes = dtype == ELORA_F32 || decode_alone((int)t, K, N, R) ? 0 : 2 * (t < (size_t)kWholeRows ? t : (size_t)kWholeRows) * (size_t)((R + 63) / 64 * 64) * sizeof(uint16_t);
+    off += align_up(l.v_rest_bytes);
+    l.part = off;
+    l.total = off + align_up(l.part_bytes);
     return l;
 }
 
-// Sums of K-slices (fp32): the matrix products of a few hundred rows cut K so that 256 tiles of up to 224 x 128 sums are
-// under way (fewer where d_out is small), the shrink at most 1024 tiles of 32 rows x 64 entries.
-size_t elora::part_want(int d_out)
+// Room for the sums of K-slices (fp32) of a call of at most T rows, never less for more rows.  The matrix products of a few
+// hundred rows cut K into up to 8 slices until 256 tiles of up to 224 x 128 sums are under way; the shrink cuts it into up to
+// 4, 512 tiles of 32 rows in all.  Calls that only the decode kernel takes have no such sums.
+size_t elora::part_want(int T, int K, int N, int R)
 {
-    const size_t by_columns = ((size_t)d_out + 127) / 128 * 128 * 8192, most = (size_t)256 * 224 * 128 * sizeof(float);
-    const size_t shrink = (size_t)1024 * 32 * 64 * sizeof(float);
-    return by_columns > most ? most : by_columns > shrink ? by_columns : shrink;
+    if (decode_alone(T, K, N, R)) return 0;
+    const size_t cols = ((size_t)N + 127) / 128 * 128, most = (size_t)256 * 224 * 128 * sizeof(float), least = (size_t)1024 * 32 * 64 * sizeof(float);
+    const size_t cap = std::min(std::max(cols * 8192, least), most);
+    size_t band = 0, shrink = 0;
+    const size_t slices = std::min(K / 64, 8);
+    if (slices > 1 && (size_t)T * slices * cols * sizeof(float) >= cap) return cap;
+    if (slices > 1)  // (rows, with those of padding, in up to two row tiles more than the fewest)
+        for (size_t m = 1; m <= ((size_t)T + 223) / 224 + 2; ++m) band = std::max(band, ((size_t)T + 32 * m - 1) / (32 * m) * (32 * m) * slices * cols * sizeof(float));
+    if (K / 64 >= 16) shrink = std::min(((size_t)T + 31) / 32 * 4, (size_t)512) * 32 * (((size_t)R + 63) / 64 * 64) * sizeof(float);
+    return std::min(std::max(band, shrink), cap);
 }
 
-// part_optional: a workspace that ends before or inside the room for the sums of K-slices will do (fewer slices then)
+// part_optional: a workspace that ends before or inside the room for the sums of K-slices and for the other parts of the shrink
+// results will do (fewer slices then, shrink results rounded to bf16)
 static int validate(const elora_linear_desc_t *d, WsLayout *wsl_out, bool part_optional = false)
 {
     if (d == nullptr) return ELORA_E_NULL;
@@ -120,11 +133,11 @@ static int validate(const elora_linear_desc_t *d, WsLayout *wsl_out, bool part_o
     if (!aligned16(d->x) || !aligned16(d->W) || !aligned16(d->y)) return ELORA_E_ALIGN;
     if (d->w_scales != nullptr && !aligned16(d->w_scales)) return ELORA_E_ALIGN;
     if (reinterpret_cast<uintptr_t>(d->workspace) % kAlign) return ELORA_E_ALIGN;
-    WsLayout wsl = ws_layout(d->n_tokens, d->d_in, d->d_out, max_rank, d->wfmt);
+    WsLayout wsl = ws_layout(d->n_tokens, d->d_in, d->d_out, max_rank, d->wfmt, d->dtype);
     if (part_optional && d->workspace_bytes < wsl.total) {
-        if (d->workspace_bytes < wsl.part) return ELORA_E_STORAGE;
-        wsl.part_bytes = std::min(wsl.part_bytes, d->workspace_bytes - wsl.part);
-        wsl.v_rest_bytes = 0;
+        if (d->workspace_bytes < wsl.v_rest) return ELORA_E_STORAGE;
+        if (d->workspace_bytes < wsl.part) wsl.v_rest_bytes = 0;
+        wsl.part_bytes = d->workspace_bytes > wsl.part ? std::min(wsl.part_bytes, d->workspace_bytes - wsl.part) : 0;
         wsl.total = d->workspace_bytes;
     }
     if (d->workspace_bytes < wsl.total) return ELORA_E_STORAGE;
@@ -151,7 +164,7 @@ static void make_plan(const elora_linear_desc_t *d, elora_plan_t *plan)
     } else if (dec) {
         // (the library's own array may end before the room for the other parts of the shrink results)
         const bool one_product = d->n_tokens > kDecodeMaxTokens && band_instead_of_passes(*d) &&
-                                 d->workspace_bytes >= ws_layout(d->n_tokens, d->d_in, d->d_out, max_rank, d->wfmt).total;
+                                 d->workspace_bytes >= ws_layout(d->n_tokens, d->d_in, d->d_out, max_rank, d->wfmt, d->dtype).total;
         path = one_product ? ELORA_PATH_GEMM : ELORA_PATH_DECODE;
     } else if (gem) {
         path = ELORA_PATH_GEMM;
@@ -206,7 +219,7 @@ size_t elora_workspace_bytes_w(int n_tokens_max, int d_in, int d_out, int max_ra
 {
     if (n_tokens_max < 0 || d_in <= 0 || d_out <= 0 || max_rank < 1 || max_rank > kMaxRank) return 0;
     if (wfmt != ELORA_W_SAME && wfmt != ELORA_W_INT4_G32 && wfmt != ELORA_W_INT8_G32) return 0;
-    return ws_layout(n_tokens_max, d_in, d_out, max_rank, wfmt).total;
+    return ws_layout(n_tokens_max, d_in, d_out, max_rank, wfmt, ELORA_BF16).total;
 }
 
 size_t elora_workspace_bytes(int n_tokens_max, int d_in, int d_out, int max_rank)
@@ -457,8 +470,8 @@ int elora_batched_lora_linear_noalloc(const elora_linear_desc_t *desc, elora_str
     // what this call's layout covers before the first call, and again, over everything calls have written so far, when
     // d_out changes (what a call with another d_out wrote may lie where this one's mailboxes are).  (The sums of K-slices,
     // the last part of the layout, need no idle state of their own.)
-    if (st.idle < wsl.part || st.d_out != d.d_out) {
-        const size_t bytes = st.used > wsl.part ? st.used : wsl.part;
+    if (st.idle < wsl.v_rest || st.d_out != d.d_out) {
+        const size_t bytes = st.used > wsl.v_rest ? st.used : wsl.v_rest;
         const size_t n_words = bytes / sizeof(uint32_t), blocks = (n_words + 255) / 256;
         hipLaunchKernelGGL(ws_init_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, stream,
                            reinterpret_cast<uint32_t *>(st.ptr), n_words, (size_t)kSyncInts);
@@ -468,7 +481,7 @@ int elora_batched_lora_linear_noalloc(const elora_linear_desc_t *desc, elora_str
     }
     elora_plan_t plan;
     make_plan(&d, &plan);
-    const size_t writes = plan.path == ELORA_PATH_GEMM ? wsl.total : wsl.part;
+    const size_t writes = plan.path == ELORA_PATH_GEMM ? wsl.total : wsl.v_rest;
     if (writes > st.used) st.used = writes;
     return enqueue_linear(&d, wsl, stream);
 }

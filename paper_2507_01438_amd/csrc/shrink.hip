@@ -445,16 +445,14 @@ void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n, const bool *w
     // as many as leave a projection at most one workgroup per compute unit, or two while a slice is still 4096 elements or
     // more (7871 rows: d_in = 14336 76 -> 71 us with two, d_in = 4096 32 -> 36), with at least two spans per wave and slice,
     // and within the room for the slices' sums and the counters.
-    size_t room = SIZE_MAX;
-    int rpad = kRankPad;
-    for (int p = 0; p < n; ++p) {
-        room = a[p].wsl.part_bytes < room ? a[p].wsl.part_bytes : room;
-        rpad = std::max(rpad, round_up(a[p].pool.max_rank, kRankPad));
-    }
-    const size_t per_slice = (size_t)s.n_tiles * kShrinkRows * rpad * sizeof(float);
+    auto room_for = [&](int ks) {
+        for (int p = 0; p < n; ++p)
+            if ((size_t)s.n_tiles * kShrinkRows * round_up(a[p].pool.max_rank, kRankPad) * sizeof(float) * ks > a[p].wsl.part_bytes) return false;
+        return true;
+    };
     s.ks = 1;
     while (s.ks < kMaxSlices && s.n_tiles * (s.ks + 1) <= (s.K / (s.ks + 1) >= 4096 ? 512 : 256) && s.n_tiles <= kSyncTileCount &&
-           s.K / kSpan >= (s.ks + 1) * 2 * kWaves && per_slice * (s.ks + 1) <= room)
+           s.K / kSpan >= (s.ks + 1) * 2 * kWaves && room_for(s.ks + 1))
         ++s.ks;
     // (at least four workgroups per row, up to two per compute unit: the rows of short runs are shared by all of them)
     s.wgs_per_xcd = std::max((s.n_tiles + kXcds - 1) / kXcds * s.ks * 2, std::min((s.T + 1) / 2, 64));
