@@ -367,8 +367,9 @@ int elora_batched_lora_linear(const elora_linear_desc_t *desc, elora_stream_t st
  * the process ends), brought into its idle state by a fill kernel on `stream` where needed (before a GPU's first call,
  * and when d_out differs from the previous call's).  Nothing is allocated or freed, on the device or through any
  * library; inputs and outputs are the caller's as ever.  A call that needs more than 32 MiB of workspace
- * (elora_workspace_bytes_w: about 2 KiB per output column on the decode path; a 4-bit W with 768 rows or more needs a
- * copy of W) is refused with E_STORAGE.  Every call on a GPU uses that GPU's one array: calls that overlap in time on
+ * (about 2 KiB per output column for the mailboxes of the decode kernel; a 4-bit W with 768 rows or more needs a copy of W)
+ * is refused with E_STORAGE; the room for sums of K-slices, in which elora_workspace_bytes_w may well go beyond 32 MiB, is
+ * not needed: with less of it a call runs in fewer K-slices, and one of 65 to 256 rows on the decode kernel.  Every call on a GPU uses that GPU's one array: calls that overlap in time on
  * one GPU race, so issue them on one stream.  Whether workgroups of a tile share an XCD is only found out by
  * elora_workspace_init; until some workspace has been initialised on the GPU the decode kernel hands partial sums over
  * through memory (same results).

@@ -438,9 +438,7 @@ constexpr size_t kScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];  // one copy per device, held until the process ends
 struct ScratchState {
     char *ptr;     // this device's copy of `scratch` (hipGetSymbolAddress; the array's name is no device address in host code)
-    size_t idle;   // bytes from the start that are known to be in a workspace's idle state, 0: none yet
-    size_t used;   // bytes from the start that calls so far may have written
-    int d_out;     // the d_out the idle state was last used with
+    int d_out;     // the d_out whose mailboxes are in their idle state, 0: none yet
 };
 ScratchState g_scratch[64];
 }  // namespace
@@ -466,23 +464,16 @@ int elora_batched_lora_linear_noalloc(const elora_linear_desc_t *desc, elora_str
     if (rc != ELORA_OK) return rc;
     if (d.n_tokens == 0) return ELORA_OK;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    // The idle state (counters zero, everything else all-ones) is written by a fill kernel on the call's stream: over
-    // what this call's layout covers before the first call, and again, over everything calls have written so far, when
-    // d_out changes (what a call with another d_out wrote may lie where this one's mailboxes are).  (The sums of K-slices,
-    // the last part of the layout, need no idle state of their own.)
-    if (st.idle < wsl.v_rest || st.d_out != d.d_out) {
-        const size_t bytes = st.used > wsl.v_rest ? st.used : wsl.v_rest;
-        const size_t n_words = bytes / sizeof(uint32_t), blocks = (n_words + 255) / 256;
+    // The idle state (counters zero, mailboxes all-ones) is what calls of one d_out leave behind in the part that follows d_out
+    // alone, up to row_slot; what lies behind it is written before it is read.  So that part is filled, on the call's
+    // stream, before the first call and when d_out changes (what calls with another d_out wrote may lie there).
+    if (st.d_out != d.d_out) {
+        const size_t n_words = wsl.row_slot / sizeof(uint32_t), blocks = (n_words + 255) / 256;
         hipLaunchKernelGGL(ws_init_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, stream,
                            reinterpret_cast<uint32_t *>(st.ptr), n_words, (size_t)kSyncInts);
         ELORA_HIP_TRY(hipGetLastError());
-        st.idle = bytes;
         st.d_out = d.d_out;
     }
-    elora_plan_t plan;
-    make_plan(&d, &plan);
-    const size_t writes = plan.path == ELORA_PATH_GEMM ? wsl.total : wsl.v_rest;
-    if (writes > st.used) st.used = writes;
     return enqueue_linear(&d, wsl, stream);
 }
 

@@ -1,5 +1,6 @@
 """The entry point that allocates nothing (elora_batched_lora_linear_noalloc: the workspace is an array inside the
-library) against the entry point with a caller-supplied workspace, through the C-ABI: same kernels, same bits."""
+library) against the entry point with a caller-supplied workspace, through the C-ABI: same kernels, same bits at these shapes
+(where the array holds less than a workspace, fewer K-slices or the decode kernel: test_noalloc_gpu.py)."""
 import numpy as np
 import pytest
 import torch
