@@ -125,6 +125,7 @@ struct LinearArgs {
 
 int launch_generic(const LinearArgs &a, hipStream_t stream);
 int launch_fp32(const LinearArgs &a, hipStream_t stream);  // (launch_generic sends every fp32 call there)
+void fp32_plan(const elora_linear_desc_t &d, elora_plan_t *plan);
 int launch_decode(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream);
 int launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream);
 int launch_gemm_group(const LinearArgs *a, int n, hipStream_t stream);  // same x and routing tables, a pool each

@@ -7,6 +7,8 @@
 // adapters, three launches of plain FMAs through 64 x 64 tiles / here: 8 rows 512 x 512 67 / 9.3 us, 155 rows 1000 x 1430
 // 162 / 21, 272 rows 2048 x 3000 322 / 91, 2000 rows 2048 x 2048 629 / 352, 4096 rows 4096 x 4096 4182 / 2376 (there the
 // loads of a 32 x 32 tile bound it: 8 products per byte); error against 64-bit sums 4 to 11 e-7 / 1.5 to 4 e-7.
+#include <algorithm>
+
 #include "common.h"
 
 using namespace elora;
@@ -37,9 +39,9 @@ constexpr int kThreads = 512, kWaves = kThreads / 64;
 // ---- route + shrink: a workgroup per row and 16 rank entries, a wave takes two of them --------------------------------------
 constexpr int kPiece = 2 * kWaves;
 __global__ __launch_bounds__(kThreads) void fp32_shrink_kernel(int K, const float *__restrict__ x, RouteView route, PoolView pool, int32_t *__restrict__ row_slot,
-                                                               float *__restrict__ row_scale, float *__restrict__ V, int R)
+                                                               float *__restrict__ row_scale, float *__restrict__ V, int R, int t_first)
 {
-    const int t = (int)blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = t_first + (int)blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool owner = blockIdx.y == 0 && threadIdx.x == 0;  // (a bad index is counted once per row)
     const RowRoute r = resolve_row(t, route, pool, owner);
     if (owner) {
@@ -101,13 +103,13 @@ __global__ __launch_bounds__(kThreads) void fp32_shrink_kernel(int K, const floa
 template <int MB, int NB>
 __global__ __launch_bounds__(kThreads) void fp32_product_kernel(int T, int K, int N, const float *__restrict__ x, const float *__restrict__ W, PoolView pool, int has_pool,
                                                                 const int32_t *__restrict__ row_slot, const float *__restrict__ row_scale,
-                                                                const float *__restrict__ V, int R, float *__restrict__ y)
+                                                                const float *__restrict__ V, int R, float *__restrict__ y, int first_tile)
 {
     constexpr int kRows = 16 * MB, kCols = 16 * NB, kAhead = 4;  // turns whose loads are in flight
     __shared__ float s_sum[kWaves][kRows][kCols + 4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
-    const int tiles_n = (N + kCols - 1) / kCols;
-    const int t0 = (int)(blockIdx.x / tiles_n) * kRows, n0 = (int)(blockIdx.x % tiles_n) * kCols;
+    const int tiles_n = (N + kCols - 1) / kCols, tile = first_tile + (int)blockIdx.x;
+    const int t0 = tile / tiles_n * kRows, n0 = tile % tiles_n * kCols;
     // rows past the end of x and W repeat the last one; what they give is never stored
     const float *xr[MB], *wr[NB];
 #pragma unroll
@@ -204,7 +206,34 @@ __global__ __launch_bounds__(kThreads) void fp32_product_kernel(int T, int K, in
     }
 }
 
+// A launch holds fewer than 2^32 threads: rows of the shrink, and tiles of the product, beyond that many workgroups go into
+// further launches.
+constexpr size_t kMaxGroups = ((size_t)1 << 32) / kThreads - 1;
+size_t launches_of(size_t workgroups) { return (workgroups + kMaxGroups - 1) / kMaxGroups; }
+
+// The largest tile that still gives every compute unit a workgroup: a turn of 32 x 32 outputs loads half as much per product
+// as one of 32 x 16.
+struct Tiles {
+    int mb, nb;
+    size_t n;
+};
+Tiles choose_tiles(int T, int N)
+{
+    const size_t m32 = ((size_t)T + 31) / 32, n16 = ((size_t)N + 15) / 16, n32 = ((size_t)N + 31) / 32;
+    if (T <= 16) return {1, 1, n16};
+    if (m32 * n32 < 256) return {2, 1, m32 * n16};
+    return {2, 2, m32 * n32};
+}
+
 }  // namespace
+
+void elora::fp32_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
+{
+    const int T = std::max(d.n_tokens, 1);
+    const size_t tiles = choose_tiles(T, d.d_out).n;
+    plan->n_launches = (int)(launches_of(tiles) + (d.pool ? launches_of((size_t)T) : 0));
+    plan->grid = (int)std::min(tiles, kMaxGroups);
+}
 
 int elora::launch_fp32(const LinearArgs &a, hipStream_t stream)
 {
@@ -212,21 +241,22 @@ int elora::launch_fp32(const LinearArgs &a, hipStream_t stream)
     float *const row_scale = reinterpret_cast<float *>(a.ws + a.wsl.row_scale), *const V = reinterpret_cast<float *>(a.ws + a.wsl.v);
     const float *const x = static_cast<const float *>(a.x), *const W = static_cast<const float *>(a.W);
     const int R = a.pool.max_rank;
-    if (a.has_pool) {
-        hipLaunchKernelGGL(fp32_shrink_kernel, dim3(a.T, (R + kPiece - 1) / kPiece), dim3(kThreads), 0, stream, a.K, x, a.route, a.pool, row_slot, row_scale, V, R);
+    for (size_t t = 0; a.has_pool && t < (size_t)a.T; t += kMaxGroups) {
+        hipLaunchKernelGGL(fp32_shrink_kernel, dim3((unsigned)std::min((size_t)a.T - t, kMaxGroups), (R + kPiece - 1) / kPiece), dim3(kThreads), 0, stream, a.K, x, a.route,
+                           a.pool, row_slot, row_scale, V, R, (int)t);
         ELORA_HIP_TRY(hipGetLastError());
     }
-    // The largest tile that still gives every compute unit a workgroup: a turn of 32 x 32 outputs loads half as much per
-    // product as one of 32 x 16.
-    const size_t m32 = ((size_t)a.T + 31) / 32, n16 = ((size_t)a.N + 15) / 16, n32 = ((size_t)a.N + 31) / 32;
-    auto go = [&](auto kern, size_t grid) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), 0, stream, a.T, a.K, a.N, x, W, a.pool, a.has_pool ? 1 : 0, row_slot, row_scale, V, R, static_cast<float *>(a.y));
+    const Tiles tiles = choose_tiles(a.T, a.N);
+    auto go = [&](auto kern) -> int {
+        for (size_t first = 0; first < tiles.n; first += kMaxGroups) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)std::min(tiles.n - first, kMaxGroups)), dim3(kThreads), 0, stream, a.T, a.K, a.N, x, W, a.pool,
+                               a.has_pool ? 1 : 0, row_slot, row_scale, V, R, static_cast<float *>(a.y), (int)first);
+            ELORA_HIP_TRY(hipGetLastError());
+        }
+        return ELORA_OK;
     };
     profile_mark_begin(stream);
-    if (a.T <= 16) go(fp32_product_kernel<1, 1>, n16);
-    else if (m32 * n32 < 256) go(fp32_product_kernel<2, 1>, m32 * n16);
-    else go(fp32_product_kernel<2, 2>, m32 * n32);
-    ELORA_HIP_TRY(hipGetLastError());
-    profile_mark_end(stream);
-    return ELORA_OK;
+    const int rc = tiles.mb == 1 ? go(fp32_product_kernel<1, 1>) : tiles.nb == 1 ? go(fp32_product_kernel<2, 1>) : go(fp32_product_kernel<2, 2>);
+    if (rc == ELORA_OK) profile_mark_end(stream);
+    return rc;
 }

@@ -177,8 +177,10 @@ static void make_plan(const elora_linear_desc_t *d, elora_plan_t *plan)
         decode_plan(*d, plan);
     } else if (path == ELORA_PATH_GEMM) {
         gemm_plan(*d, plan);
+    } else if (d->dtype == ELORA_F32) {
+        fp32_plan(*d, plan);
     } else {
-        plan->n_launches = d->pool ? (d->dtype == ELORA_F32 ? 2 : 3) : 1;
+        plan->n_launches = d->pool ? 3 : 1;
         plan->grid = ((d->n_tokens + 63) / 64) * ((d->d_out + 63) / 64);
     }
 }

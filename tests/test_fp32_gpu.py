@@ -39,3 +39,34 @@ def test_fp32_shapes(shape, segments):
     assert np.array_equal(y, case.run())       # fixed summation order
     assert case.pool.poll_error() == (0, -1)
     case.close()
+
+
+def test_more_rows_and_tiles_than_one_launch_holds():
+    """2^23 rows are 2^32 threads of the shrink, and 2^33 outputs 2^32 of the product: both go out in pieces."""
+    import torch
+
+    from paper_2507_01438_amd import binding as B
+    dev, T, N = "cuda:0", (1 << 23) + 37, 1024
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(5)
+    x, W = [torch.randn(s, generator=gen, device=dev) for s in ((T, 1), (N, 1))]
+    pool = B.AdapterPool(1, N, 1, 2, B.ELORA_F32)
+    A, Bm = torch.randn((2, 1, 1), generator=gen, device=dev), torch.randn((2, N, 1), generator=gen, device=dev)
+    for i in range(2):
+        pool.load(i, A[i].contiguous(), Bm[i].contiguous(), 0.5)
+    idx = (torch.arange(T, device=dev, dtype=torch.int32) % 3) - 1
+    lin = B.LoraLinear(1, N, B.ELORA_F32, pool, T, dev)
+    y = torch.full((T, N), 7.0, device=dev)
+    d = lin.desc(x, W, y, adapter_idx=idx)
+    assert B.elora_linear_plan(d).n_launches == 4
+    B.elora_batched_lora_linear(d)
+    torch.cuda.synchronize()
+    for a in (0, (1 << 22) - 8, (1 << 23) - 4096, T - 2000):
+        rows = slice(a, min(a + 6000, T))
+        on = (idx[rows] >= 0).double()[:, None]
+        which = idx[rows].clamp(min=0).long()
+        want = x[rows].double() @ W.double().T + 0.5 * on * (x[rows].double() * A[which, 0].double()) * Bm[which, :, 0].double()
+        assert (y[rows].double() - want).abs().max() <= 1e-6 * want.abs().max()
+    assert not (y == 7.0).all(dim=1).any()
+    assert pool.poll_error() == (0, -1)
+    pool.close()
