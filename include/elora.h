@@ -335,7 +335,7 @@ int elora_workspace_init(void *workspace, size_t workspace_bytes, elora_stream_t
 typedef struct {
     int path;        /* elora_path_t */
     int n_launches;  /* kernels one call enqueues */
-    int split_k;     /* K-slices of the streaming contraction (decode path: 1, 2, 4 or 8), else 1 */
+    int split_k;     /* K-slices of the contraction (decode path: 1, 2, 4 or 8; gemm path: 1 to 8), else 1 */
     int tile_rows;   /* W rows (decode) or output rows (gemm) per workgroup, 0 for the generic path */
     int tile_cols;   /* output columns per workgroup (gemm), else 0 */
     int grid;        /* workgroups of the dominant kernel */

@@ -674,6 +674,12 @@ static BandCall band_call(const elora_linear_desc_t &d)
                     gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0, band_only(d.n_tokens, d.d_in, d.d_out)};
 }
 
+static bool planned_band(const elora_linear_desc_t &d, BandShape *s)
+{
+    const BandCall c = band_call(d);
+    return band_shape(c, part_want(d.n_tokens, d.d_in, d.d_out, c.max_rank), s);
+}
+
 // A call of 65 to 256 rows on a W of 4 million weights or more (smaller ones were not measured).  The decode kernel reads W
 // once per 64 rows; here it is read once, and the call's fixed part (route, shrink, a tile's beginning and end) is about 30 us.
 // Decode launches / here, a row per adapter of ranks 8 to 64, 4096 x 4096, 4096 x 14336, 14336 x 4096: 65 rows 41 / 47, 88 /
@@ -689,16 +695,20 @@ bool elora::band_instead_of_passes(const elora_linear_desc_t &d)
     const bool many_runs = d.pool != nullptr && (d.adapter_idx != nullptr || (long long)d.n_segments * 32 > d.n_tokens);
     if (many_runs && d.n_tokens <= (d.wfmt == ELORA_W_SAME || d.d_out >= 8192 ? 128 : 192)) return false;
     BandShape s;
-    return band_shape(band_call(d), part_want(d.n_tokens, d.d_in, d.d_out, d.pool ? d.pool->max_rank : 1), &s);
+    return planned_band(d, &s);
+}
+
+bool elora::gemm_copies_w(const elora_linear_desc_t &d)
+{
+    BandShape s;
+    return gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0 && !planned_band(d, &s);
 }
 
 void elora::gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
 {
-    const BandCall c = band_call(d);
-    const bool copy_first = c.copied;
     BandShape s;
-    const bool band = band_shape(c, part_want(d.n_tokens, d.d_in, d.d_out, c.max_rank), &s);
-    plan->n_launches = (d.pool ? 3 : 1) + (copy_first && !band && !d.pool ? 1 : 0);  // (with a pool the copy shares the route's launch)
+    const bool band = planned_band(d, &s);
+    plan->n_launches = (d.pool ? 3 : 1) + (gemm_copies_w(d) && !d.pool ? 1 : 0);  // (with a pool the copy shares the route's launch)
     if (band) {
         plan->split_k = s.ks;
         plan->tile_rows = 32 * s.ma;

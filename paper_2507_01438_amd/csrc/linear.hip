@@ -583,6 +583,7 @@ int elora_linear_group_launches(const elora_linear_desc_t *descs, int n, int *n_
         if (decode_group_splits(descs[0].n_tokens, n, K, N, split, &wlds, descs[0].wfmt, q8)) sum = 1;
     } else if (form == kGroupGemmShared) {
         sum -= 2 * (n - 1);  // one route and one shrink launch for all of them
+        for (int i = 1; i < n; ++i) sum += gemm_copies_w(descs[i]) ? 1 : 0;  // (the first call's copy shares the route's launch)
     }
     *n_launches = sum;
     return ELORA_OK;

@@ -21,3 +21,24 @@ def test_fp32_plan(T, K, N, launches, grid):
     p = B.elora_linear_plan(d)
     assert (p.path, p.n_launches, p.grid) == (B.ELORA_PATH_GENERIC, launches, grid)
     B.elora_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("wfmt, T, n, launches", [
+    (B.ELORA_W_SAME, 5000, 2, 2 + 2),
+    (B.ELORA_W_SAME, 5000, 3, 2 + 3),
+    (B.ELORA_W_INT8_G32, 5000, 2, 2 + 1 + 2),      # the copy of the second W is a launch of its own
+    (B.ELORA_W_INT4_G32, 5000, 3, 2 + 2 + 3),
+    (B.ELORA_W_INT4_G32, 400, 3, 2 + 3),           # no copy: the product takes W as it is stored
+    (B.ELORA_W_INT8_G32, 300, 2, 2 + 2),
+])
+def test_launches_of_a_group_that_shares_its_shrink(wfmt, T, n, launches):
+    K, N = 4096, 4096
+    pools, descs = [], []
+    for i in range(n):
+        pools.append(B.elora_pool_create(K, N, 16, 4, B.ELORA_BF16, FAKE, B.elora_pool_storage_bytes(K, N, 16, 4, B.ELORA_BF16)))
+        descs.append(B.make_desc(n_tokens=T, d_in=K, d_out=N, dtype=B.ELORA_BF16, wfmt=wfmt, x=FAKE, W=FAKE, y=FAKE + (i << 30), w_scales=FAKE if wfmt else None,
+                                 workspace=FAKE + ((i + 1) << 36), workspace_bytes=B.elora_workspace_bytes_w(T, K, N, 16, wfmt), pool=pools[i], seg_offsets=FAKE, seg_adapter=FAKE, n_segments=2))
+    assert all(B.elora_linear_plan(d).path == B.ELORA_PATH_GEMM and B.elora_linear_plan(d).n_launches == 3 for d in descs)
+    assert B.elora_linear_group_launches(B.desc_array(descs)) == launches
+    for p in pools:
+        B.elora_pool_destroy(p)
