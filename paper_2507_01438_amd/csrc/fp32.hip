@@ -100,13 +100,19 @@ __global__ __launch_bounds__(kThreads) void fp32_shrink_kernel(int K, const floa
 // A lane takes four consecutive elements of row lane % 16 (elements 4 (lane / 16) .. + 3 of the turn's 16), straight from memory:
 // the four matrix instructions of a turn multiply element i of every lane, in which order K is walked does not matter.
 // The eight waves' sums meet in LDS and are added in wave order.
-template <int MB, int NB>
-__global__ __launch_bounds__(kThreads) void fp32_product_kernel(int T, int K, int N, const float *__restrict__ x, const float *__restrict__ W, PoolView pool, int has_pool,
+// A launch with at most two workgroups per compute unit has four turns' loads of a wave under way; with more of them it is the
+// other workgroups that hide a load, and with one turn ahead four of them fit (the 32 x 32 tile with four ahead: 157 registers,
+// one workgroup): rank-8 calls, four ahead / one, 272 rows 1000 x 3000 50 / 42 us, 2000 rows 128 x 10000 440 / 144, 2048 x 10000
+// 1556 / 1336; 256 rows 2048 x 2048 45 / 40.
+template <int MB, int NB, int kAhead>
+__global__ __launch_bounds__(kThreads, kAhead == 1 ? 8 : 1) void fp32_product_kernel(int T, int K, int N, const float *__restrict__ x, const float *__restrict__ W, PoolView pool, int has_pool,
                                                                 const int32_t *__restrict__ row_slot, const float *__restrict__ row_scale,
                                                                 const float *__restrict__ V, int R, float *__restrict__ y, int first_tile)
 {
-    constexpr int kRows = 16 * MB, kCols = 16 * NB, kAhead = 4;  // turns whose loads are in flight
+    constexpr int kRows = 16 * MB, kCols = 16 * NB;  // (kAhead: turns whose loads are in flight)
     __shared__ float s_sum[kWaves][kRows][kCols + 4];
+    __shared__ int s_slot[kRows], s_rank[kRows];
+    __shared__ float s_scale[kRows];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
     const int tiles_n = (N + kCols - 1) / kCols, tile = first_tile + (int)blockIdx.x;
     const int t0 = tile / tiles_n * kRows, n0 = tile % tiles_n * kCols;
@@ -164,6 +170,13 @@ __global__ __launch_bounds__(kThreads) void fp32_product_kernel(int T, int K, in
         for (int b = 0; b < NB; ++b) wt[b] = load4_until(wr[b], whole * 16, K - g * 4);
         multiply(xt, wt);
     }
+    // (one row's route per lane: asked for per output, these are two more trips to memory behind the product)
+    if (tid < kRows) {
+        const int t = min(t0 + tid, T - 1), slot = has_pool ? row_slot[t] : -1;
+        s_slot[tid] = slot;
+        s_rank[tid] = slot >= 0 ? pool.meta[slot].rank : 0;
+        s_scale[tid] = slot >= 0 ? row_scale[t] : 0.0f;
+    }
     // a lane holds columns 4 g .. + 3 of row m
 #pragma unroll
     for (int a = 0; a < MB; ++a)
@@ -176,9 +189,8 @@ __global__ __launch_bounds__(kThreads) void fp32_product_kernel(int T, int K, in
         float sum = s_sum[0][rl][cl];
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) sum += s_sum[w][rl][cl];
-        const int slot = has_pool ? row_slot[t] : -1;
+        const int slot = s_slot[rl], rank = s_rank[rl];
         if (slot >= 0) {
-            const int rank = pool.meta[slot].rank;
             const float *const Bn = reinterpret_cast<const float *>(slot_B(pool, slot)) + (size_t)n * rank, *const v = V + (size_t)t * R;
             float d = 0.0f;
             int q = 0;
@@ -200,7 +212,7 @@ __global__ __launch_bounds__(kThreads) void fp32_product_kernel(int T, int K, in
                 for (int i = 0; i < 8; ++i)
                     if (q + i < rank) d = fmaf(vq[i], bq[i], d);
             }
-            sum += row_scale[t] * d;
+            sum += s_scale[rl] * d;
         }
         y[(size_t)t * N + n] = sum;
     }
@@ -242,7 +254,8 @@ int elora::launch_fp32(const LinearArgs &a, hipStream_t stream)
     const float *const x = static_cast<const float *>(a.x), *const W = static_cast<const float *>(a.W);
     const int R = a.pool.max_rank;
     for (size_t t = 0; a.has_pool && t < (size_t)a.T; t += kMaxGroups) {
-        hipLaunchKernelGGL(fp32_shrink_kernel, dim3((unsigned)std::min((size_t)a.T - t, kMaxGroups), (R + kPiece - 1) / kPiece), dim3(kThreads), 0, stream, a.K, x, a.route,
+        // (a wave per two rank entries, none that has nothing to do)
+        hipLaunchKernelGGL(fp32_shrink_kernel, dim3((unsigned)std::min((size_t)a.T - t, kMaxGroups), (R + kPiece - 1) / kPiece), dim3(64 * std::min((R + 1) / 2, kWaves)), 0, stream, a.K, x, a.route,
                            a.pool, row_slot, row_scale, V, R, (int)t);
         ELORA_HIP_TRY(hipGetLastError());
     }
@@ -256,7 +269,8 @@ int elora::launch_fp32(const LinearArgs &a, hipStream_t stream)
         return ELORA_OK;
     };
     profile_mark_begin(stream);
-    const int rc = tiles.mb == 1 ? go(fp32_product_kernel<1, 1>) : tiles.nb == 1 ? go(fp32_product_kernel<2, 1>) : go(fp32_product_kernel<2, 2>);
+    const int rc = tiles.mb == 1 ? (tiles.n > 512 ? go(fp32_product_kernel<1, 1, 1>) : go(fp32_product_kernel<1, 1, 4>))
+                   : tiles.nb == 1 ? go(fp32_product_kernel<2, 1, 4>) : go(fp32_product_kernel<2, 2, 1>);
     if (rc == ELORA_OK) profile_mark_end(stream);
     return rc;
 }

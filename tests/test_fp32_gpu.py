@@ -70,3 +70,18 @@ def test_more_rows_and_tiles_than_one_launch_holds():
     assert not (y == 7.0).all(dim=1).any()
     assert pool.poll_error() == (0, -1)
     pool.close()
+
+
+@pytest.mark.parametrize("shape", [(40, 8216, 5, 3, (1, 8)), (300, 9001, 16, 4, (3, 17, 24)), (33, 1000, 611, 4, (1, 5, 2)), (257, 515, 1025, 3, (9, 40))])
+def test_fp32_launches_of_more_workgroups_than_fit_at_once(shape):
+    """Many outputs: one turn's loads ahead, 16 x 16 and 32 x 32 tiles; K of fewer turns than waves, of one more than a round
+    of the eight waves has, pools whose ranks need one to eight waves of the shrink."""
+    K, N, T, pool, ranks = shape
+    w = I.small_workload(4200 + K, I.F32, K, N, T, pool, ranks, no_adapter_rows=(1,))
+    case = DeviceCase(w, w.projections[0])
+    y = case.run()
+    assert case.last_plan.grid > 512
+    assert rel_err(y, case.reference()) <= 1e-5
+    assert np.array_equal(y, case.run())
+    assert case.pool.poll_error() == (0, -1)
+    case.close()
