@@ -125,14 +125,14 @@ def _shared_cases(w, projs):
 
 
 @pytest.mark.parametrize("lengths,none_segs", [([70, 1, 1, 1, 200, 30, 0, 5], (2,)), ([300, 20, 257, 15, 1, 1, 1, 90], ())])
-def test_gemm_calls_that_share_x_share_route_and_shrink(lengths, none_segs):
+def test_gemm_calls_that_share_x_share_route_and_shrink(lengths, none_segs, product):
     from paper_2507_01438_amd import binding as B
     T = sum(lengths)
     w = I.small_workload(330 + T, I.BF16, 512, 264, T, 6, (16, 8, 32, 64, 5, 24), segments=lengths, no_adapter_rows=none_segs)
     w.projections = [I.Projection("a", 512, 264), I.Projection("b", 512, 1040), I.Projection("c", 512, 72)]
     cases = _shared_cases(w, w.projections)
     descs = B.desc_array([c.desc() for c in cases])
-    assert [B.elora_linear_plan(c.desc()).path for c in cases] == [2, 2, 2]
+    assert [(B.elora_linear_plan(c.desc()).path, B.elora_linear_plan(c.desc()).tile_cols) for c in cases] == [(2, product)] * 3
     assert B.elora_linear_group_launches(descs) == 2 + 3           # route, shrink, three GEMMs (alone: 3 x 3)
     for c in cases:
         c.y.fill_(7)

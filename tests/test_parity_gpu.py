@@ -504,12 +504,12 @@ GEMM_SMALL = [
 
 
 @pytest.mark.parametrize("shape", GEMM_SMALL)
-def test_gemm_path_small_shapes(shape):
+def test_gemm_path_small_shapes(shape, product):
     K, N, pool, ranks, lengths, none_segs = shape
     w = I.small_workload(300 + K, I.BF16, K, N, sum(lengths), pool, ranks, segments=lengths, no_adapter_rows=none_segs)
     case = DeviceCase(w, w.projections[0])
     y = case.run(force_path=GEMM)
-    assert case.last_plan.path == GEMM
+    assert case.last_plan.path == GEMM and case.last_plan.tile_cols == product
     _check(case, y, case.reference())
     assert case.pool.poll_error() == (0, -1)
     y2 = case.run(force_path=GEMM)
@@ -517,41 +517,41 @@ def test_gemm_path_small_shapes(shape):
     case.close()
 
 
-def test_gemm_path_with_per_row_indices_and_scales():
+def test_gemm_path_with_per_row_indices_and_scales(product):
     w = I.small_workload(77, I.BF16, 512, 328, 333, 7, (16, 8, 32), no_adapter_rows=(0, 100, 332))
     w.adapter_idx[40:200] = 3          # a long run in the middle of scattered indices
     case = DeviceCase(w, w.projections[0])
     rs = np.linspace(0.5, 2.5, w.T).astype(np.float32)
     y = case.run(scales=to_dev(rs), force_path=GEMM)
-    assert case.last_plan.path == GEMM
+    assert case.last_plan.path == GEMM and case.last_plan.tile_cols == product
     _check(case, y, case.reference(row_scale=rs))
     case.close()
 
 
-def test_gemm_path_int4_small():
+def test_gemm_path_int4_small(product):
     lengths = [70, 1, 1, 1, 200, 30]
     w = I.small_workload(88, I.BF16, 384, 272, sum(lengths), 4, (16, 8), wfmt=I.W_INT4_G32, segments=lengths)
     case = DeviceCase(w, w.projections[0])
     y = case.run()
-    assert case.last_plan.path == GEMM
+    assert case.last_plan.path == GEMM and case.last_plan.tile_cols == product
     _check(case, y, case.reference())
     case.close()
 
 
-def test_gemm_path_int4_converted_once_for_many_rows():
-    # from 768 rows on the 4-bit W is converted to bf16 once per call instead of tile by tile, in the shrink's launch
+def test_gemm_path_int4_converted_once_for_many_rows(product):
+    # from 768 rows on the 256 x 256 tiles take a bf16 copy of the 4-bit W, made once per call in the route's launch
     lengths = [400, 1, 1, 300, 9, 60, 30]
     w = I.small_workload(89, I.BF16, 384, 272, sum(lengths), 4, (16, 8), wfmt=I.W_INT4_G32, segments=lengths)
     case = DeviceCase(w, w.projections[0])
     y = case.run()
-    assert case.last_plan.path == GEMM and case.last_plan.n_launches == 3
+    assert case.last_plan.path == GEMM and case.last_plan.n_launches == 3 and case.last_plan.tile_cols == product
     _check(case, y, case.reference())
     y2 = case.run()   # the copy in the workspace is rebuilt by every call
     assert np.array_equal(y, y2)
     case.close()
 
 
-def test_gemm_routing_probes_are_bit_exact():
+def test_gemm_routing_probes_are_bit_exact(product):
     from paper_2507_01438_amd import binding as B
     P, K, N = 300, 64, 16
     lengths = [1] * 40 + [33, 100, 17] + [1] * 25

@@ -109,12 +109,12 @@ GEMM_Q8 = [
 
 
 @pytest.mark.parametrize("shape", GEMM_Q8)
-def test_q8_pool_on_the_gemm_path(shape):
+def test_q8_pool_on_the_gemm_path(shape, product):
     K, N, pool, ranks, lengths, none_segs = shape
     w = I.small_workload(820 + K, I.BF16, K, N, sum(lengths), pool, ranks, segments=lengths, no_adapter_rows=none_segs)
     case = DeviceCase(w, w.projections[0], q8=True)
     y = case.run(force_path=GEMM)
-    assert case.last_plan.path == GEMM
+    assert case.last_plan.path == GEMM and case.last_plan.tile_cols == product
     assert_close(y, case.reference(), case.base_reference(), f"q8 gemm {shape}")
     assert np.array_equal(y, case.run(force_path=GEMM))
     # the generic kernels read the same blocks element by element
@@ -124,7 +124,7 @@ def test_q8_pool_on_the_gemm_path(shape):
     case.close()
 
 
-def test_q8_pools_share_route_and_shrink_on_the_gemm_path():
+def test_q8_pools_share_route_and_shrink_on_the_gemm_path(product):
     # gate and up of a prefill batch, each with its own pool of 8-bit blocks: one route and one shrink launch for both
     from paper_2507_01438_amd import binding as B
     lengths = [280, 40, 1, 1, 300]
@@ -132,6 +132,7 @@ def test_q8_pools_share_route_and_shrink_on_the_gemm_path():
     a = DeviceCase(w, w.projections[0], q8=True)
     b = DeviceCase(w, w.projections[0], q8=True, share=a)
     arr = B.desc_array([a.desc(), b.desc()])
+    assert [B.elora_linear_plan(c.desc()).tile_cols for c in (a, b)] == [product, product]
     assert B.elora_linear_group_launches(arr) == 4          # route, shrink, two GEMMs
     B.elora_batched_lora_linear_group(arr)
     torch.cuda.synchronize()

@@ -37,19 +37,20 @@ def test_generic_kernels_read_the_8bit_base(shape):
     case.close()
 
 
-def test_gemm_path_multiplies_from_a_bf16_copy():
-    # more rows than the decode kernel takes: W is converted once per call (in the shrink's launch), then the bf16 GEMM
+def test_gemm_path_of_the_8bit_base(product):
+    # more rows than the decode kernel takes: W is converted once per call (in the route's launch), then the bf16 GEMM; or on
+    # its way to the matrix cores
     lengths = [300, 1, 1, 200, 9, 60, 30]
     case = _case(901, 384, 272, sum(lengths), 4, (16, 8), segments=lengths)
     y = case.run()
-    assert case.last_plan.path == GEMM and case.last_plan.n_launches == 3
+    assert case.last_plan.path == GEMM and case.last_plan.n_launches == 3 and case.last_plan.tile_cols == product
     assert rel_err(y, case.reference()) <= TOL
     y2 = case.run()
     assert np.array_equal(y, y2)
     case.close()
 
 
-def test_gemm_path_without_pool():
+def test_gemm_path_without_pool(product):
     w = I.small_workload(902, I.BF16, 256, 264, 300, 2, (8,), wfmt=I.W_INT8_G32)
     case = DeviceCase(w, w.projections[0])
     case.lin.pool = None
@@ -57,7 +58,7 @@ def test_gemm_path_without_pool():
     from paper_2507_01438_amd import binding as B
     import torch
     plan = B.elora_linear_plan(d)
-    assert plan.path == GEMM
+    assert plan.path == GEMM and (plan.tile_cols, plan.n_launches) == (product, 2 if product == 256 else 1)
     B.elora_batched_lora_linear(d)
     torch.cuda.synchronize()
     from gpu_harness import y_to_f64

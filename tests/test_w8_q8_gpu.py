@@ -110,12 +110,12 @@ def test_groups_on_8bit_bases_with_8bit_adapters_run_as_one_launch(T, K, Ns):
         c.close()
 
 
-def test_many_rows_8bit_base_and_adapters_take_the_gemm_path():
+def test_many_rows_8bit_base_and_adapters_take_the_gemm_path(product):
     lengths = [300, 40, 1, 1, 280]
     w = I.small_workload(1190, I.BF16, 512, 264, sum(lengths), 4, (16, 8), wfmt=I.W_INT8_G32, segments=lengths)
     case = DeviceCase(w, w.projections[0], q8=True)
     y = case.run()
-    assert case.last_plan.path == GEMM
+    assert case.last_plan.path == GEMM and case.last_plan.tile_cols == product
     assert rel_err(y, case.reference()) <= TOL
     case.close()
 
