@@ -167,6 +167,7 @@ void band_set(int mode, int tiles_m, int slices);  // -1: where it pays, 0: neve
 bool band_instead_of_passes(const elora_linear_desc_t &d);  // a call of 65 to 256 rows: better as one product than as launches of the decode kernel
 bool gemm_eligible(const elora_linear_desc_t &d, int max_rank);
 void gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan);
+bool shrink_rows_apart(int T, bool indices, int n_segments);  // the shrink is two launches
 bool gemm_copies_w(const elora_linear_desc_t &d);  // this call of the GEMM path makes a bf16 copy of its W
 size_t gemm_wcopy_bytes(int wfmt, int n_tokens, int d_in, int d_out);  // (see below)
 size_t gemm_w4_bytes(int n_tokens, int d_in, int d_out);  // room for the bf16 copy of a 4-bit W; 0: converted tile by tile

@@ -708,7 +708,8 @@ void elora::gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
 {
     BandShape s;
     const bool band = planned_band(d, &s);
-    plan->n_launches = (d.pool ? 3 : 1) + (gemm_copies_w(d) && !d.pool ? 1 : 0);  // (with a pool the copy shares the route's launch)
+    // (with a pool the copy shares the route's launch)
+    plan->n_launches = d.pool ? 3 + (shrink_rows_apart(d.n_tokens, d.adapter_idx != nullptr, d.n_segments) ? 1 : 0) : 1 + (gemm_copies_w(d) ? 1 : 0);
     if (band) {
         plan->split_k = s.ks;
         plan->tile_rows = 32 * s.ma;

@@ -85,6 +85,7 @@ struct ShrinkArgs {
     int n_tiles;         // kShrinkRows-row tiles
     int ks;              // K-slices per tile
     int wgs_per_xcd;     // workgroups per projection and XCD
+    bool rows_apart;     // the rows of short runs are a launch of their own
     const uint16_t *x;
     ShrinkProj proj[kShrinkMulti];
 };

@@ -582,7 +582,8 @@ int elora_linear_group_launches(const elora_linear_desc_t *descs, int n, int *n_
         for (int i = 0; i < n; ++i) q8 = q8 || (descs[i].pool && descs[i].pool->q8);
         if (decode_group_splits(descs[0].n_tokens, n, K, N, split, &wlds, descs[0].wfmt, q8)) sum = 1;
     } else if (form == kGroupGemmShared) {
-        sum -= 2 * (n - 1);  // one route and one shrink launch for all of them
+        // one route and one shrink (one or two launches) for all of them
+        sum -= (2 + (shrink_rows_apart(descs[0].n_tokens, descs[0].adapter_idx != nullptr, descs[0].n_segments) ? 1 : 0)) * (n - 1);
         for (int i = 1; i < n; ++i) sum += gemm_copies_w(descs[i]) ? 1 : 0;  // (the first call's copy shares the route's launch)
     }
     *n_launches = sum;

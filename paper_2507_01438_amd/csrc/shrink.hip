@@ -59,14 +59,31 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteView route, S
 // Bound by latency: a pass over two rows of A_i is one trip to memory.  (150 rows of ranks 8 to 64, K = 4096: a whole row
 // per workgroup on half as many workgroups as rows 35 us, pieces of 16 entries on one workgroup per row 24.)
 constexpr int kRowPiece = 16;
+// Rows in short runs, as far as the host can tell, from which they are a launch of their own.  With an adapter per row, all in
+// the one launch / so: 512 rows of ranks 8 to 64, 2752 x 2896, 89 / 84 us, 2000 rows 243 / 203; 4000 rows of rank 16, 4096 x
+// 4096, 389 / 241.  With one adapter the second launch costs 2 us.
+constexpr int kRowsApart = 512;
 template <bool kQ8>
-__device__ __forceinline__ void shrink_row_piece(const ShrinkArgs &s, const ShrinkProj &pr, int t, int first)
+__device__ __forceinline__ void shrink_row_piece(const ShrinkArgs &s, const ShrinkProj &pr, int t, int first, int end)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), K = s.K;
     const int slot = pr.row_slot[t];
     const int rank = slot >= 0 ? pr.pool.meta[slot].rank : 0;
     const float sc = slot >= 0 && !pr.V_rest ? pr.row_scale[t] : 1.0f;
     const size_t at = (size_t)t * pr.Rpad;
+    auto put = [&](int j, float v0, float v1) __attribute__((always_inline)) {  // two entries of the row, final
+        auto store = [&](uint16_t *to, uint16_t lo, uint16_t hi) { *reinterpret_cast<uint32_t *>(to + at + j) = lo | ((uint32_t)hi << 16); };
+        if (pr.V_rest) {
+            uint16_t p0[3], p1[3];
+            split_bf16(v0, p0);
+            split_bf16(v1, p1);
+            store(pr.V, p0[0], p1[0]);
+            store(pr.V_rest, p0[1], p1[1]);
+            store(pr.V_rest + (size_t)s.T * pr.Rpad, p0[2], p1[2]);
+        } else {
+            store(pr.V, f32_to_bf16(v0), f32_to_bf16(v1));
+        }
+    };
     for (int j0 = first + 2 * wave; j0 < first + kRowPiece; j0 += 2 * kWaves) {
         const bool two = j0 + 1 < rank;
         float a0 = 0.0f, a1 = 0.0f;
@@ -82,21 +99,35 @@ __device__ __forceinline__ void shrink_row_piece(const ShrinkArgs &s, const Shri
                 shrink_pair(A + (size_t)j0 * K, A + (size_t)j1 * K, s.x + (size_t)t * K, K, lane, a0, a1);
             }
         }
-        if (lane == 0) {
-            const float v0 = j0 < rank ? sc * a0 : 0.0f, v1 = two ? sc * a1 : 0.0f;
-            auto store = [&](uint16_t *to, uint16_t lo, uint16_t hi) { *reinterpret_cast<uint32_t *>(to + at + j0) = lo | ((uint32_t)hi << 16); };
-            if (pr.V_rest) {
-                uint16_t p0[3], p1[3];
-                split_bf16(v0, p0);
-                split_bf16(v1, p1);
-                store(pr.V, p0[0], p1[0]);
-                store(pr.V_rest, p0[1], p1[1]);
-                store(pr.V_rest + (size_t)s.T * pr.Rpad, p0[2], p1[2]);
-            } else {
-                store(pr.V, f32_to_bf16(v0), f32_to_bf16(v1));
-            }
-        }
+        if (lane == 0) put(j0, j0 < rank ? sc * a0 : 0.0f, two ? sc * a1 : 0.0f);
     }
+    for (int j = first + kRowPiece + 2 * tid; j < end; j += 2 * kThreads) put(j, 0.0f, 0.0f);
+}
+
+// The short rows' pieces, shared by `wgs` workgroups.  Where the pieces are no more than the workgroups, those of a row are
+// side by side (a prompt whose last tile has 5 rows, K = 14336: 14.7 us, all first pieces and then all second ones 17.2).
+// Else all first pieces come first: pieces beyond most rows' ranks are nothing but zeros, and fall to all workgroups alike,
+// at the end.  (With 4 pieces always, and to a workgroup the same one of every row: 1846 rows of an adapter of rank 16 each,
+// K = 6336, the call 297 us, so 185; 150 rows of ranks 8 to 64, K = 14336 44 and 37.)
+template <bool kQ8>
+__device__ __forceinline__ void shrink_rows(const ShrinkArgs &s, const ShrinkProj &pr, int n_short, int first, int wgs)
+{
+    const int pieces = (pr.pool.max_rank + kRowPiece - 1) / kRowPiece, items = n_short * pieces;
+    for (int i = first; i < items; i += wgs) {
+        const int by = items <= wgs ? pieces : n_short, hi = i / by, lo = i - hi * by;
+        const int r = items <= wgs ? hi : lo, piece = items <= wgs ? lo : hi;
+        // (the last piece a rank can have takes the zeros up to the end of the padded row)
+        shrink_row_piece<kQ8>(s, pr, pr.short_rows[r], piece * kRowPiece, piece + 1 < pieces ? (piece + 1) * kRowPiece : pr.Rpad);
+    }
+}
+
+// Many rows in short runs: a launch of their own, without LDS, so that a compute unit holds four workgroups and not the one or
+// two that the rings leave room for.
+template <bool kQ8>
+__global__ __launch_bounds__(kThreads) void shrink_rows_kernel(ShrinkArgs s)
+{
+    const ShrinkProj &pr = s.proj[blockIdx.x % s.n];
+    shrink_rows<kQ8>(s, pr, pr.sync[kSyncShortRows], (int)(blockIdx.x / s.n), (int)(gridDim.x / s.n));
 }
 
 // ---- a 32-row tile and one K-slice of it ---------------------------------------------------------------------------------
@@ -377,9 +408,8 @@ __device__ __forceinline__ void shrink_workgroup(const ShrinkArgs &s, int wg)
     const int tile = xcd * tiles_per_xcd + u / s.ks;
     const int n_short = pr.sync[kSyncShortRows];
     if (u < units && tile < s.n_tiles) shrink_tile<kQ8, NCB>(s, pr, tile, u % s.ks, part_q, s_last, ring);
-    // the rows of short runs are shared by all workgroups (workgroups of their own would each wait for a ring's worth of LDS)
-    const int wgs = s.wgs_per_xcd * kXcds, pieces = pr.Rpad / kRowPiece;
-    for (int i = seq * kXcds + xcd; i < n_short * pieces; i += wgs) shrink_row_piece<kQ8>(s, pr, pr.short_rows[i / pieces], i % pieces * kRowPiece);
+    // the rows of short runs are shared by all workgroups (a few workgroups of their own would each wait for a ring's worth of LDS)
+    if (!s.rows_apart) shrink_rows<kQ8>(s, pr, n_short, seq * kXcds + xcd, s.wgs_per_xcd * kXcds);
 }
 int shrink_grid(const ShrinkArgs &s) { return s.wgs_per_xcd * kXcds * s.n; }
 
@@ -434,6 +464,9 @@ auto with_cols(const ShrinkArgs &s, F &&f)  // f(8-bit blocks, MFMA column block
 
 }  // namespace
 
+// (how many rows may sit in short runs: every row that has an index of its own, some at the ends of a segment)
+bool elora::shrink_rows_apart(int T, bool indices, int n_segments) { return std::min((long long)T, indices ? (long long)T : 3ll * n_segments) >= kRowsApart; }
+
 void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n, const bool *whole)
 {
     s.n = n;
@@ -454,6 +487,7 @@ void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n, const bool *w
     while (s.ks < kMaxSlices && s.n_tiles * (s.ks + 1) <= (s.K / (s.ks + 1) >= 4096 ? 512 : 256) && s.n_tiles <= kSyncTileCount &&
            s.K / kSpan >= (s.ks + 1) * 2 * kWaves && room_for(s.ks + 1))
         ++s.ks;
+    s.rows_apart = shrink_rows_apart(s.T, a[0].route.adapter_idx != nullptr, a[0].route.n_segments);
     // (at least four workgroups per row, up to two per compute unit: the rows of short runs are shared by all of them)
     s.wgs_per_xcd = std::max((s.n_tiles + kXcds - 1) / kXcds * s.ks * 2, std::min((s.T + 1) / 2, 64));
     for (int p = 0; p < n; ++p) {
@@ -501,6 +535,10 @@ int elora::launch_shrink(const ShrinkArgs &s, hipStream_t stream)
         }
         hipLaunchKernelGGL((sgmv_shrink_kernel<Q8, NCB>), dim3(shrink_grid(s)), dim3(kThreads), lds, stream, s);
         ELORA_HIP_TRY(hipGetLastError());
+        if (s.rows_apart) {
+            hipLaunchKernelGGL((shrink_rows_kernel<Q8>), dim3(1024 * s.n), dim3(kThreads), 0, stream, s);
+            ELORA_HIP_TRY(hipGetLastError());
+        }
         return ELORA_OK;
     });
 }

@@ -42,3 +42,19 @@ def test_launches_of_a_group_that_shares_its_shrink(wfmt, T, n, launches):
     assert B.elora_linear_group_launches(B.desc_array(descs)) == launches
     for p in pools:
         B.elora_pool_destroy(p)
+
+
+@pytest.mark.parametrize("T, route, launches", [
+    (600, dict(adapter_idx=FAKE), 4),                                                  # a row per adapter: their shrink is a launch of its own
+    (500, dict(adapter_idx=FAKE), 3),
+    (2168, dict(seg_offsets=FAKE, seg_adapter=FAKE, n_segments=124), 3),
+    (2168, dict(seg_offsets=FAKE, seg_adapter=FAKE, n_segments=400), 4),
+])
+def test_launches_of_calls_with_many_short_runs(T, route, launches):
+    K, N = 1024, 1024
+    pool = B.elora_pool_create(K, N, 16, 4, B.ELORA_BF16, FAKE, B.elora_pool_storage_bytes(K, N, 16, 4, B.ELORA_BF16))
+    descs = [B.make_desc(n_tokens=T, d_in=K, d_out=N, dtype=B.ELORA_BF16, x=FAKE, W=FAKE, y=FAKE + (i << 30), workspace=FAKE + ((i + 1) << 36),
+                         workspace_bytes=B.elora_workspace_bytes(T, K, N, 16), pool=pool, **route) for i in range(2)]
+    assert B.elora_linear_plan(descs[0]).n_launches == launches
+    assert B.elora_linear_group_launches(B.desc_array(descs)) == launches + 1
+    B.elora_pool_destroy(pool)

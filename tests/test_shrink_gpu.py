@@ -67,3 +67,34 @@ def test_an_infinite_scale_makes_its_rows_infinite(K, product):
     ref = case.reference(row_scale=np.where(np.isfinite(rows), rows, 1.0).astype(np.float32))[rest]
     assert np.abs(y[rest] - ref).max() <= 1e-2 * np.abs(ref).max()
     case.close()
+
+
+@pytest.mark.parametrize("q8", [False, True])
+@pytest.mark.parametrize("T, K, ranks", [(511, 320, (8, 16, 64, 24)), (512, 320, (8, 16, 64, 24)), (777, 4096, (16,)), (1300, 192, (8, 136, 72))])
+def test_many_rows_in_short_runs(T, K, ranks, q8, product):
+    """Around the count from which they are a launch of their own; more pieces than workgroups, ranks of one to nine pieces of 16,
+    rows without adapter, a long run among them, scales given; and the same batch by segments."""
+    import torch
+
+    from paper_2507_01438_amd import binding as B
+    w = I.small_workload(1800 + T, I.BF16, K, 136, T, 9, ranks, no_adapter_rows=(0, 77, T - 1))
+    w.adapter_idx[130:190] = 3
+    case = DeviceCase(w, w.projections[0], q8=q8)
+    over = np.linspace(0.25, 2.0, T).astype(np.float32)
+    y = case.run(scales=torch.from_numpy(over).to("cuda:0"), force_path=GEMM)
+    assert case.last_plan.tile_cols == product and case.last_plan.n_launches == (4 if T >= 512 else 3)
+    assert_close(y, case.reference(row_scale=over), case.base_reference(), f"{T} rows")
+    if product == 256:  # (the same shrink whichever way the rows are named; every product adds them in its own order)
+        d = case.lin.desc(case.x[:T], case.W, case.y, seg_offsets=torch.arange(T + 1, dtype=torch.int32, device="cuda:0"), seg_adapter=case.adapter_idx,
+                          scales=torch.from_numpy(over).to("cuda:0"))
+        case.y.fill_(7)
+        B.elora_force_path(GEMM)
+        try:
+            B.elora_batched_lora_linear(d)
+        finally:
+            B.elora_force_path(-1)
+        torch.cuda.synchronize()
+        from gpu_harness import y_to_f64
+        assert np.array_equal(y_to_f64(case.y[:T], I.BF16), y)
+    assert case.pool.poll_error() == (0, -1)
+    case.close()
