@@ -489,10 +489,13 @@ void elora::band_set(int mode, int tiles_m, int slices)
 // beginning and end, a step of the expand and the sums of slices were measured to take, times the rounds of 256 workgroups
 // (one per compute unit).
 //   here: a K block 270 + 160 ma (a W that is converted on the way 1550 + 105 ma), a tile 6000 + 2300 ma, an expand step
-//   1100 (adapters in 8-bit blocks 6500; ranks above 32 are taken to be mixed with smaller ones), the slices' sums 2000 + 450
-//   ma each; 20 % more than that where there is more than one round;
+//   1600 (adapters in 8-bit blocks 6500), the slices' sums 2000 + 450 ma each; 20 % more than that where there is more than
+//   one round;
 //   there: a K block 3300, in further rounds 2900 (from the bf16 copy of W 2600, converted on the way 5700), a tile 6000, 16
 //   rank entries of a short run 850 (adapters in 8-bit blocks 4000), the copy 1.04e-3 per weight.
+// Over 1488 calls of 300 to 4000 rows (eight W of 512 x 512 to 14336 x 4096 and 4096 x 14336, one prompt to a row per adapter,
+// ranks 8 to 128, all storage formats) the choice is slower than the 256 x 256 tiles by more than 3 % in 4 and by 9 % at most;
+// the mean call takes 68 % of its time there.  (Asking for the estimate to be 8 % lower is what keeps these from being 27.)
 // (4096 x 14336, here / there: 600 rows of one adapter 109 / 119 us, 800 of two 124 / 119, 1800 235 / 208, 600 of an adapter
 // each 217 / 188; 4096 x 4096: 600 of an adapter each 103 / 185, 1000 of one 58 / 121; 2560 x 7680, 3000 rows: 171 / 140.)
 bool elora::band_shape(const BandCall &c, size_t part_bytes, BandShape *s)
@@ -507,7 +510,7 @@ bool elora::band_shape(const BandCall &c, size_t part_bytes, BandShape *s)
         const int ma = ((T + tiles_m - 1) / tiles_m + 31) / 32, tm = (T + 32 * ma - 1) / (32 * ma);
         const double block = c.wfmt == ELORA_W_SAME ? 270 + 160 * ma : 1550 + 105 * ma;
         // a wave's steps: where the runs are spread over the batch, and what the tile with most of them has above that
-        const double row = (c.q8 ? 6500.0 : 1100.0) * (1 + 0.5 * ((c.max_rank - 1) / 32));
+        const double row = (c.q8 ? 6500.0 : 1600.0) * c.pieces32;
         const double spread = row * 16 * ma * c.runs / T, above = std::max(0.0, row * std::min(16 * ma, c.runs) - spread);
         for (int ks = g_mode_slices ? g_mode_slices : 1; ks <= (g_mode_slices ? g_mode_slices : kMaxSlices); ++ks) {
             if (ks > blocks || (ks > 1 && ((long long)tm * tiles_n > kSyncTileCount || (size_t)tm * tiles_n * ks * (ma * 32 * BN * 4) > part_bytes))) continue;
@@ -523,8 +526,9 @@ bool elora::band_shape(const BandCall &c, size_t part_bytes, BandShape *s)
     if (best < 0 || g_mode == 1 || c.only) return best >= 0;
     const double n = rounds((double)((T + 255) / 256) * ((N + 255) / 256));
     const double block = c.copied ? 2600 : c.wfmt != ELORA_W_SAME ? 5700 : n > 1 ? 2900 : 3300;
-    const double steps = (c.q8 ? 4000.0 : 850.0) * std::min(128, c.runs) * ((c.max_rank + 15) / 16);
-    return best < n * (blocks * block + 6000) + steps + (c.copied ? 1.04e-3 * K * N : 0);
+    // (the most that a wave of a tile has, 128 rows; where the runs are spread over the batch, every round's tiles have them)
+    const double run = (c.q8 ? 4000.0 : 850.0) * c.pieces16, spread = c.runs < T ? run * 128 * c.runs / T : run * 128, above = std::max(0.0, run * std::min(128, c.runs) - spread);
+    return best < 0.92 * (n * (blocks * block + 6000 + spread) + above + (c.copied ? 1.04e-3 * K * N : 0));
 }
 
 bool elora::band_whole(const LinearArgs &a) { return a.has_pool && a.T <= kWholeRows && a.wsl.v_rest_bytes != 0; }

@@ -98,9 +98,18 @@ struct elora_pool {
     bool device_cleared;
     elora::SlotMeta *host_meta;  // mirror of the device slot table (written through set_host_meta)
     int n_odd_ranks;             // loaded slots whose rank is no multiple of 8
+    int n_loaded, n_pieces16, n_pieces32;  // loaded slots, and the pieces of 16 and of 32 entries of their ranks
     void set_host_meta(int slot, const elora::SlotMeta &m)
     {
         n_odd_ranks += (int)(m.loaded && (m.rank & 7) != 0) - (int)(host_meta[slot].loaded && (host_meta[slot].rank & 7) != 0);
+        auto count = [&](const elora::SlotMeta &e, int by) {
+            if (!e.loaded) return;
+            n_loaded += by;
+            n_pieces16 += by * ((e.rank + 15) / 16);
+            n_pieces32 += by * ((e.rank + 31) / 32);
+        };
+        count(host_meta[slot], -1);
+        count(m, 1);
         host_meta[slot] = m;
     }
     elora::PoolView view() const;
@@ -118,6 +127,7 @@ struct LinearArgs {
     void *y;
     bool has_pool;
     PoolView pool;
+    int n_loaded, n_pieces16, n_pieces32;  // the pool's
     RouteView route;
     char *ws;
     WsLayout wsl;
@@ -153,7 +163,8 @@ struct BandShape {
 // runs: of equal adapters, at most; q8: pool of 8-bit blocks; copied: the 256 x 256 tiles would run on a bf16 copy of W; only:
 // they are no alternative to this call (band_only)
 struct BandCall {
-    int T, K, N, wfmt, runs, max_rank;
+    int T, K, N, wfmt, runs;
+    double pieces16, pieces32;  // pieces of 16 and of 32 entries of a loaded adapter's rank, on average
     bool q8, copied, only;
 };
 // Calls of 65 to 256 rows that the decode kernel takes as well, with shrink results in fp32: on this path they run as the

@@ -15,6 +15,8 @@
 //           epilogue rounds once to bf16 and stores each row at its own position.
 #include "gemm_common.h"
 
+#include <algorithm>
+
 using namespace elora;
 
 namespace {
@@ -668,16 +670,22 @@ bool elora::gemm_eligible(const elora_linear_desc_t &d, int max_rank)
     return d.wfmt != ELORA_W_INT8_G32 || gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0;
 }
 
+static BandCall make_band_call(int T, int K, int N, int wfmt, int runs, int n_loaded, int n_pieces16, int n_pieces32, bool q8, bool copied)
+{
+    const double n = n_loaded > 0 ? n_loaded : 1;
+    return BandCall{T, K, N, wfmt, runs, std::max(1.0, n_pieces16 / n), std::max(1.0, n_pieces32 / n), q8, copied, band_only(T, K, N)};
+}
+
 static BandCall band_call(const elora_linear_desc_t &d)
 {
-    return BandCall{d.n_tokens, d.d_in, d.d_out, d.wfmt, !d.pool ? 0 : d.adapter_idx ? d.n_tokens : d.n_segments, d.pool ? d.pool->max_rank : 1, d.pool && d.pool->q8,
-                    gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0, band_only(d.n_tokens, d.d_in, d.d_out)};
+    const elora_pool *const p = d.pool;
+    return make_band_call(d.n_tokens, d.d_in, d.d_out, d.wfmt, !p ? 0 : d.adapter_idx ? d.n_tokens : d.n_segments, p ? p->n_loaded : 0, p ? p->n_pieces16 : 0,
+                          p ? p->n_pieces32 : 0, p && p->q8, gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0);
 }
 
 static bool planned_band(const elora_linear_desc_t &d, BandShape *s)
 {
-    const BandCall c = band_call(d);
-    return band_shape(c, part_want(d.n_tokens, d.d_in, d.d_out, c.max_rank), s);
+    return band_shape(band_call(d), part_want(d.n_tokens, d.d_in, d.d_out, d.pool ? d.pool->max_rank : 1), s);
 }
 
 // A call of 65 to 256 rows on a W of 4 million weights or more (smaller ones were not measured).  The decode kernel reads W
@@ -791,7 +799,8 @@ static bool band_for(const LinearArgs &a, BandShape *s)
 {
     const bool copied = a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
     const int runs = !a.has_pool ? 0 : a.route.adapter_idx ? a.T : a.route.n_segments;
-    return band_shape(BandCall{a.T, a.K, a.N, a.wfmt, runs, a.pool.max_rank, a.has_pool && a.pool.q8, copied, band_only(a.T, a.K, a.N)}, a.wsl.part_bytes, s);
+    return band_shape(make_band_call(a.T, a.K, a.N, a.wfmt, runs, a.n_loaded, a.n_pieces16, a.n_pieces32, a.has_pool && a.pool.q8, copied),
+                      a.wsl.part_bytes, s);
 }
 
 int elora::launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_t stream)

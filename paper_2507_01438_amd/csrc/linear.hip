@@ -383,8 +383,12 @@ static int fill_args(const elora_linear_desc_t *d, const WsLayout &wsl, hipStrea
         rc = pool_ensure_cleared(const_cast<elora_pool *>(d->pool), stream);
         if (rc != ELORA_OK) return rc;
         a.pool = d->pool->view();
+        a.n_loaded = d->pool->n_loaded;
+        a.n_pieces16 = d->pool->n_pieces16;
+        a.n_pieces32 = d->pool->n_pieces32;
         a.route = RouteView{d->adapter_idx, d->seg_offsets, d->seg_adapter, d->n_segments, d->scales, 0};
     } else {
+        a.n_loaded = a.n_pieces16 = a.n_pieces32 = 0;
         a.pool = PoolView{nullptr, nullptr, nullptr, 0, 0, 0, 1, 0, 0, 0};
         a.route = RouteView{nullptr, nullptr, nullptr, 0, nullptr, 0};
     }

@@ -205,7 +205,7 @@ int elora_pool_create(int d_in, int d_out, int max_rank, int capacity, int dtype
         return ELORA_E_STORAGE;
     }
     for (int i = 0; i < capacity; ++i) p->host_meta[i] = SlotMeta{0, 0.0f, 0, 0};
-    p->n_odd_ranks = 0;
+    p->n_odd_ranks = p->n_loaded = p->n_pieces16 = p->n_pieces32 = 0;
     size_t e = elem_bytes(dtype);
     p->d_in = d_in;
     p->d_out = d_out;
@@ -264,7 +264,7 @@ int elora_pool_create_q8(int d_in, int d_out, int max_rank, int capacity, void *
         return ELORA_E_STORAGE;
     }
     for (int i = 0; i < capacity; ++i) p->host_meta[i] = SlotMeta{0, 0.0f, 0, 0};
-    p->n_odd_ranks = 0;
+    p->n_odd_ranks = p->n_loaded = p->n_pieces16 = p->n_pieces32 = 0;
     p->d_in = d_in;
     p->d_out = d_out;
     p->max_rank = max_rank;

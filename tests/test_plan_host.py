@@ -58,3 +58,22 @@ def test_launches_of_calls_with_many_short_runs(T, route, launches):
     assert B.elora_linear_plan(descs[0]).n_launches == launches
     assert B.elora_linear_group_launches(B.desc_array(descs)) == launches + 1
     B.elora_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("T, K, N, wfmt, n_segments, tile_cols", [
+    (2000, 1024, 1024, B.ELORA_W_SAME, None, 256),            # an adapter of up to 16 entries per row: 93 / 107 us on the two products
+    (4000, 1024, 1024, B.ELORA_W_SAME, None, 256),            # 106 / 128
+    (2000, 2752, 2896, B.ELORA_W_INT8_G32, 202, 256),         # two prompts and 200 rows of their own: 114 / 146
+    (1200, 1024, 1024, B.ELORA_W_INT4_G32, 202, 256),         # 81 / 98
+    (389, 4096, 14336, B.ELORA_W_SAME, 1, 128),               # a prompt: 121 / 73
+    (1000, 4096, 4096, B.ELORA_W_SAME, 1, 128),               # 121 / 58
+    (600, 4096, 4096, B.ELORA_W_SAME, None, 128),             # 185 / 103
+])
+def test_which_matrix_product_a_call_takes(T, K, N, wfmt, n_segments, tile_cols):
+    pool = B.elora_pool_create(K, N, 16, 4, B.ELORA_BF16, FAKE, B.elora_pool_storage_bytes(K, N, 16, 4, B.ELORA_BF16))
+    route = dict(adapter_idx=FAKE) if n_segments is None else dict(seg_offsets=FAKE, seg_adapter=FAKE, n_segments=n_segments)
+    d = B.make_desc(n_tokens=T, d_in=K, d_out=N, dtype=B.ELORA_BF16, wfmt=wfmt, x=FAKE, W=FAKE, y=FAKE, w_scales=FAKE if wfmt else None, workspace=FAKE,
+                    workspace_bytes=B.elora_workspace_bytes_w(T, K, N, 16, wfmt), pool=pool, **route)
+    p = B.elora_linear_plan(d)
+    assert (p.path, p.tile_cols) == (B.ELORA_PATH_GEMM, tile_cols)
+    B.elora_pool_destroy(pool)
