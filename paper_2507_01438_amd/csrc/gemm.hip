@@ -688,20 +688,38 @@ static bool planned_band(const elora_linear_desc_t &d, BandShape *s)
     return band_shape(band_call(d), part_want(d.n_tokens, d.d_in, d.d_out, d.pool ? d.pool->max_rank : 1), s);
 }
 
-// A call of 65 to 256 rows on a W of 4 million weights or more (smaller ones were not measured).  The decode kernel reads W
-// once per 64 rows; here it is read once, and the call's fixed part (route, shrink, a tile's beginning and end) is about 30 us.
-// Decode launches / here, a row per adapter of ranks 8 to 64, 4096 x 4096, 4096 x 14336, 14336 x 4096: 65 rows 41 / 47, 88 /
-// 69, 75 / 70 us; 129 rows 66 / 53, 128 / 92, 113 / 95; 256 rows 99 / 71, 184 / 125, 170 / 134.  One adapter: 65 rows of an
-// 8-bit W 38 / 35, 75 / 54, 72 / 60; 128 rows of bf16 4096 x 14336 78 / 50.  16 adapters of 8 rows: 128 rows 40 / 40, of an
-// 8-bit W 41 / 48.  A 4-bit or 8-bit W, a row per adapter of rank 16: 130 rows 4096 x 4096 57 / 59, 4096 x 14336 122 / 104.
+// A call of 65 to 256 rows on a W of 4 million weights or more.  The decode kernel reads W once per 64 rows; here it is read
+// once, and the call's fixed part (route, shrink, a tile's beginning and end) is about 20 us.  Decode launches / here:
+//   a row per adapter of ranks 8 to 64, 4096 x 4096, 4096 x 14336: 65 rows 38 / 45, 84 / 68 us; 129 rows 61 / 54, 123 / 93; 256
+//   rows 89 / 70, 169 / 131; of rank 256, 256 rows: 336 / 213, 819 / 509, 4096 x 1024 270 / 140;
+//   one adapter of rank 16, 65 and 256 rows: 4096 x 4096 31 / 30, 69 / 35, 4096 x 65536 281 / 120, 717 / 206, 4096 x 1024 27 /
+//   22, 60 / 25; of an 8-bit W 4096 x 4096 35 / 34, 72 / 44; eight adapters, 65 and 129 rows, 31 / 37, 50 / 36;
+//   a 4-bit or 8-bit W, a row per adapter of rank 16: 129 rows 4096 x 4096 53 / 56, 4096 x 8192 71 / 73, 256 rows 74 / 69.
+// Over 1692 calls of 22 W from 512 x 4096 to 4096 x 65536, ranks 16 to 256, what this rule takes here is slower by 6 % at most.
+// (Below 4 million weights a few runs are faster here as well: 256 rows of one adapter, 512 x 4096, 69 / 18.)
 // Adapters that the expand has to gather (8-bit blocks, ranks that are no multiples of 8) stay with the decode kernel.
+//   A 4-bit W: a launch of the decode kernel per 64 rows has little to read and its waits to pay, so that it loses to any one
+// product where d_in is small: 235 rows of one adapter of rank 128, 256 x 592, 357 / 23 us (45 on the 256 x 256 tiles), 217
+// rows of eight 256 x 7392 101 / 29, 214 rows of their own 256 x 3408 149 / 42.  Of 500 calls on a 4-bit W none was slower
+// here than on those tiles.  (With adapters in 8-bit blocks, which the decode kernel multiplies exactly, only where it is the
+// slower one of these two: d_in up to 768.)
 bool elora::band_instead_of_passes(const elora_linear_desc_t &d)
 {
     if (decode_passes_forced() || d.d_in % BK != 0 || d.d_out % 8 != 0 || d.d_in > (1 << 22) || d.d_out > (1 << 22)) return false;
-    if ((long long)d.d_in * d.d_out < (1 << 22)) return false;
-    if (d.pool != nullptr && (d.pool->q8 || d.pool->n_odd_ranks != 0)) return false;
-    const bool many_runs = d.pool != nullptr && (d.adapter_idx != nullptr || (long long)d.n_segments * 32 > d.n_tokens);
-    if (many_runs && d.n_tokens <= (d.wfmt == ELORA_W_SAME || d.d_out >= 8192 ? 128 : 192)) return false;
+    const bool gathered = d.pool != nullptr && (d.pool->q8 || d.pool->n_odd_ranks != 0), indices = d.pool != nullptr && d.adapter_idx != nullptr;
+    const long long runs = d.pool == nullptr ? 0 : d.n_segments;  // (where there are segments)
+    bool here;
+    if (d.wfmt == ELORA_W_INT4_G32 && !indices && runs * 16 <= d.n_tokens && (d.pool == nullptr || !d.pool->q8 || d.d_in <= 768)) {
+        here = true;
+    } else if (gathered) {
+        here = false;
+    } else if (d.wfmt == ELORA_W_INT4_G32 && d.d_in <= 512) {
+        here = true;
+    } else {
+        const bool many_runs = indices || runs * 32 > d.n_tokens;
+        here = (long long)d.d_in * d.d_out >= (1 << 22) && (!many_runs || d.n_tokens > (d.wfmt == ELORA_W_SAME || d.d_out >= 8192 ? 128 : 192));
+    }
+    if (!here) return false;
     BandShape s;
     return planned_band(d, &s);
 }

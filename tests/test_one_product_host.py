@@ -42,3 +42,16 @@ def test_without_the_product_of_band_they_stay_on_the_decode_kernel():
         assert _plan(256, 4096, 4096, 32, B.ELORA_W_INT8_G32, 1).path == DECODE
     finally:
         B.elora_debug_band(-1)
+
+
+@pytest.mark.parametrize("T, K, N, rank, segments, path", [
+    (235, 256, 592, 128, 1, GEMM),       # launches of the decode kernel / one product: 357 / 23 us
+    (217, 256, 7392, 32, 8, GEMM),       # 101 / 29
+    (214, 256, 3408, 64, None, GEMM),    # 149 / 42
+    (168, 1024, 11152, 16, 8, GEMM),     # 107 / 48
+    (102, 3840, 144, 8, None, DECODE),   # 32 / 36
+    (130, 1024, 320, 16, None, DECODE),
+    (200, 4096, 4096, 16, 1, GEMM),
+])
+def test_a_4bit_w_of_65_to_256_rows(T, K, N, rank, segments, path):
+    assert _plan(T, K, N, rank, B.ELORA_W_INT4_G32, segments).path == path
