@@ -32,30 +32,8 @@ constexpr int kMaxMA = 7;
 constexpr int kMaxSlices = 8;
 constexpr int kLdsBytes = 160 * 1024 - 512;  // (the rest: what the kernel declares by itself)
 
-typedef __attribute__((address_space(3))) void *lptr_t;
-
-// one direct load of the wave: 16 (4) bytes per lane from base + off to lds + 16 (4) * lane.  M0 holds the LDS address and
-// needs a cycle to settle; nothing else of this kernel keeps a value in M0 across statements.
-__device__ __forceinline__ void dma16(uint32_t lds, const void *base, uint32_t off)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
-}
-__device__ __forceinline__ void dma4(uint32_t lds, const void *base, uint32_t off)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
-}
-template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 // everybody's loads up to N younger ones have landed, and everybody's LDS reads are over
 template <int N> __device__ __forceinline__ void wait_and_meet() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory"); }
-
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (I < N) {
-        f(ic<I>{});
-        static_for<I + 1, N>(f);
-    }
-}
 
 // LDS of a workgroup: `kDepth` stages of a K block each; after the K loop the same bytes are four rings, one per wave, of
 // `kSteps` expand steps each.

@@ -52,15 +52,15 @@ struct RowRoute {
 };
 
 // Workspace sections (byte offsets from the 256-byte aligned base).
-// The first three sections belong to the decode kernel, sit at offsets that do not depend on the batch, and
-// are in their idle state between calls (counters zero, mailboxes all-ones); nothing else writes there.
+// The first three sections sit at offsets that do not depend on the batch and are in their idle state between calls: counters
+// zero (the decode kernel's and the GEMM path's), mailboxes, which only the decode kernel writes, all-ones.
 struct WsLayout {
-    size_t sync;       // int [kSyncInts] counters of the decode kernel
+    size_t sync;       // int [kSyncInts] counters
     size_t vmail;      // float [kDecodeMaxTokens][kMaxRank] mailbox for the shrink results of the decode kernel
     size_t mail;       // float mailboxes for the K-slice pieces of the decode kernel (decode_mail_bytes(d_out))
     size_t row_slot;   // int32 [T]
     size_t row_scale;  // float [T]
-    size_t row_rank;   // int32 [T]
+    size_t short_rows; // int32 [T] GEMM path: the rows that sit in short runs of equal adapters
     size_t v;          // float/bf16 shrink results of the generic and gemm kernels
     size_t wdeq;       // bf16 [d_out][d_in]: a call's dequantised copy of a 4-bit or 8-bit W (gemm_wcopy_bytes(); 0 bytes below
     size_t wdeq_bytes; //   the row count from which converting W once pays)
@@ -218,13 +218,8 @@ __device__ __forceinline__ float fp16_to_f32(uint16_t h)
     return (float)v;
 }
 
-template <typename E> __device__ __forceinline__ float load_elem(const E *p, size_t i);
-template <> __device__ __forceinline__ float load_elem<float>(const float *p, size_t i) { return p[i]; }
-template <> __device__ __forceinline__ float load_elem<uint16_t>(const uint16_t *p, size_t i) { return bf16_to_f32(p[i]); }
-
-template <typename E> __device__ __forceinline__ void store_elem(E *p, size_t i, float v);
-template <> __device__ __forceinline__ void store_elem<float>(float *p, size_t i, float v) { p[i] = v; }
-template <> __device__ __forceinline__ void store_elem<uint16_t>(uint16_t *p, size_t i, float v) { p[i] = f32_to_bf16(v); }
+__device__ __forceinline__ float load_elem(const uint16_t *p, size_t i) { return bf16_to_f32(p[i]); }
+__device__ __forceinline__ void store_elem(uint16_t *p, size_t i, float v) { p[i] = f32_to_bf16(v); }
 
 // Which adapter row t uses (Sec. 3.4: every request of the batch names its own adapter), in two steps so
 // that a caller can put other work between the dependent loads.

@@ -75,15 +75,6 @@ __device__ __forceinline__ bool run_is_short(int start, int end, int rank, int N
     return end - start <= kEpiRows && (rank & 7) == 0 && N < (1 << 22) && !q8;
 }
 constexpr int kEpiAhead = 8;  // (run, block, 16 rank entries) steps whose loads are in flight per wave
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (I < N) {
-        f(ic<I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
 
 template <int WFMT>
 __global__ __launch_bounds__(kGemmThreads) void lora_gemm_kernel(GemmArgs ga, PoolView pool, int has_pool)
@@ -230,7 +221,6 @@ __global__ __launch_bounds__(kGemmThreads) void lora_gemm_kernel(GemmArgs ga, Po
     float rs[2][kPieces];     // being parked in LDS during this iteration, set 1 = the block after it (in flight)
     const int prow = tid >> 3, pchunk = tid & 7;  // register path: piece i = row prow + 32 i, chunk pchunk
     typedef const __attribute__((address_space(1))) void *gptr_t;
-    typedef __attribute__((address_space(3))) void *lptr_t;
 
     // issue the loads of K block `blk` into stage `buf`
     auto issue_block = [&](int blk, int buf) {

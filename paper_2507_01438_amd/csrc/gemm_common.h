@@ -17,6 +17,28 @@ typedef float float2_t __attribute__((ext_vector_type(2)));
 
 template <int V> using ic = std::integral_constant<int, V>;
 
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(ic<I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+typedef __attribute__((address_space(3))) void *lptr_t;
+// one direct load of the wave: 16 (4) bytes per lane from base + off to lds + 16 (4) * lane.  M0 holds the LDS address and
+// needs a cycle to settle; nothing else of the kernels that use these keeps a value in M0 across statements.
+__device__ __forceinline__ void dma16(uint32_t lds, const void *base, uint32_t off)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
+}
+__device__ __forceinline__ void dma4(uint32_t lds, const void *base, uint32_t off)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
+}
+template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
 constexpr int kXcds = 8;     // workgroup b runs on XCD b % 8
 constexpr int kRankPad = 64; // rows of V (the shrink results) are padded to this many rank entries, with zeros
 

@@ -20,8 +20,7 @@ __global__ void route_kernel(int T, RouteView route, PoolView pool, int has_pool
 }
 
 // one workgroup per row; wave w reduces rank rows w, w+4, ...
-template <typename E>
-__global__ __launch_bounds__(256) void shrink_generic_kernel(int K, const E *__restrict__ x, PoolView pool,
+__global__ __launch_bounds__(256) void shrink_generic_kernel(int K, const uint16_t *__restrict__ x, PoolView pool,
                                                              const int32_t *__restrict__ row_slot,
                                                              float *__restrict__ V, int R)
 {
@@ -29,9 +28,9 @@ __global__ __launch_bounds__(256) void shrink_generic_kernel(int K, const E *__r
     int slot = row_slot[t];
     if (slot < 0) return;
     int rank = pool.meta[slot].rank;
-    const E *A = reinterpret_cast<const E *>(slot_A(pool, slot));
+    const uint16_t *A = reinterpret_cast<const uint16_t *>(slot_A(pool, slot));
     const uint16_t *As = slot_A_scales(pool, slot);  // (adapters kept in 8-bit blocks: value = block scale * code)
-    const E *xt = x + (size_t)t * K;
+    const uint16_t *xt = x + (size_t)t * K;
     int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int j = wave; j < rank; j += 4) {
         float s = 0.0f;
@@ -44,11 +43,11 @@ __global__ __launch_bounds__(256) void shrink_generic_kernel(int K, const E *__r
     }
 }
 
-template <int WFMT, typename E>
+template <int WFMT>
 __device__ __forceinline__ float weight_elem(const void *W, const uint16_t *w_scales, int K, int n, int k)
 {
     if (WFMT == ELORA_W_SAME) {
-        return load_elem(static_cast<const E *>(W), (size_t)n * K + k);
+        return load_elem(static_cast<const uint16_t *>(W), (size_t)n * K + k);
     } else if (WFMT == ELORA_W_INT8_G32) {
         return fp16_to_f32(w_scales[(size_t)n * (K >> 5) + (k >> 5)]) * (float)static_cast<const int8_t *>(W)[(size_t)n * K + k];
     } else {
@@ -59,13 +58,13 @@ __device__ __forceinline__ float weight_elem(const void *W, const uint16_t *w_sc
 }
 
 // 64 x 64 output tile per workgroup, 4 x 4 outputs per thread, K in steps of 16 through LDS.
-template <int WFMT, typename E>
-__global__ __launch_bounds__(256) void base_generic_kernel(int T, int K, int N, const E *__restrict__ x,
+template <int WFMT>
+__global__ __launch_bounds__(256) void base_generic_kernel(int T, int K, int N, const uint16_t *__restrict__ x,
                                                            const void *__restrict__ W,
                                                            const uint16_t *__restrict__ w_scales, PoolView pool,
                                                            const int32_t *__restrict__ row_slot,
                                                            const float *__restrict__ row_scale,
-                                                           const float *__restrict__ V, int R, E *__restrict__ y)
+                                                           const float *__restrict__ V, int R, uint16_t *__restrict__ y)
 {
     constexpr int BM = 64, BN = 64, BK = 16;
     __shared__ float xs[BK][BM + 4];
@@ -81,7 +80,7 @@ __global__ __launch_bounds__(256) void base_generic_kernel(int T, int K, int N, 
             int k = k0 + lk + i;
             int t = t0 + lr, n = n0 + lr;
             xs[lk + i][lr] = (t < T && k < K) ? load_elem(x, (size_t)t * K + k) : 0.0f;
-            ws[lk + i][lr] = (n < N && k < K) ? weight_elem<WFMT, E>(W, w_scales, K, n, k) : 0.0f;
+            ws[lk + i][lr] = (n < N && k < K) ? weight_elem<WFMT>(W, w_scales, K, n, k) : 0.0f;
         }
         __syncthreads();
 #pragma unroll
@@ -105,12 +104,12 @@ __global__ __launch_bounds__(256) void base_generic_kernel(int T, int K, int N, 
         if (t >= T) continue;
         int slot = row_slot[t];
         int rank = 0;
-        const E *B = nullptr;
+        const uint16_t *B = nullptr;
         const uint16_t *Bs = nullptr;
         float scale = 0.0f;
         if (slot >= 0) {
             rank = pool.meta[slot].rank;
-            B = reinterpret_cast<const E *>(slot_B(pool, slot));
+            B = reinterpret_cast<const uint16_t *>(slot_B(pool, slot));
             Bs = slot_B_scales(pool, slot);
             scale = row_scale[t];
         }
@@ -128,7 +127,7 @@ __global__ __launch_bounds__(256) void base_generic_kernel(int T, int K, int N, 
     }
 }
 
-template <int WFMT, typename E>
+template <int WFMT>
 int launch_typed(const LinearArgs &a, hipStream_t stream)
 {
     int32_t *row_slot = reinterpret_cast<int32_t *>(a.ws + a.wsl.row_slot);
@@ -139,15 +138,15 @@ int launch_typed(const LinearArgs &a, hipStream_t stream)
                        a.has_pool ? 1 : 0, row_slot, row_scale);
     ELORA_HIP_TRY(hipGetLastError());
     if (a.has_pool) {
-        hipLaunchKernelGGL((shrink_generic_kernel<E>), dim3(a.T), dim3(256), 0, stream, a.K,
-                           static_cast<const E *>(a.x), a.pool, row_slot, V, R);
+        hipLaunchKernelGGL(shrink_generic_kernel, dim3(a.T), dim3(256), 0, stream, a.K,
+                           static_cast<const uint16_t *>(a.x), a.pool, row_slot, V, R);
         ELORA_HIP_TRY(hipGetLastError());
     }
     dim3 grid((a.N + 63) / 64, (a.T + 63) / 64);
     profile_mark_begin(stream);
-    hipLaunchKernelGGL((base_generic_kernel<WFMT, E>), grid, dim3(256), 0, stream, a.T, a.K, a.N,
-                       static_cast<const E *>(a.x), a.W, static_cast<const uint16_t *>(a.w_scales), a.pool, row_slot,
-                       row_scale, V, R, static_cast<E *>(a.y));
+    hipLaunchKernelGGL((base_generic_kernel<WFMT>), grid, dim3(256), 0, stream, a.T, a.K, a.N,
+                       static_cast<const uint16_t *>(a.x), a.W, static_cast<const uint16_t *>(a.w_scales), a.pool, row_slot,
+                       row_scale, V, R, static_cast<uint16_t *>(a.y));
     ELORA_HIP_TRY(hipGetLastError());
     profile_mark_end(stream);
     return ELORA_OK;
@@ -158,7 +157,7 @@ int launch_typed(const LinearArgs &a, hipStream_t stream)
 int elora::launch_generic(const LinearArgs &a, hipStream_t stream)
 {
     if (a.dtype == ELORA_F32) return launch_fp32(a, stream);
-    if (a.wfmt == ELORA_W_SAME) return launch_typed<ELORA_W_SAME, uint16_t>(a, stream);
-    if (a.wfmt == ELORA_W_INT8_G32) return launch_typed<ELORA_W_INT8_G32, uint16_t>(a, stream);
-    return launch_typed<ELORA_W_INT4_G32, uint16_t>(a, stream);
+    if (a.wfmt == ELORA_W_SAME) return launch_typed<ELORA_W_SAME>(a, stream);
+    if (a.wfmt == ELORA_W_INT8_G32) return launch_typed<ELORA_W_INT8_G32>(a, stream);
+    return launch_typed<ELORA_W_INT4_G32>(a, stream);
 }

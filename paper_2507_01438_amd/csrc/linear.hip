@@ -69,7 +69,7 @@ WsLayout elora::ws_layout(int T, int K, int N, int R, int wfmt, int dtype)
     off += align_up(t * sizeof(int32_t));
     l.row_scale = off;
     off += align_up(t * sizeof(float));
-    l.row_rank = off;
+    l.short_rows = off;
     off += align_up(t * sizeof(int32_t));
     l.v = off;
     size_t v_full = t * (size_t)R * sizeof(float);

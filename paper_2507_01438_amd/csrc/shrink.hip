@@ -151,19 +151,6 @@ struct Ring {
     static constexpr int kRed = kWaves * kShrinkRows * (NCB * 16 + 4) * 4;  // the waves' sums of a run, in the same place
     static constexpr int kBytes = kWaves * kDepth * kStage > kRed ? kWaves * kDepth * kStage : kRed;
 };
-typedef __attribute__((address_space(3))) void *lptr_t;
-// one direct load of the wave: 16 (4) bytes per lane from base + off to lds + 16 (4) * lane.  M0 holds the LDS address and
-// needs a cycle to settle; nothing else of this kernel keeps a value in M0 across statements.
-__device__ __forceinline__ void dma16(uint32_t lds, const void *base, uint32_t off)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
-}
-__device__ __forceinline__ void dma4(uint32_t lds, const void *base, uint32_t off)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
-}
-template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
 // The runs of equal slots among 32 rows (lane l and l + 32: row l's slot): a mask of the rows a run starts at.
 __device__ __forceinline__ uint32_t run_starts(int slot, int lane)
 {
@@ -495,7 +482,7 @@ void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n, const bool *w
         q.pool = a[p].pool;
         q.row_slot = reinterpret_cast<int32_t *>(a[p].ws + a[p].wsl.row_slot);
         q.row_scale = reinterpret_cast<float *>(a[p].ws + a[p].wsl.row_scale);
-        q.short_rows = reinterpret_cast<int32_t *>(a[p].ws + a[p].wsl.row_rank);
+        q.short_rows = reinterpret_cast<int32_t *>(a[p].ws + a[p].wsl.short_rows);
         q.V = reinterpret_cast<uint16_t *>(a[p].ws + a[p].wsl.v);
         q.V_rest = whole[p] ? reinterpret_cast<uint16_t *>(a[p].ws + a[p].wsl.v_rest) : nullptr;
         q.part = reinterpret_cast<float *>(a[p].ws + a[p].wsl.part);
