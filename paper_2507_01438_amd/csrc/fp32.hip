@@ -4,8 +4,8 @@
 // Calls of this path are small (a model kept in fp32 to check an adapter), so what bounds them is latency: few launches, every
 // load of a wave under way at once, and K split over the waves of a workgroup so that a call of a few rows still has a
 // wave on most compute units.  Products and sums are fp32 throughout, on the fp32 matrix instructions.  Calls with rank-16
-// adapters, three launches of plain FMAs through 64 x 64 tiles / here: 8 rows 512 x 512 67 / 9.3 us, 155 rows 1000 x 1430
-// 162 / 21, 272 rows 2048 x 3000 322 / 91, 2000 rows 2048 x 2048 629 / 352, 4096 rows 4096 x 4096 4182 / 2376 (there the
+// adapters, three launches of plain FMAs through 64 x 64 tiles / here: 8 rows 512 x 512 67 / 9.5 us, 155 rows 1000 x 1430
+// 162 / 21, 272 rows 2048 x 3000 317 / 81, 2000 rows 2048 x 2048 615 / 294, 4096 rows 4096 x 4096 4182 / 2198 (there the
 // loads of a 32 x 32 tile bound it: 8 products per byte); error against 64-bit sums 4 to 11 e-7 / 1.5 to 4 e-7.
 #include <algorithm>
 

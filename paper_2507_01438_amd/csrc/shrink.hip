@@ -1,9 +1,10 @@
 // Route and shrink of the GEMM path.
 //   route   per row: validated pool slot and scale (Sec. 3.4: each request names its adapter), and the list of the rows
 //           that sit in short runs of equal adapters
-//   shrink  V[t, :] = bf16(s_t * A_i x_t) for every row (or A_i x_t whole, as the sum of three bf16), with the rows grouped by adapter inside each 32-row tile
-//           ("u-batches", Sec. 3.4 / 4.3: rows that share an adapter are computed together): one masked MFMA pass per
-//           run of equal adapters; the rows of runs shorter than 8 are computed one by one with plain FMAs
+//   shrink  V[t, :] = bf16(s_t * A_i x_t) for every row (or A_i x_t whole, as the sum of three bf16), with the rows grouped
+//           by adapter inside each 32-row tile ("u-batches", Sec. 3.4 / 4.3: rows that share an adapter are computed
+//           together): one masked MFMA pass per run of equal adapters; the rows of runs shorter than 8 are computed one
+//           by one with plain FMAs, in the same launch or, where there may be many of them, in one of their own
 #include "gemm_common.h"
 
 #include <algorithm>
