@@ -270,13 +270,7 @@ __global__ __launch_bounds__(kGemmThreads) void lora_gemm_kernel(GemmArgs ga, Po
 #pragma unroll
         for (int i = 0; i < kPieces; ++i) {
             if (i < i0 || i >= i1) continue;
-            const float sc = rs[set][i], c8 = -8.0f * sc;
-            const uint32_t lo = rq[set][i] & 0x0f0f0f0fu, hi = (rq[set][i] >> 4) & 0x0f0f0f0fu;
-            u32x4 out;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                out[q] = pack_bf16x2(fmaf((float)((lo >> (8 * q)) & 0xffu), sc, c8), fmaf((float)((hi >> (8 * q)) & 0xffu), sc, c8));
-            *reinterpret_cast<u32x4 *>(sb + lds_pos(prow + 32 * i, pchunk)) = out;
+            *reinterpret_cast<u32x4 *>(sb + lds_pos(prow + 32 * i, pchunk)) = w4_to_bf16x8(rq[set][i], rs[set][i]);
         }
     };
     // make stage `buf` hold K block `blk` (everything that is not a direct load happens here)
