@@ -126,3 +126,44 @@ def test_an_infinite_entry_of_an_adapter_gives_an_infinity_of_its_sign(lengths, 
     # (one rounding of y, 2^-9; fp32 sums of cancelling products: 2^-20 of the largest)
     assert (np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + 2.0 ** -18 * np.abs(want).max()).all()
     pool.close()
+
+
+@pytest.mark.parametrize("T, K, N, ranks, lengths, q8", [
+    (235, 256, 592, (128, 8), [235], False),
+    (217, 256, 1040, (5, 16, 30), [100, 0, 1, 116], False),      # ranks that are no multiples of 8: gathered
+    (130, 768, 272, (8, 24, 64), [64, 66], True),                # adapters in 8-bit blocks
+    (65, 256, 16, (16,), [30, 35], True),
+    (214, 512, 336, (64, 8, 32), None, False),                   # a row per adapter
+    (256, 256, 48, (16, 8), None, False),
+])
+def test_4bit_w_with_a_short_d_in(T, K, N, ranks, lengths, q8):
+    """Against the oracle and against the generic kernels, with scales given too; and by the decode kernel, which the same call
+    takes when it is asked to."""
+    from gpu_harness import DeviceCase, assert_close, rel_err
+    w = I.small_workload(5600 + T, I.BF16, K, N, T, 6, ranks, segments=lengths, wfmt=I.W_INT4_G32, no_adapter_rows=() if lengths else (0, T - 1))
+    case = DeviceCase(w, w.projections[0], q8=q8)
+    y = case.run()
+    assert (case.last_plan.path, case.last_plan.tile_cols) == (GEMM, 128)
+    ref = case.reference()
+    assert_close(y, ref, case.base_reference(), f"{T} rows")
+    assert np.array_equal(y, case.run())
+    assert rel_err(y, case.run(force_path=0)) <= 1e-2 and case.last_plan.path == 0
+    B.elora_debug_decode_passes(1)
+    try:
+        d = case.run()
+    finally:
+        B.elora_debug_decode_passes(-1)
+    if not q8 or max(ranks) <= 64:
+        assert case.last_plan.path == 1
+    assert rel_err(y, d) <= 1e-2
+    n = T if lengths is None else len(lengths)
+    over = np.linspace(0.25, 3.0, n).astype(np.float32)
+    y = case.run(scales=torch.from_numpy(over).to(DEV))
+    ref, base = case.reference(row_scale=over if lengths is None else np.repeat(over, lengths)), case.base_reference()
+    assert rel_err(y, ref) <= 1e-2
+    # (the adapter term alone: the rounding of y, 2^-9 of it, and that of the weights, as much again at most, are 2^-8 of the
+    # largest y; where a scale makes the term small that is more than the 4 % of it which assert_close allows)
+    lora = np.abs(ref - base).max()
+    assert np.abs(y - ref).max() <= max(4e-2 * lora, 2.0 ** -8 * np.abs(ref).max())
+    assert case.pool.poll_error() == (0, -1)
+    case.close()
