@@ -1,4 +1,4 @@
-// The fp32 path (any shape, any rank): two launches.
+// The fp32 path (any shape, any rank): two launches, or one for the smallest calls (fp32_one_kernel).
 //   route + shrink   per row: pool slot and scale (Sec. 3.4: each request names its adapter), v_t = A_i x_t
 //   product          y_t = W x_t + s * B_i v_t, written at row t (Sec. 3.4 closing equation)
 // Calls of this path are small (a model kept in fp32 to check an adapter), so what bounds them is latency: few launches, every
@@ -218,6 +218,188 @@ __global__ __launch_bounds__(kThreads, kAhead == 1 ? 8 : 1) void fp32_product_ke
     }
 }
 
+// ---- one launch: the product of a small call with the shrink in it -----------------------------------------------------------
+// What bounds a small call is launches and trips to memory, so here every workgroup (16 rows x 16 columns, four waves that
+// split K) forms the shrink results of its own rows: the ranks of their different adapters, one behind the other, are
+// further columns of the product, 32 beside the tile's own 16, and what there is beyond 32 in further walks over K.  Every
+// wave resolves the rows' routes by itself while its first loads of x and W are under way, and a thread's row of B_i is
+// on its way during the walk.  Two launches / one, rank-8 calls: 8 rows 512 x 512 7.8 / 7.0 us, 3 rows 64 x 64 7.4 / 4.8, 16
+// rows 300 x 2000 7.5 / 6.0, 33 rows 100 x 1000 7.5 / 4.9; see one_launch for where it ends.
+constexpr int kOneTile = 16, kOneRanks = 32, kOneWaves = 4;
+__global__ __launch_bounds__(64 * kOneWaves) void fp32_one_kernel(int T, int K, int N, const float *__restrict__ x, const float *__restrict__ W, PoolView pool, RouteView route,
+                                                                  float *__restrict__ y)
+{
+    constexpr int kBlocks = kOneRanks / 16, kAhead = 2, kPitch = kOneTile + kOneRanks + 4, kEarly = 4;
+    static_assert(kOneTile == 16 && kOneTile * kOneTile == 64 * kOneWaves, "an output per thread");
+    __shared__ __attribute__((aligned(16))) float s_sum[kOneWaves][kOneTile][kPitch];
+    __shared__ float s_v[kOneTile][kOneRanks];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
+    const int tiles_n = (N + kOneTile - 1) / kOneTile;
+    const int t0 = (int)blockIdx.x / tiles_n * kOneTile, n0 = (int)blockIdx.x % tiles_n * kOneTile;
+    // rows past the end of x and W repeat the last one; what they give is never stored
+    const int mine = min(t0 + m, T - 1);  // (the lane's row of x, and the row whose route it resolves)
+    const RouteIndex ri = route_index(mine, route);
+    SlotMeta meta{0, 0.0f, 0, 0};
+    if (ri.idx >= 0 && ri.idx < pool.capacity) meta = pool.meta[ri.idx];
+    const float given = route.scales != nullptr && ri.idx != -1 ? route.scales[ri.scale_at] : 0.0f;
+    const float *const xr = x + (size_t)mine * K + g * 4, *const wr = W + (size_t)min(n0 + m, N - 1) * K + g * 4;
+    const int whole = K / 16;  // turns that need no test
+    const int n_mine = wave < whole ? (whole - wave + kOneWaves - 1) / kOneWaves : 0;
+    auto at = [&](int turn) { return (size_t)(wave + min(turn, n_mine - 1) * kOneWaves) * 16; };
+    floatx4 xv[2][kAhead], wv[2][kAhead], av[2][kAhead][kBlocks];
+    auto fetch_x = [&](int to, int first) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) xv[to][i] = load4(xr + at(first + i));
+    };
+    auto fetch_w = [&](int to, int first) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) wv[to][i] = load4(wr + at(first + i));
+    };
+    if (n_mine > 0) {
+        fetch_x(0, 0);
+        fetch_w(0, 0);
+    }
+    // (a bad index is counted once per row)
+    const RowRoute r = route_finish(mine, ri, meta, given, route, pool, n0 == 0 && tid < kOneTile && t0 + tid < T);
+    // the different adapters of the rows: `total` ranks one behind the other, the lane's own from `off` on
+    const uint64_t served = __ballot(r.slot >= 0 && lane < kOneTile);
+    int total = 0, off = 0;
+    for (uint64_t left = served; left != 0;) {
+        const int i = (int)__builtin_ctzll(left), slot = __builtin_amdgcn_readlane(r.slot, i);
+        if (r.slot == slot) off = total;
+        left &= ~__ballot(r.slot == slot);
+        total += __builtin_amdgcn_readlane(r.rank, i);
+    }
+    // the thread's output: row rl, column n, and the first entries of its row of B_i
+    const int rl = tid / kOneTile, n = n0 + tid % kOneTile;
+    const int my_off = __shfl(off, rl), my_rank = __shfl(r.rank, rl), my_slot = __shfl(r.slot, rl);
+    const float my_scale = __shfl(r.scale, rl);
+    const float *const Bn = reinterpret_cast<const float *>(slot_B(pool, max(my_slot, 0))) + (size_t)min(n, N - 1) * my_rank;
+    floatx4 early[kEarly];
+#pragma unroll
+    for (int q = 0; q < kEarly; ++q) {
+        early[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (my_slot >= 0 && 4 * q + 4 <= my_rank) early[q] = load4(Bn + 4 * q);
+    }
+    floatx4 acc{0.f, 0.f, 0.f, 0.f};
+    float sum = 0.0f, d = 0.0f;
+    // One walk over K: `blocks` 16 ranks from first_rank on, and in the first walk the tile's own columns.
+    auto walk = [&](auto with_w_c, auto blocks_c, int first_rank) __attribute__((always_inline)) {
+        constexpr bool with_w = decltype(with_w_c)::value;
+        constexpr int blocks = decltype(blocks_c)::value;
+        const float *ar[kBlocks];
+        floatx4 accv[kBlocks];
+#pragma unroll
+        for (int p = 0; p < blocks; ++p) {
+            const int c = min(first_rank + p * 16 + m, total - 1);  // (those past the last repeat it, and nobody takes them)
+            int slot = 0, j = 0;
+            for (uint64_t left = served; left != 0;) {
+                const int i = (int)__builtin_ctzll(left), s = __builtin_amdgcn_readlane(r.slot, i), begin = __builtin_amdgcn_readlane(off, i);
+                if (c >= begin) {
+                    slot = s;
+                    j = c - begin;
+                }
+                left &= ~__ballot(r.slot == s);
+            }
+            ar[p] = reinterpret_cast<const float *>(slot_A(pool, slot)) + (size_t)j * K + g * 4;
+            accv[p] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+        auto fetch_a = [&](int to, int first) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+                for (int p = 0; p < blocks; ++p) av[to][i][p] = load4(ar[p] + at(first + i));
+        };
+        auto fetch = [&](int to, int first) __attribute__((always_inline)) {
+            fetch_x(to, first);
+            if constexpr (with_w) fetch_w(to, first);
+            fetch_a(to, first);
+        };
+        auto multiply = [&](const floatx4 &x4, const floatx4 &w4, const floatx4 *a4) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (with_w) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[i], x4[i], acc, 0, 0, 0);
+#pragma unroll
+                for (int p = 0; p < blocks; ++p) accv[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[p][i], x4[i], accv[p], 0, 0, 0);
+            }
+        };
+        auto use = [&](int from, int first) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+                if (first + i < n_mine) multiply(xv[from][i], wv[from][i], av[from][i]);
+        };
+        if (n_mine > 0) {
+            if constexpr (with_w) fetch_a(0, 0);  // (the first loads of x and W are under way)
+            else fetch(0, 0);
+            for (int i = 0; i < n_mine; i += 2 * kAhead) {
+                if (i + kAhead < n_mine) fetch(1, i + kAhead);
+                use(0, i);
+                if (i + 2 * kAhead < n_mine) fetch(0, i + 2 * kAhead);
+                if (i + kAhead < n_mine) use(1, i + kAhead);
+            }
+        }
+        if (whole * 16 < K && wave == whole % kOneWaves) {  // the turn that K ends in
+            floatx4 wt{0.f, 0.f, 0.f, 0.f}, at_[kBlocks];
+            const floatx4 xt = load4_until(xr, whole * 16, K - g * 4);
+            if constexpr (with_w) wt = load4_until(wr, whole * 16, K - g * 4);
+#pragma unroll
+            for (int p = 0; p < blocks; ++p) at_[p] = load4_until(ar[p], whole * 16, K - g * 4);
+            multiply(xt, wt, at_);
+        }
+        // the waves' sums meet in LDS and are added in wave order; a lane holds columns 4 g .. + 3 of row m
+        if constexpr (with_w) *reinterpret_cast<floatx4 *>(&s_sum[wave][m][g * 4]) = acc;
+#pragma unroll
+        for (int p = 0; p < blocks; ++p) *reinterpret_cast<floatx4 *>(&s_sum[wave][m][kOneTile + p * 16 + g * 4]) = accv[p];
+        __syncthreads();
+        auto sum_of = [&](int row, int c) __attribute__((always_inline)) {
+            float s = s_sum[0][row][c];
+#pragma unroll
+            for (int w = 1; w < kOneWaves; ++w) s += s_sum[w][row][c];
+            return s;
+        };
+        if constexpr (with_w) sum = sum_of(rl, tid % kOneTile);
+        if constexpr (blocks > 0) {
+            for (int e = tid; e < kOneTile * 16 * blocks; e += 64 * kOneWaves) s_v[e / (16 * blocks)][e % (16 * blocks)] = sum_of(e / (16 * blocks), kOneTile + e % (16 * blocks));
+            __syncthreads();
+            // what these ranks give of the thread's B_i v
+            if (my_slot >= 0) {
+                const int end = min(my_rank, first_rank + kOneRanks - my_off);
+                int j = max(first_rank - my_off, 0);
+                const float *const v = &s_v[rl][0] + my_off - first_rank;
+                if (j == 0) {
+#pragma unroll
+                    for (int q = 0; q < kEarly; ++q)
+                        if (4 * q + 4 <= end) {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) d = fmaf(v[4 * q + i], early[q][i], d);
+                            j = 4 * q + 4;
+                        }
+                }
+                for (; j < end; ++j) d = fmaf(v[j], Bn[j], d);
+            }
+        }
+    };
+    if (total == 0) walk(std::true_type{}, std::integral_constant<int, 0>{}, 0);
+    else if (total <= 16) walk(std::true_type{}, std::integral_constant<int, 1>{}, 0);
+    else walk(std::true_type{}, std::integral_constant<int, 2>{}, 0);
+    for (int first_rank = kOneRanks; first_rank < total; first_rank += kOneRanks) {
+        __syncthreads();  // (what the walk before left has been read)
+        walk(std::false_type{}, std::integral_constant<int, 2>{}, first_rank);
+    }
+    if (t0 + rl < T && n < N) y[(size_t)(t0 + rl) * N + n] = my_slot >= 0 ? sum + my_scale * d : sum;
+}
+
+// Where the call's rows meet at most 32 ranks whichever adapters they name, so that one walk over K is enough (with a second
+// one 8 rows 256 x 512 take 8.3 us, on two launches 7.4), K is short (16 rows of rank 8: 700 x 700 two launches 8.1 us / one
+// 7.7, 1000 x 1000 9.1 / 10.4: the ranks are read by every workgroup) and two workgroups per compute unit are all there are.
+// Adapters loaded later, under a captured graph, only add walks.
+long long one_tiles(int T, int N) { return (((long long)T + kOneTile - 1) / kOneTile) * (((long long)N + kOneTile - 1) / kOneTile); }
+// (n_segments: how many different adapters the routing tables can name)
+bool one_launch(int T, int K, int N, int n_loaded, int max_rank, int n_segments)
+{
+    return (long long)std::min({kOneTile, T, n_loaded, n_segments}) * max_rank <= kOneRanks && K <= 700 && one_tiles(T, N) <= 512;
+}
+
 // A launch holds fewer than 2^32 threads: rows of the shrink, and tiles of the product, beyond that many workgroups go into
 // further launches.
 constexpr size_t kMaxGroups = ((size_t)1 << 32) / kThreads - 1;
@@ -243,6 +425,11 @@ void elora::fp32_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
 {
     const int T = std::max(d.n_tokens, 1);
     const size_t tiles = choose_tiles(T, d.d_out).n;
+    if (d.pool && one_launch(T, d.d_in, d.d_out, d.pool->n_loaded, d.pool->max_rank, d.adapter_idx ? T : d.n_segments)) {
+        plan->n_launches = 1;
+        plan->grid = (int)one_tiles(T, d.d_out);
+        return;
+    }
     plan->n_launches = (int)(launches_of(tiles) + (d.pool ? launches_of((size_t)T) : 0));
     plan->grid = (int)std::min(tiles, kMaxGroups);
 }
@@ -253,6 +440,13 @@ int elora::launch_fp32(const LinearArgs &a, hipStream_t stream)
     float *const row_scale = reinterpret_cast<float *>(a.ws + a.wsl.row_scale), *const V = reinterpret_cast<float *>(a.ws + a.wsl.v);
     const float *const x = static_cast<const float *>(a.x), *const W = static_cast<const float *>(a.W);
     const int R = a.pool.max_rank;
+    if (a.has_pool && one_launch(a.T, a.K, a.N, a.n_loaded, R, a.route.adapter_idx ? a.T : a.route.n_segments)) {
+        profile_mark_begin(stream);
+        hipLaunchKernelGGL(fp32_one_kernel, dim3((unsigned)one_tiles(a.T, a.N)), dim3(64 * kOneWaves), 0, stream, a.T, a.K, a.N, x, W, a.pool, a.route, static_cast<float *>(a.y));
+        ELORA_HIP_TRY(hipGetLastError());
+        profile_mark_end(stream);
+        return ELORA_OK;
+    }
     for (size_t t = 0; a.has_pool && t < (size_t)a.T; t += kMaxGroups) {
         // (a wave per two rank entries, none that has nothing to do)
         hipLaunchKernelGGL(fp32_shrink_kernel, dim3((unsigned)std::min((size_t)a.T - t, kMaxGroups), (R + kPiece - 1) / kPiece), dim3(64 * std::min((R + 1) / 2, kWaves)), 0, stream, a.K, x, a.route,

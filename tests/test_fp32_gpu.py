@@ -85,3 +85,55 @@ def test_fp32_launches_of_more_workgroups_than_fit_at_once(shape):
     assert np.array_equal(y, case.run())
     assert case.pool.poll_error() == (0, -1)
     case.close()
+
+
+@pytest.mark.parametrize("segments", [False, True])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1, (1,)), (15, 17, 2, 2, (3, 16)), (16, 16, 16, 2, (16,)), (63, 33, 17, 2, (16, 1)), (130, 40, 33, 4, (8, 5)), (512, 512, 8, 4, (8,)), (700, 35, 100, 1, (32,))])
+def test_fp32_in_one_launch(shape, segments):
+    """Calls whose rows meet at most 32 ranks: tiles of 16 rows and columns with and without a remainder, K below, at and
+    behind a turn of 16 and a round of four waves, one and two blocks of ranks, rows without adapter and with a bad index."""
+    K, N, T, pool, ranks = shape
+    lengths = [T - T // 2, 0, T // 2] if segments else None
+    w = I.small_workload(4300 + K, I.F32, K, N, T, pool, ranks, segments=lengths, no_adapter_rows=(1,) if T > 1 else ())
+    case = DeviceCase(w, w.projections[0])
+    y = case.run()
+    assert case.last_plan.n_launches == 1
+    assert rel_err(y, case.reference()) <= 1e-5
+    assert np.array_equal(y, case.run())
+    assert case.pool.poll_error() == (0, -1)
+    if not segments and T > 2:
+        case.adapter_idx[2] = pool + 3
+        bad = case.run()
+        ref = case.reference()
+        ref[2] = case.base_reference()[2]
+        assert rel_err(bad, ref) <= 1e-5
+        assert case.pool.poll_error() == (1, 2)
+    case.close()
+
+
+def test_fp32_one_launch_captured_before_more_adapters_are_loaded():
+    """A graph keeps its kernel: with ten more adapters in the pool its rows meet 11 of ranks 3 to 9, several walks over K."""
+    import torch
+
+    K, N, T, pool = 200, 50, 21, 12
+    w = I.small_workload(4400, I.F32, K, N, T, pool, (9, 3, 8), no_adapter_rows=(4,))
+    case = DeviceCase(w, w.projections[0], load_slots=[0])
+    assert case.B.elora_linear_plan(case.desc()).n_launches == 1
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            case.B.elora_batched_lora_linear(case.desc(), stream)
+    for i in range(1, pool):
+        A, Bm, s = w.adapter(w.projections[0], i)
+        case.adapters[i] = (A, Bm, s)
+        case.pool.load(i, torch.from_numpy(A), torch.from_numpy(Bm), s)
+    torch.cuda.synchronize()
+    ref = case.reference()
+    for _ in range(3):
+        case.y.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert rel_err(case.y.cpu().numpy().astype(np.float64), ref) <= 1e-5
+    assert case.pool.poll_error() == (0, -1)
+    case.close()
