@@ -4,8 +4,8 @@
 // Calls of this path are small (a model kept in fp32 to check an adapter), so what bounds them is latency: few launches, every
 // load of a wave under way at once, and K split over the waves of a workgroup so that a call of a few rows still has a
 // wave on most compute units.  Products and sums are fp32 throughout, on the fp32 matrix instructions.  Calls with rank-16
-// adapters, three launches of plain FMAs through 64 x 64 tiles / here: 8 rows 512 x 512 67 / 9.5 us, 155 rows 1000 x 1430
-// 162 / 21, 272 rows 2048 x 3000 317 / 81, 2000 rows 2048 x 2048 615 / 294, 4096 rows 4096 x 4096 4182 / 2198 (there the
+// adapters, three launches of plain FMAs through 64 x 64 tiles / here: 8 rows 512 x 512 67 / 7.8 us, 155 rows 1000 x 1430
+// 162 / 17, 272 rows 2048 x 3000 317 / 81, 2000 rows 2048 x 2048 615 / 294, 4096 rows 4096 x 4096 4182 / 2198 (there the
 // loads of a 32 x 32 tile bound it: 8 products per byte); error against 64-bit sums 4 to 11 e-7 / 1.5 to 4 e-7.
 #include <algorithm>
 
@@ -100,10 +100,11 @@ __global__ __launch_bounds__(kThreads) void fp32_shrink_kernel(int K, const floa
 // A lane takes four consecutive elements of row lane % 16 (elements 4 (lane / 16) .. + 3 of the turn's 16), straight from memory:
 // the four matrix instructions of a turn multiply element i of every lane, in which order K is walked does not matter.
 // The eight waves' sums meet in LDS and are added in wave order.
-// A launch with at most two workgroups per compute unit has four turns' loads of a wave under way; with more of them it is the
-// other workgroups that hide a load, and with one turn ahead four of them fit (the 32 x 32 tile with four ahead: 157 registers,
-// one workgroup): rank-8 calls, four ahead / one, 272 rows 1000 x 3000 50 / 42 us, 2000 rows 128 x 10000 440 / 144, 2048 x 10000
-// 1556 / 1336; 256 rows 2048 x 2048 45 / 40.
+// One turn's loads of a wave are under way beside those that are multiplied, and it is the eight waves and the other workgroups
+// of a compute unit that hide them: with one turn ahead four workgroups fit (the 32 x 32 tile with four ahead: 157 registers,
+// one).  Rank-8 calls, four ahead / one, 272 rows 1000 x 3000 50 / 42 us, 2000 rows 128 x 10000 440 / 144, 2048 x 10000
+// 1556 / 1336; 16 rows 2048 x 3000 13.8 / 13.2.  A launch of one 32 x 16 tile per compute unit has two turns ahead (60 rows
+// 2048 x 2048 18.2 us, four 19.1).
 template <int MB, int NB, int kAhead>
 __global__ __launch_bounds__(kThreads, kAhead == 1 ? 8 : 1) void fp32_product_kernel(int T, int K, int N, const float *__restrict__ x, const float *__restrict__ W, PoolView pool, int has_pool,
                                                                 const int32_t *__restrict__ row_slot, const float *__restrict__ row_scale,
@@ -405,17 +406,19 @@ bool one_launch(int T, int K, int N, int n_loaded, int max_rank, int n_segments)
 constexpr size_t kMaxGroups = ((size_t)1 << 32) / kThreads - 1;
 size_t launches_of(size_t workgroups) { return (workgroups + kMaxGroups - 1) / kMaxGroups; }
 
-// The largest tile that still gives every compute unit a workgroup: a turn of 32 x 32 outputs loads half as much per product
-// as one of 32 x 16.
+// 16 x 16 outputs where two such tiles per compute unit are all there are (and for up to 16 rows), else 32 x 32, which loads half
+// as much per product, unless 32 x 16 come out as one round of workgroups.  Two launches, 16 x 16 / 32 x 16 / 32 x 32: 60 rows
+// 700 x 700 (176 tiles of 16) 8.7 / 10.5 / 12.2 us, 270 rows 300 x 400 (425) 8.1 / 8.4 / 9.8, 60 rows 2048 x 2048 (512; 256 of
+// 32 x 16) 21.3 / 18.2 / 22.6, 155 rows 1000 x 1430 (900; 450) 19.8 / 19.3 / 17.0, 1430 x 1000 (630; 315) 22.0 / 24.3 / 18.2.
 struct Tiles {
     int mb, nb;
     size_t n;
 };
 Tiles choose_tiles(int T, int N)
 {
-    const size_t m32 = ((size_t)T + 31) / 32, n16 = ((size_t)N + 15) / 16, n32 = ((size_t)N + 31) / 32;
-    if (T <= 16) return {1, 1, n16};
-    if (m32 * n32 < 256) return {2, 1, m32 * n16};
+    const size_t m16 = ((size_t)T + 15) / 16, m32 = ((size_t)T + 31) / 32, n16 = ((size_t)N + 15) / 16, n32 = ((size_t)N + 31) / 32;
+    if (T <= 16 || m16 * n16 < 512) return {1, 1, m16 * n16};
+    if (m32 * n16 <= 256) return {2, 1, m32 * n16};
     return {2, 2, m32 * n32};
 }
 
@@ -463,8 +466,7 @@ int elora::launch_fp32(const LinearArgs &a, hipStream_t stream)
         return ELORA_OK;
     };
     profile_mark_begin(stream);
-    const int rc = tiles.mb == 1 ? (tiles.n > 512 ? go(fp32_product_kernel<1, 1, 1>) : go(fp32_product_kernel<1, 1, 4>))
-                   : tiles.nb == 1 ? go(fp32_product_kernel<2, 1, 4>) : go(fp32_product_kernel<2, 2, 1>);
+    const int rc = tiles.mb == 1 ? go(fp32_product_kernel<1, 1, 1>) : tiles.nb == 1 ? go(fp32_product_kernel<2, 1, 2>) : go(fp32_product_kernel<2, 2, 1>);
     if (rc == ELORA_OK) profile_mark_end(stream);
     return rc;
 }
