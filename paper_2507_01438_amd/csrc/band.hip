@@ -10,8 +10,9 @@
 //     (the 32x32 form would need tiles in steps of 64 rows).  W is the first operand, so a lane holds four neighbouring
 //     outputs of one row.
 //   - a 4-bit or 8-bit W stays as it is in LDS; a fragment is converted on its way to the matrix cores.
-//   - the expand B_i v_t comes after the K loop: every wave walks the runs of equal adapters in its own rows, 16 rows and
-//     32 rank entries at a time, through a ring of its own (no barriers), and a row only takes what its own adapter gives.
+//   - the expand B_i v_t comes after the K loop: every wave walks the runs of equal adapters in its own rows, all rows of a run
+//     at a time where there are few, else 16 rows and 32 rank entries at a time through a ring of its own (no barriers), and a
+//     row only takes what its own adapter gives.
 //     Calls of up to 256 rows, which the decode kernel takes too, with fp32 shrink results, have these whole here as well:
 //     three bf16 each (24 bits), three matrix instructions in the place of one, and the scale applied to what they give.
 // A call with one adapter of rank 32 (route, shrink and product), on the 256 x 256 tiles / here: 389 rows 4096 x 4096 116 /
@@ -30,6 +31,7 @@ constexpr int BN = 128, BK = 64;
 constexpr int kThreads = 256, kWaveCols = 64;
 constexpr int kMaxMA = 7;
 constexpr int kMaxSlices = 8;
+constexpr int kRunsMost = 3;  // runs in a wave's rows that are taken one after the other, over all of their rows
 constexpr int kLdsBytes = 160 * 1024 - 512;  // (the rest: what the kernel declares by itself)
 
 // everybody's loads up to N younger ones have landed, and everybody's LDS reads are over
@@ -51,7 +53,8 @@ struct Band {
     static constexpr int kWholeLoads = 7, kRoundedLoads = 5, kStepBytes = kWholeLoads * 1024;
     // (all of LDS, unless the K loop leaves room for a second workgroup)
     static constexpr int kBytes = kDepth * kStage * 2 > kLdsBytes ? kLdsBytes / 4096 * 4096 : kDepth * kStage;
-    static constexpr int kWaveBytes = kBytes / 4 / 1024 * 1024;
+    static constexpr int kZeroBytes = 4096;                                // (of which four 16-byte places are read)
+    static constexpr int kWaveBytes = (kBytes - kZeroBytes) / 4 / 1024 * 1024;
     static constexpr int kTableBytes = kWaveRows * (kMaxRank / 32) * 8;    // the wave's expand steps at most
     static constexpr int kStepRoom = (kWaveBytes - kTableBytes) / kStepBytes;
     static constexpr int kSteps = kStepRoom < 8 ? kStepRoom : 8;
@@ -251,14 +254,22 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
     }
     wait_loads<0>();
 
-    // ---- expand, and what the wave has of y, 16 rows at a time -----------------------------------------------------------
-    // A step is (16-row block, run of equal adapters in it, 32 rank entries): 1 or 3 KiB of V and 4 of B_i for four or twelve
-    // matrix instructions; a tile's K-slices take turns at the runs.  The wave first writes its steps out as a table, a lane per row;
+    // ---- expand ------------------------------------------------------------------------------------------------------------
+    // Few runs of equal adapters in the wave's rows (prompts; up to kRunsMost): a run and 32 rank entries at a time, over all of
+    // its 16-row blocks: 4 KiB of B_i and 1 KiB of V per block straight into registers, all at once, the next ones on their way
+    // meanwhile.  (389 rows of one adapter, 4096 x 14336, from the end of the K loop to y: 23000 cycles in steps of one block,
+    // which each waited for loads of the same B_i and for the stores of the block before, so 15000.  A tile's K-slices take turns at the
+    // blocks.)
+    // Otherwise a step is (16-row block, run of equal adapters in it, 32 rank entries): 1 or 3 KiB of V and 4 of B_i for four or
+    // twelve matrix instructions; a tile's K-slices take turns at the runs.  The wave first writes its steps out as a table, a lane per row;
     // the loads of kSteps - 1 steps are under way while one is multiplied.  Ranks that are no multiples of 8, and adapters in
-    // 8-bit blocks, have rows of B_i that a 16-byte load cannot take: their fragments are gathered when the step is due.
-    // What bounds this part is instructions (fetched once, a cache line of code takes 250 cycles): so the blocks go through
-    // one loop, always as acc[0], and the others move up behind each.  (A switch over the blocks made the compiler copy all
-    // sums at every step: 2050 cycles a step; unrolled, 389 rows of one adapter took 3000.)
+    // 8-bit blocks, have rows of B_i that a 16-byte load cannot take: their fragments are gathered when the step is due, in a
+    // loop of their own.  What bounds the plain steps is instructions and waits, with one wave per SIMD: 120 instructions a step
+    // (the gathered ones 230), and no stores of y between them, whose acknowledgements the loads behind them would wait for
+    // (150 rows of mixed rank, 4096 x 14336: 75 -> 66 us).
+    // Code is fetched as it is met, so the blocks go through one loop, always as acc[0], and the others move up behind each.  (A
+    // switch over the blocks made the compiler copy all sums at every step: 2050 cycles a step; unrolled, 389 rows of one
+    // adapter took 3000.)
     int n_steps = 0, first[2] = {0, 0};  // (first: steps before the lane's row)
     unsigned char *const own = smem + wave * G::kWaveBytes;
     uint64_t *const table = reinterpret_cast<uint64_t *>(own + G::kSteps * G::kStepBytes);
@@ -295,17 +306,98 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
 #pragma unroll
         for (int i = 0; i < 4; ++i) dma16(lds + 3072 + i * 1024, Bm, col[i] * stride + j);
     };
+    // The same loads for a wave whose steps are all plain ones (ranks that are multiples of 8, no 8-bit blocks): its table holds
+    // the adapter's place in the pool instead of the slot, in units of 256 bytes.
+    const char *const slots0 = pool.slots;
+    auto issue_plain = [&](int w0, int w1, int at, auto whole_c) __attribute__((always_inline)) {
+        const uint32_t lds = ring0 + (uint32_t)at * G::kStepBytes;
+        const uint32_t j0 = (uint32_t)((w0 >> 16) & 15) * 32, rank = (uint32_t)(w0 >> 20);
+        const int row = min((w0 & 0xf0) + line, T - 1 - r0);
+        const uint32_t voff = __umul24(row, 2u * ba.Rpad) + (2u * j0 + 16u * chunk);
+        dma16(lds, vbase, voff);
+        if constexpr (decltype(whole_c)::value) {
+            dma16(lds + 1024, vmid, voff);
+            dma16(lds + 2048, vlast, voff);
+        }
+        const char *const Bm = slots0 + ((uint64_t)(uint32_t)w1 << 8);
+        const uint32_t j = j0 + 8u * chunk, jb = 2u * (j < rank ? j : j0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dma16(lds + 3072 + i * 1024, Bm, __umul24(col[i], 2u * rank) + jb);
+    };
+    bool plain = false, in_runs = false;
     if (has_pool) {
         const int before0 = __shfl_up(slot_v[0], 1), before1 = __shfl_up(slot_v[1], 1), last0 = __builtin_amdgcn_readlane(slot_v[0], 63);
         const bool cut = (lane & 15) == 0;
         const uint64_t starts[2] = {__ballot(cut || slot_v[0] != before0), __ballot(cut || slot_v[1] != (lane == 0 ? last0 : before1))};
         const uint64_t run[2] = {starts[0] & __ballot(rank_v[0] > 0), starts[1] & __ballot(rank_v[1] > 0)};  // first rows of runs with an adapter
+        plain = !q8 && (__ballot(((rank_v[0] | rank_v[1]) & 7) != 0)) == 0;
+        // ---- few runs in the wave's rows (prompts): a run and 32 rank entries at a time, over all of its 16-row blocks
+        uint64_t left[2] = {__ballot(lane == 0 || slot_v[0] != before0) & run[0], __ballot(slot_v[1] != (lane == 0 ? last0 : before1)) & run[1]};
+        in_runs = plain && !whole && (int)__popcll(left[0]) + (int)__popcll(left[1]) <= kRunsMost;
+        if (in_runs) {
+            const uint64_t ends[2] = {__ballot(slot_v[0] != before0), __ballot(slot_v[1] != (lane == 0 ? last0 : before1))};  // (lane 0 of the first: no matter)
+            int lo = 0, hi = 0, rank = 0, j0 = 0;  // the run and the entries whose fragments come next
+            const uint16_t *Bm = nullptr;
+            auto next = [&]() __attribute__((always_inline)) {
+                j0 += 32;
+                if (j0 < rank) return true;
+                if ((left[0] | left[1]) == 0) return false;
+                const int h = left[0] == 0, l = (int)__builtin_ctzll(left[h]);
+                left[h] &= left[h] - 1;
+                lo = h * 64 + l;
+                const uint64_t after0 = h == 0 && l < 63 ? ends[0] & (~0ull << (l + 1)) : 0, after1 = h == 0 ? ends[1] : l < 63 ? ends[1] & (~0ull << (l + 1)) : 0;
+                hi = after0 ? (int)__builtin_ctzll(after0) : after1 ? 64 + (int)__builtin_ctzll(after1) : 128;
+                rank = h == 0 ? __builtin_amdgcn_readlane(rank_v[0], l) : __builtin_amdgcn_readlane(rank_v[1], l);
+                Bm = reinterpret_cast<const uint16_t *>(slot_B(pool, h == 0 ? __builtin_amdgcn_readlane(slot_v[0], l) : __builtin_amdgcn_readlane(slot_v[1], l)));
+                j0 = 0;
+                return true;
+            };
+            u32x4 vf[MA], bf[4];
+            auto load = [&]() __attribute__((always_inline)) {
+                const int j = j0 + g * 8;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) bf[b] = *reinterpret_cast<const u32x4 *>(Bm + (uint32_t)min(c0 + b * 16 + m, N - 1) * (uint32_t)rank + (uint32_t)(j < rank ? j : j0));
+#pragma unroll
+                for (int a = 0; a < MA; ++a) vf[a] = *reinterpret_cast<const u32x4 *>(ba.V + (size_t)min(r0 + a * 16 + m, T - 1) * ba.Rpad + j);
+            };
+            bool more = next();
+            if (more) load();
+#pragma unroll 1
+            while (more) {
+                const int lo_ = lo, hi_ = hi;
+                const bool cut_off = j0 + g * 8 >= rank;
+                bf16x8 v[MA], bm[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) bm[b] = __builtin_bit_cast(bf16x8, cut_off ? u32x4{0, 0, 0, 0} : bf[b]);
+#pragma unroll
+                for (int a = 0; a < MA; ++a) v[a] = __builtin_bit_cast(bf16x8, vf[a]);
+                more = next();
+                if (more) load();
+#pragma unroll
+                for (int a = 0; a < MA; ++a) {
+                    if (a * 16 >= hi_ || a * 16 + 16 <= lo_ || (ba.ks > 1 && a % ba.ks != slice)) continue;
+                    if (lo_ <= a * 16 && hi_ >= min(a * 16 + 16, T - r0)) {
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v[a], acc[a][b], 0, 0, 0);
+                    } else {
+                        const bool in = (a * 16 + m >= lo_) & (a * 16 + m < hi_);  // (a row of another run takes nothing, not even zero times this adapter)
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            const floatx4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v[a], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) acc[a][b][q] += in ? d[q] : 0.0f;
+                        }
+                    }
+                }
+            }
+        }
         __syncthreads();  // every wave is done with the stages
+        if (tid < 16) *reinterpret_cast<uint32_t *>(smem + 4 * G::kWaveBytes + (tid >> 2) * 1024 + (tid & 3) * 4) = 0;  // (read by every wave: the barrier below)
 #pragma unroll
         for (int h = 0; h < (G::kWaveRows + 63) / 64; ++h) {
             const uint64_t below = (1ull << lane) - 1;
             const int number = (int)__popcll(run[h] & below) + (h ? (int)__popcll(run[0]) : 0);
-            const int n = ((run[h] >> lane) & 1) && number % ba.ks == slice ? (rank_v[h] + 31) >> 5 : 0;
+            const int n = ((run[h] >> lane) & 1) && !in_runs && number % ba.ks == slice ? (rank_v[h] + 31) >> 5 : 0;
             int upto = n;  // steps of the rows up to this one
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
@@ -317,13 +409,23 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
             const int row = h * 64 + lane, end = h * 64 + (after ? (int)__builtin_ctzll(after) : 64);
             // step record: first row | end row << 8 | 32 entries number << 16 | rank << 20, slot
             for (int i = 0; i < n; ++i)
-                table[first[h] + i] = (uint64_t)(uint32_t)(row | (end << 8) | (i << 16) | (rank_v[h] << 20)) | ((uint64_t)(uint32_t)slot_v[h] << 32);
+                table[first[h] + i] = (uint64_t)(uint32_t)(row | (end << 8) | (i << 16) | (rank_v[h] << 20)) |
+                                      ((uint64_t)(plain ? (uint32_t)((slot_v[h] * pool.slot_bytes + pool.b_offset) >> 8) : (uint32_t)slot_v[h]) << 32);
             n_steps += __builtin_amdgcn_readlane(upto, 63);
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (a wave reads what its own lanes wrote)
+        __syncthreads();
         if (n_steps > 0) {
 #pragma unroll 1
-            for (int i = 0; i < G::kSteps - 1; ++i) issue(step_at(i), i);
+            for (int i = 0; i < G::kSteps - 1; ++i) {
+                if (!plain) {
+                    issue(step_at(i), i);
+                } else {
+                    const u32x2 r = *reinterpret_cast<const u32x2 *>(table + min(i, n_steps - 1));
+                    const int w0 = __builtin_amdgcn_readfirstlane(r[0]), w1 = __builtin_amdgcn_readfirstlane(r[1]);
+                    if (whole) issue_plain(w0, w1, i, std::true_type{});
+                    else issue_plain(w0, w1, i, std::false_type{});
+                }
+            }
         }
     }
     // sums of K-slices, written through to memory and read past the first-level cache (nothing depends on where a tile's
@@ -331,28 +433,87 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
     constexpr int kFrags = MA * 4, kCoherent = 16;  // sc1
     auto rsrc = __builtin_amdgcn_make_buffer_rsrc(ba.part + (size_t)tile * ba.ks * (4 * kFrags * 256), 0, ba.ks * (4 * kFrags * 1024), 0x00020000);
     const int part_at = wave * kFrags * 1024 + lane * 16, slice_bytes = 4 * kFrags * 1024;
-    auto move_up = [&]() __attribute__((always_inline)) {
+    // a lane has four neighbouring outputs of row m of every block
+    auto store_y = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int a = 0; a + 1 < MA; ++a)
+        for (int a = 0; a < MA; ++a) {
+            const int row = r0 + a * 16 + m;
+            uint16_t *const yrow = ba.y + (size_t)row * N;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) acc[a][b] = acc[a + 1][b];
-    };
-    // block a of y, from acc[0]: a lane has four neighbouring outputs of row m
-    auto store_y = [&](int a) __attribute__((always_inline)) {
-        const int row = r0 + a * 16 + m;
-        uint16_t *const yrow = ba.y + (size_t)row * N;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int c = c0 + b * 16 + g * 4;
-            if (row < T && c < N) *reinterpret_cast<u32x2 *>(yrow + c) = u32x2{pack_bf16x2(acc[0][b][0], acc[0][b][1]), pack_bf16x2(acc[0][b][2], acc[0][b][3])};
+            for (int b = 0; b < 4; ++b) {
+                const int c = c0 + b * 16 + g * 4;
+                if (row < T && c < N) *reinterpret_cast<u32x2 *>(yrow + c) = u32x2{pack_bf16x2(acc[a][b][0], acc[a][b][1]), pack_bf16x2(acc[a][b][2], acc[a][b][3])};
+            }
         }
     };
     int step = 0, at = 0;
+    // What a step of a plain wave costs is instructions and the waits between them (one wave per SIMD): the table entries are
+    // read a step ahead, the rows' sums stay in vector registers, and a row outside the run is masked off as a lane.
+    u32x2 rec_now{0, 0}, rec_next{0, 0};  // this step's entry; that of the step to ask for
+    auto fetch_records = [&](int step) __attribute__((always_inline)) {
+        rec_now = *reinterpret_cast<const u32x2 *>(table + min(step, n_steps - 1));
+        rec_next = *reinterpret_cast<const u32x2 *>(table + min(step + G::kSteps - 1, n_steps - 1));
+    };
+    if (plain && n_steps > 0) fetch_records(0);
+    const uint32_t zero_at = (uint32_t)(4 * G::kWaveBytes);
+    auto plain_steps = [&](int a, int stop, float row_scale, auto whole_c) __attribute__((always_inline)) {
+        constexpr bool kWhole = decltype(whole_c)::value;
+        floatx4 sum[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            sum[b] = acc[0][b];
+            asm volatile("" : "+v"(sum[b]));
+        }
+        const int row = a * 16 + m;
+#pragma unroll 1
+        for (; step < stop; ++step) {
+            const int w0 = __builtin_amdgcn_readfirstlane(rec_now[0]);
+            const int n0_ = __builtin_amdgcn_readfirstlane(rec_next[0]), n1_ = __builtin_amdgcn_readfirstlane(rec_next[1]);
+            issue_plain(n0_, n1_, at == 0 ? G::kSteps - 1 : at - 1, whole_c);
+            fetch_records(step + 1);
+            wait_loads<(kWhole ? G::kWholeLoads : G::kRoundedLoads) * (G::kSteps - 1)>();
+            const uint32_t st = (uint32_t)(wave * G::kWaveBytes) + (uint32_t)at * G::kStepBytes + (uint32_t)(m * 64 + (g ^ ((m >> 2) & 3)) * 16);
+            const int rank = w0 >> 20, j = ((w0 >> 16) & 15) * 32 + g * 8;
+            // (entries past the rank: zero in V; zero here too, whatever the adapter holds)
+            const unsigned char *const bp = smem + (j < rank ? st + 3072 : zero_at);
+            bf16x8 v[kWhole ? 3 : 1], bm[4];
+#pragma unroll
+            for (int q = 0; q < (kWhole ? 3 : 1); ++q) v[q] = *reinterpret_cast<const bf16x8 *>(smem + st + q * 1024);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) bm[b] = *reinterpret_cast<const bf16x8 *>(bp + b * 1024);
+            floatx4 d[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) d[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v[0], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            if constexpr (kWhole) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) d[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v[1], d[b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) d[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v[2], d[b], 0, 0, 0);
+            }
+            if ((row >= (w0 & 255)) & (row < ((w0 >> 8) & 255))) {  // (a row of another run takes nothing, not even zero times this adapter)
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) sum[b][q] = kWhole ? fmaf(d[b][q], row_scale, sum[b][q]) : sum[b][q] + d[b][q];
+            }
+#pragma unroll
+            for (int b = 0; b < 4; ++b) asm volatile("" : "+v"(sum[b]));
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (this step's place has been read)
+            at = at + 1 == G::kSteps ? 0 : at + 1;
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[0][b] = sum[b];
+    };
+    if (n_steps > 0) {
 #pragma unroll 1
     for (int a = 0; a < MA; ++a) {
         float row_scale = 1.0f;
         if (whole) row_scale = __shfl(a < 4 ? scale_v[0] : scale_v[1], (a & 3) * 16 + m);
         const int stop = a + 1 == MA ? n_steps : __builtin_amdgcn_readlane(a + 1 < 4 ? first[0] : first[1], ((a + 1) & 3) * 16);
+        if (plain) {
+            if (whole) plain_steps(a, stop, row_scale, std::true_type{});
+            else plain_steps(a, stop, row_scale, std::false_type{});
+        }
 #pragma unroll 1
         for (; step < stop; ++step) {
             const Step cur = step_at(step);
@@ -412,17 +573,28 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (this step's place has been read)
             at = at + 1 == G::kSteps ? 0 : at + 1;
         }
-        if (ba.ks == 1) {
-            store_y(a);
-        } else {
+        // (the blocks move up, round the circle: as many turns as there are blocks put every one back)
+        floatx4 top[4];
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[0][b]), rsrc, part_at + a * 4096 + b * 1024, slice * slice_bytes, kCoherent);
-        }
-        move_up();
+        for (int b = 0; b < 4; ++b) top[b] = acc[0][b];
+#pragma unroll
+        for (int i = 0; i + 1 < MA; ++i)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[i][b] = acc[i + 1][b];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[MA - 1][b] = top[b];
     }
-    wait_loads<0>();
-    if (ba.ks == 1) return;
+    }
+    wait_loads<0>();  // (also those asked for behind the last step: they land before the LDS is given back)
+    if (ba.ks == 1) {
+        store_y();
+        return;
+    }
+#pragma unroll
+    for (int a = 0; a < MA; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[a][b]), rsrc, part_at + a * 4096 + b * 1024, slice * slice_bytes, kCoherent);
 
     // ---- sums of the K-slices: the last workgroup of the tile to come adds them, in slice order -----------------------------
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's sums have reached memory
@@ -445,11 +617,7 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
 #pragma unroll
         for (int f = 0; f < kFrags; ++f) acc[f >> 2][f & 3] += __builtin_bit_cast(floatx4, w[f]);
     }
-#pragma unroll 1
-    for (int a = 0; a < MA; ++a) {
-        store_y(a);
-        move_up();
-    }
+    store_y();
 }
 
 int g_mode = -1, g_mode_tiles = 0, g_mode_slices = 0;  // (elora_debug_band)

@@ -106,3 +106,33 @@ def test_an_infinite_adapter_stays_in_its_own_rows():
     assert not np.isfinite(y[5:8]).any() and np.isfinite(y[rest]).all()
     assert rel_err(y[rest], case.reference(rows=rest)) <= 1e-2
     case.close()
+
+
+@pytest.mark.parametrize("tiles, slices", [(2, 1), (2, 3), (3, 2), (4, 4), (7, 1)])
+@pytest.mark.parametrize("lengths", [[345], [112, 112, 121], [5, 90, 20, 200, 30], [100, 9, 1, 1, 1, 1, 1, 231], [37, 300, 8]])
+def test_few_runs_in_a_tile(lengths, tiles, slices):
+    """Prompts: up to three runs in a wave's rows go over all of its blocks, more of them step by step; runs that begin and end
+    inside 16-row blocks, ranks on both sides of the 32 entries a pass takes, blocks shared out over K-slices, one adapter full
+    of infinities (its rows take nothing but infinities and NaN, all others nothing of them)."""
+    import torch
+
+    from paper_2507_01438_amd import binding as B
+    T = sum(lengths)
+    w = I.small_workload(5500 + T + len(lengths), I.BF16, 512, 200, T, 5, (8, 24, 32, 40, 64), segments=lengths, no_adapter_rows=(2,) if len(lengths) == 3 else ())
+    case = DeviceCase(w, w.projections[0])
+    B.elora_debug_band(1, tiles, slices)
+    try:
+        y = case.run(force_path=GEMM)
+        assert np.array_equal(y, case.run(force_path=GEMM))
+        assert_close(y, case.reference(), case.base_reference(), f"{lengths} {tiles} {slices}")
+        i = int(w.seg_adapter[len(lengths) // 2])
+        own = np.repeat(np.asarray(w.seg_adapter), lengths) == i
+        if i >= 0 and not own.all():
+            A, Bm, s = case.adapters[i]
+            case.pool.load(i, torch.from_numpy(A.view(np.int16)), torch.from_numpy(np.full_like(Bm, 0x7F80).view(np.int16)), s)
+            torch.cuda.synchronize()
+            z = case.run(force_path=GEMM)
+            assert not np.isfinite(z[own]).any() and np.array_equal(z[~own], y[~own])
+    finally:
+        B.elora_debug_band(-1)
+    case.close()
