@@ -107,6 +107,7 @@ struct ShrinkArgs {
     int n_tiles;         // kShrinkRows-row tiles
     int ks;              // K-slices per tile
     int wgs_per_xcd;     // workgroups per projection and XCD
+    bool by_row;         // rings as for ranks up to 32: most rows sit in short runs
     bool rows_apart;     // the rows of short runs are a launch of their own
     const uint16_t *x;
     ShrinkProj proj[kShrinkMulti];

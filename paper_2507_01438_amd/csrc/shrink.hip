@@ -56,14 +56,87 @@ __device__ __forceinline__ void route_rows(const RouteView &route, const ShrinkA
 
 __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteView route, ShrinkArgs s) { route_rows(route, s, (int)blockIdx.x); }
 
-// ---- rows of short runs (any rank), one by one: 16 rank entries of a row per call, a wave takes two at a time --------------
-// Bound by latency: a pass over two rows of A_i is one trip to memory.  (150 rows of ranks 8 to 64, K = 4096: a whole row
-// per workgroup on half as many workgroups as rows 35 us, pieces of 16 entries on one workgroup per row 24.)
+// ---- rows of short runs (any rank), one by one: 16 rank entries of a row per call, four of them per wave (8-bit blocks: two at a time) --
+// Bound by latency and by what a compute unit takes in: a wave takes four rows of A_i, so that x_t is read four times per
+// piece, with 40 loads of 16 bytes per lane under way.  (150 rows of ranks 8 to 64, K = 4096: a whole row per workgroup on half as many
+// workgroups as rows 35 us, pieces of 16 entries on one workgroup per row 24.  Against two rows of A_i at a time, x_t read
+// eight times, 24 loads: gate + up of those rows 182 -> 166 us, down 93 -> 89, 600 rows of an adapter of rank 16 each 4096 x 4096
+// 88 -> 78, 1800 rows of rank 32 6336 x 2048 253 -> 224.)
 constexpr int kRowPiece = 16;
 // Rows in short runs, as far as the host can tell, from which they are a launch of their own.  With an adapter per row, all in
 // the one launch / so: 512 rows of ranks 8 to 64, 2752 x 2896, 89 / 84 us, 2000 rows 243 / 203; 4000 rows of rank 16, 4096 x
 // 4096, 389 / 241.  With one adapter the second launch costs 2 us.
 constexpr int kRowsApart = 512;
+// One wave: rank entries j0 .. j0 + 3 of row t (rows of A_i past the rank repeat the last one).  Two sets of loads take turns, 20
+// loads of 16 bytes per lane each; x_t is read once for the four.  Rows start their walk through K at different places:
+// rows of A_i lie a multiple of the memory channels' pitch apart.
+__device__ __forceinline__ void shrink_four(const uint16_t *__restrict__ A, const uint16_t *__restrict__ xt, int K, int j0, int rank, int turn, int lane, float v[4])
+{
+    constexpr int NL = 4;
+    const int pieces = K >> 3, chunks = (pieces + 63) >> 6, rounds = (chunks + NL - 1) / NL;  // 16-byte pieces; 64 of them; NL chunks
+    const int rot = chunks > 2 * NL ? (int)((unsigned)turn * 5u % (unsigned)chunks) : 0;
+    const bool ragged = (pieces & 63) != 0 || chunks % NL != 0;
+    const uint16_t *row[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) row[r] = A + (size_t)min(j0 + r, rank - 1) * K;
+    u32x4 x0[NL], a0[NL][4], x1[NL], a1[NL][4];
+    auto piece_of = [&](int round, int i, bool &in) __attribute__((always_inline)) {
+        int c = round * NL + i;
+        in = c < chunks;
+        c += rot;
+        if (c >= chunks) c -= chunks;
+        const int p = c * 64 + lane;
+        in = in && p < pieces;
+        return in ? p : 0;
+    };
+    auto load = [&](int round, u32x4(&x)[NL], u32x4(&a)[NL][4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            bool in;
+            const size_t off = (size_t)piece_of(round, i, in) * 8;
+            x[i] = *reinterpret_cast<const u32x4 *>(xt + off);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a[i][r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row[r] + off));
+        }
+    };
+    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto dot = [&](int round, u32x4(&x)[NL], u32x4(&a)[NL][4]) __attribute__((always_inline)) {
+        if (ragged) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                bool in;
+                (void)piece_of(round, i, in);
+                if (!in) {
+                    x[i] = u32x4{0, 0, 0, 0};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) a[i][r] = u32x4{0, 0, 0, 0};
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const uint32_t aw = a[i][r][q], xw = x[i][q];
+                    sum[r] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(elora_bf16x2, aw), __builtin_bit_cast(elora_bf16x2, xw), sum[r], false);
+                }
+    };
+    load(0, x0, a0);
+#pragma unroll 1
+    for (int round = 0; round < rounds; round += 2) {
+        if (round + 1 < rounds) load(round + 1, x1, a1);
+        dot(round, x0, a0);
+        if (round + 1 < rounds) {
+            if (round + 2 < rounds) load(round + 2, x0, a0);
+            dot(round + 1, x1, a1);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = wave_sum(sum[r]);
+}
+
 template <bool kQ8>
 __device__ __forceinline__ void shrink_row_piece(const ShrinkArgs &s, const ShrinkProj &pr, int t, int first, int end)
 {
@@ -85,22 +158,27 @@ __device__ __forceinline__ void shrink_row_piece(const ShrinkArgs &s, const Shri
             store(pr.V, f32_to_bf16(v0), f32_to_bf16(v1));
         }
     };
-    for (int j0 = first + 2 * wave; j0 < first + kRowPiece; j0 += 2 * kWaves) {
-        const bool two = j0 + 1 < rank;
-        float a0 = 0.0f, a1 = 0.0f;
-        if (j0 < rank) {
-            const int j1 = two ? j0 + 1 : j0;
-            const uint16_t *A = reinterpret_cast<const uint16_t *>(slot_A(pr.pool, slot));
-            if constexpr (kQ8) {
-                const char *Ac = reinterpret_cast<const char *>(A);
+    if constexpr (kQ8) {
+        for (int j0 = first + 2 * wave; j0 < first + kRowPiece; j0 += 2 * kWaves) {
+            const bool two = j0 + 1 < rank;
+            float a0 = 0.0f, a1 = 0.0f;
+            if (j0 < rank) {
+                const int j1 = two ? j0 + 1 : j0;
+                const char *Ac = slot_A(pr.pool, slot);
                 const uint16_t *As = slot_A_scales(pr.pool, slot);
                 shrink_pair_q8(Ac + (size_t)j0 * K, Ac + (size_t)j1 * K, As + (((size_t)j0 * K) >> 5), As + (((size_t)j1 * K) >> 5),
                                s.x + (size_t)t * K, K, lane, a0, a1);
-            } else {
-                shrink_pair(A + (size_t)j0 * K, A + (size_t)j1 * K, s.x + (size_t)t * K, K, lane, a0, a1);
             }
+            if (lane == 0) put(j0, j0 < rank ? sc * a0 : 0.0f, two ? sc * a1 : 0.0f);
         }
-        if (lane == 0) put(j0, j0 < rank ? sc * a0 : 0.0f, two ? sc * a1 : 0.0f);
+    } else {
+        const int j0 = first + 4 * wave;
+        float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (j0 < rank) shrink_four(reinterpret_cast<const uint16_t *>(slot_A(pr.pool, slot)), s.x + (size_t)t * K, K, j0, rank, t + wave, lane, v);
+        if (lane == 0) {
+            put(j0, j0 < rank ? sc * v[0] : 0.0f, j0 + 1 < rank ? sc * v[1] : 0.0f);
+            put(j0 + 2, j0 + 2 < rank ? sc * v[2] : 0.0f, j0 + 3 < rank ? sc * v[3] : 0.0f);
+        }
     }
     for (int j = first + kRowPiece + 2 * tid; j < end; j += 2 * kThreads) put(j, 0.0f, 0.0f);
 }
@@ -444,7 +522,7 @@ auto with_cols(const ShrinkArgs &s, F &&f)  // f(8-bit blocks, MFMA column block
     for (int p = 0; p < s.n; ++p) most = s.proj[p].pool.max_rank > most ? s.proj[p].pool.max_rank : most;
     auto cols = [&](auto q8) {
         if (most <= 16) return f(q8, ic<1>{});
-        if (most <= 32) return f(q8, ic<2>{});
+        if (most <= 32 || s.by_row) return f(q8, ic<2>{});
         return f(q8, ic<4>{});
     };
     return s.proj[0].pool.q8 ? cols(std::true_type{}) : cols(std::false_type{});
@@ -475,6 +553,12 @@ void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n, const bool *w
     while (s.ks < kMaxSlices && s.n_tiles * (s.ks + 1) <= (s.K / (s.ks + 1) >= 4096 ? 512 : 256) && s.n_tiles <= kSyncTileCount &&
            s.K / kSpan >= (s.ks + 1) * 2 * kWaves && room_for(s.ks + 1))
         ++s.ks;
+    // Rows with an index of their own, and more adapters than an eighth of them: long runs are unlikely, and the rings of 32 rank
+    // entries leave a compute unit two workgroups for the rows instead of one (256 rows of rank 64, q + k + v of 4096: 157 -> 144
+    // us; if they are all of one adapter after all, a second pass over x, 32.2 -> 33.3).  Not where a row takes several trips to
+    // memory anyway: 150 rows, d_in = 14336, 88.8 us with one workgroup and 93.4 with two.
+    s.by_row = a[0].route.adapter_idx != nullptr && s.K <= 8192;
+    for (int p = 0; p < n; ++p) s.by_row = s.by_row && a[p].n_loaded * 8ll > s.T;
     s.rows_apart = shrink_rows_apart(s.T, a[0].route.adapter_idx != nullptr, a[0].route.n_segments);
     // (at least four workgroups per row, up to two per compute unit: the rows of short runs are shared by all of them)
     s.wgs_per_xcd = std::max((s.n_tiles + kXcds - 1) / kXcds * s.ks * 2, std::min((s.T + 1) / 2, 64));

@@ -98,3 +98,17 @@ def test_many_rows_in_short_runs(T, K, ranks, q8, product):
         assert np.array_equal(y_to_f64(case.y[:T], I.BF16), y)
     assert case.pool.poll_error() == (0, -1)
     case.close()
+
+
+@pytest.mark.parametrize("pool_size", [40, 4])   # (more adapters than an eighth of the rows, and fewer)
+@pytest.mark.parametrize("K", [64, 576, 2048, 2560, 4096, 4672, 9280])
+def test_single_rows_over_lengths_and_ranks(K, pool_size, product):
+    """Rows of one run each: d_in below, at and beside whole loads of a wave (512 elements), one and several turns of them,
+    walks that begin in the middle; ranks around the four entries of a wave and the 16 of a workgroup."""
+    w = I.small_workload(1900 + K, I.BF16, K, 72, 70, pool_size, (1, 3, 4, 5, 15, 16, 18, 64)[:: 2 if pool_size == 4 else 1], no_adapter_rows=(0, 33))
+    case = DeviceCase(w, w.projections[0])
+    y = case.run(force_path=GEMM)
+    assert case.last_plan.tile_cols == product
+    assert_close(y, case.reference(), case.base_reference(), f"{K} {pool_size}")
+    assert np.array_equal(y, case.run(force_path=GEMM))
+    case.close()
