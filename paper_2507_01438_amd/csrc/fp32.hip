@@ -393,12 +393,13 @@ __global__ __launch_bounds__(64 * kOneWaves) void fp32_one_kernel(int T, int K, 
 // Where the call's rows meet at most 32 ranks whichever adapters they name, so that one walk over K is enough (with a second
 // one 8 rows 256 x 512 take 8.3 us, on two launches 7.4), K is short (16 rows of rank 8: 700 x 700 two launches 8.1 us / one
 // 7.7, 1000 x 1000 9.1 / 10.4: the ranks are read by every workgroup) and two workgroups per compute unit are all there are.
-// Adapters loaded later, under a captured graph, only add walks.
+// Adapters loaded later, under a captured graph, only add walks.  (A pool that holds none yet says nothing of the ranks to come: two
+// launches.)
 long long one_tiles(int T, int N) { return (((long long)T + kOneTile - 1) / kOneTile) * (((long long)N + kOneTile - 1) / kOneTile); }
 // (n_segments: how many different adapters the routing tables can name)
 bool one_launch(int T, int K, int N, int n_loaded, int max_rank, int n_segments)
 {
-    return (long long)std::min({kOneTile, T, n_loaded, n_segments}) * max_rank <= kOneRanks && K <= 700 && one_tiles(T, N) <= 512;
+    return n_loaded > 0 && (long long)std::min({kOneTile, T, n_loaded, n_segments}) * max_rank <= kOneRanks && K <= 700 && one_tiles(T, N) <= 512;
 }
 
 // A launch holds fewer than 2^32 threads: rows of the shrink, and tiles of the product, beyond that many workgroups go into
@@ -406,7 +407,7 @@ bool one_launch(int T, int K, int N, int n_loaded, int max_rank, int n_segments)
 constexpr size_t kMaxGroups = ((size_t)1 << 32) / kThreads - 1;
 size_t launches_of(size_t workgroups) { return (workgroups + kMaxGroups - 1) / kMaxGroups; }
 
-// 16 x 16 outputs where two such tiles per compute unit are all there are (and for up to 16 rows), else 32 x 32, which loads half
+// 16 x 16 outputs where such tiles leave a quarter of the compute units free (and for up to 16 rows), else 32 x 32, which loads half
 // as much per product, unless 32 x 16 come out as one round of workgroups.  Two launches, 16 x 16 / 32 x 16 / 32 x 32: 60 rows
 // 700 x 700 (176 tiles of 16) 8.7 / 10.5 / 12.2 us, 270 rows 300 x 400 (425) 8.1 / 8.4 / 9.8, 60 rows 2048 x 2048 (512; 256 of
 // 32 x 16) 21.3 / 18.2 / 22.6, 155 rows 1000 x 1430 (900; 450) 19.8 / 19.3 / 17.0, 1430 x 1000 (630; 315) 22.0 / 24.3 / 18.2.
@@ -417,7 +418,7 @@ struct Tiles {
 Tiles choose_tiles(int T, int N)
 {
     const size_t m16 = ((size_t)T + 15) / 16, m32 = ((size_t)T + 31) / 32, n16 = ((size_t)N + 15) / 16, n32 = ((size_t)N + 31) / 32;
-    if (T <= 16 || m16 * n16 < 512) return {1, 1, m16 * n16};
+    if (T <= 16 || m16 * n16 <= 192) return {1, 1, m16 * n16};
     if (m32 * n16 <= 256) return {2, 1, m32 * n16};
     return {2, 2, m32 * n32};
 }
