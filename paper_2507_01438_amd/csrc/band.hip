@@ -651,30 +651,50 @@ bool elora::band_shape(const BandCall &c, size_t part_bytes, BandShape *s)
     const int tiles_n = (N + BN - 1) / BN, blocks = K / BK;
     const int least = (T + 32 * kMaxMA - 1) / (32 * kMaxMA);
     auto rounds = [](double workgroups) { return std::ceil(workgroups / 256); };
-    double best = -1.0;
-    for (int tiles_m = g_mode_tiles > least ? g_mode_tiles : least; tiles_m <= (g_mode_tiles ? g_mode_tiles : least + 2); ++tiles_m) {
-        const int ma = ((T + tiles_m - 1) / tiles_m + 31) / 32, tm = (T + 32 * ma - 1) / (32 * ma);
-        const double block = c.wfmt == ELORA_W_SAME ? 270 + 160 * ma : 1550 + 105 * ma;
-        // a wave's steps: where the runs are spread over the batch, and what the tile with most of them has above that
-        const double row = (c.q8 ? 6500.0 : 1600.0) * c.pieces32;
-        const double spread = row * 16 * ma * c.runs / T, above = std::max(0.0, row * std::min(16 * ma, c.runs) - spread);
-        for (int ks = g_mode_slices ? g_mode_slices : 1; ks <= (g_mode_slices ? g_mode_slices : kMaxSlices); ++ks) {
-            if (ks > blocks || (ks > 1 && ((long long)tm * tiles_n > kSyncTileCount || (size_t)tm * tiles_n * ks * (ma * 32 * BN * 4) > part_bytes))) continue;
-            const double n = rounds((double)tm * tiles_n * ks);
-            const double tile = (blocks + ks - 1) / ks * block + 6000 + 2300 * ma + spread / ks;
-            const double cycles = (n * tile + above / ks) * (n > 1 ? 1.2 : 1.0) + (ks > 1 ? 2000 + 450.0 * ks * ma : 0);
-            if (best < 0 || cycles < best) {
-                best = cycles;
-                *s = BandShape{ma, tm, ks};
+    // the cheapest tiles of this kernel, on W as it is stored or on a bf16 copy of it (the copy itself not counted); negative: none
+    auto cheapest = [&](bool from_copy, BandShape *to) {
+        double best = -1.0;
+        for (int tiles_m = g_mode_tiles > least ? g_mode_tiles : least; tiles_m <= (g_mode_tiles ? g_mode_tiles : least + 2); ++tiles_m) {
+            const int ma = ((T + tiles_m - 1) / tiles_m + 31) / 32, tm = (T + 32 * ma - 1) / (32 * ma);
+            const double block = c.wfmt == ELORA_W_SAME || from_copy ? 270 + 160 * ma : 1550 + 105 * ma;
+            // a wave's steps: where the runs are spread over the batch, and what the tile with most of them has above that
+            const double row = (c.q8 ? 6500.0 : 1600.0) * c.pieces32;
+            const double spread = row * 16 * ma * c.runs / T, above = std::max(0.0, row * std::min(16 * ma, c.runs) - spread);
+            for (int ks = g_mode_slices ? g_mode_slices : 1; ks <= (g_mode_slices ? g_mode_slices : kMaxSlices); ++ks) {
+                if (ks > blocks || (ks > 1 && ((long long)tm * tiles_n > kSyncTileCount || (size_t)tm * tiles_n * ks * (ma * 32 * BN * 4) > part_bytes))) continue;
+                const double n = rounds((double)tm * tiles_n * ks);
+                const double tile = (blocks + ks - 1) / ks * block + 6000 + 2300 * ma + spread / ks;
+                const double cycles = (n * tile + above / ks) * (n > 1 ? 1.2 : 1.0) + (ks > 1 ? 2000 + 450.0 * ks * ma : 0);
+                if (best < 0 || cycles < best) {
+                    best = cycles;
+                    *to = BandShape{ma, tm, ks, from_copy};
+                }
             }
         }
-    }
+        return best;
+    };
+    double best = cheapest(false, s), copy = c.copied ? 1.04e-3 * K * N : 0.0;
     if (best < 0 || g_mode == 1 || c.only) return best >= 0;
+    // On the copy that the 256 x 256 tiles would run on, where there is room for one: next to it a converted W costs about 18000
+    // cycles a launch more than its blocks do.  A copy that does not stay in the caches costs more to make and to read, and
+    // has to be the better one by a sixth.  (One or two prompts, 8-bit W, as stored / on the copy: 389 rows 4096 x 4096 57 / 45 us,
+    // 14336 x 4096 110 / 122 (stored), 1000 rows 4096 x 4096 86 / 59, 14336 x 4096 243 / 170, 2000 rows 6144 x 2048 123 / 79, 2048 x 2048
+    // 61 / 42; 300 rows 4096 x 4096 48 / 41, where a group's second copy, a launch of its own, takes that back.)
+    const double weights = (double)K * N, in_cache = 32e6;
+    if (c.copied && T >= 320) {
+        BandShape from_copy;
+        const double made = 1.04e-3 * weights + 0.6e-3 * std::max(0.0, weights - in_cache), on_copy = cheapest(true, &from_copy) + made;
+        if (on_copy < (weights > in_cache ? 0.83 : 1.0) * (best + 18000)) {
+            best = on_copy;
+            copy = made;
+            *s = from_copy;
+        }
+    }
     const double n = rounds((double)((T + 255) / 256) * ((N + 255) / 256));
     const double block = c.copied ? 2600 : c.wfmt != ELORA_W_SAME ? 5700 : n > 1 ? 2900 : 3300;
     // (the most that a wave of a tile has, 128 rows; where the runs are spread over the batch, every round's tiles have them)
     const double run = (c.q8 ? 4000.0 : 850.0) * c.pieces16, spread = c.runs < T ? run * 128 * c.runs / T : run * 128, above = std::max(0.0, run * std::min(128, c.runs) - spread);
-    return best < 0.92 * (n * (blocks * block + 6000 + spread) + above + (c.copied ? 1.04e-3 * K * N : 0));
+    return best < 0.92 * (n * (blocks * block + 6000 + spread) + above + copy);
 }
 
 bool elora::band_whole(const LinearArgs &a) { return a.has_pool && a.T <= kWholeRows && a.wsl.v_rest_bytes != 0; }
@@ -689,7 +709,7 @@ int elora::enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t str
     b.tiles_n = (a.N + BN - 1) / BN;
     b.ks = s.ks;
     b.x = static_cast<const uint16_t *>(a.x);
-    b.W = a.W;
+    b.W = s.copied ? static_cast<const void *>(a.ws + a.wsl.wdeq) : a.W;
     b.w_scales = static_cast<const uint16_t *>(a.w_scales);
     b.row_slot = reinterpret_cast<const int32_t *>(a.ws + a.wsl.row_slot);
     b.V = reinterpret_cast<const uint16_t *>(a.ws + a.wsl.v);
@@ -724,7 +744,7 @@ int elora::enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t str
     };
     profile_mark_begin(stream);
     int rc;
-    if (a.wfmt == ELORA_W_SAME) rc = with_rows(ic<ELORA_W_SAME>{});
+    if (a.wfmt == ELORA_W_SAME || s.copied) rc = with_rows(ic<ELORA_W_SAME>{});
     else if (a.wfmt == ELORA_W_INT8_G32) rc = with_rows(ic<ELORA_W_INT8_G32>{});
     else rc = with_rows(ic<ELORA_W_INT4_G32>{});
     if (rc == ELORA_OK) profile_mark_end(stream);

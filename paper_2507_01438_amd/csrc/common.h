@@ -159,9 +159,10 @@ size_t decode_mail_bytes(int d_out);  // mailboxes of the decode kernel for d_ou
 // The product of a few hundred rows: tiles of 32 ma x 128 outputs, tiles_m of them along the rows, ks K-slices
 struct BandShape {
     int ma, tiles_m, ks;
+    bool copied;  // on a bf16 copy of W
 };
-// runs: of equal adapters, at most; q8: pool of 8-bit blocks; copied: the 256 x 256 tiles would run on a bf16 copy of W; only:
-// they are no alternative to this call (band_only)
+// runs: of equal adapters, at most; q8: pool of 8-bit blocks; copied: there is room for a bf16 copy of W (on which the 256 x 256
+// tiles would run, and this product may); only: those tiles are no alternative to this call (band_only)
 struct BandCall {
     int T, K, N, wfmt, runs;
     double pieces16, pieces32;  // pieces of 16 and of 32 entries of a loaded adapter's rank, on average

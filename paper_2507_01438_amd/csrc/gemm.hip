@@ -711,7 +711,7 @@ bool elora::band_instead_of_passes(const elora_linear_desc_t &d)
 bool elora::gemm_copies_w(const elora_linear_desc_t &d)
 {
     BandShape s;
-    return gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0 && !planned_band(d, &s);
+    return gemm_wcopy_bytes(d.wfmt, d.n_tokens, d.d_in, d.d_out) != 0 && (!planned_band(d, &s) || s.copied);
 }
 
 void elora::gemm_plan(const elora_linear_desc_t &d, elora_plan_t *plan)
@@ -812,7 +812,7 @@ int elora::launch_gemm(const LinearArgs &a, const elora_plan_t &plan, hipStream_
     const bool in_band = band_for(a, &band), whole = in_band && band_whole(a);
     ShrinkArgs s;
     shrink_args(s, &a, 1, &whole);
-    const bool copy = !in_band && a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
+    const bool copy = (!in_band || band.copied) && a.wfmt != ELORA_W_SAME && a.wsl.wdeq_bytes != 0;
     int rc = launch_route(s, &a, copy, stream);
     if (rc == ELORA_OK && a.has_pool) rc = launch_shrink(s, stream);
     if (rc != ELORA_OK) return rc;
@@ -831,7 +831,7 @@ int elora::launch_gemm_group(const LinearArgs *a, int n, hipStream_t stream)
     }
     ShrinkArgs s;
     shrink_args(s, a, n, whole);
-    auto copied = [&](int i) { return !in_band[i] && a[i].wfmt != ELORA_W_SAME && a[i].wsl.wdeq_bytes != 0; };
+    auto copied = [&](int i) { return (!in_band[i] || band[i].copied) && a[i].wfmt != ELORA_W_SAME && a[i].wsl.wdeq_bytes != 0; };
     int rc = launch_route(s, a, copied(0), stream);
     if (rc == ELORA_OK) rc = launch_shrink(s, stream);
     for (int i = 0; i < n && rc == ELORA_OK; ++i) {

@@ -136,3 +136,52 @@ def test_few_runs_in_a_tile(lengths, tiles, slices):
     finally:
         B.elora_debug_band(-1)
     case.close()
+
+
+@pytest.mark.parametrize("q8", [False, True])
+@pytest.mark.parametrize("T, K, N, wfmt", [
+    (320, 1024, 520, I.W_INT8_G32),      # the fewest rows; a ragged last column tile
+    (401, 2048, 2048, I.W_INT8_G32),
+    (1000, 1088, 1024, I.W_INT8_G32),
+    (768, 1024, 1032, I.W_INT4_G32),
+    (1001, 2048, 1024, I.W_INT4_G32),
+])
+def test_on_the_bf16_copy_of_w(T, K, N, wfmt, q8):
+    """Calls of a 4- or 8-bit W whose product runs on these tiles from the call's bf16 copy: against the oracle, against the
+    256 x 256 tiles on that copy and this kernel's own conversion (which multiply the same bf16 weights), alone and as a group
+    whose second copy is a launch of its own, and without adapters."""
+    import torch
+
+    from gpu_harness import y_to_f64
+    from paper_2507_01438_amd import binding as B
+    w = I.small_workload(5700 + T + K, I.BF16, K, N, T, 4, (16, 8, 32), segments=[T - 140, 100, 0, 39, 1], wfmt=wfmt, no_adapter_rows=(3,))
+    case = DeviceCase(w, w.projections[0], q8=q8)
+    y = case.run()
+    assert (case.last_plan.path, case.last_plan.tile_cols, case.last_plan.n_launches) == (GEMM, 128, 3)
+    assert_close(y, case.reference(), case.base_reference(), f"{T} {K} {N}")
+    assert np.array_equal(y, case.run())
+    for mode in (0, 1):
+        B.elora_debug_band(mode)
+        try:
+            other = case.run()
+        finally:
+            B.elora_debug_band(-1)
+        assert case.last_plan.tile_cols == (256, 128)[mode]
+        assert rel_err(y, other) <= 8e-3   # (sums of the same products in another order, y rounded to bf16 twice: 2 x 2^-9)
+    twin = DeviceCase(w, w.projections[0], q8=q8, share=case)
+    descs = B.desc_array([case.desc(), twin.desc()])
+    assert B.elora_linear_group_launches(descs) == 2 + 1 + 2
+    case.y.fill_(7)
+    twin.y.fill_(7)
+    B.elora_batched_lora_linear_group(descs)
+    torch.cuda.synchronize()
+    assert all(np.array_equal(y_to_f64(c.y[:T], I.BF16), y) for c in (case, twin))
+    d = case.lin.desc(case.x[:T], case.W, case.y, wfmt=wfmt, w_scales=case.w_scales)
+    d.pool = None
+    assert (B.elora_linear_plan(d).tile_cols, B.elora_linear_plan(d).n_launches) == (128, 2)
+    case.y.fill_(7)
+    B.elora_batched_lora_linear(d)
+    torch.cuda.synchronize()
+    assert rel_err(y_to_f64(case.y[:T], I.BF16), case.base_reference()) <= 1e-2
+    twin.close()
+    case.close()
