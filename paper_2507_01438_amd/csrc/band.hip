@@ -31,7 +31,7 @@ constexpr int BN = 128, BK = 64;
 constexpr int kThreads = 256, kWaveCols = 64;
 constexpr int kMaxMA = 7;
 constexpr int kMaxSlices = 8;
-constexpr int kRunsMost = 3;  // runs in a wave's rows that are taken one after the other, over all of their rows
+constexpr int kRunsMost = 3;  // runs in a wave's rows, per K-slice, that are taken one after the other, over all of their rows
 constexpr int kLdsBytes = 160 * 1024 - 512;  // (the rest: what the kernel declares by itself)
 
 // everybody's loads up to N younger ones have landed, and everybody's LDS reads are over
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
     // its 16-row blocks: 4 KiB of B_i and 1 KiB of V per block straight into registers, all at once, the next ones on their way
     // meanwhile.  (389 rows of one adapter, 4096 x 14336, from the end of the K loop to y: 23000 cycles in steps of one block,
     // which each waited for loads of the same B_i and for the stores of the block before, so 15000.  A tile's K-slices take turns at the
-    // blocks.)
+    // runs.)
     // Otherwise a step is (16-row block, run of equal adapters in it, 32 rank entries): 1 or 3 KiB of V and 4 of B_i for four or
     // twelve matrix instructions; a tile's K-slices take turns at the runs.  The wave first writes its steps out as a table, a lane per row;
     // the loads of kSteps - 1 steps are under way while one is multiplied.  Ranks that are no multiples of 8, and adapters in
@@ -333,15 +333,18 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
         plain = !q8 && (__ballot(((rank_v[0] | rank_v[1]) & 7) != 0)) == 0;
         // ---- few runs in the wave's rows (prompts): a run and 32 rank entries at a time, over all of its 16-row blocks
         uint64_t left[2] = {__ballot(lane == 0 || slot_v[0] != before0) & run[0], __ballot(slot_v[1] != (lane == 0 ? last0 : before1)) & run[1]};
-        in_runs = plain && !whole && (int)__popcll(left[0]) + (int)__popcll(left[1]) <= kRunsMost;
+        in_runs = plain && !whole && (int)__popcll(left[0]) + (int)__popcll(left[1]) <= kRunsMost * ba.ks;
         if (in_runs) {
             const uint64_t ends[2] = {__ballot(slot_v[0] != before0), __ballot(slot_v[1] != (lane == 0 ? last0 : before1))};  // (lane 0 of the first: no matter)
             int lo = 0, hi = 0, rank = 0, j0 = 0;  // the run and the entries whose fragments come next
+            int others = slice;                    // runs that fall to other slices before the next one of this slice
             const uint16_t *Bm = nullptr;
             auto next = [&]() __attribute__((always_inline)) {
                 j0 += 32;
                 if (j0 < rank) return true;
+                for (; others > 0 && (left[0] | left[1]) != 0; --others) left[left[0] == 0] &= left[left[0] == 0] - 1;
                 if ((left[0] | left[1]) == 0) return false;
+                others = ba.ks - 1;
                 const int h = left[0] == 0, l = (int)__builtin_ctzll(left[h]);
                 left[h] &= left[h] - 1;
                 lo = h * 64 + l;
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
                 if (more) load();
 #pragma unroll
                 for (int a = 0; a < MA; ++a) {
-                    if (a * 16 >= hi_ || a * 16 + 16 <= lo_ || (ba.ks > 1 && a % ba.ks != slice)) continue;
+                    if (a * 16 >= hi_ || a * 16 + 16 <= lo_) continue;
                     if (lo_ <= a * 16 && hi_ >= min(a * 16 + 16, T - r0)) {
 #pragma unroll
                         for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v[a], acc[a][b], 0, 0, 0);

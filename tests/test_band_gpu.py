@@ -111,8 +111,8 @@ def test_an_infinite_adapter_stays_in_its_own_rows():
 @pytest.mark.parametrize("tiles, slices", [(2, 1), (2, 3), (3, 2), (4, 4), (7, 1)])
 @pytest.mark.parametrize("lengths", [[345], [112, 112, 121], [5, 90, 20, 200, 30], [100, 9, 1, 1, 1, 1, 1, 231], [37, 300, 8]])
 def test_few_runs_in_a_tile(lengths, tiles, slices):
-    """Prompts: up to three runs in a wave's rows go over all of its blocks, more of them step by step; runs that begin and end
-    inside 16-row blocks, ranks on both sides of the 32 entries a pass takes, blocks shared out over K-slices, one adapter full
+    """Prompts: up to three runs in a wave's rows (and K-slice) go over all of its blocks, more of them step by step; runs that begin and end
+    inside 16-row blocks, ranks on both sides of the 32 entries a pass takes, runs shared out over K-slices, one adapter full
     of infinities (its rows take nothing but infinities and NaN, all others nothing of them)."""
     import torch
 
