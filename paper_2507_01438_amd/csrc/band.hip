@@ -16,8 +16,8 @@
 //     Calls of up to 256 rows, which the decode kernel takes too, with fp32 shrink results, have these whole here as well:
 //     three bf16 each (24 bits), three matrix instructions in the place of one, and the scale applied to what they give.
 // A call with one adapter of rank 32 (route, shrink and product), on the 256 x 256 tiles / here: 389 rows 4096 x 4096 116 /
-// 42 us, 4096 x 14336 121 / 73, 14336 x 4096 348 / 86; 1000 rows 4096 x 4096 121 / 58.  A K block of 224 x 128 takes 1300
-// cycles (matrix instructions 900, LDS 1060), a tile's beginning and end 20000, most of it code that is fetched once.
+// 37 us, 4096 x 14336 121 / 72, 14336 x 4096 348 / 83; 1000 rows 4096 x 4096 121 / 57.  A K block of 224 x 128 takes 1330
+// cycles (matrix instructions 900, LDS 1060); the first block lands after 7000, and from the last one to y it is 15500.
 #include "gemm_common.h"
 
 #include <algorithm>
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
     // loop of their own.  What bounds the plain steps is instructions and waits, with one wave per SIMD: 120 instructions a step
     // (the gathered ones 230), and no stores of y between them, whose acknowledgements the loads behind them would wait for
     // (150 rows of mixed rank, 4096 x 14336: 75 -> 66 us).
-    // Code is fetched as it is met, so the blocks go through one loop, always as acc[0], and the others move up behind each.  (A
+    // The code is kept short: the blocks go through one loop, always as acc[0], and the others move up behind each.  (A
     // switch over the blocks made the compiler copy all sums at every step: 2050 cycles a step; unrolled, 389 rows of one
     // adapter took 3000.)
     int n_steps = 0, first[2] = {0, 0};  // (first: steps before the lane's row)
