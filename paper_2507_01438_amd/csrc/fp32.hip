@@ -282,14 +282,16 @@ __global__ __launch_bounds__(64 * kOneWaves) void fp32_one_kernel(int T, int K, 
         early[q] = floatx4{0.f, 0.f, 0.f, 0.f};
         if (my_slot >= 0 && 4 * q + 4 <= my_rank) early[q] = load4(Bn + 4 * q);
     }
-    floatx4 acc{0.f, 0.f, 0.f, 0.f};
+    // two sums of every output, added at the end: as many products go into one as on the two launches, where eight waves split K
+    // (8 rows 512 x 512, error against 64-bit sums 2.6e-7 with one sum, 1.7e-7 on the two launches)
+    floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
     float sum = 0.0f, d = 0.0f;
     // One walk over K: `blocks` 16 ranks from first_rank on, and in the first walk the tile's own columns.
     auto walk = [&](auto with_w_c, auto blocks_c, int first_rank) __attribute__((always_inline)) {
         constexpr bool with_w = decltype(with_w_c)::value;
         constexpr int blocks = decltype(blocks_c)::value;
         const float *ar[kBlocks];
-        floatx4 accv[kBlocks];
+        floatx4 accv[kBlocks][2];
 #pragma unroll
         for (int p = 0; p < blocks; ++p) {
             const int c = min(first_rank + p * 16 + m, total - 1);  // (those past the last repeat it, and nobody takes them)
@@ -303,7 +305,7 @@ __global__ __launch_bounds__(64 * kOneWaves) void fp32_one_kernel(int T, int K, 
                 left &= ~__ballot(r.slot == s);
             }
             ar[p] = reinterpret_cast<const float *>(slot_A(pool, slot)) + (size_t)j * K + g * 4;
-            accv[p] = floatx4{0.f, 0.f, 0.f, 0.f};
+            accv[p][0] = accv[p][1] = floatx4{0.f, 0.f, 0.f, 0.f};
         }
         auto fetch_a = [&](int to, int first) __attribute__((always_inline)) {
 #pragma unroll
@@ -319,9 +321,9 @@ __global__ __launch_bounds__(64 * kOneWaves) void fp32_one_kernel(int T, int K, 
         auto multiply = [&](const floatx4 &x4, const floatx4 &w4, const floatx4 *a4) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if constexpr (with_w) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[i], x4[i], acc, 0, 0, 0);
+                if constexpr (with_w) acc[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[i], x4[i], acc[i & 1], 0, 0, 0);
 #pragma unroll
-                for (int p = 0; p < blocks; ++p) accv[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[p][i], x4[i], accv[p], 0, 0, 0);
+                for (int p = 0; p < blocks; ++p) accv[p][i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[p][i], x4[i], accv[p][i & 1], 0, 0, 0);
             }
         };
         auto use = [&](int from, int first) __attribute__((always_inline)) {
@@ -348,9 +350,9 @@ __global__ __launch_bounds__(64 * kOneWaves) void fp32_one_kernel(int T, int K, 
             multiply(xt, wt, at_);
         }
         // the waves' sums meet in LDS and are added in wave order; a lane holds columns 4 g .. + 3 of row m
-        if constexpr (with_w) *reinterpret_cast<floatx4 *>(&s_sum[wave][m][g * 4]) = acc;
+        if constexpr (with_w) *reinterpret_cast<floatx4 *>(&s_sum[wave][m][g * 4]) = acc[0] + acc[1];
 #pragma unroll
-        for (int p = 0; p < blocks; ++p) *reinterpret_cast<floatx4 *>(&s_sum[wave][m][kOneTile + p * 16 + g * 4]) = accv[p];
+        for (int p = 0; p < blocks; ++p) *reinterpret_cast<floatx4 *>(&s_sum[wave][m][kOneTile + p * 16 + g * 4]) = accv[p][0] + accv[p][1];
         __syncthreads();
         auto sum_of = [&](int row, int c) __attribute__((always_inline)) {
             float s = s_sum[0][row][c];
