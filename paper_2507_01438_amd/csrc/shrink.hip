@@ -68,13 +68,14 @@ constexpr int kRowPiece = 16;
 // 4096, 389 / 241.  With one adapter the second launch costs 2 us.
 constexpr int kRowsApart = 512;
 // One wave: rank entries j0 .. j0 + 3 of row t (rows of A_i past the rank repeat the last one).  Two sets of loads take turns, 20
-// loads of 16 bytes per lane each; x_t is read once for the four.  Rows start their walk through K at different places:
-// rows of A_i lie a multiple of the memory channels' pitch apart.
-__device__ __forceinline__ void shrink_four(const uint16_t *__restrict__ A, const uint16_t *__restrict__ xt, int K, int j0, int rank, int turn, int lane, float v[4])
+// loads of 16 bytes per lane each; x_t is read once for the four.  Every four rank entries start their walk through K at a
+// different place, since rows of A_i lie a multiple of the memory channels' pitch apart: at a place that depends on the entry alone, so
+// that a row's results do not depend on where in the batch it stands.
+__device__ __forceinline__ void shrink_four(const uint16_t *__restrict__ A, const uint16_t *__restrict__ xt, int K, int j0, int rank, int lane, float v[4])
 {
     constexpr int NL = 4;
     const int pieces = K >> 3, chunks = (pieces + 63) >> 6, rounds = (chunks + NL - 1) / NL;  // 16-byte pieces; 64 of them; NL chunks
-    const int rot = chunks > 2 * NL ? (int)((unsigned)turn * 5u % (unsigned)chunks) : 0;
+    const int rot = chunks > 2 * NL ? (int)((unsigned)(j0 >> 2) * 5u % (unsigned)chunks) : 0;
     const bool ragged = (pieces & 63) != 0 || chunks % NL != 0;
     const uint16_t *row[4];
 #pragma unroll
@@ -174,7 +175,7 @@ __device__ __forceinline__ void shrink_row_piece(const ShrinkArgs &s, const Shri
     } else {
         const int j0 = first + 4 * wave;
         float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (j0 < rank) shrink_four(reinterpret_cast<const uint16_t *>(slot_A(pr.pool, slot)), s.x + (size_t)t * K, K, j0, rank, t + wave, lane, v);
+        if (j0 < rank) shrink_four(reinterpret_cast<const uint16_t *>(slot_A(pr.pool, slot)), s.x + (size_t)t * K, K, j0, rank, lane, v);
         if (lane == 0) {
             put(j0, j0 < rank ? sc * v[0] : 0.0f, j0 + 1 < rank ? sc * v[1] : 0.0f);
             put(j0 + 2, j0 + 2 < rank ? sc * v[2] : 0.0f, j0 + 3 < rank ? sc * v[3] : 0.0f);

@@ -112,3 +112,45 @@ def test_single_rows_over_lengths_and_ranks(K, pool_size, product):
     assert_close(y, case.reference(), case.base_reference(), f"{K} {pool_size}")
     assert np.array_equal(y, case.run(force_path=GEMM))
     case.close()
+
+
+@pytest.mark.parametrize("by_segments", [False, True])
+@pytest.mark.parametrize("T", [70, 530])         # in the tiles' launch and in one of their own
+@pytest.mark.parametrize("K", [4608, 9280, 14336])
+def test_single_rows_do_not_depend_on_their_place(K, T, by_segments, product):
+    """Rows with the same x and the same adapter have the same bits wherever in the batch they stand and however they are named.
+    Products of 2^24 and -2^24 a few loads apart in one lane's sum make the order of its additions show: what is added between
+    them is rounded to whole numbers."""
+    import torch
+
+    from gpu_harness import y_to_f64
+    from paper_2507_01438_amd import binding as B
+    N, ranks = 72, (16, 5)
+    w = I.small_workload(1950 + K, I.BF16, K, N, T, 2, ranks)
+    w.adapter_idx = (np.arange(T) % 2).astype(np.int32)
+    case = DeviceCase(w, w.projections[0])
+    rng = np.random.default_rng(K)
+    x, As = rng.standard_normal(K), [rng.standard_normal((r, K)) for r in ranks]
+    for k, v in ((512 * 2 + 3, 4096.0), (512 * 6 + 3, -4096.0)):
+        x[k] = 4096.0
+        for A in As:
+            A[:, k] = v
+    case.x.copy_(torch.from_numpy(x).to(torch.bfloat16).view(torch.int16).to(case.x.device).expand(T, K))
+    case.W.zero_()
+    for i, A in enumerate(As):
+        case.pool.load(i, torch.from_numpy(A).to(torch.bfloat16).view(torch.int16), torch.from_numpy(case.adapters[i][1].view(np.int16)), 1.0)
+    torch.cuda.synchronize()
+    route = dict(seg_offsets=torch.arange(T + 1, dtype=torch.int32, device="cuda:0"), seg_adapter=case.adapter_idx) if by_segments else dict(adapter_idx=case.adapter_idx)
+    d = case.lin.desc(case.x[:T], case.W, case.y, **route)
+    B.elora_debug_band(0 if product == 256 else 1, 0, 1)  # (one K-slice: a tile's slices take turns at the runs)
+    B.elora_force_path(GEMM)
+    try:
+        B.elora_batched_lora_linear(d)
+    finally:
+        B.elora_force_path(-1)
+    torch.cuda.synchronize()
+    y = y_to_f64(case.y[:T], I.BF16)
+    assert np.abs(y).max() > 1.0
+    for first in (0, 1):
+        assert (y[first::2] == y[first]).all()
+    case.close()
