@@ -217,9 +217,12 @@ __global__ __launch_bounds__(kThreads) void shrink_rows_kernel(ShrinkArgs s)
 // load touches half a line of each of 16 rows, and a compute unit took in 13 GB/s.)  Three quarters of the launch's time at
 // 7871 rows x 14336 is x from memory; before / now: 153 / 71 us there, two projections of 4096 67 / 32, a prompt of 389
 // rows 25 / 9 (d_in = 4096) and 60 / 18 (14336).  A tile is cut into
-// K-slices until the launch has enough workgroups (the rule is in shrink_args); the slices' sums meet in memory (fp32), and the last workgroup of a tile to arrive adds them in slice order.  A tile and
-// slice is two workgroups, one for the tile's first long run and one for the others: where two prompts meet in a tile, one
-// workgroup going over x twice ended when the other tiles had been done for half the launch's time.
+// K-slices until the launch has enough workgroups (the rule is in shrink_args); the slices' sums meet in memory (fp32), and the
+// last workgroup of a tile to arrive adds them in slice order.  A tile and slice is two workgroups, which take its passes (a
+// long run and as many rank entries as the ring holds) in turn: where two prompts meet in a tile, one workgroup going over x
+// twice ended when the other tiles had been done for half the launch's time.  (With all passes of a run in one workgroup, the
+// call with 512 columns: 7871 rows in prompts of rank 256 181 us, so 172, 400 rows 53 and 45.6, 7871 rows in 200 prompts of
+// rank 32, d_in = 14336, 312 and 305.)
 template <bool kQ8, int NCB>
 struct Ring {
     static constexpr int kXBytes = kShrinkRows * kSpan * 2;
@@ -318,15 +321,16 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
     auto part_at = [&](int k, int r, int c) { return ((k * kShrinkRows + r) * Rpad + c) * 4; };
 
     bool x_under_way = true;
-    int n_long = 0;  // long runs with an adapter met so far
+    int turns = 0;  // passes over long runs with an adapter met so far: the two parts take them in turn
     for (int start = 0; start < kShrinkRows;) {
         const int slot = __builtin_amdgcn_readlane(slot_v, start), end = run_end(starts, start);
         const bool is_long = slot >= 0 && end - start >= kShortRun;
-        if (is_long && (n_long++ == 0) == (part_q == 0)) {
+        if (is_long) {
             const int rank = __builtin_amdgcn_readlane(rank_v, start);
             const char *const A = slot_A(pr.pool, slot);
             const char *const As = reinterpret_cast<const char *>(slot_A_scales(pr.pool, slot));  // (8-bit blocks)
             for (int j0 = 0; j0 < rank; j0 += kCols) {
+                if ((turns++ & 1) != part_q) continue;
                 // rows of A_i past the rank repeat the last one; what they give is dropped
                 uint32_t aoff[R::kALoads], soff = 0;
 #pragma unroll
@@ -413,7 +417,7 @@ __device__ __forceinline__ void shrink_tile(const ShrinkArgs &s, const ShrinkPro
                 __syncthreads();
             }
             // zeros between the last pass and the end of the padded row
-            if (slice == 0) {
+            if (slice == 0 && part_q == 0) {
                 const int done = (rank + kCols - 1) / kCols * kCols, left = (Rpad - done) / 4;
                 if (left > 0)
                     for (int e = tid; e < (end - start) * left; e += kThreads)
@@ -554,13 +558,17 @@ void elora::shrink_args(ShrinkArgs &s, const LinearArgs *a, int n, const bool *w
     while (s.ks < kMaxSlices && s.n_tiles * (s.ks + 1) <= (s.K / (s.ks + 1) >= 4096 ? 512 : 256) && s.n_tiles <= kSyncTileCount &&
            s.K / kSpan >= (s.ks + 1) * 2 * kWaves && room_for(s.ks + 1))
         ++s.ks;
-    // Rows with an index of their own, and more adapters than an eighth of them: long runs are unlikely, and the rings of 32 rank
-    // entries leave a compute unit two workgroups for the rows instead of one (256 rows of rank 64, q + k + v of 4096: 157 -> 144
-    // us; if they are all of one adapter after all, a second pass over x, 32.2 -> 33.3).  Not where a row takes several trips to
-    // memory anyway: 150 rows, d_in = 14336, 88.8 us with one workgroup and 93.4 with two.
-    s.by_row = a[0].route.adapter_idx != nullptr && s.K <= 8192;
-    for (int p = 0; p < n; ++p) s.by_row = s.by_row && a[p].n_loaded * 8ll > s.T;
     s.rows_apart = shrink_rows_apart(s.T, a[0].route.adapter_idx != nullptr, a[0].route.n_segments);
+    // Rows with an index of their own, and more adapters than an eighth of them: long runs are unlikely, and the rings of 32
+    // rank entries leave a compute unit two workgroups for the rows instead of one.  With rings of 64 / so, calls with 512
+    // columns: 300 rows of their own of rank 64, d_in = 2048 44.8 / 40.5 us, 4096 57 / 51.5, 8192 81 / 74.5, of rank 128 64 /
+    // 55, 82.5 / 75.5, 125.5 / 122.5, 400 of rank 256, 4096, 169 / 143; if they are all of one adapter after all, rank 64 25.7
+    // / 25.1, 27.6 / 26.8, 32.5 / 31, rank 128 30.9 / 31.8 (4096), rank 256 44 / 45.6.  Not where the rows are a launch of
+    // their own (700 of rank 64 89.0 / 88.0 us, 256 263 / 264), nor for 8-bit blocks, whose rings of 64 fit twice (300 of rank
+    // 64 and 256 within 1 %).  For longer rows it was measured on 150 rows of ranks 8 to 64, d_in = 14336 (88.8 us with one
+    // workgroup, 93.4 with two); 300 rows of rank 64 would gain there as well (120 / 114).
+    s.by_row = a[0].route.adapter_idx != nullptr && !s.rows_apart && s.K <= 8192;
+    for (int p = 0; p < n; ++p) s.by_row = s.by_row && !a[p].pool.q8 && a[p].n_loaded * 8ll > s.T;
     // (at least four workgroups per row, up to two per compute unit: the rows of short runs are shared by all of them)
     s.wgs_per_xcd = std::max((s.n_tiles + kXcds - 1) / kXcds * s.ks * 2, std::min((s.T + 1) / 2, 64));
     for (int p = 0; p < n; ++p) {

@@ -105,7 +105,7 @@ def test_many_rows_in_short_runs(T, K, ranks, q8, product):
 def test_single_rows_over_lengths_and_ranks(K, pool_size, product):
     """Rows of one run each: d_in below, at and beside whole loads of a wave (512 elements), one and several turns of them,
     walks that begin in the middle; ranks around the four entries of a wave and the 16 of a workgroup."""
-    w = I.small_workload(1900 + K, I.BF16, K, 72, 70, pool_size, (1, 3, 4, 5, 15, 16, 18, 64)[:: 2 if pool_size == 4 else 1], no_adapter_rows=(0, 33))
+    w = I.small_workload(1900 + K, I.BF16, K, 72, 70, pool_size, (1, 3, 4, 5, 15, 16, 18, 64) if pool_size == 40 else (1, 4, 18, 64), no_adapter_rows=(0, 33))
     case = DeviceCase(w, w.projections[0])
     y = case.run(force_path=GEMM)
     assert case.last_plan.tile_cols == product
@@ -153,4 +153,41 @@ def test_single_rows_do_not_depend_on_their_place(K, T, by_segments, product):
     assert np.abs(y).max() > 1.0
     for first in (0, 1):
         assert (y[first::2] == y[first]).all()
+    case.close()
+
+
+@pytest.mark.parametrize("q8", [False, True])
+@pytest.mark.parametrize("T, pool", [(300, 40), (330, 40), (530, 80)])   # (more adapters than an eighth of the rows, fewer, a launch of their own)
+@pytest.mark.parametrize("K", [64, 1024, 4096, 8256])
+def test_long_runs_among_rows_that_name_their_adapters(K, T, pool, q8, product):
+    """Runs of 8 rows and more in a batch of which the host expects none: ranks of several passes through the rings of 32 entries
+    and of 64, which a tile's two workgroups take in turn; one, two and three such runs in a tile, a run over three tiles, a
+    run without adapter; with and without K-slices.  The shrink is the same when the rows are named by segments."""
+    import torch
+
+    from gpu_harness import y_to_f64
+    from paper_2507_01438_amd import binding as B
+    w = I.small_workload(1980 + K + T, I.BF16, K, 96, T, pool, (8, 64, 136, 40, 16), no_adapter_rows=(0, T - 1))
+    idx = w.adapter_idx
+    idx[10:90] = 1                                        # rank 64 over three tiles
+    idx[96:108], idx[108:128] = 2, 6                      # ranks 136 and 64 in one tile
+    idx[128:138], idx[138:148], idx[148:160] = 3, 12, 4   # ranks 40, 136 and 16
+    idx[160:192] = 7                                      # a whole tile, rank 136
+    idx[200:212] = -1
+    case = DeviceCase(w, w.projections[0], q8=q8)
+    y = case.run(force_path=GEMM)
+    assert case.last_plan.tile_cols == product
+    assert_close(y, case.reference(), case.base_reference(), f"{K} {T}")
+    assert np.array_equal(y, case.run(force_path=GEMM))
+    if product == 256:  # (every product adds the shrink results in its own order)
+        d = case.lin.desc(case.x[:T], case.W, case.y, seg_offsets=torch.arange(T + 1, dtype=torch.int32, device="cuda:0"), seg_adapter=case.adapter_idx)
+        case.y.fill_(7)
+        B.elora_force_path(GEMM)
+        try:
+            B.elora_batched_lora_linear(d)
+        finally:
+            B.elora_force_path(-1)
+        torch.cuda.synchronize()
+        assert np.array_equal(y_to_f64(case.y[:T], I.BF16), y)
+    assert case.pool.poll_error() == (0, -1)
     case.close()
