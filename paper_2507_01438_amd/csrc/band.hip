@@ -76,7 +76,8 @@ struct BandArgs {
     int *sync;
 };
 
-template <int WFMT, int MA>
+// kGather: for pools whose rows of B_i all have to be gathered (expand, below); takes any adapter, as the other does
+template <int WFMT, int MA, bool kGather>
 __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolView pool, int has_pool)
 {
     typedef Band<WFMT, MA> G;
@@ -330,72 +331,74 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
         const bool cut = (lane & 15) == 0;
         const uint64_t starts[2] = {__ballot(cut || slot_v[0] != before0), __ballot(cut || slot_v[1] != (lane == 0 ? last0 : before1))};
         const uint64_t run[2] = {starts[0] & __ballot(rank_v[0] > 0), starts[1] & __ballot(rank_v[1] > 0)};  // first rows of runs with an adapter
-        plain = !q8 && (__ballot(((rank_v[0] | rank_v[1]) & 7) != 0)) == 0;
-        // ---- few runs in the wave's rows (prompts): a run and 32 rank entries at a time, over all of its 16-row blocks
-        uint64_t left[2] = {__ballot(lane == 0 || slot_v[0] != before0) & run[0], __ballot(slot_v[1] != (lane == 0 ? last0 : before1)) & run[1]};
-        in_runs = plain && !whole && (int)__popcll(left[0]) + (int)__popcll(left[1]) <= kRunsMost * ba.ks;
-        if (in_runs) {
-            const uint64_t ends[2] = {__ballot(slot_v[0] != before0), __ballot(slot_v[1] != (lane == 0 ? last0 : before1))};  // (lane 0 of the first: no matter)
-            int lo = 0, hi = 0, rank = 0, j0 = 0;  // the run and the entries whose fragments come next
-            int others = slice;                    // runs that fall to other slices before the next one of this slice
-            const uint16_t *Bm = nullptr;
-            auto next = [&]() __attribute__((always_inline)) {
-                j0 += 32;
-                if (j0 < rank) return true;
-                for (; others > 0 && (left[0] | left[1]) != 0; --others) left[left[0] == 0] &= left[left[0] == 0] - 1;
-                if ((left[0] | left[1]) == 0) return false;
-                others = ba.ks - 1;
-                const int h = left[0] == 0, l = (int)__builtin_ctzll(left[h]);
-                left[h] &= left[h] - 1;
-                lo = h * 64 + l;
-                const uint64_t after0 = h == 0 && l < 63 ? ends[0] & (~0ull << (l + 1)) : 0, after1 = h == 0 ? ends[1] : l < 63 ? ends[1] & (~0ull << (l + 1)) : 0;
-                hi = after0 ? (int)__builtin_ctzll(after0) : after1 ? 64 + (int)__builtin_ctzll(after1) : 128;
-                rank = h == 0 ? __builtin_amdgcn_readlane(rank_v[0], l) : __builtin_amdgcn_readlane(rank_v[1], l);
-                Bm = reinterpret_cast<const uint16_t *>(slot_B(pool, h == 0 ? __builtin_amdgcn_readlane(slot_v[0], l) : __builtin_amdgcn_readlane(slot_v[1], l)));
-                j0 = 0;
-                return true;
-            };
-            u32x4 vf[MA], bf[4];
-            auto load = [&]() __attribute__((always_inline)) {
-                const int j = j0 + g * 8;
+        if constexpr (!kGather) {
+            plain = !q8 && (__ballot(((rank_v[0] | rank_v[1]) & 7) != 0)) == 0;
+            // ---- few runs in the wave's rows (prompts): a run and 32 rank entries at a time, over all of its 16-row blocks
+            uint64_t left[2] = {__ballot(lane == 0 || slot_v[0] != before0) & run[0], __ballot(slot_v[1] != (lane == 0 ? last0 : before1)) & run[1]};
+            in_runs = plain && !whole && (int)__popcll(left[0]) + (int)__popcll(left[1]) <= kRunsMost * ba.ks;
+            if (in_runs) {
+                const uint64_t ends[2] = {__ballot(slot_v[0] != before0), __ballot(slot_v[1] != (lane == 0 ? last0 : before1))};  // (lane 0 of the first: no matter)
+                int lo = 0, hi = 0, rank = 0, j0 = 0;  // the run and the entries whose fragments come next
+                int others = slice;                    // runs that fall to other slices before the next one of this slice
+                const uint16_t *Bm = nullptr;
+                auto next = [&]() __attribute__((always_inline)) {
+                    j0 += 32;
+                    if (j0 < rank) return true;
+                    for (; others > 0 && (left[0] | left[1]) != 0; --others) left[left[0] == 0] &= left[left[0] == 0] - 1;
+                    if ((left[0] | left[1]) == 0) return false;
+                    others = ba.ks - 1;
+                    const int h = left[0] == 0, l = (int)__builtin_ctzll(left[h]);
+                    left[h] &= left[h] - 1;
+                    lo = h * 64 + l;
+                    const uint64_t after0 = h == 0 && l < 63 ? ends[0] & (~0ull << (l + 1)) : 0, after1 = h == 0 ? ends[1] : l < 63 ? ends[1] & (~0ull << (l + 1)) : 0;
+                    hi = after0 ? (int)__builtin_ctzll(after0) : after1 ? 64 + (int)__builtin_ctzll(after1) : 128;
+                    rank = h == 0 ? __builtin_amdgcn_readlane(rank_v[0], l) : __builtin_amdgcn_readlane(rank_v[1], l);
+                    Bm = reinterpret_cast<const uint16_t *>(slot_B(pool, h == 0 ? __builtin_amdgcn_readlane(slot_v[0], l) : __builtin_amdgcn_readlane(slot_v[1], l)));
+                    j0 = 0;
+                    return true;
+                };
+                u32x4 vf[MA], bf[4];
+                auto load = [&]() __attribute__((always_inline)) {
+                    const int j = j0 + g * 8;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) bf[b] = *reinterpret_cast<const u32x4 *>(Bm + (uint32_t)min(c0 + b * 16 + m, N - 1) * (uint32_t)rank + (uint32_t)(j < rank ? j : j0));
+                    for (int b = 0; b < 4; ++b) bf[b] = *reinterpret_cast<const u32x4 *>(Bm + (uint32_t)min(c0 + b * 16 + m, N - 1) * (uint32_t)rank + (uint32_t)(j < rank ? j : j0));
 #pragma unroll
-                for (int a = 0; a < MA; ++a) vf[a] = *reinterpret_cast<const u32x4 *>(ba.V + (size_t)min(r0 + a * 16 + m, T - 1) * ba.Rpad + j);
-            };
-            bool more = next();
-            if (more) load();
-#pragma unroll 1
-            while (more) {
-                const int lo_ = lo, hi_ = hi;
-                const bool cut_off = j0 + g * 8 >= rank;
-                bf16x8 v[MA], bm[4];
-#pragma unroll
-                for (int b = 0; b < 4; ++b) bm[b] = __builtin_bit_cast(bf16x8, cut_off ? u32x4{0, 0, 0, 0} : bf[b]);
-#pragma unroll
-                for (int a = 0; a < MA; ++a) v[a] = __builtin_bit_cast(bf16x8, vf[a]);
-                more = next();
+                    for (int a = 0; a < MA; ++a) vf[a] = *reinterpret_cast<const u32x4 *>(ba.V + (size_t)min(r0 + a * 16 + m, T - 1) * ba.Rpad + j);
+                };
+                bool more = next();
                 if (more) load();
+#pragma unroll 1
+                while (more) {
+                    const int lo_ = lo, hi_ = hi;
+                    const bool cut_off = j0 + g * 8 >= rank;
+                    bf16x8 v[MA], bm[4];
 #pragma unroll
-                for (int a = 0; a < MA; ++a) {
-                    if (a * 16 >= hi_ || a * 16 + 16 <= lo_) continue;
-                    if (lo_ <= a * 16 && hi_ >= min(a * 16 + 16, T - r0)) {
+                    for (int b = 0; b < 4; ++b) bm[b] = __builtin_bit_cast(bf16x8, cut_off ? u32x4{0, 0, 0, 0} : bf[b]);
 #pragma unroll
-                        for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v[a], acc[a][b], 0, 0, 0);
-                    } else {
-                        const bool in = (a * 16 + m >= lo_) & (a * 16 + m < hi_);  // (a row of another run takes nothing, not even zero times this adapter)
+                    for (int a = 0; a < MA; ++a) v[a] = __builtin_bit_cast(bf16x8, vf[a]);
+                    more = next();
+                    if (more) load();
 #pragma unroll
-                        for (int b = 0; b < 4; ++b) {
-                            const floatx4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v[a], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    for (int a = 0; a < MA; ++a) {
+                        if (a * 16 >= hi_ || a * 16 + 16 <= lo_) continue;
+                        if (lo_ <= a * 16 && hi_ >= min(a * 16 + 16, T - r0)) {
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) acc[a][b][q] += in ? d[q] : 0.0f;
+                            for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v[a], acc[a][b], 0, 0, 0);
+                        } else {
+                            const bool in = (a * 16 + m >= lo_) & (a * 16 + m < hi_);  // (a row of another run takes nothing, not even zero times this adapter)
+#pragma unroll
+                            for (int b = 0; b < 4; ++b) {
+                                const floatx4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[b], v[a], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) acc[a][b][q] += in ? d[q] : 0.0f;
+                            }
                         }
                     }
                 }
             }
         }
         __syncthreads();  // every wave is done with the stages
-        if (tid < 16) *reinterpret_cast<uint32_t *>(smem + 4 * G::kWaveBytes + (tid >> 2) * 1024 + (tid & 3) * 4) = 0;  // (read by every wave: the barrier below)
+        if (!kGather && tid < 16) *reinterpret_cast<uint32_t *>(smem + 4 * G::kWaveBytes + (tid >> 2) * 1024 + (tid & 3) * 4) = 0;  // (read by every wave: the barrier below)
 #pragma unroll
         for (int h = 0; h < (G::kWaveRows + 63) / 64; ++h) {
             const uint64_t below = (1ull << lane) - 1;
@@ -416,7 +419,8 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
                                       ((uint64_t)(plain ? (uint32_t)((slot_v[h] * pool.slot_bytes + pool.b_offset) >> 8) : (uint32_t)slot_v[h]) << 32);
             n_steps += __builtin_amdgcn_readlane(upto, 63);
         }
-        __syncthreads();
+        if constexpr (kGather) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (a wave reads what its own lanes wrote)
+        else __syncthreads();
         if (n_steps > 0) {
 #pragma unroll 1
             for (int i = 0; i < G::kSteps - 1; ++i) {
@@ -436,18 +440,24 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
     constexpr int kFrags = MA * 4, kCoherent = 16;  // sc1
     auto rsrc = __builtin_amdgcn_make_buffer_rsrc(ba.part + (size_t)tile * ba.ks * (4 * kFrags * 256), 0, ba.ks * (4 * kFrags * 1024), 0x00020000);
     const int part_at = wave * kFrags * 1024 + lane * 16, slice_bytes = 4 * kFrags * 1024;
-    // a lane has four neighbouring outputs of row m of every block
+    // block a of y, or of the slice's sums, from acc[at]: a lane has four neighbouring outputs of row m
+    auto store_block = [&](int a, int at) __attribute__((always_inline)) {
+        const int row = r0 + a * 16 + m;
+        uint16_t *const yrow = ba.y + (size_t)row * N;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int c = c0 + b * 16 + g * 4;
+            if (row < T && c < N) *reinterpret_cast<u32x2 *>(yrow + c) = u32x2{pack_bf16x2(acc[at][b][0], acc[at][b][1]), pack_bf16x2(acc[at][b][2], acc[at][b][3])};
+        }
+    };
+    auto store_part = [&](int a, int at) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[at][b]), rsrc, part_at + a * 4096 + b * 1024, slice * slice_bytes, kCoherent);
+    };
     auto store_y = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int a = 0; a < MA; ++a) {
-            const int row = r0 + a * 16 + m;
-            uint16_t *const yrow = ba.y + (size_t)row * N;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int c = c0 + b * 16 + g * 4;
-                if (row < T && c < N) *reinterpret_cast<u32x2 *>(yrow + c) = u32x2{pack_bf16x2(acc[a][b][0], acc[a][b][1]), pack_bf16x2(acc[a][b][2], acc[a][b][3])};
-            }
-        }
+        for (int a = 0; a < MA; ++a) store_block(a, a);
     };
     int step = 0, at = 0;
     // What a step of a plain wave costs is instructions and the waits between them (one wave per SIMD): the table entries are
@@ -576,6 +586,10 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (this step's place has been read)
             at = at + 1 == G::kSteps ? 0 : at + 1;
         }
+        if constexpr (kGather) {
+            if (ba.ks == 1) store_block(a, 0);
+            else store_part(a, 0);
+        }
         // (the blocks move up, round the circle: as many turns as there are blocks put every one back)
         floatx4 top[4];
 #pragma unroll
@@ -589,15 +603,15 @@ __global__ __launch_bounds__(kThreads) void lora_band_kernel(BandArgs ba, PoolVi
     }
     }
     wait_loads<0>();  // (also those asked for behind the last step: they land before the LDS is given back)
+    const bool stored = kGather && n_steps > 0;
     if (ba.ks == 1) {
-        store_y();
+        if (!stored) store_y();
         return;
     }
+    if (!stored) {
 #pragma unroll
-    for (int a = 0; a < MA; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[a][b]), rsrc, part_at + a * 4096 + b * 1024, slice * slice_bytes, kCoherent);
+        for (int a = 0; a < MA; ++a) store_part(a, a);
+    }
 
     // ---- sums of the K-slices: the last workgroup of the tile to come adds them, in slice order -----------------------------
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's sums have reached memory
@@ -723,16 +737,25 @@ int elora::enqueue_band(const LinearArgs &a, const BandShape &s, hipStream_t str
     b.part = reinterpret_cast<float *>(a.ws + a.wsl.part);
     b.sync = reinterpret_cast<int *>(a.ws + a.wsl.sync);
     const dim3 grid(round_up(b.tiles_m * b.tiles_n * b.ks, kXcds));
+    // Adapters in 8-bit blocks, and pools that hold none but ranks that are no multiples of 8: a wave has no plain steps.
+    // Without the code for these, and with what is stored of a block behind its last step, as the loads of the next step are
+    // waited for anyway, calls of one prompt of 389 rows in one kernel for all / so: rank 5 4096 x 4096 42.3 / 40.6 us, rank 36
+    // 48.7 / 46.9, twice 4096 x 14336 191 / 187, rank 16 in 8-bit blocks 42.9 / 41.6, 151 / 148; 14336 x 4096 90.3 / 89.7.
+    const bool gather = a.has_pool && (a.pool.q8 || (a.n_loaded > 0 && a.pool.n_odd_ranks == a.n_loaded));
     auto launch = [&](auto wfmt, auto ma) -> int {
         constexpr int WFMT = decltype(wfmt)::value, MA = decltype(ma)::value, lds = Band<WFMT, MA>::kBytes;
-        static bool attr_done = false;
-        if (!attr_done) {
-            ELORA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&lora_band_kernel<WFMT, MA>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-            attr_done = true;
-        }
-        hipLaunchKernelGGL((lora_band_kernel<WFMT, MA>), grid, dim3(kThreads), lds, stream, b, a.pool, a.has_pool ? 1 : 0);
-        ELORA_HIP_TRY(hipGetLastError());
-        return ELORA_OK;
+        auto go = [&](auto gather_c) -> int {
+            constexpr bool kGather = decltype(gather_c)::value;
+            static bool attr_done = false;
+            if (!attr_done) {
+                ELORA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&lora_band_kernel<WFMT, MA, kGather>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+                attr_done = true;
+            }
+            hipLaunchKernelGGL((lora_band_kernel<WFMT, MA, kGather>), grid, dim3(kThreads), lds, stream, b, a.pool, a.has_pool ? 1 : 0);
+            ELORA_HIP_TRY(hipGetLastError());
+            return ELORA_OK;
+        };
+        return gather ? go(std::true_type{}) : go(std::false_type{});
     };
     auto with_rows = [&](auto wfmt) -> int {
         switch (s.ma) {

@@ -185,3 +185,54 @@ def test_on_the_bf16_copy_of_w(T, K, N, wfmt, q8):
     assert rel_err(y_to_f64(case.y[:T], I.BF16), case.base_reference()) <= 1e-2
     twin.close()
     case.close()
+
+
+@pytest.mark.parametrize("ks", [1, 3])
+@pytest.mark.parametrize("T, lengths", [(27, None), (59, [50, 9]), (91, None), (123, [123]), (155, [1, 154]), (187, None), (219, [100, 119]), (389, [150, 1, 238]), (389, None)])
+@pytest.mark.parametrize("ranks, q8", [((5, 12, 36), False), ((5, 16, 36, 64), False), ((8, 40), True)], ids=["gathered", "both", "blocks"])
+def test_adapters_that_are_gathered(ranks, q8, T, lengths, ks):
+    """Pools whose rows of B_i are all gathered, which have an instance of their own, and pools where some are: every tile
+    height, shrink results whole and rounded, with K-slices and without, waves with and without steps."""
+    from paper_2507_01438_amd import binding as B
+    w = I.small_workload(6200 + T, I.BF16, 832, 200, T, 6, ranks, segments=lengths, no_adapter_rows=(0,) if lengths is None else ())
+    case = DeviceCase(w, w.projections[0], q8=q8)
+    B.elora_debug_band(1, 0 if T > 224 else 1, ks)
+    try:
+        y = case.run(force_path=GEMM)
+        again = case.run(force_path=GEMM)
+    finally:
+        B.elora_debug_band(-1)
+    assert case.last_plan.tile_cols == 128 and case.last_plan.split_k == ks
+    assert_close(y, case.reference(), case.base_reference(), f"{ranks} {T}")
+    assert np.array_equal(y, again)
+    assert case.pool.poll_error() == (0, -1)
+    case.close()
+
+
+def test_a_graph_captured_over_gathered_adapters_takes_others_loaded_later():
+    import torch
+
+    from gpu_harness import y_to_f64
+    K, N, T = 832, 200, 389
+    w = I.small_workload(6300, I.BF16, K, N, T, 3, (5, 12, 64), segments=[130, 9, 250])
+    w.seg_adapter = np.array([0, 2, 1], dtype=np.int32)
+    case = DeviceCase(w, w.projections[0], load_slots=[0, 1])
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            case.B.elora_batched_lora_linear(case.desc(), stream)
+    assert case.B.elora_linear_plan(case.desc()).tile_cols == 128
+    A, Bm, s = w.adapter(w.projections[0], 2)
+    assert A.shape[0] == 64
+    case.adapters[2] = (A, Bm, s)
+    case.pool.load(2, torch.from_numpy(A.view(np.int16)), torch.from_numpy(Bm.view(np.int16)), s)
+    torch.cuda.synchronize()
+    ref, base = case.reference(), case.base_reference()
+    for _ in range(3):
+        case.y.fill_(7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_close(y_to_f64(case.y[:T], I.BF16), ref, base)
+    assert case.pool.poll_error() == (0, -1)
+    case.close()
