@@ -64,8 +64,10 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteView route, S
 // 88 -> 78, 1800 rows of rank 32 6336 x 2048 253 -> 224.)
 constexpr int kRowPiece = 16;
 // Rows in short runs, as far as the host can tell, from which they are a launch of their own.  With an adapter per row, all in
-// the one launch / so: 512 rows of ranks 8 to 64, 2752 x 2896, 89 / 84 us, 2000 rows 243 / 203; 4000 rows of rank 16, 4096 x
-// 4096, 389 / 241.  With one adapter the second launch costs 2 us.
+// the one launch / so, calls with 512 columns of W and d_in = 4096: 300 rows of rank 16 36 / 42.5 us, 512 42 / 49.5, 1000 63 /
+// 71, 2000 108 / 112, 4000 176 / 180; of ranks 8 to 64 512 rows 62 / 68, 2000 163 / 166, 4000 315 / 288.  With one adapter the
+// second launch costs 2 to 3 us.  (The line was drawn when a wave took two rows of A_i and 512 rows were 89 / 84 us, 2000 243 /
+// 203, 4000 of rank 16 389 / 241: what it still buys are the largest batches of mixed rank.)
 constexpr int kRowsApart = 512;
 // One wave: rank entries j0 .. j0 + 3 of row t (rows of A_i past the rank repeat the last one).  Two sets of loads take turns, 20
 // loads of 16 bytes per lane each; x_t is read once for the four.  Every four rank entries start their walk through K at a
@@ -201,8 +203,11 @@ __device__ __forceinline__ void shrink_rows(const ShrinkArgs &s, const ShrinkPro
     }
 }
 
-// Many rows in short runs: a launch of their own, without LDS, so that a compute unit holds four workgroups and not the one or
-// two that the rings leave room for.
+// Many rows in short runs: a launch of their own, without LDS, so that a compute unit holds the two workgroups that the
+// registers of four rows of A_i leave room for, where the rings of 64 rank entries leave one.  (Two rows of A_i at a time and
+// four workgroups / so: 2000 rows of rank 64, d_in = 4096, 250 / 244 us, 600 of d_in = 14336 230 / 225, of rank 16 96 / 93,
+// 4000 of ranks 8 to 64 296 / 288.  In the tiles' launch, where prompts may be all there is: within 1 % of each other for
+// prompts of 389 to 7871 rows, rank 16 to 64, and 300 single rows of rank 64 55.4 / 54.5.)
 template <bool kQ8>
 __global__ __launch_bounds__(kThreads) void shrink_rows_kernel(ShrinkArgs s)
 {
