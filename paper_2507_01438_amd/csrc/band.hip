@@ -53,7 +53,9 @@ struct Band {
     static constexpr int kWholeLoads = 7, kRoundedLoads = 5, kStepBytes = kWholeLoads * 1024;
     // (all of LDS, unless the K loop leaves room for a second workgroup)
     static constexpr int kBytes = kDepth * kStage * 2 > kLdsBytes ? kLdsBytes / 4096 * 4096 : kDepth * kStage;
-    static constexpr int kZeroBytes = 4096;                                // (of which four 16-byte places are read)
+    // (four 16-byte zeros, 1024 apart, are read.  Less room for them would give tiles of 128 rows a fifth step; four / five:
+    // gate + up of 256 rows of rank 16, 4096 x 14336, 168.4 / 170.6 us, of ranks 8 to 64 222 / 224, q + k + v of 500 180.4 / 179.7)
+    static constexpr int kZeroBytes = 4096;
     static constexpr int kWaveBytes = (kBytes - kZeroBytes) / 4 / 1024 * 1024;
     static constexpr int kTableBytes = kWaveRows * (kMaxRank / 32) * 8;    // the wave's expand steps at most
     static constexpr int kStepRoom = (kWaveBytes - kTableBytes) / kStepBytes;
@@ -654,11 +656,14 @@ void elora::band_set(int mode, int tiles_m, int slices)
 //   here: a K block 270 + 160 ma (a W that is converted on the way 1550 + 105 ma), a tile 6000 + 2300 ma, an expand step
 //   1600 (adapters in 8-bit blocks 6500), the slices' sums 2000 + 450 ma each; 20 % more than that where there is more than
 //   one round;
+//   (the step of 1600 is from when it took 230 instructions, not the 120 that plain adapters take now: with an adapter per row
+//   this kernel stays the faster one beyond where the rule ends, there / here: 1000 rows of rank 64, 2560 x 7680, 513 / 284 us,
+//   3000 rows 4096 x 4096 661 / 454, 2000 of rank 16, 1024 x 1024, 98 / 82)
 //   there: a K block 3300, in further rounds 2900 (from the bf16 copy of W 2600, converted on the way 5700), a tile 6000, 16
 //   rank entries of a short run 850 (adapters in 8-bit blocks 4000), the copy 1.04e-3 per weight.
 // Over 1488 calls of 300 to 4000 rows (eight W of 512 x 512 to 14336 x 4096 and 4096 x 14336, one prompt to a row per adapter,
 // ranks 8 to 128, all storage formats) the choice is slower than the 256 x 256 tiles by more than 3 % in 4 and by 9 % at most;
-// the mean call takes 68 % of its time there.  (Asking for the estimate to be 8 % lower is what keeps these from being 27.)
+// the mean call takes 68 % of its time there (measured with the constants).  (Asking for the estimate to be 8 % lower is what keeps these from being 27.)
 // (4096 x 14336, here / there: 600 rows of one adapter 109 / 119 us, 800 of two 124 / 119, 1800 235 / 208, 600 of an adapter
 // each 217 / 188; 4096 x 4096: 600 of an adapter each 103 / 185, 1000 of one 58 / 121; 2560 x 7680, 3000 rows: 171 / 140.)
 bool elora::band_shape(const BandCall &c, size_t part_bytes, BandShape *s)
@@ -707,6 +712,9 @@ bool elora::band_shape(const BandCall &c, size_t part_bytes, BandShape *s)
             *s = from_copy;
         }
     }
+    // (The 18000 stay out of what follows: they would send 30 of 40000 drawn calls to the 256 x 256 tiles, of which twelve were
+    // timed.  Ten are faster here, 413 rows of 50 prompts 6144 x 11008 8-bit 161 / 170 us, 376 of 8 2560 x 14336 83 / 96, and two
+    // slower by 2 and 3 %.)
     const double n = rounds((double)((T + 255) / 256) * ((N + 255) / 256));
     const double block = c.copied ? 2600 : c.wfmt != ELORA_W_SAME ? 5700 : n > 1 ? 2900 : 3300;
     // (the most that a wave of a tile has, 128 rows; where the runs are spread over the batch, every round's tiles have them)
