@@ -354,6 +354,9 @@ int elora_linear_plan(const elora_linear_desc_t *desc, elora_plan_t *plan);
  * W x is shared by the whole batch; every row adds s * B_i (A_i x) with the
  * adapter its request names; results land at the rows' own positions in y.
  * Accumulation is fp32; y is rounded once (bf16: round-to-nearest-even).
+ * Which kernels run, and so the order of the fp32 additions, follows from the
+ * batch's sizes and from how many adapters of which ranks the pool holds: a
+ * load can change the last bits of calls that do not name the loaded adapter.
  * Rows with adapter -1 get y = W x.  Invalid indices: see elora_pool_poll_error.
  * The segment table itself is trusted to be well-formed (it is device data).
  * Errors: those of elora_linear_plan, plus E_HIP.

@@ -137,3 +137,19 @@ def test_fp32_one_launch_captured_before_more_adapters_are_loaded():
         assert rel_err(case.y.cpu().numpy().astype(np.float64), ref) <= 1e-5
     assert case.pool.poll_error() == (0, -1)
     case.close()
+
+
+@pytest.mark.parametrize("K, N, T, pool, ranks, launches", [
+    (700, 64, 8, 2, (16,), 1), (701, 64, 8, 2, (16,), 2),                     # d_in
+    (96, 8192, 16, 2, (8,), 1), (96, 8193, 16, 2, (8,), 2),                   # 512 tiles of 16 x 16, and 513
+    (96, 4096, 17, 2, (8,), 1), (96, 4097, 17, 2, (8,), 2),                   # two rows of tiles
+    (200, 64, 20, 4, (8,), 1), (200, 64, 20, 3, (11,), 2),                    # 32 ranks of the adapters there are, and 33
+    (200, 64, 2, 9, (16,), 1), (200, 64, 3, 9, (16,), 2),                     # of the rows
+])
+def test_fp32_where_one_launch_ends(K, N, T, pool, ranks, launches):
+    w = I.small_workload(4500 + K + N + T, I.F32, K, N, T, pool, ranks)
+    case = DeviceCase(w, w.projections[0])
+    y = case.run()
+    assert case.last_plan.n_launches == launches
+    assert rel_err(y, case.reference()) <= 1e-5
+    case.close()
